@@ -1,4 +1,4 @@
-"""Build step of libmrfmp: three hipcc compilations side by side and a link, in-tree output next to
+"""Build step of libmrfmp: nine hipcc compilations side by side and a link, in-tree output next to
 the sources."""
 from __future__ import annotations
 
@@ -8,7 +8,7 @@ import subprocess
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 LIB_PATH = os.path.join(CSRC, "libmrfmp.so")
 SOURCES = ["mrfmp.hip"]
-HEADERS = ["mrfmp_device.h", "mrfmp_fwd.h", "mrfmp_bwd.h", "mrfmp_head.h", "../../include/mrfmp.h"]
+HEADERS = ["mrfmp_device.h", "mrfmp_fwd.h", "mrfmp_bwd.h", "mrfmp_bwd_sum.h", "mrfmp_head.h", "../../include/mrfmp.h"]
 
 # -ffp-contract=off: the only fused multiply-add is the explicit one of the message update,
 #   so that floating point decisions (argmins) match a plain C evaluation order.
@@ -25,14 +25,14 @@ def is_stale() -> bool:
 
 
 def build(verbose: bool = False) -> str:
-    """Compile libmrfmp.so for gfx950 (cross-compiles without a GPU): the one source as three
-    translation units (forward pass, backward pass, entry points) side by side, then link."""
+    """Compile libmrfmp.so for gfx950 (cross-compiles without a GPU): the one source as nine
+    translation units (the schedules, the entry points, a family of sweeps each) side by side, then link."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(CSRC, "_build")
     os.makedirs(objdir, exist_ok=True)
     flags = [f for f in HIPCC_FLAGS if f != "-shared"]
     jobs = []
-    for part in (1, 2, 3):
+    for part in range(1, 10):
         obj = os.path.join(objdir, "mrfmp_part%d.o" % part)
         cmd = [hipcc, *flags, "-DMRF_PART=%d" % part, "-c", "-o", obj, *SOURCES]
         jobs.append((obj, subprocess.Popen(cmd, cwd=CSRC, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))

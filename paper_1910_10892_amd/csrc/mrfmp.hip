@@ -1,24 +1,33 @@
 // libmrfmp host side: argument checks, workspace layout and launch schedules of the
 // ISGMR / TRWP forward and backward passes (Alg. 1-4).  Allocates nothing.
 //
-// One source, up to three translation units: compiled as it stands it holds everything; with
-// -DMRF_PART=1 / 2 / 3 it holds the forward pass, the backward pass, or the entry points and
-// the heads, so that the build can compile the three in parallel and link them.
+// One source, up to nine translation units: compiled as it stands it holds everything; with
+// -DMRF_PART=n it holds one part (the list below), so that the build can compile the parts in
+// parallel and link them.  The sweep templates of a family are instantiated in one part only.
 #include "../../include/mrfmp.h"
 #include "mrfmp_device.h"
 
 #ifndef MRF_PART
 #define MRF_PART 0
 #endif
-#define MRF_HAS_FWD (MRF_PART == 0 || MRF_PART == 1)
-#define MRF_HAS_BWD (MRF_PART == 0 || MRF_PART == 2)
-#define MRF_HAS_API (MRF_PART == 0 || MRF_PART == 3)
+#define MRF_HAS_FWD (MRF_PART == 0 || MRF_PART == 1)          // forward schedule, per-edge sweep, aggregation
+#define MRF_HAS_BWD (MRF_PART == 0 || MRF_PART == 2)          // backward schedule, split sweep, combine pass
+#define MRF_HAS_API (MRF_PART == 0 || MRF_PART == 3)          // entry points, heads
+#define MRF_HAS_FWD_PACKED (MRF_PART == 0 || MRF_PART == 4)   // packed forward sweep
+#define MRF_HAS_FWD_DUO (MRF_PART == 0 || MRF_PART == 5)      // value / index / loader window sweep
+#define MRF_HAS_FWD_WINDOW (MRF_PART == 0 || MRF_PART == 6)   // the other window sweeps
+#define MRF_HAS_FWD_DENSE (MRF_PART == 0 || MRF_PART == 7)    // dense sweeps
+#define MRF_HAS_BWD_CHAIN (MRF_PART == 0 || MRF_PART == 8)    // chain backward sweep
+#define MRF_HAS_BWD_PLAIN (MRF_PART == 0 || MRF_PART == 9)    // the other backward sweeps
 
-#if MRF_HAS_FWD
+#if MRF_HAS_FWD || MRF_HAS_FWD_PACKED || MRF_HAS_FWD_DUO || MRF_HAS_FWD_WINDOW || MRF_HAS_FWD_DENSE
 #include "mrfmp_fwd.h"
 #endif
-#if MRF_HAS_BWD
+#if MRF_HAS_BWD || MRF_HAS_BWD_CHAIN || MRF_HAS_BWD_PLAIN
 #include "mrfmp_bwd.h"
+#endif
+#if MRF_HAS_BWD
+#include "mrfmp_bwd_sum.h"
 #endif
 #if MRF_HAS_API
 #include "mrfmp_head.h"
@@ -167,7 +176,7 @@ inline void note_launch(int backward, const char *name, long long grid, int bloc
 
 // Workspace header (the first 256 bytes): float [0] = the scalar edge weight, int at byte 128 = the
 // fault word that a wait between wavefronts raises when it runs out (mrf_wait_again).
-constexpr size_t kFaultOffset = 128;
+[[maybe_unused]] constexpr size_t kFaultOffset = 128;
 // how long after its start a workgroup may still find one of its wavefronts waiting for another, in microseconds
 // (sweeps take milliseconds)
 constexpr int kSpinLimit = 4000000;
@@ -199,7 +208,7 @@ inline int window_width(const mrf_problem *pr)
     return ti <= 2 ? 2 : (ti <= 4 ? 4 : (ti <= 8 ? 8 : (ti <= 12 ? 12 : 16)));
 }
 
-// the three parts
+// the schedules and the entry points
 hipError_t fill(float *dst, long long n, float v, hipStream_t st);
 int run_forward(const mrf_problem *pr, int algo, float *cost, uint8_t *labels, uint8_t *p, uint8_t *q,
                 float *messages, void *workspace, size_t workspace_bytes, void *hip_stream);
@@ -207,78 +216,139 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
                  float *grad_unary, float *grad_w, float *grad_V, void *workspace, size_t workspace_bytes,
                  void *hip_stream);
 
-#if MRF_HAS_FWD
-template <int LP, int MCH, int RMAX, int D>
-hipError_t launch_fwd(const MrfFwdParams &P, int algo, long long blocks, hipStream_t st)
+// launchers of the families, each in the part that instantiates its kernels
+#if MRF_HAS_FWD || MRF_HAS_FWD_PACKED || MRF_HAS_FWD_DUO || MRF_HAS_FWD_WINDOW || MRF_HAS_FWD_DENSE
+hipError_t run_packed(MrfFwdParams &P, int seg, int algo, int rmax, long long scanlines, hipStream_t st);
+hipError_t run_window_duo(MrfFwdParams &P, int algo, int tw, int ni, int ms, long long blocks, hipStream_t st);
+hipError_t run_window_loader(MrfFwdParams &P, int tw, long long blocks, hipStream_t st);
+hipError_t run_window_split(MrfFwdParams &P, int algo, int tw, int ms, long long blocks, hipStream_t st);
+hipError_t run_window_squad(MrfFwdParams &P, int algo, int tw, int ni, int ms, long long blocks, hipStream_t st);
+hipError_t run_window(MrfFwdParams &P, int algo, int tw, int ms, long long blocks, hipStream_t st);
+hipError_t run_dense(MrfFwdParams &P, int algo, long long blocks, hipStream_t st);
+#endif
+#if MRF_HAS_BWD || MRF_HAS_BWD_CHAIN || MRF_HAS_BWD_PLAIN
+#define MRF_BWD_TILE_WAVES 8
+// LDS a workgroup of the chain sweep may take: the whole 160 KB of a compute unit when every
+// compute unit gets at most one workgroup, half when two, else the 64 KB any launch may have.
+inline size_t chain_lds_cap(long long scanlines)
 {
-    note_launch(0, "mrf_fwd_sweep", blocks, 64 * P.NW, "%d,%d,%d,%d,%s", LP, MCH, RMAX, D, algo == MRF_TRWP ? "true" : "false");
-    constexpr int NWMAX = (64 * LP + MCH - 1) / MCH;
-    const size_t lds = (size_t)NWMAX * NWMAX * MCH * sizeof(float) +
-                       (NWMAX > 1 ? (size_t)2 * NWMAX * 64 * LP * sizeof(float2) : 0);
-    if (algo == MRF_TRWP)
-        hipLaunchKernelGGL((mrf_fwd_sweep<LP, MCH, RMAX, D, true>), dim3((unsigned)blocks), dim3(64 * P.NW), lds, st, P);
-    else
-        hipLaunchKernelGGL((mrf_fwd_sweep<LP, MCH, RMAX, D, false>), dim3((unsigned)blocks), dim3(64 * P.NW), lds, st, P);
-    return hipGetLastError();
+    if (scanlines <= 256) return 156 * 1024;
+    if (scanlines <= 512) return 78 * 1024;
+    return 64 * 1024;
 }
 
-template <int LP, int RMAX, int D>
-hipError_t launch_fwd_sliced(const MrfFwdParams &P, int algo, long long blocks, hipStream_t st)
-{
-    note_launch(0, "mrf_fwd_sweep_sliced", blocks, 64 * P.NW, "%d,%d,%d,%s", LP, RMAX, D, algo == MRF_TRWP ? "true" : "false");
-    if (algo == MRF_TRWP)
-        hipLaunchKernelGGL((mrf_fwd_sweep_sliced<LP, RMAX, D, true>), dim3((unsigned)blocks), dim3(64 * P.NW), 0, st, P);
-    else
-        hipLaunchKernelGGL((mrf_fwd_sweep_sliced<LP, RMAX, D, false>), dim3((unsigned)blocks), dim3(64 * P.NW), 0, st, P);
-    return hipGetLastError();
-}
+hipError_t run_bwd_chain(MrfBwdParams &P, int ns, int ni, bool vg, hipStream_t st);
+hipError_t run_bwd_chain_pk(MrfBwdParams &P, int ns, int ni, hipStream_t st);
+hipError_t run_bwd_packed(MrfBwdParams &P, int seg, int ns, hipStream_t st);
+hipError_t run_bwd_plain(MrfBwdParams &P, int ns, long long blocks, size_t lds, hipStream_t st);
+hipError_t run_bwd_tile(MrfBwdParams &P, int ns, long long blocks, size_t lds, hipStream_t st);
+#endif
 
-// source labels per wavefront: small enough that the slice of V fits in registers, large
-// enough that at most 16 wavefronts share a node
-// (33..64 labels: four wavefronts of 16 source labels while the launch leaves SIMD slots free, two of 32 from
-// 2,048 scanlines on: 512 x 512, 64 labels, ISGMR 2.64 -> 2.02 ms; TRWP on 4 x 512 x 512 11.4 -> 8.2 ms, but on
-// 1 x 512 x 512 4.5 against 5.2 ms)
-int pick_mch(int L, int LP, bool many_sources, long long blocks)
+#if MRF_HAS_FWD_PACKED
+template <int SEG, int MU>
+hipError_t launch_packed_mu(const MrfFwdParams &P, int algo, int rmax, long long scanlines, hipStream_t st)
 {
-    static const int allowed[4][5] = { {8, 16, 32, 0, 0}, {8, 12, 16, 24, 32}, {16, 24, 32, 48, 0}, {32, 0, 0, 0, 0} };
-    int want = g_tune_mch;
-    if (want <= 0) want = LP == 1 ? ((L <= 32 || blocks >= 2048) ? 32 : 16) : (LP == 2 ? 24 : 32);
-    if (many_sources) want = (LP <= 2) ? (want < 16 ? 16 : (want == 24 || want == 12 ? 16 : want)) : 32;
-    int best = 0;
-    for (int i = 0; i < 5; ++i) {
-        const int m = allowed[LP - 1][i];
-        if (m == 0) continue;
-        if (many_sources && m != 16 && m != 32) continue;
-        if (best == 0 || mrf_iabs(m - want) < mrf_iabs(best - want)) best = m;
-    }
-    return best;
-}
-
-// pairwise potentials per edge (L <= 64): the table is fetched in two halves of ceil(L/2) rows
-// (rounded up to a multiple of four)
-hipError_t launch_edge(const MrfFwdParams &P, int algo, long long blocks, hipStream_t st)
-{
-    int ms = 0;
-    for (int r = P.r_first; r < P.r_first + P.r_count; ++r)
-        if (P.n_src[r] > ms) ms = P.n_src[r];
-    const int rmax = (ms + 1 <= 4) ? 4 : ((ms + 1 <= 8) ? 8 : 16);
-    const int L = P.g.L;
-    note_launch(0, "mrf_fwd_sweep_edge", blocks, 64, "%d,%d,%s", (L + 7) / 8 * 4, rmax, algo == MRF_TRWP ? "true" : "false");
-    if (L > 64) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(64);
-#define MRF_E(half, rm) \
-    if (L <= 2 * half && rmax == rm) { \
-        if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_edge<half, rm, true>), grid, block, 0, st, P); \
-        else hipLaunchKernelGGL((mrf_fwd_sweep_edge<half, rm, false>), grid, block, 0, st, P); \
+    const unsigned blocks = (unsigned)((scanlines + 64 / SEG - 1) / (64 / SEG));
+    // few wavefronts in the launch: further ones per workgroup for the argmin tables and the stores
+    // (two of them: an index wavefront has more to do per node than the value wavefront)
+    const bool idx = g_tune_pack_idx != 1 && (g_tune_pack_idx == 2 || blocks <= 1024);
+    note_launch(0, "mrf_fwd_sweep_packed", blocks, idx ? 192 : 64, "%d,%d,%d,%d,%s,%d", SEG, MU, rmax, rmax == 4 ? 4 : (rmax == 8 ? 2 : 1),
+                algo == MRF_TRWP ? "true" : "false", idx ? 2 : 0);
+#define MRF_P(rm, d) \
+    if (rmax == rm) { \
+        if (idx) { \
+            if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, MU, rm, d, true, 2>), dim3(blocks), dim3(192), 0, st, P); \
+            else hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, MU, rm, d, false, 2>), dim3(blocks), dim3(192), 0, st, P); \
+        } else { \
+            if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, MU, rm, d, true, 0>), dim3(blocks), dim3(64), 0, st, P); \
+            else hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, MU, rm, d, false, 0>), dim3(blocks), dim3(64), 0, st, P); \
+        } \
         return hipGetLastError(); \
     }
-#define MRF_EH(half) MRF_E(half, 4) MRF_E(half, 8) MRF_E(half, 16)
-    MRF_EH(4) MRF_EH(8) MRF_EH(12) MRF_EH(16) MRF_EH(20) MRF_EH(24) MRF_EH(28) MRF_EH(32)
-#undef MRF_EH
-#undef MRF_E
+    MRF_P(4, 4) MRF_P(8, 2) MRF_P(16, 1)
+#undef MRF_P
     return hipErrorInvalidValue;
 }
 
+template <int SEG>
+hipError_t launch_packed(const MrfFwdParams &P, int algo, int rmax, long long scanlines, hipStream_t st)
+{
+    // three scanlines of up to 21 labels per wavefront: always 24 source labels
+    if constexpr (SEG == 21) {
+        return launch_packed_mu<21, 24>(P, algo, rmax, scanlines, st);
+    } else {
+        // source labels per node: L rounded up to a multiple of four
+        const int mu = (P.g.L + 3) / 4 * 4;
+        if (mu <= SEG - 12) return launch_packed_mu<SEG, SEG - 12>(P, algo, rmax, scanlines, st);
+        if (mu <= SEG - 8) return launch_packed_mu<SEG, SEG - 8>(P, algo, rmax, scanlines, st);
+        if (mu <= SEG - 4) return launch_packed_mu<SEG, SEG - 4>(P, algo, rmax, scanlines, st);
+        return launch_packed_mu<SEG, SEG>(P, algo, rmax, scanlines, st);
+    }
+}
+
+hipError_t run_packed(MrfFwdParams &P, int seg, int algo, int rmax, long long scanlines, hipStream_t st)
+{
+    if (seg == 21) return launch_packed<21>(P, algo, rmax, scanlines, st);
+    return seg == 16 ? launch_packed<16>(P, algo, rmax, scanlines, st) : launch_packed<32>(P, algo, rmax, scanlines, st);
+}
+#endif  // MRF_HAS_FWD_PACKED
+
+#if MRF_HAS_FWD_DUO
+template <int LP, int RMAX, int D, int NI>
+hipError_t launch_window_duo(const MrfFwdParams &P, int algo, int tw, long long blocks, hipStream_t st)
+{
+    note_launch(0, "mrf_fwd_sweep_window_duo", blocks, 64 * (1 + NI), "%d,%d,%d,%s,%d,%d,false", LP, RMAX, D,
+                algo == MRF_TRWP ? "true" : "false", tw, NI);
+#define MRF_W(twv) \
+    if (tw == twv) { \
+        if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_window_duo<LP, RMAX, D, true, twv, NI, false>), dim3((unsigned)blocks), dim3(64 * (1 + NI)), 0, st, P); \
+        else hipLaunchKernelGGL((mrf_fwd_sweep_window_duo<LP, RMAX, D, false, twv, NI, false>), dim3((unsigned)blocks), dim3(64 * (1 + NI)), 0, st, P); \
+        return hipGetLastError(); \
+    }
+    MRF_W(2) MRF_W(4) MRF_W(8) MRF_W(12) MRF_W(16)
+#undef MRF_W
+    return hipErrorInvalidValue;
+}
+
+// value + loader + two index wavefronts (TRWP, up to three other directions)
+template <int LP>
+hipError_t launch_window_loader(const MrfFwdParams &P, int tw, long long blocks, hipStream_t st)
+{
+    note_launch(0, "mrf_fwd_sweep_window_duo", blocks, 256, "%d,4,%d,true,%d,2,true", LP, (LP <= 2 ? 4 : 2), tw);
+#define MRF_W(twv) \
+    if (tw == twv) { \
+        hipLaunchKernelGGL((mrf_fwd_sweep_window_duo<LP, 4, (LP <= 2 ? 4 : 2), true, twv, 2, true>), dim3((unsigned)blocks), dim3(256), 0, st, P); \
+        return hipGetLastError(); \
+    }
+    MRF_W(2) MRF_W(4) MRF_W(8) MRF_W(12) MRF_W(16)
+#undef MRF_W
+    return hipErrorInvalidValue;
+}
+
+hipError_t run_window_loader(MrfFwdParams &P, int tw, long long blocks, hipStream_t st)
+{
+    const int LPw = (P.g.L + 63) / 64;
+    if (LPw == 1) return launch_window_loader<1>(P, tw, blocks, st);
+    if (LPw == 2) return launch_window_loader<2>(P, tw, blocks, st);
+    if (LPw == 3) return launch_window_loader<3>(P, tw, blocks, st);
+    return launch_window_loader<4>(P, tw, blocks, st);
+}
+
+hipError_t run_window_duo(MrfFwdParams &P, int algo, int tw, int ni, int ms, long long blocks, hipStream_t st)
+{
+    const int LPw = (P.g.L + 63) / 64;
+#define MRF_WCASE(lp) \
+    if (LPw == lp && ms + 1 <= 4 && ni == 2) return launch_window_duo<lp, 4, (lp <= 2 ? 4 : 2), 2>(P, algo, tw, blocks, st); \
+    if (LPw == lp && ms + 1 <= 4) return launch_window_duo<lp, 4, (lp <= 2 ? 4 : 2), 1>(P, algo, tw, blocks, st); \
+    if (LPw == lp && ni == 2) return launch_window_duo<lp, 8, (lp <= 2 ? 2 : 1), 2>(P, algo, tw, blocks, st); \
+    if (LPw == lp) return launch_window_duo<lp, 8, (lp <= 2 ? 2 : 1), 1>(P, algo, tw, blocks, st);
+    MRF_WCASE(1) MRF_WCASE(2) MRF_WCASE(3) MRF_WCASE(4)
+#undef MRF_WCASE
+    return hipErrorInvalidValue;
+}
+#endif  // MRF_HAS_FWD_DUO
+
+#if MRF_HAS_FWD_WINDOW
 template <int LP, int RMAX, int D>
 hipError_t launch_window(const MrfFwdParams &P, int algo, int tw, long long blocks, hipStream_t st)
 {
@@ -326,37 +396,6 @@ hipError_t launch_window_many(const MrfFwdParams &P, int tw, long long blocks, h
     return hipErrorInvalidValue;
 }
 
-template <int LP, int RMAX, int D, int NI>
-hipError_t launch_window_duo(const MrfFwdParams &P, int algo, int tw, long long blocks, hipStream_t st)
-{
-    note_launch(0, "mrf_fwd_sweep_window_duo", blocks, 64 * (1 + NI), "%d,%d,%d,%s,%d,%d,false", LP, RMAX, D,
-                algo == MRF_TRWP ? "true" : "false", tw, NI);
-#define MRF_W(twv) \
-    if (tw == twv) { \
-        if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_window_duo<LP, RMAX, D, true, twv, NI, false>), dim3((unsigned)blocks), dim3(64 * (1 + NI)), 0, st, P); \
-        else hipLaunchKernelGGL((mrf_fwd_sweep_window_duo<LP, RMAX, D, false, twv, NI, false>), dim3((unsigned)blocks), dim3(64 * (1 + NI)), 0, st, P); \
-        return hipGetLastError(); \
-    }
-    MRF_W(2) MRF_W(4) MRF_W(8) MRF_W(12) MRF_W(16)
-#undef MRF_W
-    return hipErrorInvalidValue;
-}
-
-// value + loader + two index wavefronts (TRWP, up to three other directions)
-template <int LP>
-hipError_t launch_window_loader(const MrfFwdParams &P, int tw, long long blocks, hipStream_t st)
-{
-    note_launch(0, "mrf_fwd_sweep_window_duo", blocks, 256, "%d,4,%d,true,%d,2,true", LP, (LP <= 2 ? 4 : 2), tw);
-#define MRF_W(twv) \
-    if (tw == twv) { \
-        hipLaunchKernelGGL((mrf_fwd_sweep_window_duo<LP, 4, (LP <= 2 ? 4 : 2), true, twv, 2, true>), dim3((unsigned)blocks), dim3(256), 0, st, P); \
-        return hipGetLastError(); \
-    }
-    MRF_W(2) MRF_W(4) MRF_W(8) MRF_W(12) MRF_W(16)
-#undef MRF_W
-    return hipErrorInvalidValue;
-}
-
 template <int RMAX, int D>
 hipError_t launch_window_split(const MrfFwdParams &P, int algo, int tw, long long blocks, hipStream_t st)
 {
@@ -390,153 +429,96 @@ hipError_t launch_window_squad(const MrfFwdParams &P, int algo, int tw, int ni, 
     return hipErrorInvalidValue;
 }
 
-// Distance from which a truncated pairwise function is constant, or 0 if the window
-// kernel does not apply (dense kind, no truncation inside the label range, wide window).
-
-template <int SEG, int MU>
-hipError_t launch_packed_mu(const MrfFwdParams &P, int algo, int rmax, long long scanlines, hipStream_t st)
+hipError_t run_window_split(MrfFwdParams &P, int algo, int tw, int ms, long long blocks, hipStream_t st)
 {
-    const unsigned blocks = (unsigned)((scanlines + 64 / SEG - 1) / (64 / SEG));
-    // few wavefronts in the launch: further ones per workgroup for the argmin tables and the stores
-    // (two of them: an index wavefront has more to do per node than the value wavefront)
-    const bool idx = g_tune_pack_idx != 1 && (g_tune_pack_idx == 2 || blocks <= 1024);
-    note_launch(0, "mrf_fwd_sweep_packed", blocks, idx ? 192 : 64, "%d,%d,%d,%d,%s,%d", SEG, MU, rmax, rmax == 4 ? 4 : (rmax == 8 ? 2 : 1),
-                algo == MRF_TRWP ? "true" : "false", idx ? 2 : 0);
-#define MRF_P(rm, d) \
-    if (rmax == rm) { \
-        if (idx) { \
-            if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, MU, rm, d, true, 2>), dim3(blocks), dim3(192), 0, st, P); \
-            else hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, MU, rm, d, false, 2>), dim3(blocks), dim3(192), 0, st, P); \
-        } else { \
-            if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, MU, rm, d, true, 0>), dim3(blocks), dim3(64), 0, st, P); \
-            else hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, MU, rm, d, false, 0>), dim3(blocks), dim3(64), 0, st, P); \
-        } \
-        return hipGetLastError(); \
+    if (ms + 1 <= 4) return launch_window_split<4, 4>(P, algo, tw, blocks, st);
+    return launch_window_split<8, 2>(P, algo, tw, blocks, st);
+}
+
+hipError_t run_window_squad(MrfFwdParams &P, int algo, int tw, int ni, int ms, long long blocks, hipStream_t st)
+{
+    if (ms + 1 <= 4) return launch_window_squad<4, 4>(P, algo, tw, ni, blocks, st);
+    return launch_window_squad<8, 2>(P, algo, tw, ni, blocks, st);
+}
+
+hipError_t run_window(MrfFwdParams &P, int algo, int tw, int ms, long long blocks, hipStream_t st)
+{
+    const int LPw = (P.g.L + 63) / 64;
+    if (ms + 1 <= 8) {
+        P.NW = 1;
+        // (nothing but the start term to read: the first iteration of ISGMR, and its later ones after
+        // mrf_isgmr_presum; a deeper prefetch fits in the registers the other sources would take)
+#define MRF_WCASE(lp) \
+        if (LPw == lp && ms == 0 && algo == MRF_ISGMR) return launch_window_one<lp>(P, tw, blocks, st);
+        MRF_WCASE(1) MRF_WCASE(2) MRF_WCASE(3) MRF_WCASE(4)
+#undef MRF_WCASE
+#define MRF_WCASE(lp) \
+        if (LPw == lp && ms + 1 <= 4) return launch_window<lp, 4, (lp <= 2 ? 4 : 2)>(P, algo, tw, blocks, st); \
+        if (LPw == lp) return launch_window<lp, 8, (lp <= 2 ? 2 : 1)>(P, algo, tw, blocks, st);
+        MRF_WCASE(1) MRF_WCASE(2) MRF_WCASE(3) MRF_WCASE(4)
+#undef MRF_WCASE
     }
-    MRF_P(4, 4) MRF_P(8, 2) MRF_P(16, 1)
-#undef MRF_P
+    if (algo == MRF_TRWP && ms + 1 <= 16) {
+        P.NW = 1;
+        if (LPw == 1) return launch_window_many<1>(P, tw, blocks, st);
+        if (LPw == 2) return launch_window_many<2>(P, tw, blocks, st);
+        if (LPw == 3) return launch_window_many<3>(P, tw, blocks, st);
+        if (LPw == 4) return launch_window_many<4>(P, tw, blocks, st);
+    }
     return hipErrorInvalidValue;
 }
+#endif  // MRF_HAS_FWD_WINDOW
 
-template <int SEG>
-hipError_t launch_packed(const MrfFwdParams &P, int algo, int rmax, long long scanlines, hipStream_t st)
+#if MRF_HAS_FWD_DENSE
+template <int LP, int MCH, int RMAX, int D>
+hipError_t launch_fwd(const MrfFwdParams &P, int algo, long long blocks, hipStream_t st)
 {
-    // three scanlines of up to 21 labels per wavefront: always 24 source labels
-    if constexpr (SEG == 21) {
-        return launch_packed_mu<21, 24>(P, algo, rmax, scanlines, st);
-    } else {
-        // source labels per node: L rounded up to a multiple of four
-        const int mu = (P.g.L + 3) / 4 * 4;
-        if (mu <= SEG - 12) return launch_packed_mu<SEG, SEG - 12>(P, algo, rmax, scanlines, st);
-        if (mu <= SEG - 8) return launch_packed_mu<SEG, SEG - 8>(P, algo, rmax, scanlines, st);
-        if (mu <= SEG - 4) return launch_packed_mu<SEG, SEG - 4>(P, algo, rmax, scanlines, st);
-        return launch_packed_mu<SEG, SEG>(P, algo, rmax, scanlines, st);
-    }
+    note_launch(0, "mrf_fwd_sweep", blocks, 64 * P.NW, "%d,%d,%d,%d,%s", LP, MCH, RMAX, D, algo == MRF_TRWP ? "true" : "false");
+    constexpr int NWMAX = (64 * LP + MCH - 1) / MCH;
+    const size_t lds = (size_t)NWMAX * NWMAX * MCH * sizeof(float) +
+                       (NWMAX > 1 ? (size_t)2 * NWMAX * 64 * LP * sizeof(float2) : 0);
+    if (algo == MRF_TRWP)
+        hipLaunchKernelGGL((mrf_fwd_sweep<LP, MCH, RMAX, D, true>), dim3((unsigned)blocks), dim3(64 * P.NW), lds, st, P);
+    else
+        hipLaunchKernelGGL((mrf_fwd_sweep<LP, MCH, RMAX, D, false>), dim3((unsigned)blocks), dim3(64 * P.NW), lds, st, P);
+    return hipGetLastError();
 }
 
-hipError_t dispatch_fwd(MrfFwdParams &P, int algo, int tw, long long blocks, hipStream_t st)
+template <int LP, int RMAX, int D>
+hipError_t launch_fwd_sliced(const MrfFwdParams &P, int algo, long long blocks, hipStream_t st)
 {
-    // few labels: several scanlines per wavefront (dense evaluation), unless the launch is so
-    // small that it is latency bound and a truncated model can use the shorter window step
-    // (up to 16 labels the window templates evaluate 15 candidates, no fewer than the dense step)
-    if (P.Te) return launch_edge(P, algo, blocks, st);
-    // (TRW coefficients per edge: the two one-wavefront-per-scanline sweeps read them)
+    note_launch(0, "mrf_fwd_sweep_sliced", blocks, 64 * P.NW, "%d,%d,%d,%s", LP, RMAX, D, algo == MRF_TRWP ? "true" : "false");
+    if (algo == MRF_TRWP)
+        hipLaunchKernelGGL((mrf_fwd_sweep_sliced<LP, RMAX, D, true>), dim3((unsigned)blocks), dim3(64 * P.NW), 0, st, P);
+    else
+        hipLaunchKernelGGL((mrf_fwd_sweep_sliced<LP, RMAX, D, false>), dim3((unsigned)blocks), dim3(64 * P.NW), 0, st, P);
+    return hipGetLastError();
+}
+
+// source labels per wavefront: small enough that the slice of V fits in registers, large
+// enough that at most 16 wavefronts share a node
+// (33..64 labels: four wavefronts of 16 source labels while the launch leaves SIMD slots free, two of 32 from
+// 2,048 scanlines on: 512 x 512, 64 labels, ISGMR 2.64 -> 2.02 ms; TRWP on 4 x 512 x 512 11.4 -> 8.2 ms, but on
+// 1 x 512 x 512 4.5 against 5.2 ms)
+int pick_mch(int L, int LP, bool many_sources, long long blocks)
+{
+    static const int allowed[4][5] = { {8, 16, 32, 0, 0}, {8, 12, 16, 24, 32}, {16, 24, 32, 48, 0}, {32, 0, 0, 0, 0} };
+    int want = g_tune_mch;
+    if (want <= 0) want = LP == 1 ? ((L <= 32 || blocks >= 2048) ? 32 : 16) : (LP == 2 ? 24 : 32);
+    if (many_sources) want = (LP <= 2) ? (want < 16 ? 16 : (want == 24 || want == 12 ? 16 : want)) : 32;
+    int best = 0;
+    for (int i = 0; i < 5; ++i) {
+        const int m = allowed[LP - 1][i];
+        if (m == 0) continue;
+        if (many_sources && m != 16 && m != 32) continue;
+        if (best == 0 || mrf_iabs(m - want) < mrf_iabs(best - want)) best = m;
+    }
+    return best;
+}
+
+hipError_t run_dense(MrfFwdParams &P, int algo, long long blocks, hipStream_t st)
+{
     const bool generic = P.rho_e != nullptr;
-    if (P.sgm_std) tw = 0;         // standard SGM: the dense sweep is the one that knows it
-    if (!P.sgm_std && !generic && P.g.L <= 32 && g_tune_pack != 1 && (g_tune_pack == 2 || tw == 0 || blocks >= 1024 || P.g.L <= 16)) {
-        int ms = 0;
-        for (int r = P.r_first; r < P.r_first + P.r_count; ++r)
-            if (P.n_src[r] > ms) ms = P.n_src[r];
-        const int rmax = (ms + 1 <= 4) ? 4 : ((ms + 1 <= 8) ? 8 : 16);
-        P.NW = 1;
-        // 17..21 labels (the 21 classes of the segmentation shape): three scanlines per wavefront once the
-        // launch has wavefronts to spare, else two (a latency-bound launch gains nothing from fewer wavefronts)
-        if (P.g.L > 16 && P.g.L <= 21 && g_tune_pack3 != 1 && (g_tune_pack3 == 2 || blocks >= 3072))
-            return launch_packed<21>(P, algo, rmax, blocks, st);
-        return P.g.L <= 16 ? launch_packed<16>(P, algo, rmax, blocks, st) : launch_packed<32>(P, algo, rmax, blocks, st);
-    }
-    if (tw > 0) {
-        const int LPw = (P.g.L + 63) / 64;
-        int ms = 0;
-        for (int r = P.r_first; r < P.r_first + P.r_count; ++r)
-            if (P.n_src[r] > ms) ms = P.n_src[r];
-        // few scanlines in the launch and many labels: spread each node step over one
-        // wavefront per 64 labels
-        // (wide windows over many labels only: otherwise the value/index pair below is faster)
-        // (measured with four directions: window 16, 192 or 256 labels, ISGMR with 1,536 to 3,072 scanlines: 2.2
-        // against 3.8 ms, 2.6 against 5.4 ms, 5.0 against 7.2 ms, 7.3 against 8.2 ms for the next best layout; window
-        // 8, 192 or 256 labels: the value/index pair is ahead, TRWP 2.3 against 3.9 ms, ISGMR 1.3 against 1.6 ms)
-        const int tws = tw == 4 ? 8 : (tw == 12 ? 16 : tw);      // (these two layouts exist for windows 2, 8 and 16: a wider window is as exact)
-        const bool split = !generic && LPw > 1 && g_tune_split != 1 &&
-                           (g_tune_split == 2 || (LPw >= 3 && tws >= 16 && blocks * LPw <= 16384));
-        if (ms + 1 <= 8 && split && g_tune_squad != 1 && (g_tune_squad == 2 || blocks <= 512)) {
-            // the value wavefronts of the split layout, with the index work on wavefronts of their own
-            P.NW = LPw;
-            const int ni = (g_tune_squad_ni == 4 || g_tune_squad_ni == 8) ? g_tune_squad_ni : 8;
-            if (ms + 1 <= 4) return launch_window_squad<4, 4>(P, algo, tws, ni, blocks, st);
-            return launch_window_squad<8, 2>(P, algo, tws, ni, blocks, st);
-        }
-        if (ms + 1 <= 8 && split) {
-            P.NW = LPw;
-            if (ms + 1 <= 4) return launch_window_split<4, 4>(P, algo, tws, blocks, st);
-            return launch_window_split<8, 2>(P, algo, tws, blocks, st);
-        }
-        // few scanlines: a second wavefront per scanline takes the argmin tables and the
-        // stores off the dependency chain
-        // (its addressing wants a node step times L in 32 bits)
-        bool step_fits = true;
-        for (int r = P.r_first; r < P.r_first + P.r_count; ++r) {
-            const long long st = ((long long)mrf_iabs(P.g.dh[r]) * P.g.W + mrf_iabs(P.g.dw[r])) * P.g.L;
-            if (st > 0x7fffffffLL) step_fits = false;
-        }
-        // (a second wavefront per scanline pays while the scanlines alone leave SIMD slots free; measured on
-        // square grids with four directions: ISGMR at 2,048 scanlines 1.41 ms with it against 1.52 ms without,
-        // at 2,560 scanlines 2.74 against 2.21 ms with 96 labels but 1.27 against 1.37 ms with 40; TRWP at 2,048
-        // scanlines 4.92 against 4.32 ms)
-        const long long duo_max = algo == MRF_TRWP ? 1536 : (LPw == 1 ? 3072 : 2048);
-        const bool duo = !generic && step_fits && g_tune_duo != 1 && (g_tune_duo == 2 || blocks <= duo_max);
-        if (ms + 1 <= 8 && duo) {
-            P.NW = 1;
-            // two index wavefronts while the launch is far from filling the machine
-            const int ni = g_tune_duo_ni ? g_tune_duo_ni : (blocks <= 1536 ? 2 : 1);
-            // TRWP launches that leave SIMDs idle: a loader wavefront in front of the value wavefront
-            if (algo == MRF_TRWP && ms + 1 <= 4 && ni == 2 && g_tune_loader != 1 &&
-                (g_tune_loader == 2 || blocks <= 512)) {
-                if (LPw == 1) return launch_window_loader<1>(P, tw, blocks, st);
-                if (LPw == 2) return launch_window_loader<2>(P, tw, blocks, st);
-                if (LPw == 3) return launch_window_loader<3>(P, tw, blocks, st);
-                if (LPw == 4) return launch_window_loader<4>(P, tw, blocks, st);
-            }
-#define MRF_WCASE(lp) \
-            if (LPw == lp && ms + 1 <= 4 && ni == 2) return launch_window_duo<lp, 4, (lp <= 2 ? 4 : 2), 2>(P, algo, tw, blocks, st); \
-            if (LPw == lp && ms + 1 <= 4) return launch_window_duo<lp, 4, (lp <= 2 ? 4 : 2), 1>(P, algo, tw, blocks, st); \
-            if (LPw == lp && ni == 2) return launch_window_duo<lp, 8, (lp <= 2 ? 2 : 1), 2>(P, algo, tw, blocks, st); \
-            if (LPw == lp) return launch_window_duo<lp, 8, (lp <= 2 ? 2 : 1), 1>(P, algo, tw, blocks, st);
-            MRF_WCASE(1) MRF_WCASE(2) MRF_WCASE(3) MRF_WCASE(4)
-#undef MRF_WCASE
-        }
-        if (ms + 1 <= 8) {
-            P.NW = 1;
-            // (nothing but the start term to read: the first iteration of ISGMR, and its later ones after
-            // mrf_isgmr_presum; a deeper prefetch fits in the registers the other sources would take)
-#define MRF_WCASE(lp) \
-            if (LPw == lp && ms == 0 && algo == MRF_ISGMR) return launch_window_one<lp>(P, tw, blocks, st);
-            MRF_WCASE(1) MRF_WCASE(2) MRF_WCASE(3) MRF_WCASE(4)
-#undef MRF_WCASE
-#define MRF_WCASE(lp) \
-            if (LPw == lp && ms + 1 <= 4) return launch_window<lp, 4, (lp <= 2 ? 4 : 2)>(P, algo, tw, blocks, st); \
-            if (LPw == lp) return launch_window<lp, 8, (lp <= 2 ? 2 : 1)>(P, algo, tw, blocks, st);
-            MRF_WCASE(1) MRF_WCASE(2) MRF_WCASE(3) MRF_WCASE(4)
-#undef MRF_WCASE
-        }
-        if (algo == MRF_TRWP && ms + 1 <= 16) {
-            P.NW = 1;
-            if (LPw == 1) return launch_window_many<1>(P, tw, blocks, st);
-            if (LPw == 2) return launch_window_many<2>(P, tw, blocks, st);
-            if (LPw == 3) return launch_window_many<3>(P, tw, blocks, st);
-            if (LPw == 4) return launch_window_many<4>(P, tw, blocks, st);
-        }
-    }
     const int L = P.g.L;
     const int LP = (L + 63) / 64;
     int max_src = 0;
@@ -578,6 +560,110 @@ hipError_t dispatch_fwd(MrfFwdParams &P, int algo, int tw, long long blocks, hip
 #undef MRF_CASE
 #undef MRF_CASE_MANY
     return hipErrorInvalidValue;
+}
+#endif  // MRF_HAS_FWD_DENSE
+
+#if MRF_HAS_FWD
+// pairwise potentials per edge (L <= 64): the table is fetched in two halves of ceil(L/2) rows
+// (rounded up to a multiple of four)
+hipError_t launch_edge(const MrfFwdParams &P, int algo, long long blocks, hipStream_t st)
+{
+    int ms = 0;
+    for (int r = P.r_first; r < P.r_first + P.r_count; ++r)
+        if (P.n_src[r] > ms) ms = P.n_src[r];
+    const int rmax = (ms + 1 <= 4) ? 4 : ((ms + 1 <= 8) ? 8 : 16);
+    const int L = P.g.L;
+    note_launch(0, "mrf_fwd_sweep_edge", blocks, 64, "%d,%d,%s", (L + 7) / 8 * 4, rmax, algo == MRF_TRWP ? "true" : "false");
+    if (L > 64) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block(64);
+#define MRF_E(half, rm) \
+    if (L <= 2 * half && rmax == rm) { \
+        if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_edge<half, rm, true>), grid, block, 0, st, P); \
+        else hipLaunchKernelGGL((mrf_fwd_sweep_edge<half, rm, false>), grid, block, 0, st, P); \
+        return hipGetLastError(); \
+    }
+#define MRF_EH(half) MRF_E(half, 4) MRF_E(half, 8) MRF_E(half, 16)
+    MRF_EH(4) MRF_EH(8) MRF_EH(12) MRF_EH(16) MRF_EH(20) MRF_EH(24) MRF_EH(28) MRF_EH(32)
+#undef MRF_EH
+#undef MRF_E
+    return hipErrorInvalidValue;
+}
+
+hipError_t dispatch_fwd(MrfFwdParams &P, int algo, int tw, long long blocks, hipStream_t st)
+{
+    // few labels: several scanlines per wavefront (dense evaluation), unless the launch is so
+    // small that it is latency bound and a truncated model can use the shorter window step
+    // (up to 16 labels the window templates evaluate 15 candidates, no fewer than the dense step)
+    if (P.Te) return launch_edge(P, algo, blocks, st);
+    // (TRW coefficients per edge: the two one-wavefront-per-scanline sweeps read them)
+    const bool generic = P.rho_e != nullptr;
+    if (P.sgm_std) tw = 0;         // standard SGM: the dense sweep is the one that knows it
+    if (!P.sgm_std && !generic && P.g.L <= 32 && g_tune_pack != 1 && (g_tune_pack == 2 || tw == 0 || blocks >= 1024 || P.g.L <= 16)) {
+        int ms = 0;
+        for (int r = P.r_first; r < P.r_first + P.r_count; ++r)
+            if (P.n_src[r] > ms) ms = P.n_src[r];
+        const int rmax = (ms + 1 <= 4) ? 4 : ((ms + 1 <= 8) ? 8 : 16);
+        P.NW = 1;
+        // 17..21 labels (the 21 classes of the segmentation shape): three scanlines per wavefront once the
+        // launch has wavefronts to spare, else two (a latency-bound launch gains nothing from fewer wavefronts)
+        if (P.g.L > 16 && P.g.L <= 21 && g_tune_pack3 != 1 && (g_tune_pack3 == 2 || blocks >= 3072))
+            return run_packed(P, 21, algo, rmax, blocks, st);
+        return run_packed(P, P.g.L <= 16 ? 16 : 32, algo, rmax, blocks, st);
+    }
+    if (tw > 0) {
+        const int LPw = (P.g.L + 63) / 64;
+        int ms = 0;
+        for (int r = P.r_first; r < P.r_first + P.r_count; ++r)
+            if (P.n_src[r] > ms) ms = P.n_src[r];
+        // few scanlines in the launch and many labels: spread each node step over one
+        // wavefront per 64 labels
+        // (wide windows over many labels only: otherwise the value/index pair below is faster)
+        // (measured with four directions: window 16, 192 or 256 labels, ISGMR with 1,536 to 3,072 scanlines: 2.2
+        // against 3.8 ms, 2.6 against 5.4 ms, 5.0 against 7.2 ms, 7.3 against 8.2 ms for the next best layout; window
+        // 8, 192 or 256 labels: the value/index pair is ahead, TRWP 2.3 against 3.9 ms, ISGMR 1.3 against 1.6 ms)
+        const int tws = tw == 4 ? 8 : (tw == 12 ? 16 : tw);      // (these two layouts exist for windows 2, 8 and 16: a wider window is as exact)
+        const bool split = !generic && LPw > 1 && g_tune_split != 1 &&
+                           (g_tune_split == 2 || (LPw >= 3 && tws >= 16 && blocks * LPw <= 16384));
+        if (ms + 1 <= 8 && split && g_tune_squad != 1 && (g_tune_squad == 2 || blocks <= 512)) {
+            // the value wavefronts of the split layout, with the index work on wavefronts of their own
+            P.NW = LPw;
+            const int ni = (g_tune_squad_ni == 4 || g_tune_squad_ni == 8) ? g_tune_squad_ni : 8;
+            return run_window_squad(P, algo, tws, ni, ms, blocks, st);
+        }
+        if (ms + 1 <= 8 && split) {
+            P.NW = LPw;
+            return run_window_split(P, algo, tws, ms, blocks, st);
+        }
+        // few scanlines: a second wavefront per scanline takes the argmin tables and the
+        // stores off the dependency chain
+        // (its addressing wants a node step times L in 32 bits)
+        bool step_fits = true;
+        for (int r = P.r_first; r < P.r_first + P.r_count; ++r) {
+            const long long st = ((long long)mrf_iabs(P.g.dh[r]) * P.g.W + mrf_iabs(P.g.dw[r])) * P.g.L;
+            if (st > 0x7fffffffLL) step_fits = false;
+        }
+        // (a second wavefront per scanline pays while the scanlines alone leave SIMD slots free; measured on
+        // square grids with four directions: ISGMR at 2,048 scanlines 1.41 ms with it against 1.52 ms without,
+        // at 2,560 scanlines 2.74 against 2.21 ms with 96 labels but 1.27 against 1.37 ms with 40; TRWP at 2,048
+        // scanlines 4.92 against 4.32 ms)
+        const long long duo_max = algo == MRF_TRWP ? 1536 : (LPw == 1 ? 3072 : 2048);
+        const bool duo = !generic && step_fits && g_tune_duo != 1 && (g_tune_duo == 2 || blocks <= duo_max);
+        if (ms + 1 <= 8 && duo) {
+            P.NW = 1;
+            // two index wavefronts while the launch is far from filling the machine
+            const int ni = g_tune_duo_ni ? g_tune_duo_ni : (blocks <= 1536 ? 2 : 1);
+            // TRWP launches that leave SIMDs idle: a loader wavefront in front of the value wavefront
+            if (algo == MRF_TRWP && ms + 1 <= 4 && ni == 2 && g_tune_loader != 1 &&
+                (g_tune_loader == 2 || blocks <= 512))
+                return run_window_loader(P, tw, blocks, st);
+            return run_window_duo(P, algo, tw, ni, ms, blocks, st);
+        }
+        if (ms + 1 <= 8 || (algo == MRF_TRWP && ms + 1 <= 16)) {
+            P.NW = 1;
+            return run_window(P, algo, tw, ms, blocks, st);
+        }
+    }
+    return run_dense(P, algo, blocks, st);
 }
 
 // Which message arrays enter h at the previous node, in the order they are summed, for the
@@ -725,81 +811,7 @@ int run_forward(const mrf_problem *pr, int algo, float *cost, uint8_t *labels, u
 
 #endif  // MRF_HAS_FWD
 
-#if MRF_HAS_BWD
-template <int LP, int NS, int D>
-hipError_t launch_bwd(const MrfBwdParams &P, long long blocks, size_t lds, hipStream_t st)
-{
-    const dim3 grid((unsigned)blocks), block(64 * MRF_BWD_WAVES);
-    const bool hot = !(P.rho_e || P.gE) && !(P.gw && P.v_mode == 0) && P.hot_label;
-    const bool no_unary = hot && NS == 1 && P.unary_dir < 0;
-    note_launch(1, "mrf_bwd_sweep", blocks, 64 * MRF_BWD_WAVES, "%d,%d,%d,%s,%s,%s%s", LP, NS, D,
-                (P.gw && P.v_mode == 0) ? "true" : "false", hot ? "true" : "false",
-                (P.rho_e || P.gE) ? "true" : "false", no_unary ? ",false" : "");
-    if (P.rho_e && P.gw && P.v_mode == 0)
-        hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, true, false, true>), grid, block, lds, st, P);
-    else if (P.rho_e || P.gE)
-        hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, false, false, true>), grid, block, lds, st, P);
-    else if (P.gw && P.v_mode == 0)
-        hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, true, false>), grid, block, lds, st, P);
-    else if (no_unary) {
-        if constexpr (NS == 1) {
-            if (P.g.L == 64 * LP)
-                hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, false, true, false, false, MRF_BWD_WAVES, true>), grid, block, lds, st, P);
-            else
-                hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, false, true, false, false>), grid, block, lds, st, P);
-        }
-    } else if (P.hot_label)
-        hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, false, true>), grid, block, lds, st, P);
-    else
-        hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, false, false>), grid, block, lds, st, P);
-    return hipGetLastError();
-}
-
-// The V gradient in one LDS table per workgroup of MRF_BWD_TILE_WAVES wavefronts (33..128 labels)
-#define MRF_BWD_TILE_WAVES 8
-template <int LP, int NS, int D>
-hipError_t launch_bwd_tile(const MrfBwdParams &P, long long blocks, size_t lds, hipStream_t st)
-{
-    const dim3 grid((unsigned)blocks), block(64 * MRF_BWD_TILE_WAVES);
-    const bool vg = P.gw && P.v_mode == 0;
-    note_launch(1, "mrf_bwd_sweep", blocks, 64 * MRF_BWD_TILE_WAVES, "%d,%d,%d,%s,false,false,true,%d", LP, NS, D, vg ? "true" : "false",
-                MRF_BWD_TILE_WAVES);
-#define MRF_T_GO(...) \
-    do { \
-        if (lds > 64 * 1024) { \
-            const hipError_t ea_ = hipFuncSetAttribute(reinterpret_cast<const void *>(&__VA_ARGS__), \
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
-            if (ea_ != hipSuccess) return ea_; \
-        } \
-        hipLaunchKernelGGL((__VA_ARGS__), grid, block, lds, st, P); \
-    } while (0)
-    if (vg) MRF_T_GO(mrf_bwd_sweep<LP, NS, D, true, false, false, true, MRF_BWD_TILE_WAVES>);
-    else MRF_T_GO(mrf_bwd_sweep<LP, NS, D, false, false, false, true, MRF_BWD_TILE_WAVES>);
-#undef MRF_T_GO
-    return hipGetLastError();
-}
-
-template <int NS, int D>
-hipError_t launch_bwd_split(const MrfBwdParams &P, long long blocks, size_t lds, hipStream_t st)
-{
-    const dim3 grid((unsigned)blocks), block(64u * (unsigned)((P.g.L + 63) / 64));
-    note_launch(1, "mrf_bwd_sweep_split", blocks, (int)block.x, "%d,%d,%s", NS, D, (P.gw && P.v_mode == 0) ? "true" : "false");
-    if (P.gw && P.v_mode == 0)
-        hipLaunchKernelGGL((mrf_bwd_sweep_split<NS, D, true>), grid, block, lds, st, P);
-    else
-        hipLaunchKernelGGL((mrf_bwd_sweep_split<NS, D, false>), grid, block, lds, st, P);
-    return hipGetLastError();
-}
-
-// LDS a workgroup of the chain sweep may take: the whole 160 KB of a compute unit when every
-// compute unit gets at most one workgroup, half when two, else the 64 KB any launch may have.
-inline size_t chain_lds_cap(long long scanlines)
-{
-    if (scanlines <= 256) return 156 * 1024;
-    if (scanlines <= 512) return 78 * 1024;
-    return 64 * 1024;
-}
-
+#if MRF_HAS_BWD_CHAIN
 template <int LP, int NS, int D>
 hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t st)
 {
@@ -848,6 +860,72 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
     return hipErrorInvalidValue;
 }
 
+hipError_t run_bwd_chain(MrfBwdParams &P, int ns, int ni, bool vg, hipStream_t st)
+{
+    const int LP = (P.g.L + 63) / 64;
+#define MRF_CCASE(lp) \
+    if (LP == lp && ns == 1) return launch_bwd_chain<lp, 1, 2>(P, ni, vg, st); \
+    if (LP == lp && ns == 4) return launch_bwd_chain<lp, 4, (lp <= 2 ? 2 : 1)>(P, ni, vg, st); \
+    if (LP == lp && ns == 8) return launch_bwd_chain<lp, 8, 1>(P, ni, vg, st);
+    MRF_CCASE(1) MRF_CCASE(2) MRF_CCASE(3) MRF_CCASE(4)
+#undef MRF_CCASE
+    return hipErrorInvalidValue;
+}
+#endif  // MRF_HAS_BWD_CHAIN
+
+#if MRF_HAS_BWD_PLAIN
+template <int LP, int NS, int D>
+hipError_t launch_bwd(const MrfBwdParams &P, long long blocks, size_t lds, hipStream_t st)
+{
+    const dim3 grid((unsigned)blocks), block(64 * MRF_BWD_WAVES);
+    const bool hot = !(P.rho_e || P.gE) && !(P.gw && P.v_mode == 0) && P.hot_label;
+    const bool no_unary = hot && NS == 1 && P.unary_dir < 0;
+    note_launch(1, "mrf_bwd_sweep", blocks, 64 * MRF_BWD_WAVES, "%d,%d,%d,%s,%s,%s%s", LP, NS, D,
+                (P.gw && P.v_mode == 0) ? "true" : "false", hot ? "true" : "false",
+                (P.rho_e || P.gE) ? "true" : "false", no_unary ? ",false" : "");
+    if (P.rho_e && P.gw && P.v_mode == 0)
+        hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, true, false, true>), grid, block, lds, st, P);
+    else if (P.rho_e || P.gE)
+        hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, false, false, true>), grid, block, lds, st, P);
+    else if (P.gw && P.v_mode == 0)
+        hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, true, false>), grid, block, lds, st, P);
+    else if (no_unary) {
+        if constexpr (NS == 1) {
+            if (P.g.L == 64 * LP)
+                hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, false, true, false, false, MRF_BWD_WAVES, true>), grid, block, lds, st, P);
+            else
+                hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, false, true, false, false>), grid, block, lds, st, P);
+        }
+    } else if (P.hot_label)
+        hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, false, true>), grid, block, lds, st, P);
+    else
+        hipLaunchKernelGGL((mrf_bwd_sweep<LP, NS, D, false, false>), grid, block, lds, st, P);
+    return hipGetLastError();
+}
+
+// The V gradient in one LDS table per workgroup of MRF_BWD_TILE_WAVES wavefronts (33..128 labels)
+template <int LP, int NS, int D>
+hipError_t launch_bwd_tile(const MrfBwdParams &P, long long blocks, size_t lds, hipStream_t st)
+{
+    const dim3 grid((unsigned)blocks), block(64 * MRF_BWD_TILE_WAVES);
+    const bool vg = P.gw && P.v_mode == 0;
+    note_launch(1, "mrf_bwd_sweep", blocks, 64 * MRF_BWD_TILE_WAVES, "%d,%d,%d,%s,false,false,true,%d", LP, NS, D, vg ? "true" : "false",
+                MRF_BWD_TILE_WAVES);
+#define MRF_T_GO(...) \
+    do { \
+        if (lds > 64 * 1024) { \
+            const hipError_t ea_ = hipFuncSetAttribute(reinterpret_cast<const void *>(&__VA_ARGS__), \
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+            if (ea_ != hipSuccess) return ea_; \
+        } \
+        hipLaunchKernelGGL((__VA_ARGS__), grid, block, lds, st, P); \
+    } while (0)
+    if (vg) MRF_T_GO(mrf_bwd_sweep<LP, NS, D, true, false, false, true, MRF_BWD_TILE_WAVES>);
+    else MRF_T_GO(mrf_bwd_sweep<LP, NS, D, false, false, false, true, MRF_BWD_TILE_WAVES>);
+#undef MRF_T_GO
+    return hipGetLastError();
+}
+
 // two scanlines of up to 32 labels per workgroup: chain wavefront + ni helpers
 template <int NS, int D>
 hipError_t launch_bwd_chain_pk(const MrfBwdParams &P, int ni, hipStream_t st)
@@ -885,6 +963,59 @@ hipError_t launch_bwd_packed(const MrfBwdParams &P, int ns, hipStream_t st)
     else if (ns == 4) hipLaunchKernelGGL((mrf_bwd_sweep_packed<SEG, 4, 4>), grid, block, lds, st, P);
     else if (ns == 8) hipLaunchKernelGGL((mrf_bwd_sweep_packed<SEG, 8, 2>), grid, block, lds, st, P);
     else hipLaunchKernelGGL((mrf_bwd_sweep_packed<SEG, 16, 1>), grid, block, lds, st, P);
+    return hipGetLastError();
+}
+
+hipError_t run_bwd_chain_pk(MrfBwdParams &P, int ns, int ni, hipStream_t st)
+{
+    if (ns == 1) return launch_bwd_chain_pk<1, 2>(P, ni, st);
+    if (ns == 4) return launch_bwd_chain_pk<4, 2>(P, ni, st);
+    return launch_bwd_chain_pk<8, 1>(P, ni, st);
+}
+
+hipError_t run_bwd_packed(MrfBwdParams &P, int seg, int ns, hipStream_t st)
+{
+    if (seg == 21) return launch_bwd_packed<21>(P, ns, st);
+    return seg == 16 ? launch_bwd_packed<16>(P, ns, st) : launch_bwd_packed<32>(P, ns, st);
+}
+
+hipError_t run_bwd_tile(MrfBwdParams &P, int ns, long long blocks, size_t lds, hipStream_t st)
+{
+    const int LP = (P.g.L + 63) / 64;
+#define MRF_TCASE(lp) \
+    if (LP == lp && ns == 1) return launch_bwd_tile<lp, 1, 4>(P, blocks, lds, st); \
+    if (LP == lp && ns == 4) return launch_bwd_tile<lp, 4, 4>(P, blocks, lds, st); \
+    if (LP == lp && ns == 8) return launch_bwd_tile<lp, 8, 2>(P, blocks, lds, st); \
+    if (LP == lp && ns == 16) return launch_bwd_tile<lp, 16, 1>(P, blocks, lds, st);
+    MRF_TCASE(1) MRF_TCASE(2)
+#undef MRF_TCASE
+    return hipErrorInvalidValue;
+}
+
+hipError_t run_bwd_plain(MrfBwdParams &P, int ns, long long blocks, size_t lds, hipStream_t st)
+{
+    const int LP = (P.g.L + 63) / 64;
+#define MRF_BCASE(lp) \
+    if (LP == lp && ns == 1) return launch_bwd<lp, 1, (lp >= 3 ? 2 : 4)>(P, blocks, lds, st); \
+    if (LP == lp && ns == 4) return launch_bwd<lp, 4, (lp <= 2 ? 4 : 2)>(P, blocks, lds, st); \
+    if (LP == lp && ns == 8) return launch_bwd<lp, 8, 2>(P, blocks, lds, st); \
+    if (LP == lp && ns == 16) return launch_bwd<lp, 16, 1>(P, blocks, lds, st);
+    MRF_BCASE(1) MRF_BCASE(2) MRF_BCASE(3) MRF_BCASE(4)
+#undef MRF_BCASE
+    return hipErrorInvalidValue;
+}
+#endif  // MRF_HAS_BWD_PLAIN
+
+#if MRF_HAS_BWD
+template <int NS, int D>
+hipError_t launch_bwd_split(const MrfBwdParams &P, long long blocks, size_t lds, hipStream_t st)
+{
+    const dim3 grid((unsigned)blocks), block(64u * (unsigned)((P.g.L + 63) / 64));
+    note_launch(1, "mrf_bwd_sweep_split", blocks, (int)block.x, "%d,%d,%s", NS, D, (P.gw && P.v_mode == 0) ? "true" : "false");
+    if (P.gw && P.v_mode == 0)
+        hipLaunchKernelGGL((mrf_bwd_sweep_split<NS, D, true>), grid, block, lds, st, P);
+    else
+        hipLaunchKernelGGL((mrf_bwd_sweep_split<NS, D, false>), grid, block, lds, st, P);
     return hipGetLastError();
 }
 
@@ -962,9 +1093,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
         const int nip = (g_tune_chain_ni == 2 || g_tune_chain_ni == 4 || g_tune_chain_ni == 8) ? g_tune_chain_ni
                                                                                             : (P.total_scanlines <= 1536 ? 8 : 4);
         if (!(gv_any && (P.total_scanlines + 1) / 2 * 2 > grad_slots(L))) {
-            if (ns == 1) return launch_bwd_chain_pk<1, 2>(P, nip, st);
-            if (ns == 4) return launch_bwd_chain_pk<4, 2>(P, nip, st);
-            return launch_bwd_chain_pk<8, 1>(P, nip, st);
+            return run_bwd_chain_pk(P, ns, nip, st);
         }
     }
     // few labels: several scanlines per wavefront, once there are enough of them
@@ -974,8 +1103,8 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
         // three scanlines per wavefront: measured slower than two on the segmentation shape (the LDS
         // scatter, not instruction issue, bounds this sweep), so only on request
         if (L > 16 && L <= 21 && g_tune_pack3 == 2)
-            return launch_bwd_packed<21>(P, ns, st);
-        return L <= 16 ? launch_bwd_packed<16>(P, ns, st) : launch_bwd_packed<32>(P, ns, st);
+            return run_bwd_packed(P, 21, ns, st);
+        return run_bwd_packed(P, L <= 16 ? 16 : 32, ns, st);
     }
     if (chain) {
         // truncated models: the chain wavefront sums the lanes of the most popular scatter target
@@ -986,10 +1115,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
         if (gv_apart) {
             double *const slots = P.gV;
             P.gV = nullptr; P.gstore = P.gstore_buf;
-            hipError_t e = hipErrorInvalidValue;
-            if (ns == 1) e = launch_bwd_chain<2, 1, 2>(P, ni, vg, st);
-            else if (ns == 4) e = launch_bwd_chain<2, 4, 2>(P, ni, vg, st);
-            else if (ns == 8) e = launch_bwd_chain<2, 8, 1>(P, ni, vg, st);
+            const hipError_t e = run_bwd_chain(P, ns, ni, vg, st);
             P.gV = slots; P.gstore = nullptr;
             if (e != hipSuccess) return e;
             MrfGvParams G;
@@ -1006,12 +1132,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
             hipLaunchKernelGGL(mrf_bwd_gv_from_g, dim3(256), dim3(512), glds, st, G);
             return hipGetLastError();
         }
-#define MRF_CCASE(lp) \
-        if (LP == lp && ns == 1) return launch_bwd_chain<lp, 1, 2>(P, ni, vg, st); \
-        if (LP == lp && ns == 4) return launch_bwd_chain<lp, 4, (lp <= 2 ? 2 : 1)>(P, ni, vg, st); \
-        if (LP == lp && ns == 8) return launch_bwd_chain<lp, 8, 1>(P, ni, vg, st);
-        MRF_CCASE(1) MRF_CCASE(2) MRF_CCASE(3) MRF_CCASE(4)
-#undef MRF_CCASE
+        return run_bwd_chain(P, ns, ni, vg, st);
     }
     // few scanlines and many labels: one wavefront per 64 labels
     const bool split = !generic && LP >= 3 && g_tune_split != 1 && ns <= 8 &&
@@ -1034,23 +1155,10 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
             if (tblocks > grad_slots(L)) tblocks = grad_slots(L);
             P.gv_lds = 2;
             P.hot_label = 0;
-#define MRF_TCASE(lp) \
-            if (LP == lp && ns == 1) return launch_bwd_tile<lp, 1, 4>(P, tblocks, tlds, st); \
-            if (LP == lp && ns == 4) return launch_bwd_tile<lp, 4, 4>(P, tblocks, tlds, st); \
-            if (LP == lp && ns == 8) return launch_bwd_tile<lp, 8, 2>(P, tblocks, tlds, st); \
-            if (LP == lp && ns == 16) return launch_bwd_tile<lp, 16, 1>(P, tblocks, tlds, st);
-            MRF_TCASE(1) MRF_TCASE(2)
-#undef MRF_TCASE
+            return run_bwd_tile(P, ns, tblocks, tlds, st);
         }
     }
-#define MRF_BCASE(lp) \
-    if (LP == lp && ns == 1) return launch_bwd<lp, 1, (lp >= 3 ? 2 : 4)>(P, blocks, lds, st); \
-    if (LP == lp && ns == 4) return launch_bwd<lp, 4, (lp <= 2 ? 4 : 2)>(P, blocks, lds, st); \
-    if (LP == lp && ns == 8) return launch_bwd<lp, 8, 2>(P, blocks, lds, st); \
-    if (LP == lp && ns == 16) return launch_bwd<lp, 16, 1>(P, blocks, lds, st);
-    MRF_BCASE(1) MRF_BCASE(2) MRF_BCASE(3) MRF_BCASE(4)
-#undef MRF_BCASE
-    return hipErrorInvalidValue;
+    return run_bwd_plain(P, ns, blocks, lds, st);
 }
 
 hipError_t fill(float *dst, long long n, float v, hipStream_t st)
