@@ -41,8 +41,8 @@
 namespace mrf_host {
 
 constexpr size_t kAlign = 256;
-// wavefront-private V-gradient accumulators: many small ones (flushed from LDS once per
-// wavefront) for few labels, fewer large ones (updated in place) otherwise
+// private V-gradient accumulators, one per workgroup or wavefront of a sweep: many small ones (flushed from LDS
+// once) for few labels, fewer large ones otherwise
 inline long long grad_slots(int L) { return L <= 32 ? 16384 : 1024; }
 
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -822,7 +822,7 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
     note_launch(1, "mrf_bwd_sweep_chain", P.total_scanlines, 64 * (1 + ni), "%d,%d,%d,%d,%s,%s,%s", LP, NS, D, ni,
                 (!(LP == 1 && gv) && vg) ? "true" : "false", ((LP == 1 && gv) || gs) ? "true" : "false",
                 (!(LP == 1 && gv) && !gs && !vg && P.hot_label) ? "true" : "false");
-    if (gv && (LP != 1 || P.total_scanlines * ni > grad_slots(P.g.L))) return hipErrorInvalidValue;
+    if (gv && (LP != 1 || P.total_scanlines > grad_slots(P.g.L))) return hipErrorInvalidValue;
     const size_t lds = mrf_bwd_chain_lds_bytes(LP, ni, P.g.L, P.unary_dir >= 0, vg, gv || gs);
     if (lds > chain_lds_cap(P.total_scanlines)) return hipErrorInvalidValue;
     // (more than 64 KB of dynamic LDS has to be announced per kernel)
@@ -933,7 +933,7 @@ hipError_t launch_bwd_chain_pk(const MrfBwdParams &P, int ni, hipStream_t st)
     const long long blocks = (P.total_scanlines + 1) / 2;
     const bool gv = P.gV != nullptr;
     note_launch(1, "mrf_bwd_sweep_chain_pk", blocks, 64 * (1 + ni), "%d,%d,%d,%s", NS, D, ni, gv ? "true" : "false");
-    if (gv && blocks * 2 > grad_slots(P.g.L)) return hipErrorInvalidValue;
+    if (gv && blocks > grad_slots(P.g.L)) return hipErrorInvalidValue;
     const size_t lds = mrf_bwd_chain_pk_lds_bytes(ni, P.g.L, gv);
     if (lds > 64 * 1024) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(64 * (1 + ni));
@@ -954,7 +954,7 @@ hipError_t launch_bwd_packed(const MrfBwdParams &P, int ns, hipStream_t st)
     constexpr int NSEG = 64 / SEG;
     const int L = P.g.L;
     long long blocks = (P.total_scanlines + NSEG - 1) / NSEG;
-    if (P.gV && blocks > grad_slots(L) / NSEG) blocks = grad_slots(L) / NSEG;
+    if (P.gV && blocks > grad_slots(L)) blocks = grad_slots(L);
     note_launch(1, "mrf_bwd_sweep_packed", blocks, 64, "%d,%d,%d", SEG, ns, ns <= 4 ? 4 : (ns == 8 ? 2 : 1));
     const size_t lds = sizeof(double) * (64 + (P.gV ? (size_t)NSEG * L * L : 0)) + sizeof(float) * (size_t)L * L;
     const dim3 grid((unsigned)blocks), block(64);
@@ -1019,6 +1019,8 @@ hipError_t launch_bwd_split(const MrfBwdParams &P, long long blocks, size_t lds,
     return hipGetLastError();
 }
 
+#define MRF_GV_BLOCKS 256      // workgroups (and slots) of mrf_bwd_gv_from_g
+
 hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
 {
     const int L = P.g.L;
@@ -1068,12 +1070,12 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // (LDS of the chain layout: with the node gradients stored apart it holds all of V, as with its own tables)
     const bool vg_lds = vg && !gv_apart, gv_lds = gv || gv_apart;
     while (ni > 2 && (mrf_bwd_chain_lds_bytes(LP, ni, L, P.unary_dir >= 0, vg_lds, gv_lds) > chain_lds_cap(P.total_scanlines) ||
-                      (gv && P.total_scanlines * ni > grad_slots(L)))) ni = (ni == 12) ? 8 : ni - 2;
+                      (gv && P.total_scanlines > grad_slots(L)))) ni = (ni == 12) ? 8 : ni - 2;
     // TRW coefficients or pairwise tables per edge: mrf_bwd_sweep handles them (and is the one
     // sweep that never touches V when no edge-weight gradient is asked for)
     const bool generic = P.rho_e != nullptr || P.force_plain;
     const bool chain_fits = !generic && step_fits && ns <= 8 && g_tune_chain != 1 &&
-                            (!gv || (LP == 1 && P.total_scanlines * ni <= grad_slots(L))) &&
+                            (!gv || (LP == 1 && P.total_scanlines <= grad_slots(L))) &&
                             mrf_bwd_chain_lds_bytes(LP, ni, L, P.unary_dir >= 0, vg_lds, gv_lds) <= chain_lds_cap(P.total_scanlines);
     // (65..128 labels with several source arrays, TRWP: at 2,048 scanlines per launch the plain sweep is ahead,
     // 5.1 against 7.5 ms on 4 x 512 x 512 with 96 labels; at 1,024 the chain, 2.3 against 3.6 ms)
@@ -1092,9 +1094,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
         // which four such workgroups share, sets the pace)
         const int nip = (g_tune_chain_ni == 2 || g_tune_chain_ni == 4 || g_tune_chain_ni == 8) ? g_tune_chain_ni
                                                                                             : (P.total_scanlines <= 1536 ? 8 : 4);
-        if (!(gv_any && (P.total_scanlines + 1) / 2 * 2 > grad_slots(L))) {
-            return run_bwd_chain_pk(P, ns, nip, st);
-        }
+        return run_bwd_chain_pk(P, ns, nip, st);
     }
     // few labels: several scanlines per wavefront, once there are enough of them
     if (!generic && L <= 32 && g_tune_pack != 1 && (g_tune_pack == 2 || P.total_scanlines >= 256) &&
@@ -1129,7 +1129,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)glds);
                 if (ea != hipSuccess) return ea;
             }
-            hipLaunchKernelGGL(mrf_bwd_gv_from_g, dim3(256), dim3(512), glds, st, G);
+            hipLaunchKernelGGL(mrf_bwd_gv_from_g, dim3(MRF_GV_BLOCKS), dim3(512), glds, st, G);
             return hipGetLastError();
         }
         return run_bwd_chain(P, ns, ni, vg, st);
@@ -1170,12 +1170,19 @@ hipError_t fill(float *dst, long long n, float v, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t fill64(double *dst, long long n, hipStream_t st)
+// Slots that the sweeps of a backward call can add to: a layout has at most one per scanline of a launch (the
+// last workgroup of mrf_bwd_sweep may hold up to three wavefronts without one), mrf_bwd_gv_from_g one per workgroup.
+long long slots_in_use(const mrf_problem *pr, const MrfGeom &g, int algo)
 {
-    long long blocks = (n + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(mrf_fill_f64, dim3((unsigned)blocks), dim3(256), 0, st, dst, n, 0.0);
-    return hipGetLastError();
+    long long most = 0, all = 0;
+    for (int r = 0; r < g.R; ++r) {
+        const long long n = (long long)g.B * g.nscan[r];
+        all += n;
+        if (n > most) most = n;
+    }
+    long long n = (algo == MRF_ISGMR ? all : most) + MRF_BWD_WAVES - 1;
+    if (gstore_bytes(pr) > 0 && n < MRF_GV_BLOCKS) n = MRF_GV_BLOCKS;
+    return n < grad_slots(g.L) ? n : grad_slots(g.L);
 }
 
 int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const uint8_t *p, const uint8_t *q,
@@ -1221,18 +1228,24 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     if (pr->edge_weight) { P.w = pr->edge_weight; P.w_mul = 1; }
     else { P.w = scal; P.w_mul = 0; }
 
-    if (grad_w) {
-        const hipError_t e_ = fill(grad_w, (long long)R * N, 0.0f, st);
-        if (e_ != hipSuccess) return hip_fail(e_, "fill");
+    long long slots = 0;
+    if (grad_V && !edge_tables) {
+        P.gV = gvslots;
+        slots = slots_in_use(pr, P.g, algo);
+        if (gstore_bytes(pr) > 0) P.gstore_buf = (double *)((char *)gvslots + gradv_bytes(pr));
+    }
+    if (grad_w || slots > 0) {
+        const long long n_gw = grad_w ? (long long)R * N : 0, n_slots = slots * L * L;
+        long long blocks = ((n_gw > n_slots ? n_gw : n_slots) + 255) / 256;
+        if (blocks > 16384) blocks = 16384;
+        hipLaunchKernelGGL(mrf_bwd_clear, dim3((unsigned)blocks), dim3(256), 0, st, grad_w, n_gw, gvslots, n_slots);
+        const hipError_t e_ = hipGetLastError();
+        if (e_ != hipSuccess) return hip_fail(e_, "mrf_bwd_clear");
     }
     P.force_plain = edge_tables ? 1 : 0;
     if (edge_tables && grad_V) {
         P.gE = grad_V;
         { const hipError_t e_ = fill(grad_V, (long long)R * N * L * L, 0.0f, st); if (e_ != hipSuccess) return hip_fail(e_, "fill"); }
-    } else if (grad_V) {
-        P.gV = gvslots;
-        if (gstore_bytes(pr) > 0) P.gstore_buf = (double *)((char *)gvslots + gradv_bytes(pr));
-        { const hipError_t e_ = fill64(gvslots, grad_slots(L) * L * L, st); if (e_ != hipSuccess) return hip_fail(e_, "fill64"); }
     }
 
     mark(g_ev_start, st);
@@ -1362,13 +1375,15 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     mark(g_ev_stop, st);
     if (grad_V && !edge_tables) {
         const long long n = (long long)L * L;
-        const long long slots = grad_slots(L), chunk = 128;
-        const unsigned eb = (unsigned)((n + 255) / 256);
-        hipLaunchKernelGGL(mrf_reduce_slot_chunks, dim3(eb, (unsigned)((slots + chunk - 1) / chunk)), dim3(256), 0, st,
-                           gvslots, n, slots, chunk);
-        { const hipError_t e_ = hipGetLastError(); if (e_ != hipSuccess) return hip_fail(e_, "hipGetLastError"); }
-        hipLaunchKernelGGL(mrf_reduce_slot_heads, dim3(eb), dim3(256), 0, st, (const double *)gvslots, grad_V, n, slots, chunk);
-        { const hipError_t e_ = hipGetLastError(); if (e_ != hipSuccess) return hip_fail(e_, "hipGetLastError"); }
+        const long long chunk = slots <= MRF_SLOTS_ONE_PASS ? 1 : 64;
+        if (chunk > 1) {
+            hipLaunchKernelGGL(mrf_reduce_slots<64>, dim3((unsigned)((n + 63) / 64), (unsigned)((slots + chunk - 1) / chunk)), dim3(256),
+                               0, st, gvslots, grad_V, n, slots, chunk, 0);
+            const hipError_t e_ = hipGetLastError();
+            if (e_ != hipSuccess) return hip_fail(e_, "mrf_reduce_slots");
+        }
+        hipLaunchKernelGGL(mrf_reduce_slots<16>, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, st, gvslots, grad_V, n, slots, chunk, 1);
+        { const hipError_t e_ = hipGetLastError(); if (e_ != hipSuccess) return hip_fail(e_, "mrf_reduce_slots"); }
     }
     return MRF_OK;
 }

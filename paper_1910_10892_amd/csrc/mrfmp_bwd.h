@@ -33,7 +33,6 @@
 //   mrf_bwd_sweep_split    one wavefront per 64 labels in lock step
 //   mrf_bwd_sweep_packed   L <= 32: several scanlines per wavefront
 //   mrf_isgmr_bwd_combine  ISGMR's sums over directions between two iterations
-//   mrf_reduce_slot_*      fixed-order reduction of the private V-gradient accumulators
 // Which sweep a launch gets is host arithmetic on the launch shape (dispatch_bwd).
 #pragma once
 
@@ -83,6 +82,14 @@ struct MrfBwdParams {
 };
 
 #define MRF_BWD_WAVES 4   // wavefronts (= scanlines in flight) per workgroup
+
+// Adds to an entry of a V-gradient slot.  An entry has one writer per launch, so the order of its additions
+// is fixed; the no-return atomic keeps the end of a sweep from waiting a memory round trip for every 64 entries
+// of the table (7 of them for 21 labels: 5 us of a 14 us launch).
+__device__ inline void mrf_slot_add(double *slot, double v)
+{
+    __hip_atomic_fetch_add(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 #define MRF_CHAIN_MAX_HELPERS 12
 
 // dynamic LDS of mrf_bwd_sweep_chain (host and device agree through this one expression)
@@ -134,13 +141,12 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
     __syncthreads();
 
     for (long long sl = slot; sl < P.total_scanlines; sl += nslots) {
-        int ri = 0;
-        while (ri + 1 < P.r_count && sl >= P.blk_begin[ri + 1]) ++ri;
+        const int ri = mrf_direction_of(P.blk_begin, P.r_count, sl);
         const int r = P.r_first + ri;
-        const long long local = sl - P.blk_begin[ri];
-        const int nsc = P.g.nscan[r];
+        const unsigned local = (unsigned)(sl - P.blk_begin[ri]);
+        const unsigned nsc = (unsigned)P.g.nscan[r];
         const int b = (int)(local / nsc);
-        const long long t = local - (long long)b * nsc;
+        const unsigned t = local - (unsigned)b * nsc;
         const int dh = P.g.dh[r], dw = P.g.dw[r];
         int y0, x0, len;
         mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -438,13 +444,13 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
     }
     if (gVs && P.gv_lds == 1) {
         mrf_wave_lds_fence();
-        for (int e = lane; e < L * L; e += 64) gVs[e] += gvl[e];
+        for (int e = lane; e < L * L; e += 64) mrf_slot_add(&gVs[e], gvl[e]);
     }
     if (P.gv_lds == 2) {
         // (every wavefront of the workgroup arrives here; the slot belongs to this workgroup alone)
         __syncthreads();
         if (gVs)
-            for (int e = threadIdx.x; e < L * L; e += blockDim.x) gVs[e] += gvl[e];
+            for (int e = threadIdx.x; e < L * L; e += blockDim.x) mrf_slot_add(&gVs[e], gvl[e]);
     }
 }
 
@@ -472,7 +478,7 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
 // pre(t) in its helper, needs the chain to have passed step t - 2 NI + 1 only.
 //
 // GV (L <= 64, as far as LDS has room): the launch also wants the V gradient; every helper keeps an accumulator of
-// its own in LDS, lane lambda owning column lambda, and adds it to its own slot at the end.  With more than
+// its own in LDS, lane lambda owning column lambda; their sum goes to the workgroup's slot at the end.  With more than
 // one label per lane the tables do not fit: GV then means that the helpers store the gradient vector g of every
 // node in P.gstore (0 where no update is replayed), from which mrf_bwd_gv_from_g forms the table afterwards;
 // V is still copied to LDS for the edge-weight gradient.
@@ -522,13 +528,12 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
     __syncthreads();
 
     const long long sl = blockIdx.x;       // one scanline per workgroup
-    int ri = 0;
-    while (ri + 1 < P.r_count && sl >= P.blk_begin[ri + 1]) ++ri;
+    const int ri = mrf_direction_of(P.blk_begin, P.r_count, sl);
     const int r = P.r_first + ri;
-    const long long local = sl - P.blk_begin[ri];
-    const int nsc = P.g.nscan[r];
+    const unsigned local = (unsigned)(sl - P.blk_begin[ri]);
+    const unsigned nsc = (unsigned)P.g.nscan[r];
     const int b = (int)(local / nsc);
-    const long long t = local - (long long)b * nsc;
+    const unsigned t = local - (unsigned)b * nsc;
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -846,10 +851,16 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
         }
     }
     if (GVT) {
-        // one slot per helper of every workgroup
-        mrf_wave_lds_fence();
-        double *gVs = P.gV + ((size_t)blockIdx.x * NI + jw) * L * L;
-        for (int e = lane; e < L * L; e += 64) gVs[e] += gvl[e];
+        // one slot per workgroup: the helpers' tables are summed here, in helper order.  (The chain wavefront
+        // has ended or will; a barrier waits for the wavefronts that are left.)
+        __syncthreads();
+        double *gVs = P.gV + (size_t)blockIdx.x * L * L;
+        for (int e = (int)threadIdx.x - 64; e < L * L; e += 64 * NI) {
+            double v = gvacc[e];
+#pragma unroll
+            for (int j = 1; j < NI; ++j) v += gvacc[j * L * L + e];
+            mrf_slot_add(&gVs[e], v);
+        }
     }
 }
 
@@ -889,13 +900,12 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_split(const MrfBwdParams P)
     if (threadIdx.x < 8) { (&psum[0][0])[threadIdx.x] = 0.0; (&gwp[0][0])[threadIdx.x] = 0.0; }
 
     for (long long sl = blockIdx.x; sl < P.total_scanlines; sl += gridDim.x) {
-        int ri = 0;
-        while (ri + 1 < P.r_count && sl >= P.blk_begin[ri + 1]) ++ri;
+        const int ri = mrf_direction_of(P.blk_begin, P.r_count, sl);
         const int r = P.r_first + ri;
-        const long long local = sl - P.blk_begin[ri];
-        const int nsc = P.g.nscan[r];
+        const unsigned local = (unsigned)(sl - P.blk_begin[ri]);
+        const unsigned nsc = (unsigned)P.g.nscan[r];
         const int b = (int)(local / nsc);
-        const long long t = local - (long long)b * nsc;
+        const unsigned t = local - (unsigned)b * nsc;
         const int dh = P.g.dh[r], dw = P.g.dw[r];
         int y0, x0, len;
         mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -1112,7 +1122,7 @@ __global__ void __launch_bounds__(64) mrf_bwd_sweep_packed(const MrfBwdParams P)
     double *sbuf = reinterpret_cast<double *>(mrf_bsmem) + seg * SEG;                       // [NSEG][SEG]
     double *gvl = reinterpret_cast<double *>(mrf_bsmem) + NSEG * SEG + (P.gV ? seg * L * L : 0);  // [NSEG][L*L]
     float *vl = reinterpret_cast<float *>(reinterpret_cast<double *>(mrf_bsmem) + NSEG * SEG + (P.gV ? NSEG * L * L : 0));
-    double *gVs = P.gV ? P.gV + ((size_t)blockIdx.x * NSEG + seg) * L * L : nullptr;
+    double *gVs = P.gV ? P.gV + (size_t)blockIdx.x * L * L : nullptr;      // one slot per workgroup
 
     for (int e = lane; e < L * L; e += 64) vl[e] = P.V[e];
     if (gVs && lane_on)
@@ -1126,8 +1136,8 @@ __global__ void __launch_bounds__(64) mrf_bwd_sweep_packed(const MrfBwdParams P)
         const long long sl = pk * NSEG + seg;
         const bool act_seg = lane_on && sl < P.total_scanlines;
 
-        int r = P.r_first, nsc = 1, dh = 0, dw = 1, nsrc = 0;
-        long long local = 0;
+        int r = P.r_first, dh = 0, dw = 1, nsrc = 0;
+        unsigned nsc = 1, local = 0;
         float cscale_f = 1.0f;
         int sdir[NS];
         float cGf[NS], cTf[NS];
@@ -1137,7 +1147,7 @@ __global__ void __launch_bounds__(64) mrf_bwd_sweep_packed(const MrfBwdParams P)
             const int rr = P.r_first + ri;
             const bool mine = act_seg && sl >= P.blk_begin[ri] && sl < P.blk_begin[ri + 1];
             if (mine) {
-                r = rr; local = sl - P.blk_begin[ri]; nsc = P.g.nscan[rr]; dh = P.g.dh[rr]; dw = P.g.dw[rr];
+                r = rr; local = (unsigned)(sl - P.blk_begin[ri]); nsc = (unsigned)P.g.nscan[rr]; dh = P.g.dh[rr]; dw = P.g.dw[rr];
                 cscale_f = P.carry_scale[rr]; nsrc = P.n_src[rr];
 #pragma unroll
                 for (int c = 0; c < NS; ++c) { sdir[c] = P.src_dir[rr][c]; cGf[c] = P.coefG[rr][c]; cTf[c] = P.coefT[rr][c]; }
@@ -1147,7 +1157,7 @@ __global__ void __launch_bounds__(64) mrf_bwd_sweep_packed(const MrfBwdParams P)
         long long head = 0;
         if (act_seg) {
             const int b = (int)(local / nsc);
-            const long long t = local - (long long)b * nsc;
+            const unsigned t = local - (unsigned)b * nsc;
             mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
             head = ((long long)b * P.g.H + y0) * P.g.W + x0;
         }
@@ -1267,9 +1277,15 @@ __global__ void __launch_bounds__(64) mrf_bwd_sweep_packed(const MrfBwdParams P)
         }
     }
     if (gVs) {
+        // the segments' tables are summed in segment order
         mrf_wave_lds_fence();
-        if (lane_on)
-            for (int e = lam; e < L * L; e += SEG) gVs[e] += gvl[e];
+        const double *t0 = reinterpret_cast<double *>(mrf_bsmem) + NSEG * SEG;
+        for (int e = lane; e < L * L; e += 64) {
+            double v = t0[e];
+#pragma unroll
+            for (int sg = 1; sg < NSEG; ++sg) v += t0[sg * L * L + e];
+            mrf_slot_add(&gVs[e], v);
+        }
     }
 }
 
@@ -1323,7 +1339,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain_pk(const Mr
     if (GV)
         for (int e = threadIdx.x; e < 2 * L * L; e += blockDim.x) gvacc[e] = 0.0;
     if (threadIdx.x < MRF_CHAIN_MAX_HELPERS) pre_done[threadIdx.x] = (int)threadIdx.x - NI;
-    if (threadIdx.x == 0) { *chain_done = -1; chain_done[1] = 0; mrf_wait_init(&wait_lds, P.fault, P.spin_limit); }
+    if (threadIdx.x == 0) { *chain_done = -1; mrf_wait_init(&wait_lds, P.fault, P.spin_limit); }
     for (int e = threadIdx.x; e < LL; e += blockDim.x) sbuf[e] = 0.0;
     __syncthreads();
 
@@ -1335,9 +1351,9 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain_pk(const Mr
     int y0 = 0, x0 = 0, len = 0;
     long long head = 0;
     if (act_seg) {
-        const int nsc = P.g.nscan[r];
-        const int b = (int)(sl / nsc);
-        const long long t = sl - (long long)b * nsc;
+        const unsigned nsc = (unsigned)P.g.nscan[r];
+        const int b = (int)((unsigned)sl / nsc);
+        const unsigned t = (unsigned)sl - (unsigned)b * nsc;
         mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
         head = ((long long)b * P.g.H + y0) * P.g.W + x0;
     }
@@ -1535,18 +1551,11 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain_pk(const Mr
         }
     }
     if (GV) {
-        // the helper that finishes last adds the two tables to the workgroup's two slots
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_wave_barrier();
-        int before = 0;
-        if (lane == 0) before = __hip_atomic_fetch_add(&chain_done[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        before = __builtin_amdgcn_readfirstlane(before);
-        if (before == NI - 1) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-            double *gVs = P.gV + ((size_t)blockIdx.x * 2 + seg) * L * L;
-            if (valid)
-                for (int e = lam; e < L * L; e += L) gVs[e] += gvl[e];
-        }
+        // the two tables, summed, go to the workgroup's slot (the barrier waits for the helpers: the chain
+        // wavefront has ended or will)
+        __syncthreads();
+        double *gVs = P.gV + (size_t)blockIdx.x * L * L;
+        for (int e = (int)threadIdx.x - 64; e < L * L; e += 64 * NI) mrf_slot_add(&gVs[e], gvacc[e] + gvacc[L * L + e]);
     }
 }
 

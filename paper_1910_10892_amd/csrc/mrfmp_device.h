@@ -39,18 +39,20 @@ __host__ __device__ inline long long mrf_geom_scanlines(int H, int W, int dh, in
 __host__ __device__ inline void mrf_geom_head(int H, int W, int dh, int dw, long long t,
                                               int &y0, int &x0, int &len)
 {
-    int adh = mrf_imin(mrf_iabs(dh), H), adw = mrf_imin(mrf_iabs(dw), W);
-    long long band = (long long)adh * W;
-    if (t < band) {
-        int yy = (int)(t / W);
-        x0 = (int)(t - (long long)yy * W);
-        y0 = dh > 0 ? yy : H - adh + yy;
+    // (t counts scanlines of one image: it and every product below fit 32 bits, and a 32-bit division costs a
+    // fifth of a 64-bit one in the few microseconds a launch takes to start)
+    const unsigned adh = (unsigned)mrf_imin(mrf_iabs(dh), H), adw = (unsigned)mrf_imin(mrf_iabs(dw), W);
+    const unsigned band = adh * (unsigned)W, tu = (unsigned)t;
+    if (tu < band) {
+        const unsigned yy = tu / (unsigned)W;
+        x0 = (int)(tu - yy * (unsigned)W);
+        y0 = dh > 0 ? (int)yy : H - (int)adh + (int)yy;
     } else {
-        long long tt = t - band;
-        int ry = (int)(tt / adw);
-        int cx = (int)(tt - (long long)ry * adw);
-        y0 = dh > 0 ? adh + ry : ry;
-        x0 = dw > 0 ? cx : W - adw + cx;
+        const unsigned tt = tu - band;
+        const unsigned ry = tt / adw;
+        const int cx = (int)(tt - ry * adw);
+        y0 = dh > 0 ? (int)(adh + ry) : (int)ry;
+        x0 = dw > 0 ? cx : W - (int)adw + cx;
     }
     int sy = dh > 0 ? (H - 1 - y0) / dh : (dh < 0 ? y0 / (-dh) : INT_MAX);
     int sx = dw > 0 ? (W - 1 - x0) / dw : (dw < 0 ? x0 / (-dw) : INT_MAX);
@@ -58,6 +60,14 @@ __host__ __device__ inline void mrf_geom_head(int H, int W, int dh, int dw, long
 }
 
 #ifdef __HIPCC__
+// which of the launch's `count` directions scanline `sl` belongs to; begin[] holds prefix sums
+__device__ inline int mrf_direction_of(const long long (&begin)[MRF_MAXR + 1], int count, long long sl)
+{
+    int ri = 0;
+    while (ri + 1 < count && sl >= begin[ri + 1]) ++ri;
+    return ri;
+}
+
 // ---- wavefront helpers (gfx950: 64 lanes, DPP row = 16 lanes) -------------------------
 // DPP controls: quad_perm [1,0,3,2] = 0xB1, [2,3,0,1] = 0x4E, row_half_mirror = 0x141,
 // row_mirror = 0x140.  After the four steps every lane holds the reduction of its row.

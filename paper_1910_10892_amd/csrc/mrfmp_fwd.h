@@ -77,13 +77,12 @@ mrf_fwd_sweep(const MrfFwdParams P)
 
     // workgroup -> (direction r, image b, scanline t)
     const long long blk = blockIdx.x;
-    int ri = 0;
-    while (ri + 1 < P.r_count && blk >= P.blk_begin[ri + 1]) ++ri;
+    const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
-    const long long local = blk - P.blk_begin[ri];
-    const int nsc = P.g.nscan[r];
+    const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
+    const unsigned nsc = (unsigned)P.g.nscan[r];
     const int b = (int)(local / nsc);
-    const long long t = local - (long long)b * nsc;
+    const unsigned t = local - (unsigned)b * nsc;
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -367,13 +366,12 @@ mrf_fwd_sweep_sliced(const MrfFwdParams P)
     float *hbuf = hbuf_all[wv];
 
     const long long blk = blockIdx.x;
-    int ri = 0;
-    while (ri + 1 < P.r_count && blk >= P.blk_begin[ri + 1]) ++ri;
+    const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
-    const long long local = blk - P.blk_begin[ri];
-    const int nsc = P.g.nscan[r];
+    const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
+    const unsigned nsc = (unsigned)P.g.nscan[r];
     const int b = (int)(local / nsc);
-    const long long t = local - (long long)b * nsc;
+    const unsigned t = local - (unsigned)b * nsc;
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -566,13 +564,12 @@ mrf_fwd_sweep_edge(const MrfFwdParams P)
     const int lamc = valid ? lane : 0;
 
     const long long blk = blockIdx.x;
-    int ri = 0;
-    while (ri + 1 < P.r_count && blk >= P.blk_begin[ri + 1]) ++ri;
+    const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
-    const long long local = blk - P.blk_begin[ri];
-    const int nsc = P.g.nscan[r];
+    const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
+    const unsigned nsc = (unsigned)P.g.nscan[r];
     const int b = (int)(local / nsc);
-    const long long t = local - (long long)b * nsc;
+    const unsigned t = local - (unsigned)b * nsc;
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -808,13 +805,12 @@ mrf_fwd_sweep_window(const MrfFwdParams P)
     const int lane = threadIdx.x;
 
     const long long blk = blockIdx.x;
-    int ri = 0;
-    while (ri + 1 < P.r_count && blk >= P.blk_begin[ri + 1]) ++ri;
+    const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
-    const long long local = blk - P.blk_begin[ri];
-    const int nsc = P.g.nscan[r];
+    const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
+    const unsigned nsc = (unsigned)P.g.nscan[r];
     const int b = (int)(local / nsc);
-    const long long t = local - (long long)b * nsc;
+    const unsigned t = local - (unsigned)b * nsc;
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -1100,13 +1096,12 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
     if (!index_wave) __builtin_amdgcn_s_setprio(3);
 
     const long long blk = blockIdx.x;
-    int ri = 0;
-    while (ri + 1 < P.r_count && blk >= P.blk_begin[ri + 1]) ++ri;
+    const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
-    const long long local = blk - P.blk_begin[ri];
-    const int nsc = P.g.nscan[r];
+    const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
+    const unsigned nsc = (unsigned)P.g.nscan[r];
     const int b = (int)(local / nsc);
-    const long long t = local - (long long)b * nsc;
+    const unsigned t = local - (unsigned)b * nsc;
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -1738,13 +1733,12 @@ mrf_fwd_sweep_window_split(const MrfFwdParams P)
     const int lamc = valid ? lam : 0;
 
     const long long blk = blockIdx.x;
-    int ri = 0;
-    while (ri + 1 < P.r_count && blk >= P.blk_begin[ri + 1]) ++ri;
+    const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
-    const long long local = blk - P.blk_begin[ri];
-    const int nsc = P.g.nscan[r];
+    const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
+    const unsigned nsc = (unsigned)P.g.nscan[r];
     const int b = (int)(local / nsc);
-    const long long t = local - (long long)b * nsc;
+    const unsigned t = local - (unsigned)b * nsc;
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -1970,13 +1964,12 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
     const int NWV = (int)(blockDim.x >> 6) - NI;   // value wavefronts come first
 
     const long long blk = blockIdx.x;
-    int ri = 0;
-    while (ri + 1 < P.r_count && blk >= P.blk_begin[ri + 1]) ++ri;
+    const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
-    const long long local = blk - P.blk_begin[ri];
-    const int nsc = P.g.nscan[r];
+    const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
+    const unsigned nsc = (unsigned)P.g.nscan[r];
     const int b = (int)(local / nsc);
-    const long long t = local - (long long)b * nsc;
+    const unsigned t = local - (unsigned)b * nsc;
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -2420,8 +2413,8 @@ mrf_fwd_sweep_packed(const MrfFwdParams P)
     const bool act_seg = sl < total && seg < NSEG;
 
     // per-lane description of the segment's scanline
-    int r = P.r_first, nsc = 1, dh = 0, dw = 1, n_pre = 0, n_src = 0, rm_slot = -1;
-    long long local = 0;
+    int r = P.r_first, dh = 0, dw = 1, n_pre = 0, n_src = 0, rm_slot = -1;
+    unsigned nsc = 1, local = 0;
     float rho = 1.0f;
     int sdir[RMAX];
 #pragma unroll
@@ -2430,7 +2423,7 @@ mrf_fwd_sweep_packed(const MrfFwdParams P)
         const int rr = P.r_first + ri;
         const bool mine = act_seg && sl >= P.blk_begin[ri] && sl < P.blk_begin[ri + 1];
         if (mine) {
-            r = rr; local = sl - P.blk_begin[ri]; nsc = P.g.nscan[rr]; dh = P.g.dh[rr]; dw = P.g.dw[rr];
+            r = rr; local = (unsigned)(sl - P.blk_begin[ri]); nsc = (unsigned)P.g.nscan[rr]; dh = P.g.dh[rr]; dw = P.g.dw[rr];
             rho = P.rho[rr]; n_pre = P.n_pre[rr]; n_src = P.n_src[rr]; rm_slot = P.rm_slot[rr];
 #pragma unroll
             for (int c = 0; c + 1 < RMAX; ++c) sdir[c] = P.src_dir[rr][c];
@@ -2440,7 +2433,7 @@ mrf_fwd_sweep_packed(const MrfFwdParams P)
     long long head = 0;
     if (act_seg) {
         const int b = (int)(local / nsc);
-        const long long t = local - (long long)b * nsc;
+        const unsigned t = local - (unsigned)b * nsc;
         mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
         head = ((long long)b * P.g.H + y0) * P.g.W + x0;
     }
