@@ -307,7 +307,9 @@ int mrf_set_sweep_events(void *start_event, void *stop_event);
  *           helpers store the gradient vector of every node and a streaming pass adds them into the table
  *           afterwards: 0 = yes, 1 = no (then another sweep accumulates the table itself)
  *   knob 20: backward sweep of knob 6 with two scanlines of up to 32 labels per workgroup (one direction per
- *           launch, TRWP): 0 = for 1,025 to 2,048 scanlines per launch, 1 = never, 2 = whenever it applies
+ *           launch, TRWP): 0 = by launch size, 1 = never, 2 = whenever it applies
+ *   knob 21: lanes per scanline in the backward sweep for up to 32 labels that gives a lane several labels:
+ *           0 = by launch size, 8, 16 (more than 8 labels), 32 (more than 16 labels)
  * Returns MRF_OK, or MRF_ERR_BAD_ALGORITHM for an unknown knob. */
 int mrf_tune(int knob, int value);
 

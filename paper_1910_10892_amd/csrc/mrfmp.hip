@@ -138,7 +138,7 @@ MRF_G(int g_tune_squad_ni, 0);   // how many: 0 auto, 4, 8
 MRF_G(int g_tune_pack3, 0);      // three scanlines per wavefront for 17..21 labels: 0 by launch size, 1 never, 2 always
 MRF_G(int g_tune_isgmr_lazy, 0); // ISGMR backward without a combine pass per iteration (up to 4 directions): 0 auto, 1 never
 MRF_G(int g_tune_isgmr_presum, 0); // ISGMR forward with the per-pair sums of the previous iteration formed once: 0 from six directions, 1 never, 2 always
-MRF_G(int g_tune_chain_pk, 0);     // chain backward with two scanlines of up to 32 labels per workgroup: 0 = 1,025..2,048 scanlines of one direction, 1 never, 2 always
+MRF_G(int g_tune_chain_pk, 0);     // chain backward with two scanlines of up to 32 labels per workgroup: 0 by launch size, 1 never, 2 always
 MRF_G(int g_tune_gv_apart, 0);     // V gradient of 65..128 labels by a streaming pass behind the chain backward sweep: 0 yes, 1 no
 MRF_G(int g_tune_gv_tile, 0);      // V gradient of 33..128 labels in one LDS table per workgroup: 0 yes, 1 no (a slot per wavefront in global memory)
 MRF_G(int g_tune_dense_sliced, 0); // dense sweep for more than 64 labels with a slice of the labels per wavefront: 0 yes, 1 no
@@ -147,6 +147,7 @@ MRF_G(int g_tune_pack_idx, 0);   // index wavefronts in the packed dense sweep: 
 MRF_G(int g_tune_chain, 0);      // backward sweep with a chain wavefront: 0 auto, 1 never, 2 whenever possible
 MRF_G(int g_tune_chain_hot, 0);  // its pre-reduction of the most popular scatter target: 0 auto, 1 never, 2 whenever V is no dense table
 MRF_G(int g_tune_chain_ni, 0);   // its helpers per scanline: 0 auto, 2, 4, 6, 8
+MRF_G(int g_tune_narrow, 0);     // lanes per scanline of the narrow backward sweep: 0 by launch size, 8, 16, 32
 MRF_G(hipEvent_t g_ev_start, nullptr);
 MRF_G(hipEvent_t g_ev_stop, nullptr);
 #undef MRF_G
@@ -239,7 +240,8 @@ inline size_t chain_lds_cap(long long scanlines)
 
 hipError_t run_bwd_chain(MrfBwdParams &P, int ns, int ni, bool vg, hipStream_t st);
 hipError_t run_bwd_chain_pk(MrfBwdParams &P, int ns, int ni, hipStream_t st);
-hipError_t run_bwd_packed(MrfBwdParams &P, int seg, int ns, hipStream_t st);
+hipError_t run_bwd_packed(MrfBwdParams &P, int ns, hipStream_t st);
+hipError_t run_bwd_narrow(MrfBwdParams &P, int seg, int ns, hipStream_t st);
 hipError_t run_bwd_plain(MrfBwdParams &P, int ns, long long blocks, size_t lds, hipStream_t st);
 hipError_t run_bwd_tile(MrfBwdParams &P, int ns, long long blocks, size_t lds, hipStream_t st);
 #endif
@@ -973,10 +975,59 @@ hipError_t run_bwd_chain_pk(MrfBwdParams &P, int ns, int ni, hipStream_t st)
     return launch_bwd_chain_pk<8, 1>(P, ni, st);
 }
 
-hipError_t run_bwd_packed(MrfBwdParams &P, int seg, int ns, hipStream_t st)
+hipError_t run_bwd_packed(MrfBwdParams &P, int ns, hipStream_t st) { return launch_bwd_packed<21>(P, ns, st); }
+
+template <int SEG, int NL>
+hipError_t launch_bwd_narrow(MrfBwdParams &P, int ns, long long packs, hipStream_t st)
 {
-    if (seg == 21) return launch_bwd_packed<21>(P, ns, st);
-    return seg == 16 ? launch_bwd_packed<16>(P, ns, st) : launch_bwd_packed<32>(P, ns, st);
+    // four wavefronts per workgroup share V and the V-gradient tables, but a launch that does not fill the machine
+    // spreads its wavefronts over the compute units
+    const int waves = packs >= 1024 ? 4 : (packs >= 512 ? 2 : 1);
+    const long long blocks = (packs + waves - 1) / waves;
+    const int L = P.g.L, nseg = 64 / SEG;
+    const bool gv = P.gV != nullptr;
+    if (gv && blocks > grad_slots(L)) return hipErrorInvalidValue;
+    const size_t lds = sizeof(double) * ((size_t)waves * (nseg * mrf_bwd_narrow_row<SEG, NL>() + 64) + (gv ? (size_t)mrf_bwd_narrow_tables(nseg, L) * mrf_bwd_narrow_table<SEG, NL>(L) : 0)) +
+                       sizeof(float) * (size_t)L * mrf_bwd_narrow_pitch(L);
+    if (lds > 64 * 1024) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block(64u * (unsigned)waves);
+    // (one source and no grad theta: ISGMR, every coefficient 1; TRWP forms grad theta in the sweep of one direction)
+    const bool unary = ns == 1 ? P.unary_dir >= 0 : !(P.r_count == 1 && P.r_first != P.unary_dir);
+    const bool full = L % NL == 0;
+#define MRF_N(n, d, un) \
+    if (ns == n && unary == un) { \
+        note_launch(1, "mrf_bwd_sweep_narrow", blocks, 64 * waves, "%d,%d,%d,%d,%s,%s,%s", SEG, NL, n, d, un ? "true" : "false", \
+                    gv ? "true" : "false", full ? "true" : "false"); \
+        if (gv && full) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, true, true>), grid, block, lds, st, P); \
+        else if (gv) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, true, NL == 1>), grid, block, lds, st, P); \
+        else if (full) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, false, true>), grid, block, lds, st, P); \
+        else hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, false, NL == 1>), grid, block, lds, st, P); \
+        return hipGetLastError(); \
+    }
+    MRF_N(1, 4, false) MRF_N(1, 4, true) MRF_N(4, 2, false) MRF_N(4, 2, true)
+    MRF_N(8, (NL <= 2 ? 2 : 1), false) MRF_N(8, (NL <= 2 ? 2 : 1), true) MRF_N(16, 1, false) MRF_N(16, 1, true)
+#undef MRF_N
+    return hipErrorInvalidValue;
+}
+
+hipError_t run_bwd_narrow(MrfBwdParams &P, int seg, int ns, hipStream_t st)
+{
+    const int L = P.g.L, nseg = 64 / seg;
+    long long packs = 0;
+    for (int ri = 0; ri < P.r_count; ++ri) {
+        P.pack_begin[ri] = (int)packs;
+        packs += ((long long)P.g.B * P.g.nscan[P.r_first + ri] + nseg - 1) / nseg;
+    }
+    P.pack_begin[P.r_count] = (int)packs;
+    const int nl = (L + seg - 1) / seg;
+    if (seg == 32 && nl == 1) return launch_bwd_narrow<32, 1>(P, ns, packs, st);
+    if (seg == 16 && nl == 1) return launch_bwd_narrow<16, 1>(P, ns, packs, st);
+    if (seg == 16 && nl == 2) return launch_bwd_narrow<16, 2>(P, ns, packs, st);
+    if (seg == 8 && nl == 1) return launch_bwd_narrow<8, 1>(P, ns, packs, st);
+    if (seg == 8 && nl == 2) return launch_bwd_narrow<8, 2>(P, ns, packs, st);
+    if (seg == 8 && nl == 3) return launch_bwd_narrow<8, 3>(P, ns, packs, st);
+    if (seg == 8 && nl == 4) return launch_bwd_narrow<8, 4>(P, ns, packs, st);
+    return hipErrorInvalidValue;
 }
 
 hipError_t run_bwd_tile(MrfBwdParams &P, int ns, long long blocks, size_t lds, hipStream_t st)
@@ -1017,6 +1068,20 @@ hipError_t launch_bwd_split(const MrfBwdParams &P, long long blocks, size_t lds,
     else
         hipLaunchKernelGGL((mrf_bwd_sweep_split<NS, D, false>), grid, block, lds, st, P);
     return hipGetLastError();
+}
+
+// Lanes per scanline of mrf_bwd_sweep_narrow, or 0 where its 32-bit offsets do not reach.  Eight where that leaves
+// three labels per lane at most and fills the lanes (backward pass, 4 x 512 x 512, 21 labels, K = 3: ISGMR 1.14 / 1.45 /
+// 1.87 ms with 8 / 16 / 32 lanes, TRWP 2.8 / 3.5 / 3.1 ms); two labels per lane are no faster than one (256 x 512, 16
+// labels, 16 directions 0.69 ms with 16 lanes, 0.77 with 8), and with four the V-gradient tables of eight scanlines
+// crowd LDS (32 labels, 16 directions 1.53 / 1.26 / 1.17 ms; without that gradient 16 lanes are ahead).
+int narrow_lanes(const MrfBwdParams &P, int L)
+{
+    if (P.g.N * L > MRF_BUF_MOST) return 0;
+    if (g_tune_narrow == 8 || (g_tune_narrow == 16 && L > 8) || (g_tune_narrow == 32 && L > 16)) return g_tune_narrow;
+    if (L <= 8) return 8;
+    if (L <= 16) return 16;
+    return L <= 24 ? 8 : (P.gV ? 32 : 16);
 }
 
 #define MRF_GV_BLOCKS 256      // workgroups (and slots) of mrf_bwd_gv_from_g
@@ -1085,26 +1150,31 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // 0.80 against 1.04 ms at 2,876 scanlines of a 160 x 320 grid, 0.81 against 0.89 ms at 3,452 of 192 x 384)
     const long long chain_max = LP <= 2 ? ((LP == 2 && ns >= 4) ? 1536 : (P.r_count >= 8 ? 3584 : 2560)) : (ns == 1 ? 1536 : 512);
     const bool chain = chain_fits && (g_tune_chain == 2 || P.total_scanlines <= chain_max);
-    // few labels, one direction per launch (TRWP), more scanlines than the chain layout takes one by one: two
-    // scanlines per workgroup around a chain wavefront
+    // Few labels, one direction per launch (TRWP): the chain layout for one scanline per compute unit, two scanlines
+    // around a chain wavefront beyond that, mrf_bwd_sweep_narrow for more than the machine holds that way.  (Backward
+    // pass of 256 x 512 grids, 21 labels, 4 directions, K = 3, one / two / four images: 0.83 / 1.35 / 2.15 ms chain,
+    // 0.78 / 1.00 / 1.81 ms two scanlines, 2.1 ms narrow; 4 x 512 x 512: 3.4 ms two scanlines, 2.8 ms narrow.)
+    const long long pk_max = L <= 8 ? 1024 : 1536;
     if (!generic && L <= 32 && P.r_count == 1 && ns <= 8 && g_tune_chain != 1 && g_tune_pack != 2 && g_tune_chain_pk != 1 &&
-        (g_tune_chain_pk == 2 || (P.total_scanlines > 1024 && P.total_scanlines <= 2048))) {
-        // (helpers: 4 x 512 x 512, 32 labels, 2,048 scanlines: 3.0 ms with four, 3.2 with eight, 3.5 ms for the packed
-        // sweep; 3 x 512 x 512, 16 labels, 8 directions, 1,536 scanlines: 5.0 / 4.3 / 5.4 ms; the LDS of a compute unit,
-        // which four such workgroups share, sets the pace)
+        (g_tune_chain_pk == 2 || (g_tune_chain != 2 && P.total_scanlines > 256 && P.total_scanlines <= pk_max))) {
+        // (helpers: 3 x 512 x 512, 16 labels, 8 directions, 1,536 scanlines: 4.3 ms with eight, 5.0 with four; the LDS
+        // of a compute unit, which several such workgroups share, sets the pace)
         const int nip = (g_tune_chain_ni == 2 || g_tune_chain_ni == 4 || g_tune_chain_ni == 8) ? g_tune_chain_ni
                                                                                             : (P.total_scanlines <= 1536 ? 8 : 4);
         return run_bwd_chain_pk(P, ns, nip, st);
     }
     // few labels: several scanlines per wavefront, once there are enough of them
+    // (all directions in one launch, ISGMR, 1,536 scanlines: 0.47 against 0.56 ms for the chain with 16 labels, 0.63
+    // against 0.74 with 32, but 0.66 against 0.59 with 21, where a lane's three labels make the node step long)
+    const long long chain_few = (P.r_count > 1 && L > 16 && L <= 24) ? 1536 : 1024;
     if (!generic && L <= 32 && g_tune_pack != 1 && (g_tune_pack == 2 || P.total_scanlines >= 256) &&
-        !(chain && g_tune_pack != 2 && (g_tune_chain == 2 || P.total_scanlines <= ((ns == 1 && !gv) ? 1536 : 1024))))
+        !(chain && g_tune_pack != 2 && (g_tune_chain == 2 || P.total_scanlines <= chain_few)))
     {
-        // three scanlines per wavefront: measured slower than two on the segmentation shape (the LDS
-        // scatter, not instruction issue, bounds this sweep), so only on request
+        // three scanlines per wavefront, one label per lane: on request only
         if (L > 16 && L <= 21 && g_tune_pack3 == 2)
-            return run_bwd_packed(P, 21, ns, st);
-        return run_bwd_packed(P, L <= 16 ? 16 : 32, ns, st);
+            return run_bwd_packed(P, ns, st);
+        const int seg = narrow_lanes(P, L);
+        if (seg > 0) return run_bwd_narrow(P, seg, ns, st);
     }
     if (chain) {
         // truncated models: the chain wavefront sums the lanes of the most popular scatter target
@@ -1682,6 +1752,7 @@ int mrf_tune(int knob, int value)
     if (knob == 18) { g_tune_gv_tile = value; return MRF_OK; }
     if (knob == 19) { g_tune_gv_apart = value; return MRF_OK; }
     if (knob == 20) { g_tune_chain_pk = value; return MRF_OK; }
+    if (knob == 21) { g_tune_narrow = (value == 8 || value == 16 || value == 32) ? value : 0; return MRF_OK; }
     if (knob == 7) { g_tune_chain_ni = (value == 2 || value == 4 || value == 6 || value == 8 || value == 12) ? value : 0; return MRF_OK; }
     return MRF_ERR_BAD_ALGORITHM;
 }

@@ -31,7 +31,8 @@
 //   mrf_bwd_sweep_chain    the node-to-node chain on a wavefront of its own, helper wavefronts
 //                          for everything else (launches with few scanlines)
 //   mrf_bwd_sweep_split    one wavefront per 64 labels in lock step
-//   mrf_bwd_sweep_packed   L <= 32: several scanlines per wavefront
+//   mrf_bwd_sweep_packed   L <= 32: several scanlines per wavefront, one label per lane
+//   mrf_bwd_sweep_narrow   L <= 32: up to eight scanlines per wavefront, several labels per lane
 //   mrf_isgmr_bwd_combine  ISGMR's sums over directions between two iterations
 // Which sweep a launch gets is host arithmetic on the launch shape (dispatch_bwd).
 #pragma once
@@ -43,6 +44,7 @@ struct MrfBwdParams {
     int r_first, r_count;
     long long blk_begin[MRF_MAXR + 1];     // prefix sums of B*nscan over the launch's directions
     long long total_scanlines;
+    int pack_begin[MRF_MAXR + 1];          // mrf_bwd_sweep_narrow: the same in wavefronts, every direction padded to whole ones
     const float *V;
     const float *w;                        // [R][N] edge weights, or one float when w_mul == 0
     int w_mul;
@@ -1095,6 +1097,7 @@ __device__ inline double mrf_segment_sum_f64(double v)
     v += mrf_dpp_f64<0xB1>(v);
     v += mrf_dpp_f64<0x4E>(v);
     v += mrf_dpp_f64<0x141>(v);
+    if (SEG == 8) return v;
     v += mrf_dpp_f64<0x140>(v);
     if (SEG == 32) {
         const long long b = __builtin_bit_cast(long long, v);
@@ -1103,6 +1106,22 @@ __device__ inline double mrf_segment_sum_f64(double v)
         v += __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
     }
     return v;
+}
+
+// the value of the segment's first lane (SEG = 8, 16, 32)
+template <int SEG>
+__device__ inline int mrf_segment_lane0(int v)
+{
+    v = __builtin_amdgcn_mov_dpp(v, 0x00, 0xF, 0xF, true);                         // quads: their first lane
+    const int h = __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);              // row_half_mirror: the other quad of the eight
+    const int lane = (int)(threadIdx.x & 63);
+    if (SEG == 8) return (lane & 4) ? h : v;
+    v = (lane & 4) ? h : v;
+    const int m = __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true);              // row_mirror: the other eight of the row
+    v = (lane & 8) ? m : v;
+    if (SEG == 16) return v;
+    const auto x = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    return (int)x[0];                                                              // (rows 0, 2 of v in rows 0 and 1, 2 and 3)
 }
 
 // UNARY = false: no direction of the launch forms grad theta_i (ISGMR with its combine passes)
@@ -1285,6 +1304,325 @@ __global__ void __launch_bounds__(64) mrf_bwd_sweep_packed(const MrfBwdParams P)
 #pragma unroll
             for (int sg = 1; sg < NSEG; ++sg) v += t0[sg * L * L + e];
             mrf_slot_add(&gVs[e], v);
+        }
+    }
+}
+
+// ---- index replay for few labels: several labels per lane, narrow segments -----------------------
+//
+// The same replay for launches of up to 32 labels that have scanlines to spare.  A segment of SEG = 8, 16 or
+// 32 lanes walks a scanline, a lane owns NL neighbouring labels (NL li, NL li + 1, ...), so a wavefront of 64 / SEG
+// scanlines spends its addresses, its reductions over labels (three DPP levels for 8 lanes) and its bookkeeping on
+// eight nodes at a time instead of two, and hardly any lane is idle (21 labels: 21 of 24 entries).  Scanlines of one
+// wavefront belong to one direction (the host pads every direction to whole wavefronts), so directions, coefficients
+// and base addresses are scalars, and an entry is a 32-bit offset into a buffer view (the host checks that N L fits);
+// a lane past its scanline's end or without a label has an offset past the view's.
+// Per node: everything from memory is prefetched D nodes ahead into one of two register sets that take turns;
+// the label sums of D nodes are formed at once (they do not depend on the carry, as in mrf_bwd_sweep_packed); the
+// chain is one add per label, the scatter into the segment's row in LDS and its read; the pairwise gradients of
+// a node are formed behind the scatter of the next one, while that is under way.
+// FULL: L is a multiple of NL, so that a lane's labels are one access of NL floats.
+// GV: every segment position has a table of its own in LDS, shared by the workgroup's wavefronts (LDS adds).
+template <int SEG, int NL>
+__host__ __device__ constexpr int mrf_bwd_narrow_row()
+{
+    // doubles per row of the scatter target: lanes are NL doubles apart, and the rows of a wavefront start on banks
+    // that those lanes leave free (24 doubles for three labels per lane, else an odd number for several)
+    return (NL == 1 || NL == 3) ? SEG * NL : SEG * NL + 1;
+}
+
+// rows of V and of the V-gradient tables have an odd length in LDS (an even one puts a label on the same bank in
+// every row); tables start on different banks as the rows above do
+__host__ __device__ inline int mrf_bwd_narrow_pitch(int L) { return L | 1; }
+template <int SEG, int NL>
+__host__ __device__ inline int mrf_bwd_narrow_table(int L)
+{
+    const int n = L * mrf_bwd_narrow_pitch(L), want = mrf_bwd_narrow_row<SEG, NL>() % 32;
+    return n + (want - n % 32 + 32) % 32;
+}
+
+__host__ __device__ inline int mrf_bwd_narrow_tables(int nseg, int L) { return L <= 22 || nseg < 4 ? nseg : nseg / 2; }
+
+template <int SEG, int NL, int NS, int D, bool UNARY, bool GV, bool FULL>
+__global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P)
+{
+    constexpr int NSEG = 64 / SEG;
+    constexpr int RS = mrf_bwd_narrow_row<SEG, NL>();
+    constexpr bool UNIT = NS == 1 && !UNARY;       // ISGMR between its combine passes: one source, coefficients 1
+    extern __shared__ __align__(16) unsigned char mrf_bsmem[];
+    const int L = P.g.L;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int waves = (int)(blockDim.x >> 6);
+    const int seg = lane / SEG, li = lane % SEG;
+    const int lam0 = li * NL;                                 // the lane's first label
+    const int ntab = GV ? mrf_bwd_narrow_tables(NSEG, L) : 0, tsize = mrf_bwd_narrow_table<SEG, NL>(L), pitch = mrf_bwd_narrow_pitch(L);
+    double *rows = reinterpret_cast<double *>(mrf_bsmem) + wv * (NSEG * RS + 64);            // [waves]{[NSEG][RS], 64 spare}
+    double *tabs = reinterpret_cast<double *>(mrf_bsmem) + waves * (NSEG * RS + 64);         // [ntab][tsize]
+    float *vl = reinterpret_cast<float *>(tabs + ntab * tsize);                              // [L][pitch] V
+    double *sb = rows + seg * RS;
+    double *spare = rows + NSEG * RS + lane;                  // where a lane with nothing to add adds
+
+    for (int e = threadIdx.x; e < L * pitch; e += blockDim.x) {
+        const int mu = e / pitch, lam = e - mu * pitch;
+        vl[e] = lam < L ? P.V[mu * L + lam] : 0.0f;
+    }
+    for (int e = threadIdx.x; e < waves * (NSEG * RS + 64) + ntab * tsize; e += blockDim.x) reinterpret_cast<double *>(mrf_bsmem)[e] = 0.0;
+    __syncthreads();
+
+    // this wavefront's scanlines: NSEG consecutive ones of direction r
+    const int pk = (int)blockIdx.x * waves + wv;
+    int ri = 0;
+    while (ri + 1 < P.r_count && pk >= P.pack_begin[ri + 1]) ++ri;
+    const int r = P.r_first + ri;
+    const unsigned nsc = (unsigned)P.g.nscan[r];
+    const unsigned sl = (unsigned)(pk - P.pack_begin[ri]) * NSEG + seg;
+    const bool act = pk < P.pack_begin[P.r_count] && sl < (unsigned)P.g.B * nsc;
+    const int dh = P.g.dh[r], dw = P.g.dw[r];
+    int y0 = 0, x0 = 0, len = 0;
+    int last = 0;                                             // the scanline's last node, where the replay starts
+    const int nstep = dh * P.g.W + dw;
+    if (act) {
+        const int b = (int)(sl / nsc);
+        mrf_geom_head(P.g.H, P.g.W, dh, dw, sl - (unsigned)b * nsc, y0, x0, len);
+        last = (b * P.g.H + y0) * P.g.W + x0 + (len - 1) * nstep;
+    }
+    int maxlen = 0;
+#pragma unroll
+    for (int sg = 0; sg < NSEG; ++sg) {
+        const int l2 = __builtin_amdgcn_readlane(len, sg * SEG);
+        maxlen = l2 > maxlen ? l2 : maxlen;
+    }
+
+    const size_t N = (size_t)P.g.N, NL4 = N * L * 4;
+    const double cscale = (double)P.carry_scale[r];
+    const bool own_unary = UNARY && r == P.unary_dir;
+    const unsigned no_store = own_unary ? 0u : MRF_BUF_NONE, no_old = own_unary && !P.unary_init ? 0u : MRF_BUF_NONE;
+    const mrf_buf bp = mrf_buffer(P.p + (size_t)r * N * L, N * L), bq = mrf_buffer(P.q + (size_t)r * N, N);
+    const mrf_buf bw = mrf_buffer(P.w + (P.w_mul ? (size_t)r * N : 0), P.w_mul ? N * 4 : 4);
+    const mrf_buf bs = mrf_buffer(P.S + (size_t)r * N * L, NL4), bu = mrf_buffer(P.gunary, NL4);
+    const mrf_buf bgw = mrf_buffer(P.gw ? P.gw + (size_t)r * N : nullptr, P.gw ? N * 4 : 0);
+    mrf_buf src[NS];
+    double cG[NS], cT[NS];
+    const int nsrc = P.n_src[r];
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+        const bool live = c < nsrc;
+        const bool isgc = (c == nsrc) && P.use_gc;
+        src[c] = mrf_buffer(live ? P.src_base + (size_t)P.src_dir[r][c] * P.src_stride : P.gc, NL4);
+        cG[c] = live ? (double)P.coefG[r][c] : (isgc ? 1.0 : 0.0);
+        cT[c] = live ? (double)P.coefT[r][c] : (isgc ? 1.0 : 0.0);
+    }
+
+    // accesses of the lane's labels at byte offset `at` of its first one (MRF_BUF_NONE: none of them)
+    const bool any = lam0 < L;
+    auto load = [&](mrf_buf b, unsigned at, float (&v)[NL]) {
+        if constexpr (FULL) {
+            mrf_buf_f32xn<NL>(b, at, v);
+        } else {
+#pragma unroll
+            for (int s = 0; s < NL; ++s) v[s] = mrf_buf_f32(b, lam0 + s < L ? at + 4u * s : MRF_BUF_NONE);
+        }
+    };
+    auto store = [&](mrf_buf b, unsigned at, const float (&v)[NL]) {
+        if constexpr (FULL) {
+            mrf_buf_store_f32xn<NL>(b, at, v);
+        } else {
+#pragma unroll
+            for (int s = 0; s < NL; ++s) mrf_buf_store_f32(b, lam0 + s < L ? at + 4u * s : MRF_BUF_NONE, v[s]);
+        }
+    };
+    // p of the lane's labels: one access of 1, 2 or 4 bytes that stays inside the node's L bytes, and a shift
+    constexpr int PB = NL == 1 ? 1 : (NL == 2 ? 2 : 4);
+    const int p_at = any ? (lam0 < L - PB ? lam0 : L - PB) : 0, p_shift = any ? 8 * (lam0 - p_at) : 0;
+    auto load_p = [&](unsigned at) {
+        if constexpr (PB == 1) return (unsigned)mrf_buf_u8(bp, at);
+        else if constexpr (PB == 2) return (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(bp, at, 0, 0);
+        else return (unsigned)__builtin_amdgcn_raw_buffer_load_b32(bp, at, 0, 0);
+    };
+
+    struct In {
+        float v[NS][NL];
+        float u[UNARY ? NL : 1];         // old grad theta_i (0 unless accumulating)
+        unsigned p;
+        int q;
+        float w;
+    };
+    In A[D], B[D];
+    // The prefetch walks from the last node towards the first and on: what it then loads is another node or nothing,
+    // and never used.  Slots without a label load 0.
+    unsigned pi = (unsigned)last, pe = (unsigned)last * (unsigned)L;
+    const unsigned estep = (unsigned)(nstep * L);
+    auto prefetch = [&](In &in) {
+        const unsigned at = any ? (pe + (unsigned)lam0) << 2 : MRF_BUF_NONE;
+#pragma unroll
+        for (int c = 0; c < NS; ++c) load(src[c], at, in.v[c]);
+        if constexpr (UNARY) load(bu, no_old ? MRF_BUF_NONE : at, in.u);
+        in.p = load_p(any ? pe + (unsigned)p_at : MRF_BUF_NONE);
+        in.q = mrf_buf_u8(bq, pi);
+        in.w = GV ? mrf_buf_f32(bw, P.w_mul ? pi * 4u : 0u) : 0.0f;
+        pe -= estep;
+        pi -= (unsigned)nstep;
+    };
+
+    // the last node of a scanline has no successor in direction r
+    {
+        float zero[NL];
+#pragma unroll
+        for (int s = 0; s < NL; ++s) zero[s] = 0.0f;
+        store(bs, act && any ? ((unsigned)last * (unsigned)L + (unsigned)lam0) << 2 : MRF_BUF_NONE, zero);
+    }
+
+    // the node whose pairwise gradients are still to be formed
+    double gP[NL];
+    int pP[NL];
+    double wP = 0.0;
+    bool updP = false;
+#pragma unroll
+    for (int s = 0; s < NL; ++s) { gP[s] = 0.0; pP[s] = 0; }
+    // edge-weight gradients of a group of D nodes: lane li keeps that of the group's node li, one access adds them all
+    static_assert(D <= SEG, "lanes that keep edge-weight gradients");
+    float gwkeep = 0.0f;
+    int gwleft = 0;                                           // lane's node of the group counts if positive
+    unsigned gwat = 0;
+    double *tab = tabs + (ntab > 0 ? (seg % ntab) * tsize : 0);
+    auto pairwise = [&](int slot) {
+        int at[NL];
+#pragma unroll
+        for (int s = 0; s < NL; ++s) at[s] = __mul24(pP[s], pitch) + (FULL && NL > 1 ? (any ? lam0 + s : 0) : (lam0 + s < L ? lam0 + s : 0));
+        // (formed whether it is wanted or not: the view of an array that is not there holds nothing)
+        double acc = gP[0] * (double)vl[at[0]];
+#pragma unroll
+        for (int s = 1; s < NL; ++s) acc = __builtin_fma(gP[s], (double)vl[at[s]], acc);     // (g is 0 where there is no label)
+        acc = mrf_segment_sum_f64<SEG>(acc);
+        gwkeep = li == slot ? (float)acc : gwkeep;
+        // one writer per entry and launch: a no-return atomic is a plain accumulate
+        if (slot == D - 1) mrf_buf_add_f32(bgw, gwleft > 0 ? gwat : MRF_BUF_NONE, gwkeep);
+        if (GV) {
+            // (no short-circuit in the conditions: it would become a branch)
+#pragma unroll
+            for (int s = 0; s < NL; ++s)
+                __hip_atomic_fetch_add((int)updP & (int)(FULL ? any : lam0 + s < L) ? &tab[at[s]] : spare, wP * gP[s], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    };
+
+    double carry[NL];
+#pragma unroll
+    for (int s = 0; s < NL; ++s) carry[s] = 0.0;
+    unsigned ci = (unsigned)last, ce = (unsigned)last * (unsigned)L + (unsigned)lam0;
+    auto group = [&](const In (&in)[D], int t0) {
+        double ext[D][NL];
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            double part = 0.0;
+#pragma unroll
+            for (int s = 0; s < NL; ++s) {
+                double e = UNIT ? (double)in[u].v[0][s] : cG[0] * (double)in[u].v[0][s];
+#pragma unroll
+                for (int c = 1; c < NS; ++c) e = __builtin_fma(cG[c], (double)in[u].v[c][s], e);
+                ext[u][s] = e;
+                part = s == 0 ? e : part + e;
+            }
+            // back Eq. isgmr-norm: the entry at q loses the label sum
+            const double tot = mrf_segment_sum_f64<SEG>(part);
+            const int qv = in[u].q < L ? in[u].q : L - 1;
+#pragma unroll
+            for (int s = 0; s < NL; ++s)
+                if (lam0 + s == qv) ext[u][s] -= tot;
+        }
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            const int tt = t0 + u;
+            double g[NL];
+            int pv[NL];
+            if constexpr (UNARY) {
+                // grad theta_i: everything every direction passed back to node i
+                float out[NL];
+#pragma unroll
+                for (int s = 0; s < NL; ++s) {
+                    double accT = carry[s];
+#pragma unroll
+                    for (int c = 0; c < NS; ++c) accT = __builtin_fma(cT[c], (double)in[u].v[c][s], accT);
+                    out[s] = (float)(accT + (double)in[u].u[s]);
+                }
+                store(bu, (int)(tt < len) & (int)(any && !no_store) ? ce << 2 : MRF_BUF_NONE, out);
+            }
+            // Where one label beats all others every lane scatters to it, and LDS would add them one by one (8 lanes
+            // on one word take 92 clocks, on words of their own 8): a lane merges its labels that go where its
+            // first one goes, and lanes whose first label goes where lane 0's does are summed by DPP for lane 0.
+            const unsigned pw = in[u].p >> p_shift;
+#pragma unroll
+            for (int s = 0; s < NL; ++s) {
+                g[s] = carry[s] + ext[u][s];
+                const int pr = (int)((pw >> (8 * s)) & 255u);
+                pv[s] = pr < L ? pr : L - 1;
+            }
+            double g0 = g[0];
+#pragma unroll
+            for (int s = 1; s < NL; ++s) g0 += pv[s] == pv[0] ? g[s] : 0.0;
+            const bool common = pv[0] == mrf_segment_lane0<SEG>(pv[0]);
+            const double gc0 = mrf_segment_sum_f64<SEG>(common ? g0 : 0.0);
+            __hip_atomic_fetch_add((int)!common | (int)(li == 0) ? &sb[pv[0]] : spare, common ? gc0 : g0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+            for (int s = 1; s < NL; ++s)
+                __hip_atomic_fetch_add(pv[s] != pv[0] ? &sb[pv[s]] : spare, g[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            mrf_wave_lds_fence();
+            double sv[NL];
+#pragma unroll
+            for (int s = 0; s < NL; ++s) sv[s] = sb[lam0 + s];
+            mrf_wave_lds_fence();
+#pragma unroll
+            for (int s = 0; s < NL; ++s) sb[lam0 + s] = 0.0;
+            pairwise(u == 0 ? D - 1 : u - 1);
+            if (u == 0) {
+                gwleft = li < D ? len - 1 - t0 - li : 0;
+                gwat = (ci - (unsigned)(li * nstep)) << 2;
+            }
+            const bool update = tt < len - 1;            // node i has a predecessor: replay its update
+            ce -= estep;
+            {
+                float out[NL];
+#pragma unroll
+                for (int s = 0; s < NL; ++s) out[s] = (float)sv[s];
+                store(bs, (int)update & (int)any ? ce << 2 : MRF_BUF_NONE, out);
+            }
+#pragma unroll
+            for (int s = 0; s < NL; ++s) { carry[s] = UNIT ? sv[s] : cscale * sv[s]; gP[s] = g[s]; pP[s] = pv[s]; }
+            wP = (double)in[u].w;
+            updP = update;
+            ci -= (unsigned)nstep;
+        }
+    };
+    if (maxlen > 0) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) prefetch(A[u]);
+        // (as many dropped stores as a group makes: what is in flight when the loop is entered then looks to the
+        // compiler like what is in flight when it comes round, else it waits for the newest stores each time)
+#pragma unroll
+        for (int u = 0; u < D * (UNARY ? 2 : 1) * (FULL ? 1 : NL) + 1; ++u) mrf_buf_store_f32(bs, MRF_BUF_NONE, 0.0f);
+        for (int t0 = 0; t0 < maxlen; t0 += 2 * D) {
+#pragma unroll
+            for (int u = 0; u < D; ++u) prefetch(B[u]);
+            __builtin_amdgcn_sched_barrier(0);           // (the loads stay in front)
+            group(A, t0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < D; ++u) prefetch(A[u]);
+            __builtin_amdgcn_sched_barrier(0);
+            group(B, t0 + D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        pairwise(D - 1);
+    }
+    if (GV) {
+        __syncthreads();
+        double *slot = P.gV + (size_t)blockIdx.x * L * L;
+        for (int e = threadIdx.x; e < L * L; e += blockDim.x) {
+            const int mu = e / L, at = mu * pitch + (e - mu * L);
+            double v = tabs[at];
+            for (int k = 1; k < ntab; ++k) v += tabs[k * tsize + at];
+            mrf_slot_add(&slot[e], v);
         }
     }
 }

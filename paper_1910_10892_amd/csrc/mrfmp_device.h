@@ -446,6 +446,71 @@ __device__ inline float mrf_opaque_zero_f()
     return z;
 }
 
+// Buffer views: 32-bit byte offsets from a scalar base, range-checked by the hardware (a load past the end returns
+// 0, a store or an atomic past it is dropped).  Lanes that have nothing to load or store get an offset past any end
+// (MRF_BUF_NONE) instead of a branch: the compiler must assume that a branch around a memory operation is not taken
+// when it counts what is in flight, and then waits for newer loads than the ones it needs.
+typedef __amdgpu_buffer_rsrc_t mrf_buf;
+#define MRF_BUF_NONE 0xFFFFF000u         // past every view; as it stands also with up to 4 KB added, or-ed into an offset
+                                         // only as the last step (the low bits are then anything)
+#define MRF_BUF_MOST ((1LL << 30) - 1024)    // elements of 4 bytes that a view may hold
+
+__device__ inline mrf_buf mrf_buffer(const void *base, size_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)(unsigned)bytes, 0x00027000);
+}
+__device__ inline float mrf_buf_f32(mrf_buf b, unsigned off)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, 0));
+}
+// NL consecutive floats
+template <int NL>
+__device__ inline void mrf_buf_f32xn(mrf_buf b, unsigned off, float (&v)[NL])
+{
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    typedef unsigned u3 __attribute__((ext_vector_type(3)));
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    if constexpr (NL == 1) {
+        v[0] = mrf_buf_f32(b, off);
+    } else if constexpr (NL == 2) {
+        const u2 x = __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0);
+        for (int i = 0; i < 2; ++i) v[i] = __builtin_bit_cast(float, (unsigned)x[i]);
+    } else if constexpr (NL == 3) {
+        const u3 x = __builtin_amdgcn_raw_buffer_load_b96(b, off, 0, 0);
+        for (int i = 0; i < 3; ++i) v[i] = __builtin_bit_cast(float, (unsigned)x[i]);
+    } else {
+        static_assert(NL == 4, "floats per access");
+        const u4 x = __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0);
+        for (int i = 0; i < 4; ++i) v[i] = __builtin_bit_cast(float, (unsigned)x[i]);
+    }
+}
+template <int NL>
+__device__ inline void mrf_buf_store_f32xn(mrf_buf b, unsigned off, const float (&v)[NL])
+{
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    typedef unsigned u3 __attribute__((ext_vector_type(3)));
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    unsigned x[4] = {0, 0, 0, 0};
+    for (int i = 0; i < NL; ++i) x[i] = __builtin_bit_cast(unsigned, v[i]);
+    if constexpr (NL == 1) __builtin_amdgcn_raw_buffer_store_b32(x[0], b, off, 0, 0);
+    else if constexpr (NL == 2) __builtin_amdgcn_raw_buffer_store_b64(u2{x[0], x[1]}, b, off, 0, 0);
+    else if constexpr (NL == 3) __builtin_amdgcn_raw_buffer_store_b96(u3{x[0], x[1], x[2]}, b, off, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b128(u4{x[0], x[1], x[2], x[3]}, b, off, 0, 0);
+}
+__device__ inline int mrf_buf_u8(mrf_buf b, unsigned off) { return (int)__builtin_amdgcn_raw_buffer_load_b8(b, off, 0, 0); }
+__device__ inline void mrf_buf_store_f32(mrf_buf b, unsigned off, float v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, off, 0, 0);
+}
+__device__ inline void mrf_buf_store_u8(mrf_buf b, unsigned off, int v)
+{
+    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)v, b, off, 0, 0);
+}
+__device__ inline void mrf_buf_add_f32(mrf_buf b, unsigned off, float v)
+{
+    (void)__builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(v, b, off, 0, 0);
+}
+
 // Workgroup barrier that orders LDS traffic only: global loads issued as prefetch stay in
 // flight across it (a full __syncthreads would wait for them).
 __device__ inline void mrf_block_sync_lds()

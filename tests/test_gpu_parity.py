@@ -275,6 +275,47 @@ def test_chain_backward_with_two_scanlines_per_workgroup(oracle, case):
         check_grad(name + " (two layouts)", getattr(a, name), None, getattr(b, name).astype(np.float64))
 
 
+NARROW_CASES = [
+    # seed, algo, B, H, W, L, dirs, K, integer_valued, per_edge: label counts at the edges of 8-lane segments
+    (781, "isgmr", 2, 9, 11, 21, DIRS8, 3, False, True), (782, "trwp", 1, 7, 13, 32, DIRS4, 2, True, True),
+    (783, "isgmr", 1, 6, 10, 25, DIRS16, 2, False, False), (784, "trwp", 3, 5, 6, 24, DIRS8, 2, False, True),
+    (785, "isgmr", 1, 1, 37, 8, DIRS4, 2, True, True), (786, "trwp", 1, 23, 3, 9, ((0, 1), (1, 0), (1, 1)), 3, False, True),
+    (787, "trwp", 1, 3, 9, 1, DIRS4, 2, False, True), (788, "isgmr", 1, 33, 2, 17, DIRS8, 2, False, True),
+    (789, "trwp", 1, 4, 5, 16, DIRS16, 2, False, True),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", NARROW_CASES, ids=lambda c: "seed%d" % c[0])
+def test_backward_with_several_labels_per_lane(oracle, case):
+    """Up to 32 labels, segments of 8, 16 and 32 lanes per scanline: scanline counts that do not fill a
+    wavefront, scanlines of unequal length and of one node, with and without grad_pairwise, against the oracle
+    and against the one-wavefront sweep."""
+    import paper_1910_10892_amd as mrf
+    print("case narrow backward", case[:6], len(case[6]), case[7:], flush=True)
+    seed, algo, B, H, W, L, dirs, K, iv, pe = case
+    pr = random_problem(seed, algo, B, H, W, L, dirs, K, integer_valued=iv, per_edge=pe, symmetric=False,
+                        rho=np.linspace(0.3, 0.9, len(dirs)))
+    pr.grad_cost = (pr.grad_cost * (0.02 if len(dirs) > 8 else 0.2)).astype(np.float32)
+    got = {}
+    try:
+        assert mrf.mrf_tune(6, 1) == 0 and mrf.mrf_tune(20, 1) == 0 and mrf.mrf_tune(3, 2) == 0
+        for seg in (8, 16, 32):
+            for want_V in (True, False):
+                assert mrf.mrf_tune(21, seg) == 0
+                got[seg, want_V] = full_check(oracle, pr, want_V=want_V)
+                assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_narrow", mrf.mrf_last_sweep_launch(True)
+        assert mrf.mrf_tune(3, 1) == 0
+        plain = full_check(oracle, pr, want_V=True)
+        assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep"
+    finally:
+        for knob in (3, 6, 20, 21):
+            mrf.mrf_tune(knob, 0)
+    for (seg, want_V), g in got.items():
+        for name in ("grad_unary", "grad_edge_weight") + (("grad_pairwise",) if want_V else ()):
+            check_grad("%s (%d lanes)" % (name, seg), getattr(g, name), None, getattr(plain, name).astype(np.float64))
+
+
 GV_APART_CASES = [
     # seed, B, H, W, L, dirs, K, integer_valued, per_edge
     (751, 1, 6, 9, 96, DIRS4, 3, False, True), (752, 2, 5, 7, 128, DIRS8, 2, True, True),
