@@ -112,10 +112,10 @@ inline size_t gradv_bytes(const mrf_problem *pr)
     return align_up((size_t)grad_slots(pr->L) * pr->L * pr->L * sizeof(double));
 }
 
-// room for the node gradients that mrf_bwd_gv_from_g reads (65..128 labels)
+// room for the node gradients that mrf_bwd_pairwise_from_g reads (33..128 labels)
 inline size_t gstore_bytes(const mrf_problem *pr)
 {
-    if (pr->L <= 64 || pr->L > 128) return 0;
+    if (pr->L <= 32 || pr->L > 128) return 0;
     return align_up((size_t)pr->B * pr->H * pr->W * pr->L * sizeof(double));
 }
 
@@ -819,13 +819,13 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
 {
     const dim3 grid((unsigned)P.total_scanlines);
     const bool gv = P.gV != nullptr;
-    const bool gs = LP == 2 && P.gstore != nullptr;       // the helpers store the node gradients (V in LDS, no tables)
-    if (gs) vg = false;
+    const bool gs = LP <= 2 && P.gstore != nullptr;       // the helpers store the node gradients (no tables, no V)
+    if (gs) vg = true;
+    const bool hot = P.hot_label && (gs || !((LP == 1 && gv) || vg));
     note_launch(1, "mrf_bwd_sweep_chain", P.total_scanlines, 64 * (1 + ni), "%d,%d,%d,%d,%s,%s,%s", LP, NS, D, ni,
-                (!(LP == 1 && gv) && vg) ? "true" : "false", ((LP == 1 && gv) || gs) ? "true" : "false",
-                (!(LP == 1 && gv) && !gs && !vg && P.hot_label) ? "true" : "false");
+                (!(LP == 1 && gv) && vg) ? "true" : "false", ((LP == 1 && gv) || gs) ? "true" : "false", hot ? "true" : "false");
     if (gv && (LP != 1 || P.total_scanlines > grad_slots(P.g.L))) return hipErrorInvalidValue;
-    const size_t lds = mrf_bwd_chain_lds_bytes(LP, ni, P.g.L, P.unary_dir >= 0, vg, gv || gs);
+    const size_t lds = mrf_bwd_chain_lds_bytes(LP, ni, P.g.L, P.unary_dir >= 0, vg, gv);
     if (lds > chain_lds_cap(P.total_scanlines)) return hipErrorInvalidValue;
     // (more than 64 KB of dynamic LDS has to be announced per kernel)
 #define MRF_CH_GO(...) \
@@ -845,9 +845,10 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
                 return hipGetLastError(); \
             } \
         } \
-        if constexpr (LP == 2) { \
+        if constexpr (LP <= 2) { \
             if (gs) { \
-                MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, false, true, false>); \
+                if (hot) MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, true, true, true>); \
+                else MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, true, true, false>); \
                 return hipGetLastError(); \
             } \
         } \
@@ -869,6 +870,8 @@ hipError_t run_bwd_chain(MrfBwdParams &P, int ns, int ni, bool vg, hipStream_t s
     if (LP == lp && ns == 1) return launch_bwd_chain<lp, 1, 2>(P, ni, vg, st); \
     if (LP == lp && ns == 4) return launch_bwd_chain<lp, 4, (lp <= 2 ? 2 : 1)>(P, ni, vg, st); \
     if (LP == lp && ns == 8) return launch_bwd_chain<lp, 8, 1>(P, ni, vg, st);
+    if (LP == 1 && ns == 16) return launch_bwd_chain<1, 16, 1>(P, ni, vg, st);
+    if (LP == 2 && ns == 16) return launch_bwd_chain<2, 16, 1>(P, ni, vg, st);
     MRF_CCASE(1) MRF_CCASE(2) MRF_CCASE(3) MRF_CCASE(4)
 #undef MRF_CCASE
     return hipErrorInvalidValue;
@@ -991,8 +994,8 @@ hipError_t launch_bwd_narrow(MrfBwdParams &P, int ns, long long packs, hipStream
                        sizeof(float) * (size_t)L * mrf_bwd_narrow_pitch(L);
     if (lds > 64 * 1024) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(64u * (unsigned)waves);
-    // (one source and no grad theta: ISGMR, every coefficient 1; TRWP forms grad theta in the sweep of one direction)
-    const bool unary = ns == 1 ? P.unary_dir >= 0 : !(P.r_count == 1 && P.r_first != P.unary_dir);
+    // (one source, no grad theta and several directions: ISGMR, every coefficient 1)
+    const bool unary = ns == 1 ? (P.unary_dir >= 0 || P.r_count == 1) : P.unary_dir >= 0;
     const bool full = L % NL == 0;
 #define MRF_N(n, d, un) \
     if (ns == n && unary == un) { \
@@ -1084,7 +1087,7 @@ int narrow_lanes(const MrfBwdParams &P, int L)
     return L <= 24 ? 8 : (P.gV ? 32 : 16);
 }
 
-#define MRF_GV_BLOCKS 256      // workgroups (and slots) of mrf_bwd_gv_from_g
+#define MRF_GV_BLOCKS 256      // workgroups (and slots) of mrf_bwd_pairwise_from_g
 
 hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
 {
@@ -1117,12 +1120,14 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
         if (stp > 0x7fffffffLL) step_fits = false;
     }
     const bool gv_any = P.gV != nullptr;
-    // 65..128 labels, one direction per launch: the chain layout has no room for V-gradient tables, so its
-    // helpers store the node gradients and a streaming pass adds them up afterwards (mrf_bwd_gv_from_g)
-    // (up to 512 scanlines per launch: beyond that the helpers' gathers from V in global memory hold the chain
-    // layout back, 7.8 against 4.5 ms at 1,024 scanlines of 2 x 512 x 512 with 96 labels)
-    const bool gv_apart = gv_any && LP == 2 && P.gstore_buf && P.r_count == 1 && !P.rho_e && !P.force_plain &&
-                          P.total_scanlines <= 512 && g_tune_gv_apart != 1;
+    // 33..128 labels, one direction per launch: the chain layout has no room for V-gradient tables, so its
+    // helpers store the node gradients and a streaming pass forms both pairwise gradients (mrf_bwd_pairwise_from_g)
+    // (backward pass per iteration with all gradients, 256 x 512, 8 directions: 96 labels 3.6 -> 1.3 ms, 64 labels 2.1 ->
+    // 0.9, 40 labels 1.0 -> 0.75; 16 directions on 128 x 256, 96 labels, 3.8 -> 1.35.  Up to 48 labels a launch of one
+    // scanline per compute unit has room for eight helpers with tables of their own: 64 x 96, 40 labels, 4 directions,
+    // 0.10 against 0.13 ms)
+    const bool gv_apart = gv_any && L > 32 && LP <= 2 && P.gstore_buf && P.r_count == 1 && !P.rho_e && !P.force_plain &&
+                          P.total_scanlines <= 1536 && !(L <= 48 && P.total_scanlines <= 256) && g_tune_gv_apart != 1;
     const bool gv = gv_any && !gv_apart;      // the V gradient inside the sweep that runs
     // as many helpers as keep up with the chain while the machine and the LDS have room
     // (measured per launch shape at L = 96: 256 scanlines 165 / 121 / 98 / 90 us with 4 / 6 / 8 / 12
@@ -1130,16 +1135,19 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     int ni = g_tune_chain_ni ? g_tune_chain_ni
                              : (P.total_scanlines <= 256 ? 12
                                 : (P.total_scanlines <= 512 ? (LP >= 2 ? 6 : 8) : (P.total_scanlines <= 1024 ? 6 : 4)));
+    // (the helpers of many source arrays, and those that leave the pairwise gradients to a later pass: six. 128 x 256, 16
+    // directions, 96 labels: 3.1 / 2.7 / 3.0 / 3.6 ms with 4 / 6 / 8 / 12; 256 x 512, 8 directions, 40 labels: 1.75 / 1.50 /
+    // 1.66 / 1.80 ms)
+    if (!g_tune_chain_ni && gv_apart && (ns == 16 || LP == 1 || P.total_scanlines > 512)) ni = 6;
     if (!g_tune_chain_ni && gv && P.total_scanlines > 384 && ni > 6) ni = 6;   // (the accumulators take LDS)
     const bool vg = P.gw && pairwise_kind == MRF_PAIRWISE_DENSE;
-    // (LDS of the chain layout: with the node gradients stored apart it holds all of V, as with its own tables)
-    const bool vg_lds = vg && !gv_apart, gv_lds = gv || gv_apart;
+    const bool vg_lds = vg || gv_apart, gv_lds = gv;
     while (ni > 2 && (mrf_bwd_chain_lds_bytes(LP, ni, L, P.unary_dir >= 0, vg_lds, gv_lds) > chain_lds_cap(P.total_scanlines) ||
                       (gv && P.total_scanlines > grad_slots(L)))) ni = (ni == 12) ? 8 : ni - 2;
     // TRW coefficients or pairwise tables per edge: mrf_bwd_sweep handles them (and is the one
     // sweep that never touches V when no edge-weight gradient is asked for)
     const bool generic = P.rho_e != nullptr || P.force_plain;
-    const bool chain_fits = !generic && step_fits && ns <= 8 && g_tune_chain != 1 &&
+    const bool chain_fits = !generic && step_fits && ns <= (LP <= 2 ? 16 : 8) && g_tune_chain != 1 &&
                             (!gv || (LP == 1 && P.total_scanlines <= grad_slots(L))) &&
                             mrf_bwd_chain_lds_bytes(LP, ni, L, P.unary_dir >= 0, vg_lds, gv_lds) <= chain_lds_cap(P.total_scanlines);
     // (65..128 labels with several source arrays, TRWP: at 2,048 scanlines per launch the plain sweep is ahead,
@@ -1180,7 +1188,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
         // truncated models: the chain wavefront sums the lanes of the most popular scatter target
         // in registers
         // where LDS throughput, not the latency of the chain, bounds the launch
-        P.hot_label = (pairwise_kind != MRF_PAIRWISE_DENSE && !gv && g_tune_chain_hot != 1 &&
+        P.hot_label = ((pairwise_kind != MRF_PAIRWISE_DENSE || gv_apart) && !gv && g_tune_chain_hot != 1 &&
                        (g_tune_chain_hot == 2 || L > 128 || P.total_scanlines > 1024)) ? 1 : 0;
         if (gv_apart) {
             double *const slots = P.gV;
@@ -1192,14 +1200,21 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
             G.N = P.g.N; G.L = L; G.g = P.gstore_buf;
             G.p = P.p + (size_t)P.r_first * P.g.N * L;
             G.w = P.w + (P.w_mul ? (size_t)P.r_first * P.g.N : 0); G.w_mul = P.w_mul;
+            G.V = P.V; G.gw = P.gw ? P.gw + (size_t)P.r_first * P.g.N : nullptr;
             G.gV = slots;
-            const size_t glds = sizeof(double) * (size_t)L * L;
+            const size_t tile = sizeof(double) * (size_t)L * L, both = tile + sizeof(float) * (size_t)L * L;
+            G.v_lds = both <= 156 * 1024 ? 1 : 0;
+            const size_t glds = G.v_lds ? both : tile;
+            // (a workgroup per compute unit at most; for few nodes fewer, so that the table's flush stays small)
+            long long gblocks = P.g.N / 256;
+            gblocks = gblocks < 1 ? 1 : (gblocks > MRF_GV_BLOCKS ? MRF_GV_BLOCKS : gblocks);
+            const void *fn = LP == 1 ? reinterpret_cast<const void *>(&mrf_bwd_pairwise_from_g<1>) : reinterpret_cast<const void *>(&mrf_bwd_pairwise_from_g<2>);
             if (glds > 64 * 1024) {
-                const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void *>(&mrf_bwd_gv_from_g),
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)glds);
+                const hipError_t ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)glds);
                 if (ea != hipSuccess) return ea;
             }
-            hipLaunchKernelGGL(mrf_bwd_gv_from_g, dim3(MRF_GV_BLOCKS), dim3(512), glds, st, G);
+            if (LP == 1) hipLaunchKernelGGL(mrf_bwd_pairwise_from_g<1>, dim3((unsigned)gblocks), dim3(1024), glds, st, G);
+            else hipLaunchKernelGGL(mrf_bwd_pairwise_from_g<2>, dim3((unsigned)gblocks), dim3(1024), glds, st, G);
             return hipGetLastError();
         }
         return run_bwd_chain(P, ns, ni, vg, st);
@@ -1241,7 +1256,7 @@ hipError_t fill(float *dst, long long n, float v, hipStream_t st)
 }
 
 // Slots that the sweeps of a backward call can add to: a layout has at most one per scanline of a launch (the
-// last workgroup of mrf_bwd_sweep may hold up to three wavefronts without one), mrf_bwd_gv_from_g one per workgroup.
+// last workgroup of mrf_bwd_sweep may hold up to three wavefronts without one), mrf_bwd_pairwise_from_g one per workgroup.
 long long slots_in_use(const mrf_problem *pr, const MrfGeom &g, int algo)
 {
     long long most = 0, all = 0;
@@ -1286,7 +1301,7 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     P.rho_e = (algo == MRF_TRWP) ? pr->rho_edge : nullptr;
     const size_t pk = (size_t)R * N * L, qk = (size_t)R * N;
 
-    // workspace: [scalars 256 B][buf0][buf1 (ISGMR only)][V-gradient slots][node gradients for mrf_bwd_gv_from_g (65..128 labels)]
+    // workspace: [scalars 256 B][buf0][buf1 (ISGMR only)][V-gradient slots][node gradients for mrf_bwd_pairwise_from_g (65..128 labels)]
     char *ws = (char *)workspace;
     float *scal = (float *)ws;
     float *buf0 = (float *)(ws + kAlign);                   // ISGMR: grad m-hat   TRWP: s per direction
@@ -1414,7 +1429,6 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     } else {
         P.S = buf0;
         P.src_base = buf0; P.src_stride = NL;
-        P.unary_dir = 0;
         for (int k = K - 1; k >= 0; --k) {
             for (int d = R - 1; d >= 0; --d) {      // reverse of the forward direction order
                 P.r_first = d; P.r_count = 1;
@@ -1435,6 +1449,7 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
                 P.n_src[d] = (signed char)n;
                 P.carry_scale[d] = pr->rho ? pr->rho[d] : 1.0f;
                 P.use_gc = (k == K - 1);
+                P.unary_dir = d == 0 ? 0 : -1;         // (the sweep of direction 0 forms grad theta_i)
                 P.unary_init = (k == K - 1);
                 P.p = p + (size_t)k * pk;
                 P.q = q + (size_t)k * qk;

@@ -78,7 +78,8 @@ struct MrfBwdParams {
     int force_plain;                       // the problem has no V: only mrf_bwd_sweep may run
     double *gstore_buf;                    // [N][L] room for gstore (workspace), or NULL
     double *gstore;                        // mrf_bwd_sweep_chain: if not NULL, its helpers store the gradient vector g of
-                                           // every node here (0 where no update is replayed) for mrf_bwd_gv_from_g
+                                           // every node here (0 where no update is replayed) for mrf_bwd_pairwise_from_g,
+                                           // which forms both pairwise gradients from it
     int *fault;                            // launch-wide word raised when a wait between wavefronts is given up (mrf_wait_turn)
     int spin_limit;                        // microseconds after which a wait is given up
 };
@@ -479,11 +480,13 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
 // step late; with NI >= 2 no wait can depend on itself: post(t - 2 NI), which precedes
 // pre(t) in its helper, needs the chain to have passed step t - 2 NI + 1 only.
 //
-// GV (L <= 64, as far as LDS has room): the launch also wants the V gradient; every helper keeps an accumulator of
-// its own in LDS, lane lambda owning column lambda; their sum goes to the workgroup's slot at the end.  With more than
-// one label per lane the tables do not fit: GV then means that the helpers store the gradient vector g of every
-// node in P.gstore (0 where no update is replayed), from which mrf_bwd_gv_from_g forms the table afterwards;
-// V is still copied to LDS for the edge-weight gradient.
+// GV without VG (L <= 64, as far as LDS has room): the launch also wants the V gradient; every helper keeps an
+// accumulator of its own in LDS, lane lambda owning column lambda; their sum goes to the workgroup's slot at the end.
+// GV with VG (33..128 labels): there is no room for the tables; the helpers store the gradient vector g of every node
+// in P.gstore (0 where no update is replayed) and leave both pairwise gradients to mrf_bwd_pairwise_from_g, a streaming
+// pass that has all of LDS for V and the table.  What is left for a helper is short enough that four of them keep
+// up with the chain, so the layout stays ahead to 1,536 scanlines per launch (it did to 512 while the helpers
+// gathered from V).
 // HOT: truncated models send most labels to one source label, and the chain wavefront's LDS
 // adds would queue at that one word; the helpers guess it (as in mrf_bwd_sweep) and the chain
 // sums its lanes with a DPP tree while the LDS round trip is under way.  Costs the chain some
@@ -502,14 +505,15 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
     double *b_sv = b_cin + NR * LL;                              // [NR][LL]                scattered vector that left it
     double *sbuf = b_sv + NR * LL;                               // [LL] scatter target of the chain
     double *gvacc = sbuf + LL;                                   // [NI][L*L] V-gradient accumulators (GV)
-    constexpr bool GVT = GV && LP == 1;      // V-gradient tables in LDS
-    constexpr bool GS = GV && LP != 1;       // node gradients stored for mrf_bwd_gv_from_g
+    constexpr bool GVT = GV && !VG;          // V-gradient tables in LDS
+    constexpr bool GS = GV && VG;            // node gradients stored for mrf_bwd_pairwise_from_g
+    static_assert(!GVT || LP == 1, "V-gradient tables");
     float *a_extT = reinterpret_cast<float *>(gvacc + (GVT ? NI * P.g.L * P.g.L : 0));   // [NR][LL] pre -> post (launches that form grad theta)
     int *pre_done = reinterpret_cast<int *>(a_extT + (P.unary_dir >= 0 ? NR * LL : 0));   // [MRF_CHAIN_MAX_HELPERS] per helper: last step published
     int *chain_done = pre_done + MRF_CHAIN_MAX_HELPERS;          // last step the chain finished
     int *a_hot = chain_done + 1;                                 // [NR] pre -> chain: most popular scatter target, or -1
-    float *vl = reinterpret_cast<float *>(a_hot + 2 * MRF_CHAIN_MAX_HELPERS);   // [L] first row of V (unless VG), all of V (GV)
-    uint8_t *a_p = reinterpret_cast<uint8_t *>(vl + (GV ? P.g.L * P.g.L : (VG ? 0 : P.g.L)));   // [NR][LL]
+    float *vl = reinterpret_cast<float *>(a_hot + 2 * MRF_CHAIN_MAX_HELPERS);   // [L] first row of V (unless VG), all of V (tables)
+    uint8_t *a_p = reinterpret_cast<uint8_t *>(vl + (GVT ? P.g.L * P.g.L : (VG ? 0 : P.g.L)));   // [NR][LL]
     MrfWaitBlock &wait_lds = *reinterpret_cast<MrfWaitBlock *>(
         mrf_bsmem + ((a_p + NR * LL - mrf_bsmem) + 7) / 8 * 8);  // for the waits below (mrf_wait_turn)
     const int L = P.g.L;
@@ -517,10 +521,9 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // uniform, and known to be
     const long long N = P.g.N;
 
-    if (GV) {
+    if (GVT) {
         for (int e = threadIdx.x; e < L * L; e += blockDim.x) vl[e] = P.V[e];
-        if (GVT)
-            for (int e = threadIdx.x; e < NI * L * L; e += blockDim.x) gvacc[e] = 0.0;
+        for (int e = threadIdx.x; e < NI * L * L; e += blockDim.x) gvacc[e] = 0.0;
     } else if (!VG) {
         for (int e = threadIdx.x; e < L; e += blockDim.x) vl[e] = P.V[e];
     }
@@ -813,7 +816,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
                         const double g = cin + a_ext[slot * LL + lam];    // as the chain formed it
                         const int pv = a_p[slot * LL + lam];
                         if constexpr (GS) gsw[oi + lam] = update ? g : 0.0;
-                        if (P.gw) {
+                        if (!GS && P.gw) {
                             float vv;
                             if (GV) {
                                 vv = vl[__mul24(pv, L) + lam];
@@ -829,7 +832,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
                             gvl[__mul24(pv, L) + lam] = __builtin_fma((double)wlast, g, gvl[__mul24(pv, L) + lam]);
                     }
                 }
-                if (P.gw) {
+                if (!GS && P.gw) {
                     acc = mrf_wave_sum_f64(acc);
                     // one writer per entry and launch: a no-return atomic is a plain accumulate
                     if (update && lane == 0)

@@ -4,12 +4,14 @@
 
 #include "mrfmp_device.h"
 
-// ---- grad V apart from the sweep (65..128 labels beside mrf_bwd_sweep_chain) --------------------
-// Eq. supp-gradient-smoothness: entry (p(lambda), lambda) of the table receives theta_{i-r,i} g(lambda) at
-// every replayed update.  Nothing of it depends on the order of the nodes, so where the chain layout has no
-// room for the table its helpers store g per node and this streaming pass does the additions: one wavefront
-// per node, lanes over lambda, the L x L table of a workgroup in LDS (`ds_add_f64`), added to the workgroup's
-// slot at the end.
+// ---- pairwise gradients apart from the sweep (33..128 labels beside mrf_bwd_sweep_chain) ------------
+// Eq. supp-gradient-smoothness and Eq. supp-gradient-edge: at every replayed update, entry (p(lambda), lambda) of the
+// table receives theta_{i-r,i} g(lambda), and theta_{i-r,i} receives sum_lambda g(lambda) V(p(lambda), lambda).
+// Nothing of them depends on the order of the nodes, so where the chain layout has no room for the tables its
+// helpers store g per node and this streaming pass does the rest: lanes over lambda, one node after the other per
+// wavefront, the L x L table of a workgroup and V in LDS, the table added to the workgroup's slot at the end.
+// Bound by HBM (9 bytes per label); with a single node in flight per wavefront it was bound by the latency of the
+// loads, 129 us at 256 x 512, 96 labels.
 struct MrfGvParams {
     long long N;
     int L;
@@ -17,47 +19,65 @@ struct MrfGvParams {
     const uint8_t *p;        // [N][L] of this direction and iteration
     const float *w;          // [N] edge weights of this direction, or the scalar at w[0] when w_mul == 0
     int w_mul;
+    const float *V;          // [L][L]
+    int v_lds;               // V fits in LDS next to the table
+    float *gw;               // [N] edge-weight gradient of this direction, accumulated, or NULL
     double *gV;              // [gridDim.x][L][L] slots
 };
 
-// Bound by the latency of the loads unless several nodes are in flight per wavefront: with one, 2,048 wavefronts
-// took 129 us for the 113 MB of a 256 x 512 grid with 96 labels.
-__global__ void __launch_bounds__(512) mrf_bwd_gv_from_g(const MrfGvParams P)
+template <int LP>
+__global__ void __launch_bounds__(1024) mrf_bwd_pairwise_from_g(const MrfGvParams P)
 {
     extern __shared__ __align__(16) unsigned char mrf_gvsmem[];
     double *tile = reinterpret_cast<double *>(mrf_gvsmem);
+    float *vl = reinterpret_cast<float *>(tile + P.L * P.L);
     constexpr int U = 4;                 // nodes in flight per wavefront
     const int L = P.L;
     for (int e = threadIdx.x; e < L * L; e += blockDim.x) tile[e] = 0.0;
+    if (P.v_lds)
+        for (int e = threadIdx.x; e < L * L; e += blockDim.x) vl[e] = P.V[e];
     __syncthreads();
+    const float *V = P.v_lds ? vl : P.V;
     const int lane = threadIdx.x & 63;
     const long long wave = (long long)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const long long nwaves = (long long)gridDim.x * (blockDim.x >> 6);
-    const int lc0 = lane < L ? lane : 0, lc1 = lane + 64 < L ? lane + 64 : 0;
+    int lc[LP];
+#pragma unroll
+    for (int s = 0; s < LP; ++s) lc[s] = lane + 64 * s < L ? lane + 64 * s : 0;
     for (long long i0 = wave * U; i0 < P.N; i0 += nwaves * U) {
-        double g[U][2];
-        int pv[U][2];
+        double g[U][LP];
+        int at[U][LP];
         float w[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const long long i = i0 + u < P.N ? i0 + u : P.N - 1;
             w[u] = P.w[(size_t)(i * P.w_mul)];
-            g[u][0] = P.g[(size_t)i * L + lc0];
-            g[u][1] = P.g[(size_t)i * L + lc1];
-            pv[u][0] = P.p[(size_t)i * L + lc0];
-            pv[u][1] = P.p[(size_t)i * L + lc1];
-        }
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const int lam = lane + 64 * s;
-                if (lam < L && i0 + u < P.N && g[u][s] != 0.0) {
-                    const int pc = pv[u][s] < L ? pv[u][s] : L - 1;
-                    __hip_atomic_fetch_add(&tile[__mul24(pc, L) + lam], (double)w[u] * g[u][s], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
+            for (int s = 0; s < LP; ++s) {
+                g[u][s] = P.g[(size_t)i * L + lc[s]];
+                at[u][s] = P.p[(size_t)i * L + lc[s]];
             }
+        }
+        float mine = 0.0f;               // lane u: edge-weight gradient of node i0 + u
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            double acc = 0.0;
+#pragma unroll
+            for (int s = 0; s < LP; ++s) {
+                const bool live = lane + 64 * s < L && i0 + u < P.N && g[u][s] != 0.0;
+                const int pc = at[u][s] < L ? at[u][s] : L - 1;
+                const int e = __mul24(pc, L) + lc[s];
+                if (live) __hip_atomic_fetch_add(&tile[e], (double)w[u] * g[u][s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (P.gw) acc = __builtin_fma(live ? g[u][s] : 0.0, (double)V[e], acc);
+            }
+            if (P.gw) {
+                acc = mrf_wave_sum_f64(acc);
+                if (lane == u) mine = (float)acc;
+            }
+        }
+        // one writer per entry and launch: a no-return atomic is a plain accumulate
+        if (P.gw && lane < U && i0 + lane < P.N)
+            __hip_atomic_fetch_add(&P.gw[(size_t)(i0 + lane)], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     double *slot = P.gV + (size_t)blockIdx.x * L * L;
