@@ -497,6 +497,26 @@ hipError_t launch_fwd_sliced(const MrfFwdParams &P, int algo, long long blocks, 
     return hipGetLastError();
 }
 
+template <int NW, int RMAX, int D>
+hipError_t launch_fwd_halves(const MrfFwdParams &P, int algo, long long blocks, hipStream_t st)
+{
+    note_launch(0, "mrf_fwd_sweep_halves", blocks, 64 * NW, "%d,%d,%d,%s", NW, RMAX, D, algo == MRF_TRWP ? "true" : "false");
+    constexpr int lds = mrf_fwd_halves_lds<NW>();
+#define MRF_H_GO(...) \
+    do { \
+        if (lds > 64 * 1024) { \
+            const hipError_t ea_ = hipFuncSetAttribute(reinterpret_cast<const void *>(&__VA_ARGS__), \
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds); \
+            if (ea_ != hipSuccess) return ea_; \
+        } \
+        hipLaunchKernelGGL((__VA_ARGS__), dim3((unsigned)blocks), dim3(64 * NW), lds, st, P); \
+    } while (0)
+    if (algo == MRF_TRWP) MRF_H_GO(mrf_fwd_sweep_halves<NW, RMAX, D, true>);
+    else MRF_H_GO(mrf_fwd_sweep_halves<NW, RMAX, D, false>);
+#undef MRF_H_GO
+    return hipGetLastError();
+}
+
 // source labels per wavefront: small enough that the slice of V fits in registers, large
 // enough that at most 16 wavefronts share a node
 // (33..64 labels: four wavefronts of 16 source labels while the launch leaves SIMD slots free, two of 32 from
@@ -527,6 +547,20 @@ hipError_t run_dense(MrfFwdParams &P, int algo, long long blocks, hipStream_t st
     for (int r = P.r_first; r < P.r_first + P.r_count; ++r)
         if (P.n_src[r] > max_src) max_src = P.n_src[r];
     const int rmax = (max_src + 1 <= 4) ? 4 : ((max_src + 1 <= 8) ? 8 : 16);
+    // 33..128 labels: chunk minima (any launch size, as far as its 32-bit offsets reach)
+    // (256 x 512, K = 2, against the better of the other two sweeps: 96 labels TRWP 3.6 -> 2.3 ms with 4 directions, 7.9 ->
+    // 4.7 with 8, ISGMR 2.1 -> 1.2; 64 labels 2.1 -> 1.8, 4.0 -> 3.3, 0.91 -> 0.69; 128 labels 4.0 -> 2.9, 8.2 -> 6.0, 2.3 ->
+    // 2.0; ahead at every size tried from 64 x 96 to 4 x 256 x 512)
+    if (L > 32 && L <= 128 && P.g.N * L * P.g.R <= MRF_BUF_MOST && !generic && !P.sgm_std && g_tune_mch == 0 && g_tune_dense_sliced == 0) {
+        const int nw = (L + 31) / 32;
+        P.NW = nw;
+#define MRF_HCASE(n) \
+        if (nw == n && rmax == 4) return launch_fwd_halves<n, 4, 4>(P, algo, blocks, st); \
+        if (nw == n && rmax == 8) return launch_fwd_halves<n, 8, 2>(P, algo, blocks, st); \
+        if (nw == n && rmax == 16) return launch_fwd_halves<n, 16, 1>(P, algo, blocks, st);
+        MRF_HCASE(2) MRF_HCASE(3) MRF_HCASE(4)
+#undef MRF_HCASE
+    }
     // more than 64 labels: every wavefront owns 32 of them (unless a tuning knob or a per-edge variant asks
     // for the sweep in which every wavefront does the O(L) work of the whole node)
     // (for 65..128 labels where the work outside the candidates is large: many source arrays, or a launch that

@@ -497,6 +497,11 @@ __device__ inline void mrf_buf_store_f32xn(mrf_buf b, unsigned off, const float 
     else if constexpr (NL == 3) __builtin_amdgcn_raw_buffer_store_b96(u3{x[0], x[1], x[2]}, b, off, 0, 0);
     else __builtin_amdgcn_raw_buffer_store_b128(u4{x[0], x[1], x[2], x[3]}, b, off, 0, 0);
 }
+// the same with a uniform part of the offset in a scalar register
+__device__ inline float mrf_buf_f32s(mrf_buf b, unsigned off, unsigned soff)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, off, soff, 0));
+}
 __device__ inline int mrf_buf_u8(mrf_buf b, unsigned off) { return (int)__builtin_amdgcn_raw_buffer_load_b8(b, off, 0, 0); }
 __device__ inline void mrf_buf_store_f32(mrf_buf b, unsigned off, float v)
 {

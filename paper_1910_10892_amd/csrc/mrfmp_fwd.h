@@ -18,6 +18,7 @@
 // Kernels in this file, all computing the same update in the same rounding order:
 //   mrf_fwd_sweep               dense O(L^2), NW wavefronts per scanline split the source labels
 //   mrf_fwd_sweep_sliced        dense, L > 64: the same with the O(L) work of a node divided among the wavefronts
+//   mrf_fwd_sweep_halves        dense, 33..128 labels: chunk minima, argmin by a second look at the winning chunk
 //   mrf_fwd_sweep_packed        dense, L <= 32: several scanlines per wavefront
 //   mrf_fwd_sweep_edge          pairwise potentials given per edge (L <= 64)
 //   mrf_aggregate               final costs and labels
@@ -542,6 +543,248 @@ mrf_fwd_sweep_sliced(const MrfFwdParams P)
             for (int c = 0; c < RMAX; ++c) cur[u][c] = nxt[u][c];
         }
     }
+}
+
+// ---- dense sweep for 33..128 labels: chunk minima, argmin by a second look ----------------------------
+//
+// The O(L^2) update with fewer instructions per candidate.  A running (minimum, argmin) costs four per candidate
+// (fma, compare, minimum, select).  Here eight candidates form their minimum with three-operand minima and only that
+// enters the running (minimum, chunk): 15 instructions for eight.  The index inside the winning chunk is found
+// afterwards by evaluating its eight candidates once more for the label and comparing with the minimum (the same fma
+// on the same operands gives the same bits); V for that comes from a transposed copy in LDS, h from the node's LDS row.
+// Wavefront w owns the 32 destination labels 32 w .. 32 w + 31 (as in mrf_fwd_sweep_sliced: it loads, forms h,
+// normalises and stores for them); its lower 32 lanes evaluate the first half of the source labels, its upper 32 lanes the
+// second half, for the same destination labels, so no lane idles at 96 labels and the two halves meet by one lane
+// swap; nothing is merged across wavefronts.  One barrier per node: after it every wavefront reads all of h.
+// Where V is non-negative with a zero diagonal (looked at once per workgroup) and the weight is not negative, every
+// candidate is >= its h and the one at the smallest h with lambda = mu equals it, so the minimum over lambda that
+// Eq. isgmr-norm takes off is the minimum of h, which travels with h; otherwise a second barrier exchanges the minima of
+// the new message.  q of a node is assembled behind the next barrier.
+// Per node and wavefront at 96 labels about 240 instructions (mrf_fwd_sweep_sliced: 360, two barriers).
+template <int NW>
+__host__ __device__ constexpr int mrf_fwd_halves_lds() { return NW * 32 * (NW * 32 + 4) * (int)sizeof(float); }
+
+template <int NW, int RMAX, int D, bool TRWP>
+__global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdParams P)
+{
+    constexpr int LA = 32 * NW;                   // labels, rounded up
+    constexpr int LH = LA / 2;                    // source labels per half
+    constexpr int PT = LA + 4;                    // pitch of the transposed table (16-byte rows on different banks)
+    constexpr int NCH = LH / 8;                   // chunks per half
+    extern __shared__ __align__(16) unsigned char mrf_smem[];
+    float *vt = reinterpret_cast<float *>(mrf_smem);             // [LA][PT] V transposed: row lambda
+    __shared__ __align__(16) float hrow[2][LA];                  // h of the node, by step parity
+    __shared__ __align__(16) float hmin_w[2][4];                 // minimum of h per wavefront
+    __shared__ __align__(16) float tmin_w[4];                    // minimum of the new message per wavefront (general case)
+    __shared__ __align__(16) int q_w[2][4];                      // lowest label that attains the minimum, per wavefront
+    const int L = P.g.L;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int hf = lane >> 5;
+    const int lam = 32 * wv + (lane & 31);
+    const bool valid = lam < L;
+    const int lamc = valid ? lam : 0;
+
+    const long long blk = blockIdx.x;
+    const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
+    const int r = P.r_first + ri;
+    const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
+    const unsigned nsc = (unsigned)P.g.nscan[r];
+    const int b = (int)(local / nsc);
+    const unsigned t = local - (unsigned)b * nsc;
+    const int dh = P.g.dh[r], dw = P.g.dw[r];
+    int y0, x0, len;
+    mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
+    const long long N = P.g.N;
+    const long long head = ((long long)b * P.g.H + y0) * P.g.W + x0;
+    const long long nstep = (long long)dh * P.g.W + dw;
+    const float rho = P.rho[r];
+    const int n_pre = P.n_pre[r], n_src = P.n_src[r], rm_slot = P.rm_slot[r];
+
+    // Sources of h in summation order: the unary, then message arrays; unused slots load 0 and enter with factor 0
+    // (fma(0, 0, v) = v and fma(1, x, v) = v + x exactly).  r^- once more by itself.  All of them through buffer views:
+    // a lane's offset is its label, the node's is a scalar.
+    const unsigned NLb = (unsigned)(N * L) * 4u, headb = (unsigned)(head * L) * 4u;
+    const mrf_buf bu = mrf_buffer(P.unary + (size_t)__builtin_amdgcn_readfirstlane((int)P.unary_slab[r]) * N * L, NLb);
+    const mrf_buf bm = mrf_buffer(P.m_in, (size_t)P.g.R * N * L * 4), bmo = mrf_buffer(P.m_out + (size_t)r * N * L, NLb);
+    const mrf_buf bp = mrf_buffer(P.p + (size_t)r * N * L, (size_t)(N * L)), bq = mrf_buffer(P.q + (size_t)r * N, (size_t)N);
+    const mrf_buf bw = mrf_buffer(P.w + (P.w_mul ? (size_t)r * N : 0), P.w_mul ? (size_t)N * 4 : 4);
+    unsigned slab[RMAX], slab_rm = 0;
+    float before[RMAX], after[RMAX];
+    const float vz = mrf_opaque_zero_f();
+    slab[0] = 0;
+#pragma unroll
+    for (int c = 1; c < RMAX; ++c) {
+        // (what came through byte loads is uniform, which the compiler cannot know)
+        slab[c] = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)P.src_dir[r][c <= n_src ? c - 1 : 0] * NLb));
+        before[c] = ((c <= n_src && (!TRWP || c <= n_pre)) ? 1.0f : 0.0f) + vz;
+        after[c] = ((c <= n_src && TRWP && c > n_pre) ? 1.0f : 0.0f) + vz;
+    }
+    if (TRWP && rm_slot >= 0) slab_rm = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)P.src_dir[r][rm_slot] * NLb));
+
+    // V: the lane's column of its half's rows in registers, all of it transposed in LDS
+    bool plain = true;                             // V >= 0 with a zero diagonal, as far as this lane looks
+    float Vr[LH];
+#pragma unroll
+    for (int i = 0; i < LH; ++i) {
+        const int mu = hf * LH + i;
+        Vr[i] = (mu < L && valid) ? P.V[(size_t)mu * L + lam] : 0.0f;
+        plain = plain && !(Vr[i] < 0.0f) && !(mu == lam && Vr[i] != 0.0f);
+        vt[lam * PT + mu] = Vr[i];
+    }
+    if (threadIdx.x < 8) { (&hmin_w[0][0])[threadIdx.x] = INFINITY; (&q_w[0][0])[threadIdx.x] = 255; }
+    if (threadIdx.x < 4) tmin_w[threadIdx.x] = INFINITY;
+    // sign bit set: some node step may not take the minimum of h for that of the new message
+    const int slow = __syncthreads_and(plain ? 1 : 0) != 0 ? 0 : (int)0x80000000;
+
+    const unsigned moff = valid && hf == 0 ? 4u * (unsigned)lam : MRF_BUF_NONE;      // the lower half stores m, the upper one p
+    const unsigned poff = valid && hf == 1 ? (unsigned)lam : MRF_BUF_NONE;
+    const unsigned qoff = wv == NW - 1 && lane == 0 ? 0u : MRF_BUF_NONE;
+    auto store_f32 = [](mrf_buf bb, unsigned off, unsigned soff, float x) { __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), bb, off, soff, 0); };
+    auto store_u8 = [](mrf_buf bb, unsigned off, unsigned soff, int x) { __builtin_amdgcn_raw_buffer_store_b8((unsigned char)x, bb, off, soff, 0); };
+    // first node of the scanline: message 0, p = q = 0
+    store_f32(bmo, moff, headb, 0.0f);
+    store_u8(bp, poff, headb >> 2, 0);
+    store_u8(bq, qoff, (unsigned)head, 0);
+    if (len < 2) return;
+
+    const unsigned lane4 = 4u * (unsigned)lamc;
+    unsigned laneof[RMAX];
+#pragma unroll
+    for (int c = 0; c < RMAX; ++c) laneof[c] = c <= n_src ? lane4 : MRF_BUF_NONE;
+    const unsigned laneof_rm = rm_slot >= 0 ? lane4 : MRF_BUF_NONE;
+    const unsigned step_lb = (unsigned)((int)nstep * L) * 4u, step_n = (unsigned)(int)nstep;
+    struct In {
+        float v[RMAX];
+        float rm, w;
+    };
+    In A[D], B[D];
+    int pleft = len - 2;                           // the prefetch stays at the last source node, whose further copies are never used
+    unsigned pb = headb, pw = (unsigned)head + step_n;
+    auto prefetch = [&](In &in) {
+        in.v[0] = mrf_buf_f32s(bu, lane4, pb);
+#pragma unroll
+        for (int c = 1; c < RMAX; ++c) in.v[c] = mrf_buf_f32s(bm, laneof[c], pb + slab[c]);
+        in.rm = TRWP ? mrf_buf_f32s(bm, laneof_rm, pb + slab_rm) : 0.0f;
+        in.w = mrf_buf_f32s(bw, 0, P.w_mul ? pw * 4u : 0u);
+        if (pleft > 0) { pb += step_lb; pw += step_n; }
+        --pleft;
+    };
+
+    float carry = 0.0f;
+    unsigned ob = headb, on = (unsigned)head;      // the node before the one that is formed
+    auto group = [&](const In (&in)[D], int n0) {
+        float pre[D];
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            pre[u] = in[u].v[0];
+#pragma unroll
+            for (int c = 1; c < RMAX; ++c) pre[u] = __builtin_fmaf(before[c], in[u].v[c], pre[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            const int n = n0 + u;
+            if (n >= len) break;                   // (uniform)
+            const int par = n & 1;
+            // ---- h at node i-r for the home labels, its minimum (entries past L hold +inf: they never win) ----
+            float v = pre[u] + carry;
+            if (TRWP) {
+#pragma unroll
+                for (int c = 1; c < RMAX; ++c) v = __builtin_fmaf(after[c], in[u].v[c], v);
+                v = rho * v;
+                v = v - in[u].rm;
+            }
+            v = valid ? v : INFINITY;
+            hrow[par][lam] = v;
+            hmin_w[par][wv] = mrf_wave_min(v);     // (every lane writes the same word)
+            const float wgt = in[u].w;
+            mrf_block_sync_lds();
+
+            // all of the half's h and the minima in one batch of LDS reads
+            const float *hh = &hrow[par][hf * LH];
+            float hq[LH];
+#pragma unroll
+            for (int i = 0; i < LH; i += 4) {
+                const float4 x = *reinterpret_cast<const float4 *>(&hh[i]);
+                hq[i] = x.x; hq[i + 1] = x.y; hq[i + 2] = x.z; hq[i + 3] = x.w;
+            }
+            const float4 h4 = *reinterpret_cast<const float4 *>(&hmin_w[par][0]);
+            const int4 qc = *reinterpret_cast<const int4 *>(&q_w[par ^ 1][0]);
+            __builtin_amdgcn_sched_barrier(0);
+
+            // ---- chunk minima over the half's source labels ----
+            float best = INFINITY;
+            int cid = 0;
+            mrf_static_for<NCH>([&](auto cc) {
+                constexpr int ch = decltype(cc)::value;
+                float d[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) d[j] = __builtin_fmaf(wgt, Vr[8 * ch + j], hq[8 * ch + j]);
+                const float m = mrf_min3(mrf_min3(d[0], d[1], d[2]), mrf_min3(d[3], d[4], d[5]), mrf_min(d[6], d[7]));
+                if constexpr (ch == 0) {
+                    best = m;
+                } else {
+                    cid = m < best ? ch : cid;
+                    best = mrf_min(best, m);
+                }
+            });
+            // the halves meet: source labels of the lower half come first, so they keep a tie
+            const auto bx = __builtin_amdgcn_permlane32_swap(__float_as_uint(best), __float_as_uint(best), false, false);
+            const auto cx = __builtin_amdgcn_permlane32_swap((unsigned)cid, (unsigned)cid, false, false);
+            const float blo = __uint_as_float(bx[0]), bhi = __uint_as_float(bx[1]);
+            const float tv = mrf_min(blo, bhi);
+            const int mu0 = bhi < blo ? LH + 8 * (int)cx[1] : 8 * (int)cx[0];
+
+            // ---- minimum over the labels (Eq. isgmr-norm) ----
+            float tq = mrf_min(mrf_min(h4.x, h4.y), mrf_min(h4.z, h4.w));
+            if (__builtin_expect((__builtin_amdgcn_readfirstlane(__float_as_int(wgt)) | slow) < 0, 0)) {
+                tmin_w[wv] = mrf_wave_min(valid ? tv : INFINITY);
+                mrf_block_sync_lds();
+                const float4 t4 = *reinterpret_cast<const float4 *>(&tmin_w[0]);
+                tq = mrf_min(mrf_min(t4.x, t4.y), mrf_min(t4.z, t4.w));
+            }
+            carry = tv - tq;
+            const unsigned qb = (unsigned)__ballot((int)valid & (int)(tv == tq));
+            q_w[par][wv] = qb != 0u ? 32 * wv + __ffs((int)qb) - 1 : 255;
+
+            // ---- p: the lowest source label of the winning chunk that attains the minimum, four per half ----
+            const int m4 = mu0 + 4 * hf;
+            const float4 va = *reinterpret_cast<const float4 *>(&vt[lam * PT + m4]), hv = *reinterpret_cast<const float4 *>(&hrow[par][m4]);
+            int pf = 255;
+            pf = __builtin_fmaf(wgt, va.w, hv.w) == tv ? m4 + 3 : pf;
+            pf = __builtin_fmaf(wgt, va.z, hv.z) == tv ? m4 + 2 : pf;
+            pf = __builtin_fmaf(wgt, va.y, hv.y) == tv ? m4 + 1 : pf;
+            pf = __builtin_fmaf(wgt, va.x, hv.x) == tv ? m4 : pf;
+            const auto px = __builtin_amdgcn_permlane32_swap((unsigned)pf, (unsigned)pf, false, false);
+
+            // q of the node before (for the second node: of the first, whose q is 0 again)
+            store_u8(bq, qoff, on, n > 1 ? min(min(qc.x, qc.y), min(qc.z, qc.w)) : 0);
+            ob += step_lb;
+            on += step_n;
+            store_f32(bmo, moff, ob, carry);
+            store_u8(bp, poff, ob >> 2, (int)min(px[0], px[1]));
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < D; ++u) prefetch(A[u]);
+    // (dropped stores: what is in flight at the loop's entry then looks like what is in flight when it comes round)
+#pragma unroll
+    for (int u = 0; u < 3 * D; ++u) store_u8(bq, MRF_BUF_NONE, 0, 0);
+    for (int n0 = 1; n0 < len; n0 += 2 * D) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) prefetch(B[u]);
+        __builtin_amdgcn_sched_barrier(0);
+        group(A, n0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < D; ++u) prefetch(A[u]);
+        __builtin_amdgcn_sched_barrier(0);
+        group(B, n0 + D);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    mrf_block_sync_lds();
+    const int4 qc = *reinterpret_cast<const int4 *>(&q_w[(len - 1) & 1][0]);
+    store_u8(bq, qoff, on, min(min(qc.x, qc.y), min(qc.z, qc.w)));
 }
 
 // ---- sweep for pairwise potentials given per edge ---------------------------------------------

@@ -170,6 +170,45 @@ def test_dense_sweep_with_a_slice_of_labels_per_wavefront(oracle, case):
         np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
 
 
+HALVES_CASES = [
+    # seed, algo, B, H, W, L, dirs, K, integer_valued, V: "plain" (>= 0, zero diagonal) | "mixed signs", some weights negative
+    (611, "trwp", 1, 5, 9, 33, DIRS4, 3, False, "plain", False), (612, "isgmr", 2, 4, 7, 64, DIRS8, 2, True, "plain", False),
+    (613, "trwp", 1, 6, 5, 65, DIRS8, 2, False, "plain", True), (614, "isgmr", 1, 3, 11, 96, DIRS16, 2, False, "mixed", False),
+    (615, "trwp", 1, 7, 6, 97, DIRS4, 3, True, "mixed", True), (616, "isgmr", 1, 4, 8, 128, DIRS4, 2, False, "plain", True),
+    (617, "trwp", 1, 1, 40, 127, [(0, 1), (1, 0), (-1, 0)], 2, True, "plain", False), (618, "trwp", 1, 3, 7, 40, DIRS16, 2, True, "plain", False),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", HALVES_CASES, ids=lambda c: "seed%d" % c[0])
+def test_dense_sweep_with_chunk_minima(oracle, case):
+    """33..128 labels, dense table: the sweep that finds the argmin by a second look at the winning chunk, with
+    tables for which the minimum of the new message is that of h and with tables and weights for which it is not,
+    ties included; against the oracle and bit for bit against the sweep with a running argmin."""
+    import paper_1910_10892_amd as mrf
+    seed, algo, B, H, W, L, dirs, K, iv, table, neg = case
+    print("case dense halves", case[:6], len(dirs), case[7:], flush=True)
+    pr = random_problem(seed, algo, B, H, W, L, dirs, K, integer_valued=iv, symmetric=False, rho=np.linspace(0.3, 0.9, len(dirs)))
+    pr.grad_cost = (pr.grad_cost * (0.02 if len(dirs) > 8 else 0.2)).astype(np.float32)
+    if table == "plain":
+        np.fill_diagonal(pr.pairwise, 0.0)
+    else:
+        pr.pairwise = (pr.pairwise - np.float32(1.0 if iv else 0.3)).astype(np.float32)
+    if neg:
+        sign = np.where(np.random.default_rng(seed).random(pr.edge_weight.shape) > 0.2, 1.0, -0.5)
+        pr.edge_weight = (pr.edge_weight * sign).astype(np.float32)
+    try:
+        a = full_check(oracle, pr, want_V=False)
+        assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_halves", mrf.mrf_last_sweep_launch(False)
+        assert mrf.mrf_tune(16, 1) == 0
+        b = full_check(oracle, pr, want_V=False)
+        assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep"
+    finally:
+        mrf.mrf_tune(16, 0)
+    for name in ("p", "q", "labels", "cost", "messages"):
+        np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
+
+
 PRESUM_CASES = [
     # seed, B, H, W, L, dirs, K, integer_valued, truncated
     (701, 1, 6, 7, 40, DIRS8, 3, False, False), (702, 2, 5, 6, 21, DIRS8, 3, True, False),
