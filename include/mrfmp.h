@@ -282,7 +282,7 @@ int mrf_set_sweep_events(void *start_event, void *stop_event);
  *           1 = never, 2 = always
  *   knob 10: index wavefronts per scanline in that layout: 0 = default, 4, 8
  *   knob 11: two index wavefronts next to the value wavefront in the sweep of knob 3: 0 = by launch size,
- *           1 = never, 2 = always
+ *           1 = never, 2 = always, 3 = never, with 64-bit offsets
  *   knob 12: in the sweep of knob 6, sum the lanes of the most popular scatter target in registers
  *           (truncated models): 0 = by launch shape, 1 = never, 2 = whenever V is not a dense table
  *   knob 13: three scanlines per wavefront (segments of 21 lanes) in the sweeps of knob 3 for 17..21 labels:

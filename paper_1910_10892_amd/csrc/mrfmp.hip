@@ -143,7 +143,7 @@ MRF_G(int g_tune_gv_apart, 0);     // V gradient of 65..128 labels by a streamin
 MRF_G(int g_tune_gv_tile, 0);      // V gradient of 33..128 labels in one LDS table per workgroup: 0 yes, 1 no (a slot per wavefront in global memory)
 MRF_G(int g_tune_dense_sliced, 0); // dense sweep for more than 64 labels with a slice of the labels per wavefront: 0 yes, 1 no
 MRF_G(int g_tune_spin_limit, 0); // turns a wait between wavefronts may take: 0 = default
-MRF_G(int g_tune_pack_idx, 0);   // index wavefronts in the packed dense sweep: 0 by launch size, 1 never, 2 always
+MRF_G(int g_tune_pack_idx, 0);   // index wavefronts in the packed dense sweep: 0 by launch size, 1 never, 2 always, 3 never and 64-bit offsets
 MRF_G(int g_tune_chain, 0);      // backward sweep with a chain wavefront: 0 auto, 1 never, 2 whenever possible
 MRF_G(int g_tune_chain_hot, 0);  // its pre-reduction of the most popular scatter target: 0 auto, 1 never, 2 whenever V is no dense table
 MRF_G(int g_tune_chain_ni, 0);   // its helpers per scanline: 0 auto, 2, 4, 6, 8
@@ -248,12 +248,39 @@ hipError_t run_bwd_tile(MrfBwdParams &P, int ns, long long blocks, size_t lds, h
 
 #if MRF_HAS_FWD_PACKED
 template <int SEG, int MU>
+hipError_t launch_narrow_mu(MrfFwdParams P, int algo, int rmax, hipStream_t st)
+{
+    constexpr int NSEG = 64 / SEG;
+    P.pack_begin[0] = 0;
+    for (int ri = 0; ri < P.r_count; ++ri)
+        P.pack_begin[ri + 1] = P.pack_begin[ri] + (int)((P.blk_begin[ri + 1] - P.blk_begin[ri] + NSEG - 1) / NSEG);
+    const unsigned blocks = (unsigned)P.pack_begin[P.r_count];
+    note_launch(0, "mrf_fwd_sweep_narrow", blocks, 64, "%d,%d,%d,%d,%s", SEG, MU, rmax, rmax <= 4 ? 4 : (rmax == 8 ? 2 : 1),
+                algo == MRF_TRWP ? "true" : "false");
+#define MRF_P(rm, d) \
+    if (rmax == rm) { \
+        if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_narrow<SEG, MU, rm, d, true>), dim3(blocks), dim3(64), 0, st, P); \
+        else hipLaunchKernelGGL((mrf_fwd_sweep_narrow<SEG, MU, rm, d, false>), dim3(blocks), dim3(64), 0, st, P); \
+        return hipGetLastError(); \
+    }
+    MRF_P(1, 4) MRF_P(4, 4) MRF_P(8, 2) MRF_P(16, 1)
+#undef MRF_P
+    return hipErrorInvalidValue;
+}
+
+template <int SEG, int MU>
 hipError_t launch_packed_mu(const MrfFwdParams &P, int algo, int rmax, long long scanlines, hipStream_t st)
 {
     const unsigned blocks = (unsigned)((scanlines + 64 / SEG - 1) / (64 / SEG));
     // few wavefronts in the launch: further ones per workgroup for the argmin tables and the stores
     // (two of them: an index wavefront has more to do per node than the value wavefront)
-    const bool idx = g_tune_pack_idx != 1 && (g_tune_pack_idx == 2 || blocks <= 1024);
+    const bool idx = g_tune_pack_idx == 2 || (g_tune_pack_idx == 0 && blocks <= 1024);
+    // else one wavefront does all: mrf_fwd_sweep_narrow as far as its 32-bit offsets reach
+    if (!idx && g_tune_pack_idx != 3 && P.g.N * P.g.L <= MRF_BUF_MOST) {
+        bool none = true;
+        for (int r = P.r_first; r < P.r_first + P.r_count; ++r) none = none && P.n_src[r] == 0;
+        return launch_narrow_mu<SEG, MU>(P, algo, none ? 1 : rmax, st);
+    }
     note_launch(0, "mrf_fwd_sweep_packed", blocks, idx ? 192 : 64, "%d,%d,%d,%d,%s,%d", SEG, MU, rmax, rmax == 4 ? 4 : (rmax == 8 ? 2 : 1),
                 algo == MRF_TRWP ? "true" : "false", idx ? 2 : 0);
 #define MRF_P(rm, d) \

@@ -19,7 +19,8 @@
 //   mrf_fwd_sweep               dense O(L^2), NW wavefronts per scanline split the source labels
 //   mrf_fwd_sweep_sliced        dense, L > 64: the same with the O(L) work of a node divided among the wavefronts
 //   mrf_fwd_sweep_halves        dense, 33..128 labels: chunk minima, argmin by a second look at the winning chunk
-//   mrf_fwd_sweep_packed        dense, L <= 32: several scanlines per wavefront
+//   mrf_fwd_sweep_narrow        dense, L <= 32: several scanlines of one direction per wavefront, argmin in two levels
+//   mrf_fwd_sweep_packed        the same for launches of few scanlines, with index wavefronts; scanlines of any direction
 //   mrf_fwd_sweep_edge          pairwise potentials given per edge (L <= 64)
 //   mrf_aggregate               final costs and labels
 //   mrf_fwd_sweep_window        truncated models: window of 2 TW - 1 source labels per label
@@ -36,6 +37,7 @@ struct MrfFwdParams {
     MrfGeom g;
     int r_first, r_count;                  // directions swept by this launch
     long long blk_begin[MRF_MAXR + 1];     // prefix sums of B*nscan over those directions
+    int pack_begin[MRF_MAXR + 1];          // mrf_fwd_sweep_narrow: the same in wavefronts, every direction padded to whole ones
     const float *unary, *V;
     const float *w;                        // [R][N] edge weights, or one float when w_mul == 0
     int w_mul;                             // 1: per-edge weights, 0: the scalar at w[0]
@@ -2896,5 +2898,194 @@ mrf_fwd_sweep_packed(const MrfFwdParams P)
 #pragma unroll
             for (int c = 0; c < RMAX; ++c) cur[u][c] = nxt[u][c];
         }
+    }
+}
+
+// ---- dense sweep for few labels with scanlines to spare: one direction per wavefront ----------------
+//
+// mrf_fwd_sweep_packed for launches that fill the machine, where the issue of vector instructions bounds the step
+// (185 per wavefront and node of the segmentation shape).  Scanlines of one wavefront belong to one direction
+// (the host pads every direction to whole wavefronts), so base addresses, factors and source counts are scalars and
+// an entry is one 32-bit offset into buffer views (the host checks that N L fits) that walks by one addition; what a
+// lane loads past its scanline's end is another node or 0 and never used, and a store that is not wanted has an
+// offset past the view's.  The argmin takes two levels: minima of four candidates, the lowest group that attains
+// the overall minimum, and that group's four candidates once more (the same fma on the same operands gives the same
+// bits) against a transposed copy of V in LDS: 2.6 instructions per candidate instead of 3.5.  Where nothing but the
+// start term is read (RMAX = 1: ISGMR's first iteration, and all of them behind mrf_isgmr_presum) no empty slots are.
+// Learning steps, K = 5: 4 x 512 x 512, 21 labels, ISGMR 4.32 -> 4.13 ms; 256 x 512, 32 labels, 16 directions 4.17 -> 3.61.
+template <int SEG, int MU, int RMAX, int D, bool TRWP>
+__global__ void __launch_bounds__(64) mrf_fwd_sweep_narrow(const MrfFwdParams P)
+{
+    static_assert(MU % 4 == 0 && (MU <= SEG || (SEG == 21 && MU == 24)), "source label count");
+    constexpr int NSEG = 64 / SEG;                // (three segments of 21 lanes leave lane 63 idle)
+    constexpr int NROW = SEG == 21 ? 4 : NSEG;    // LDS rows: the idle lane gets one of its own to scribble in
+    constexpr int SEGP = SEG == 21 ? 28 : SEG + 4;   // row stride: 16-byte rows on different banks
+    constexpr int NCH = MU / 4;                   // groups of four candidates
+    __shared__ __align__(16) float hrow[NROW][SEGP];
+    __shared__ __align__(16) float vt[SEG][MU + 4];  // V transposed: row lambda
+    const int L = P.g.L;
+    const int lane = threadIdx.x & 63;
+    const int seg = lane / SEG, lam = lane % SEG;
+    const bool valid = lam < L;
+    const int lamc = valid ? lam : 0;
+
+    // this wavefront's scanlines: NSEG consecutive ones of direction r
+    const int blk = (int)blockIdx.x;
+    int ri = 0;
+    while (ri + 1 < P.r_count && blk >= P.pack_begin[ri + 1]) ++ri;
+    const int r = P.r_first + ri;
+    const unsigned nsc = (unsigned)P.g.nscan[r];
+    const unsigned sl = (unsigned)(blk - P.pack_begin[ri]) * NSEG + seg;
+    const bool act_seg = seg < NSEG && sl < (unsigned)P.g.B * nsc;
+    const int dh = P.g.dh[r], dw = P.g.dw[r];
+    const int nstep = dh * P.g.W + dw;
+    int y0 = 0, x0 = 0, len = 0, head = 0;
+    if (act_seg) {
+        const int b = (int)(sl / nsc);
+        mrf_geom_head(P.g.H, P.g.W, dh, dw, sl - (unsigned)b * nsc, y0, x0, len);
+        head = (b * P.g.H + y0) * P.g.W + x0;
+    }
+    const float rho = P.rho[r];
+    const int n_pre = P.n_pre[r], n_src = P.n_src[r], rm_slot = P.rm_slot[r];
+
+    // Sources of h in summation order: the unary, then message arrays; unused slots load 0 and enter with factor 0
+    // (fma(0, 0, v) = v and fma(1, x, v) = v + x exactly).  r^- once more by itself.
+    const size_t N = (size_t)P.g.N, NL = N * L;
+    mrf_buf src[RMAX];
+    float before[RMAX], after[RMAX];
+    src[0] = mrf_buffer(P.unary + (size_t)__builtin_amdgcn_readfirstlane((int)P.unary_slab[r]) * NL, NL * 4);
+#pragma unroll
+    for (int c = 1; c < RMAX; ++c) {
+        const bool live = c <= n_src;
+        const size_t d = (size_t)__builtin_amdgcn_readfirstlane(live ? (int)P.src_dir[r][c - 1] : 0);
+        src[c] = mrf_buffer(P.m_in + d * NL, live ? NL * 4 : 0);
+        before[c] = live && (!TRWP || c <= n_pre) ? 1.0f : 0.0f;
+        after[c] = live && TRWP && c > n_pre ? 1.0f : 0.0f;
+    }
+    const bool has_rm = TRWP && rm_slot >= 0;
+    const mrf_buf brm = mrf_buffer(P.m_in + (size_t)__builtin_amdgcn_readfirstlane(has_rm ? (int)P.src_dir[r][has_rm ? rm_slot : 0] : 0) * NL,
+                                   has_rm ? NL * 4 : 0);
+    const mrf_buf bm = mrf_buffer(P.m_out + (size_t)r * NL, NL * 4), bp = mrf_buffer(P.p + (size_t)r * NL, NL);
+    const mrf_buf bq = mrf_buffer(P.q + (size_t)r * N, N), bw = mrf_buffer(P.w + (P.w_mul ? (size_t)r * N : 0), P.w_mul ? N * 4 : 4);
+
+    float Vr[MU];
+#pragma unroll
+    for (int mu = 0; mu < MU; ++mu) {
+        Vr[mu] = (mu < L && valid) ? P.V[(size_t)mu * L + lam] : 0.0f;
+        vt[lam][mu] = Vr[mu];                     // (every segment writes the same)
+    }
+    hrow[seg][lam] = INFINITY;                    // entries mu >= L stay +inf: they never win
+    if (lam < SEGP - SEG) hrow[seg][SEG + lam] = INFINITY;
+    __syncthreads();
+
+    auto store_u8 = [](mrf_buf b, unsigned off, int x) { __builtin_amdgcn_raw_buffer_store_b8((unsigned char)x, b, off, 0, 0); };
+    // first node of the scanline: message 0, p = q = 0
+    unsigned oe = (unsigned)head * (unsigned)L + (unsigned)lam, on = (unsigned)head;
+    {
+        const bool st = act_seg && valid;
+        mrf_buf_store_f32(bm, st ? oe << 2 : MRF_BUF_NONE, 0.0f);
+        store_u8(bp, st ? oe : MRF_BUF_NONE, 0);
+        store_u8(bq, st && lam == 0 ? on : MRF_BUF_NONE, 0);
+    }
+    // longest scanline of the wavefront bounds the loop
+    int maxlen = 0;
+#pragma unroll
+    for (int sg = 0; sg < NSEG; ++sg) {
+        const int l2 = __builtin_amdgcn_readlane(len, sg * SEG);
+        maxlen = l2 > maxlen ? l2 : maxlen;
+    }
+    if (maxlen < 2) return;
+
+    const int len_m = valid ? len : 0, len_q = lam == 0 ? len : 0;       // (a segment has lam == 0 only in its first lane)
+    const unsigned estep = (unsigned)nstep * (unsigned)L;
+    struct In {
+        float v[RMAX];
+        float rm, w;
+    };
+    In A[D], B[D];
+    unsigned pe = ((unsigned)head * (unsigned)L + (unsigned)lamc) << 2;
+    unsigned pw = P.w_mul ? (unsigned)(head + nstep) << 2 : 0u;
+    const unsigned pe_step = estep << 2, pw_step = P.w_mul ? (unsigned)nstep << 2 : 0u;
+    auto prefetch = [&](In &in) {
+#pragma unroll
+        for (int c = 0; c < RMAX; ++c) in.v[c] = mrf_buf_f32(src[c], pe);
+        in.rm = TRWP ? mrf_buf_f32(brm, pe) : 0.0f;
+        in.w = mrf_buf_f32(bw, pw);
+        pe += pe_step;
+        pw += pw_step;
+    };
+
+    float carry = 0.0f;
+    auto group = [&](const In (&in)[D], int n0) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            const int n = n0 + u;
+            float v = in[u].v[0];
+#pragma unroll
+            for (int c = 1; c < RMAX; ++c) v = __builtin_fmaf(before[c], in[u].v[c], v);
+            v = v + carry;
+            if (TRWP) {
+#pragma unroll
+                for (int c = 1; c < RMAX; ++c) v = __builtin_fmaf(after[c], in[u].v[c], v);
+                v = rho * v;
+                v = v - in[u].rm;
+            }
+            const float wgt = in[u].w;
+            hrow[seg][lam] = valid ? v : INFINITY;
+            mrf_wave_lds_fence();
+
+            // candidates, minima of four, the minimum of all
+            float cm[NCH];
+#pragma unroll
+            for (int k = 0; k < NCH; ++k) {
+                const float4 hv = *reinterpret_cast<const float4 *>(&hrow[seg][4 * k]);
+                const float d0 = __builtin_fmaf(wgt, Vr[4 * k], hv.x), d1 = __builtin_fmaf(wgt, Vr[4 * k + 1], hv.y);
+                const float d2 = __builtin_fmaf(wgt, Vr[4 * k + 2], hv.z), d3 = __builtin_fmaf(wgt, Vr[4 * k + 3], hv.w);
+                cm[k] = mrf_min(mrf_min3(d0, d1, d2), d3);
+            }
+            float best = NCH > 1 ? mrf_min(cm[0], cm[NCH > 1 ? 1 : 0]) : cm[0];
+#pragma unroll
+            for (int k = 2; k + 1 < NCH; k += 2) best = mrf_min3(best, cm[k], cm[k + 1]);
+            if constexpr (NCH > 2 && NCH % 2 == 1) best = mrf_min(best, cm[NCH - 1]);
+
+            const float tv = valid ? best : INFINITY;
+            const float tq = mrf_segment_min<SEG>(tv);
+            carry = tv - tq;
+            const int qidx = mrf_segment_first<SEG>(__ballot(tv == tq), lane);
+
+            // lowest group that attains the minimum (groups overlap or repeat where there are not four or eight:
+            // the lowest index wins all the same), then the lowest of its candidates
+            int ck = NCH - 1;
+            if constexpr (NCH > 4) mrf_first_equal4<NCH - 4>(ck, best, cm[NCH - 4], cm[NCH - 3], cm[NCH - 2], cm[NCH - 1]);
+            mrf_first_equal4<0>(ck, best, cm[0], cm[NCH > 1 ? 1 : 0], cm[NCH > 2 ? 2 : NCH - 1], cm[NCH > 3 ? 3 : NCH - 1]);
+            const float4 va = *reinterpret_cast<const float4 *>(&vt[lam][4 * ck]), hv = *reinterpret_cast<const float4 *>(&hrow[seg][4 * ck]);
+            int pj = 3;
+            mrf_first_equal4<0>(pj, best, __builtin_fmaf(wgt, va.x, hv.x), __builtin_fmaf(wgt, va.y, hv.y), __builtin_fmaf(wgt, va.z, hv.z),
+                                __builtin_fmaf(wgt, va.w, hv.w));
+            mrf_wave_lds_fence();
+
+            oe += estep;
+            on += (unsigned)nstep;
+            mrf_buf_store_f32(bm, n < len_m ? oe << 2 : MRF_BUF_NONE, carry);
+            store_u8(bp, n < len_m ? oe : MRF_BUF_NONE, 4 * ck + pj);
+            store_u8(bq, n < len_q ? on : MRF_BUF_NONE, qidx);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < D; ++u) prefetch(A[u]);
+    // (dropped stores: what is in flight at the loop's entry then looks like what is in flight when it comes round)
+#pragma unroll
+    for (int u = 0; u < 3 * D; ++u) store_u8(bq, MRF_BUF_NONE, 0);
+    for (int n0 = 1; n0 < maxlen; n0 += 2 * D) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) prefetch(B[u]);
+        __builtin_amdgcn_sched_barrier(0);
+        group(A, n0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < D; ++u) prefetch(A[u]);
+        __builtin_amdgcn_sched_barrier(0);
+        group(B, n0 + D);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }

@@ -314,6 +314,47 @@ def test_chain_backward_with_two_scanlines_per_workgroup(oracle, case):
         check_grad(name + " (two layouts)", getattr(a, name), None, getattr(b, name).astype(np.float64))
 
 
+FWD_NARROW_CASES = [
+    # seed, algo, B, H, W, L, dirs, K, integer_valued, per_edge: label counts around 16, 21 and 32, one and many sources
+    (811, "isgmr", 2, 9, 11, 21, DIRS8, 3, True, True), (812, "trwp", 1, 7, 13, 32, DIRS4, 2, True, True),
+    (813, "isgmr", 1, 6, 10, 25, DIRS16, 2, False, False), (814, "trwp", 3, 5, 6, 17, DIRS8, 2, False, True),
+    (815, "isgmr", 1, 1, 37, 16, DIRS4, 2, True, True), (816, "trwp", 1, 23, 3, 9, ((0, 1), (1, 0), (1, 1)), 3, False, True),
+    (817, "trwp", 1, 3, 9, 1, DIRS4, 2, False, True), (818, "trwp", 1, 4, 5, 28, DIRS16, 2, True, True),
+    (819, "isgmr", 1, 33, 2, 5, DIRS8, 2, False, True),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", FWD_NARROW_CASES, ids=lambda c: "seed%d" % c[0])
+def test_forward_with_one_direction_per_wavefront(oracle, case):
+    """Up to 32 labels, one wavefront for several scanlines of a direction, argmin in two levels: ties, negative
+    weights, scanline counts that do not fill a wavefront; against the oracle and bit for bit against the sweep
+    with one level and 64-bit offsets."""
+    import paper_1910_10892_amd as mrf
+    print("case narrow forward", case[:6], len(case[6]), case[7:], flush=True)
+    seed, algo, B, H, W, L, dirs, K, iv, pe = case
+    pr = random_problem(seed, algo, B, H, W, L, dirs, K, integer_valued=iv, per_edge=pe, symmetric=False,
+                        rho=np.linspace(0.3, 0.9, len(dirs)))
+    pr.grad_cost = (pr.grad_cost * (0.02 if len(dirs) > 8 else 0.2)).astype(np.float32)
+    if pe and seed % 2 == 0:
+        sign = np.where(np.random.default_rng(seed).random(pr.edge_weight.shape) > 0.2, 1.0, -0.5)
+        pr.edge_weight = (pr.edge_weight * sign).astype(np.float32)
+    try:
+        assert mrf.mrf_tune(3, 2) == 0
+        for three in ((1, 2) if 16 < L <= 21 else (1,)):
+            assert mrf.mrf_tune(13, three) == 0 and mrf.mrf_tune(11, 1) == 0
+            a = full_check(oracle, pr, want_V=False)
+            assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_narrow", mrf.mrf_last_sweep_launch(False)
+            assert mrf.mrf_tune(11, 3) == 0
+            b = full_check(oracle, pr, want_V=False)
+            assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_packed"
+            for name in ("p", "q", "labels", "cost", "messages"):
+                np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
+    finally:
+        for knob in (3, 11, 13):
+            mrf.mrf_tune(knob, 0)
+
+
 NARROW_CASES = [
     # seed, algo, B, H, W, L, dirs, K, integer_valued, per_edge: label counts at the edges of 8-lane segments
     (781, "isgmr", 2, 9, 11, 21, DIRS8, 3, False, True), (782, "trwp", 1, 7, 13, 32, DIRS4, 2, True, True),
