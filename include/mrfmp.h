@@ -268,7 +268,9 @@ int mrf_set_sweep_events(void *start_event, void *stop_event);
  *   knob 1: non-zero = ignore pairwise_kind and always run the dense forward sweep
  *   knob 2: window sweep layout: 0 = by launch size, 1 = one wavefront per scanline,
  *           2 = one wavefront per 64 labels whenever L > 64
- *   knob 3: several scanlines per wavefront for L <= 32: 0 = by launch shape, 1 = never, 2 = always
+ *   knob 3: several scanlines per wavefront for L <= 32: 0 = by launch shape, 1 = never, 2 = always;
+ *           8, 16 (more than 8 labels), 32 (more than 16 labels) = always, with that many lanes per
+ *           scanline in the backward sweep that gives a lane several labels
  *   knob 4: window sweep with separate value and index wavefronts: 0 = by launch size, 1 = never,
  *           2 = whenever the window sweep applies (knob 2 = 2 takes precedence for L > 64)
  *   knob 5: index wavefronts per scanline in that sweep: 0 = by launch size, 1, 2
@@ -308,8 +310,6 @@ int mrf_set_sweep_events(void *start_event, void *stop_event);
  *           afterwards: 0 = yes, 1 = no (then another sweep accumulates the table itself)
  *   knob 20: backward sweep of knob 6 with two scanlines of up to 32 labels per workgroup (one direction per
  *           launch, TRWP): 0 = by launch size, 1 = never, 2 = whenever it applies
- *   knob 21: lanes per scanline in the backward sweep for up to 32 labels that gives a lane several labels:
- *           0 = by launch size, 8, 16 (more than 8 labels), 32 (more than 16 labels)
  * Returns MRF_OK, or MRF_ERR_BAD_ALGORITHM for an unknown knob. */
 int mrf_tune(int knob, int value);
 

@@ -1811,7 +1811,11 @@ int mrf_tune(int knob, int value)
     if (knob == 0) { g_tune_mch = value; return MRF_OK; }
     if (knob == 1) { g_tune_no_window = value; return MRF_OK; }
     if (knob == 2) { g_tune_split = value; return MRF_OK; }
-    if (knob == 3) { g_tune_pack = value; return MRF_OK; }
+    if (knob == 3) {
+        g_tune_narrow = (value == 8 || value == 16 || value == 32) ? value : 0;
+        g_tune_pack = g_tune_narrow ? 2 : value;
+        return MRF_OK;
+    }
     if (knob == 4) { g_tune_duo = value; return MRF_OK; }
     if (knob == 5) { g_tune_duo_ni = (value == 1 || value == 2) ? value : 0; return MRF_OK; }
     if (knob == 6) { g_tune_chain = value; return MRF_OK; }
@@ -1828,7 +1832,6 @@ int mrf_tune(int knob, int value)
     if (knob == 18) { g_tune_gv_tile = value; return MRF_OK; }
     if (knob == 19) { g_tune_gv_apart = value; return MRF_OK; }
     if (knob == 20) { g_tune_chain_pk = value; return MRF_OK; }
-    if (knob == 21) { g_tune_narrow = (value == 8 || value == 16 || value == 32) ? value : 0; return MRF_OK; }
     if (knob == 7) { g_tune_chain_ni = (value == 2 || value == 4 || value == 6 || value == 8 || value == 12) ? value : 0; return MRF_OK; }
     return MRF_ERR_BAD_ALGORITHM;
 }
