@@ -274,6 +274,9 @@ hipError_t launch_packed_mu(const MrfFwdParams &P, int algo, int rmax, long long
     const unsigned blocks = (unsigned)((scanlines + 64 / SEG - 1) / (64 / SEG));
     // few wavefronts in the launch: further ones per workgroup for the argmin tables and the stores
     // (two of them: an index wavefront has more to do per node than the value wavefront)
+    // (forward pass, K = 3, 4 directions, index wavefronts / mrf_fwd_sweep_narrow, at 1,024 wavefronts: TRWP 4 x 512 x 512 2.85 /
+    // 2.95 ms with 32 labels, 2.43 / 2.84 with 21; at half of that 1.98 / 2.89; at 2,048 6.37 / 4.09 with 32 labels, ISGMR 1.58 /
+    // 0.92)
     const bool idx = g_tune_pack_idx == 2 || (g_tune_pack_idx == 0 && blocks <= 1024);
     // else one wavefront does all: mrf_fwd_sweep_narrow as far as its 32-bit offsets reach
     if (!idx && g_tune_pack_idx != 3 && P.g.N * P.g.L <= MRF_BUF_MOST) {

@@ -1638,8 +1638,8 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
 // stored as 32 seg + p, so the chain wavefront's step is that of mrf_bwd_sweep_chain unchanged: it neither
 // knows nor cares that its 64 entries are two vectors.  A scanline that is shorter than its neighbour gets
 // zeros with targets of their own for the steps past its first node, and nothing of those steps is stored.
-// For launches of more than 1,024 scanlines of up to 32 labels with one direction (TRWP), where
-// mrf_bwd_sweep_packed leaves a lone wavefront per SIMD to do all of a node's work in sequence.
+// For launches of 257 to 1,536 scanlines of up to 32 labels with one direction (TRWP), where the wavefronts of
+// mrf_bwd_sweep_narrow would have a SIMD to themselves and do all of a node's work in sequence.
 __host__ __device__ inline size_t mrf_bwd_chain_pk_lds_bytes(int NI, int L, bool gv)
 {
     const size_t NR = 2 * (size_t)NI, LL = 64;
