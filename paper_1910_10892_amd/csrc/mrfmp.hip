@@ -1053,23 +1053,31 @@ hipError_t launch_bwd_narrow(MrfBwdParams &P, int ns, long long packs, hipStream
     const long long blocks = (packs + waves - 1) / waves;
     const int L = P.g.L, nseg = 64 / SEG;
     const bool gv = P.gV != nullptr;
-    if (gv && blocks > grad_slots(L)) return hipErrorInvalidValue;
+    // a workgroup has a V-gradient slot of its own: what is more than there are slots goes into further launches, which
+    // add to the same slots one after the other
+    const long long most = gv && blocks > grad_slots(L) ? grad_slots(L) : blocks;
     const size_t lds = sizeof(double) * ((size_t)waves * (nseg * mrf_bwd_narrow_row<SEG, NL>() + 64) + (gv ? (size_t)mrf_bwd_narrow_tables(nseg, L) * mrf_bwd_narrow_table<SEG, NL>(L) : 0)) +
                        sizeof(float) * (size_t)L * mrf_bwd_narrow_pitch(L);
     if (lds > 64 * 1024) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(64u * (unsigned)waves);
+    const dim3 block(64u * (unsigned)waves);
     // (one source, no grad theta and several directions: ISGMR, every coefficient 1)
     const bool unary = ns == 1 ? (P.unary_dir >= 0 || P.r_count == 1) : P.unary_dir >= 0;
     const bool full = L % NL == 0;
 #define MRF_N(n, d, un) \
     if (ns == n && unary == un) { \
-        note_launch(1, "mrf_bwd_sweep_narrow", blocks, 64 * waves, "%d,%d,%d,%d,%s,%s,%s", SEG, NL, n, d, un ? "true" : "false", \
-                    gv ? "true" : "false", full ? "true" : "false"); \
-        if (gv && full) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, true, true>), grid, block, lds, st, P); \
-        else if (gv) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, true, NL == 1>), grid, block, lds, st, P); \
-        else if (full) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, false, true>), grid, block, lds, st, P); \
-        else hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, false, NL == 1>), grid, block, lds, st, P); \
-        return hipGetLastError(); \
+        for (long long first = 0; first < blocks; first += most) { \
+            const dim3 grid((unsigned)(blocks - first < most ? blocks - first : most)); \
+            P.pack_first = (int)(first * waves); \
+            note_launch(1, "mrf_bwd_sweep_narrow", grid.x, 64 * waves, "%d,%d,%d,%d,%s,%s,%s", SEG, NL, n, d, un ? "true" : "false", \
+                        gv ? "true" : "false", full ? "true" : "false"); \
+            if (gv && full) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, true, true>), grid, block, lds, st, P); \
+            else if (gv) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, true, NL == 1>), grid, block, lds, st, P); \
+            else if (full) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, false, true>), grid, block, lds, st, P); \
+            else hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, false, NL == 1>), grid, block, lds, st, P); \
+            const hipError_t e_ = hipGetLastError(); \
+            if (e_ != hipSuccess) return e_; \
+        } \
+        return hipSuccess; \
     }
     MRF_N(1, 4, false) MRF_N(1, 4, true) MRF_N(4, 2, false) MRF_N(4, 2, true)
     MRF_N(8, (NL <= 2 ? 2 : 1), false) MRF_N(8, (NL <= 2 ? 2 : 1), true) MRF_N(16, 1, false) MRF_N(16, 1, true)

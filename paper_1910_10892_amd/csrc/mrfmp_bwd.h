@@ -45,6 +45,7 @@ struct MrfBwdParams {
     long long blk_begin[MRF_MAXR + 1];     // prefix sums of B*nscan over the launch's directions
     long long total_scanlines;
     int pack_begin[MRF_MAXR + 1];          // mrf_bwd_sweep_narrow: the same in wavefronts, every direction padded to whole ones
+    int pack_first;                        // mrf_bwd_sweep_narrow: first of those wavefronts in this launch
     const float *V;
     const float *w;                        // [R][N] edge weights, or one float when w_mul == 0
     int w_mul;
@@ -1374,7 +1375,7 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
     __syncthreads();
 
     // this wavefront's scanlines: NSEG consecutive ones of direction r
-    const int pk = (int)blockIdx.x * waves + wv;
+    const int pk = P.pack_first + (int)blockIdx.x * waves + wv;
     int ri = 0;
     while (ri + 1 < P.r_count && pk >= P.pack_begin[ri + 1]) ++ri;
     const int r = P.r_first + ri;

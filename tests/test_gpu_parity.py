@@ -396,6 +396,24 @@ def test_backward_with_several_labels_per_lane(oracle, case):
             check_grad("%s (%d lanes)" % (name, seg), getattr(g, name), None, getattr(plain, name).astype(np.float64))
 
 
+MANY_SMALL_IMAGES = [
+    # seed, algo, images, L: more workgroups of the narrow sweep than there are V-gradient slots (16,384)
+    (791, "isgmr", 6600, 25), (792, "isgmr", 13200, 12), (793, "isgmr", 26400, 5),
+]
+
+
+@pytest.mark.parametrize("case", MANY_SMALL_IMAGES, ids=lambda c: "seed%d" % c[0])
+def test_pairwise_gradient_of_more_scanlines_than_slots(oracle, case):
+    """Up to 32 labels with grad_pairwise and a batch whose scanlines take more workgroups than the workspace has
+    V-gradient slots: the sweep goes into several launches."""
+    import paper_1910_10892_amd as mrf
+    print("case many small images", case, flush=True)
+    seed, algo, B, L = case
+    pr = random_problem(seed, algo, B, 2, 2, L, DIRS8, 2, symmetric=False)
+    full_check(oracle, pr)
+    assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_narrow", mrf.mrf_last_sweep_launch(True)
+
+
 GV_APART_CASES = [
     # seed, B, H, W, L, dirs, K, integer_valued, per_edge
     (751, 1, 6, 9, 96, DIRS4, 3, False, True), (752, 2, 5, 7, 128, DIRS8, 2, True, True),
