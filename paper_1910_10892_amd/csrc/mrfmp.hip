@@ -1236,7 +1236,8 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // 0.78 / 1.00 / 1.81 ms two scanlines, 2.1 ms narrow; 4 x 512 x 512: 3.4 ms two scanlines, 2.8 ms narrow.)
     const long long pk_max = L <= 8 ? 1024 : 1536;
     if (!generic && L <= 32 && P.r_count == 1 && ns <= 8 && g_tune_chain != 1 && g_tune_pack != 2 && g_tune_chain_pk != 1 &&
-        (g_tune_chain_pk == 2 || (g_tune_chain != 2 && P.total_scanlines > 256 && P.total_scanlines <= pk_max))) {
+        (g_tune_chain_pk == 2 || (g_tune_chain != 2 && P.total_scanlines > 256 && P.total_scanlines <= pk_max)) &&
+        !(gv_any && (P.total_scanlines + 1) / 2 > grad_slots(L))) {
         // (helpers: 3 x 512 x 512, 16 labels, 8 directions, 1,536 scanlines: 4.3 ms with eight, 5.0 with four; the LDS
         // of a compute unit, which several such workgroups share, sets the pace)
         const int nip = (g_tune_chain_ni == 2 || g_tune_chain_ni == 4 || g_tune_chain_ni == 8) ? g_tune_chain_ni

@@ -414,6 +414,22 @@ def test_pairwise_gradient_of_more_scanlines_than_slots(oracle, case):
     assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_narrow", mrf.mrf_last_sweep_launch(True)
 
 
+def test_two_scanlines_per_workgroup_need_a_slot_each(oracle):
+    """Chain backward with two scanlines per workgroup on request, for launches with more workgroups than V-gradient
+    slots: another sweep takes them."""
+    import paper_1910_10892_amd as mrf
+    print("case pair layout without slots", flush=True)
+    pr = random_problem(794, "trwp", 16500, 2, 2, 6, DIRS4, 2, symmetric=False)
+    try:
+        assert mrf.mrf_tune(20, 2) == 0
+        full_check(oracle, pr)
+        assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_narrow", mrf.mrf_last_sweep_launch(True)
+        full_check(oracle, pr, want_V=False)
+        assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_chain_pk", mrf.mrf_last_sweep_launch(True)
+    finally:
+        mrf.mrf_tune(20, 0)
+
+
 GV_APART_CASES = [
     # seed, B, H, W, L, dirs, K, integer_valued, per_edge
     (751, 1, 6, 9, 96, DIRS4, 3, False, True), (752, 2, 5, 7, 128, DIRS8, 2, True, True),
