@@ -268,7 +268,8 @@ int mrf_set_sweep_events(void *start_event, void *stop_event);
  *   knob 1: non-zero = ignore pairwise_kind and always run the dense forward sweep
  *   knob 2: window sweep layout: 0 = by launch size, 1 = one wavefront per scanline,
  *           2 = one wavefront per 64 labels whenever L > 64
- *   knob 3: several scanlines per wavefront for L <= 32: 0 = by launch shape, 1 = never, 2 = always;
+ *   knob 3: several scanlines per wavefront for L <= 32: 0 = by launch shape, 1 = never, 2 = always, 3 = always, the
+ *           backward sweep with one label per lane and 64-bit offsets;
  *           8, 16 (more than 8 labels), 32 (more than 16 labels) = always, with that many lanes per
  *           scanline in the backward sweep that gives a lane several labels
  *   knob 4: window sweep with separate value and index wavefronts: 0 = by launch size, 1 = never,

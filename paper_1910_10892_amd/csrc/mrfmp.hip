@@ -147,7 +147,7 @@ MRF_G(int g_tune_pack_idx, 0);   // index wavefronts in the packed dense sweep: 
 MRF_G(int g_tune_chain, 0);      // backward sweep with a chain wavefront: 0 auto, 1 never, 2 whenever possible
 MRF_G(int g_tune_chain_hot, 0);  // its pre-reduction of the most popular scatter target: 0 auto, 1 never, 2 whenever V is no dense table
 MRF_G(int g_tune_chain_ni, 0);   // its helpers per scanline: 0 auto, 2, 4, 6, 8
-MRF_G(int g_tune_narrow, 0);     // lanes per scanline of the narrow backward sweep: 0 by launch size, 8, 16, 32
+MRF_G(int g_tune_narrow, 0);     // lanes per scanline of the narrow backward sweep: 0 by launch size, 8, 16, 32; -1: not that sweep
 MRF_G(hipEvent_t g_ev_start, nullptr);
 MRF_G(hipEvent_t g_ev_stop, nullptr);
 #undef MRF_G
@@ -240,7 +240,7 @@ inline size_t chain_lds_cap(long long scanlines)
 
 hipError_t run_bwd_chain(MrfBwdParams &P, int ns, int ni, bool vg, hipStream_t st);
 hipError_t run_bwd_chain_pk(MrfBwdParams &P, int ns, int ni, hipStream_t st);
-hipError_t run_bwd_packed(MrfBwdParams &P, int ns, hipStream_t st);
+hipError_t run_bwd_packed(MrfBwdParams &P, int seg, int ns, hipStream_t st);
 hipError_t run_bwd_narrow(MrfBwdParams &P, int seg, int ns, hipStream_t st);
 hipError_t run_bwd_plain(MrfBwdParams &P, int ns, long long blocks, size_t lds, hipStream_t st);
 hipError_t run_bwd_tile(MrfBwdParams &P, int ns, long long blocks, size_t lds, hipStream_t st);
@@ -1042,7 +1042,11 @@ hipError_t run_bwd_chain_pk(MrfBwdParams &P, int ns, int ni, hipStream_t st)
     return launch_bwd_chain_pk<8, 1>(P, ni, st);
 }
 
-hipError_t run_bwd_packed(MrfBwdParams &P, int ns, hipStream_t st) { return launch_bwd_packed<21>(P, ns, st); }
+hipError_t run_bwd_packed(MrfBwdParams &P, int seg, int ns, hipStream_t st)
+{
+    if (seg == 21) return launch_bwd_packed<21>(P, ns, st);
+    return seg == 16 ? launch_bwd_packed<16>(P, ns, st) : launch_bwd_packed<32>(P, ns, st);
+}
 
 template <int SEG, int NL>
 hipError_t launch_bwd_narrow(MrfBwdParams &P, int ns, long long packs, hipStream_t st)
@@ -1152,7 +1156,7 @@ hipError_t launch_bwd_split(const MrfBwdParams &P, long long blocks, size_t lds,
 // crowd LDS (32 labels, 16 directions 1.53 / 1.26 / 1.17 ms; without that gradient 16 lanes are ahead).
 int narrow_lanes(const MrfBwdParams &P, int L)
 {
-    if (P.g.N * L > MRF_BUF_MOST) return 0;
+    if (g_tune_narrow < 0 || P.g.N * L > MRF_BUF_MOST) return 0;
     if (g_tune_narrow == 8 || (g_tune_narrow == 16 && L > 8) || (g_tune_narrow == 32 && L > 16)) return g_tune_narrow;
     if (L <= 8) return 8;
     if (L <= 16) return 16;
@@ -1253,9 +1257,13 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     {
         // three scanlines per wavefront, one label per lane: on request only
         if (L > 16 && L <= 21 && g_tune_pack3 == 2)
-            return run_bwd_packed(P, ns, st);
+            return run_bwd_packed(P, 21, ns, st);
         const int seg = narrow_lanes(P, L);
         if (seg > 0) return run_bwd_narrow(P, seg, ns, st);
+        // arrays beyond 32-bit offsets: one label per lane, 64-bit addresses.  (Backward pass, ISGMR with grad V, eight
+        // images, 2 directions, K = 1, N L = 1.08e9, against one wavefront per scanline: 20 / 58 ms with 8 labels, 15 / 31
+        // with 16, 18 / 25 with 21, 19.5 / 20.5 with 32)
+        return run_bwd_packed(P, L <= 16 ? 16 : 32, ns, st);
     }
     if (chain) {
         // truncated models: the chain wavefront sums the lanes of the most popular scatter target
@@ -1824,7 +1832,7 @@ int mrf_tune(int knob, int value)
     if (knob == 1) { g_tune_no_window = value; return MRF_OK; }
     if (knob == 2) { g_tune_split = value; return MRF_OK; }
     if (knob == 3) {
-        g_tune_narrow = (value == 8 || value == 16 || value == 32) ? value : 0;
+        g_tune_narrow = (value == 8 || value == 16 || value == 32) ? value : (value == 3 ? -1 : 0);
         g_tune_pack = g_tune_narrow ? 2 : value;
         return MRF_OK;
     }

@@ -31,7 +31,7 @@
 //   mrf_bwd_sweep_chain    the node-to-node chain on a wavefront of its own, helper wavefronts
 //                          for everything else (launches with few scanlines)
 //   mrf_bwd_sweep_split    one wavefront per 64 labels in lock step
-//   mrf_bwd_sweep_packed   L <= 32: several scanlines per wavefront, one label per lane
+//   mrf_bwd_sweep_packed   L <= 32: several scanlines per wavefront, one label per lane; arrays of any size
 //   mrf_bwd_sweep_narrow   L <= 32: up to eight scanlines per wavefront, several labels per lane
 //   mrf_isgmr_bwd_combine  ISGMR's sums over directions between two iterations
 // Which sweep a launch gets is host arithmetic on the launch shape (dispatch_bwd).

@@ -385,6 +385,11 @@ def test_backward_with_several_labels_per_lane(oracle, case):
                 assert mrf.mrf_tune(3, seg) == 0
                 got[seg, want_V] = full_check(oracle, pr, want_V=want_V)
                 assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_narrow", mrf.mrf_last_sweep_launch(True)
+        # one label per lane, 64-bit offsets (what takes over where arrays outgrow the views of the narrow sweep)
+        assert mrf.mrf_tune(3, 3) == 0
+        for want_V in (True, False):
+            got[0, want_V] = full_check(oracle, pr, want_V=want_V)
+            assert mrf.mrf_last_sweep_launch(True).startswith("mrf_bwd_sweep_packed<%d," % (16 if L <= 16 else 32))
         assert mrf.mrf_tune(3, 1) == 0
         plain = full_check(oracle, pr, want_V=True)
         assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep"
@@ -428,6 +433,45 @@ def test_two_scanlines_per_workgroup_need_a_slot_each(oracle):
         assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_chain_pk", mrf.mrf_last_sweep_launch(True)
     finally:
         mrf.mrf_tune(20, 0)
+
+
+@pytest.mark.parametrize("algo,L,H,W", [("isgmr", 8, 1451, 1457), ("trwp", 21, 893, 897)])
+def test_backward_of_arrays_beyond_32_bit_offsets(algo, L, H, W):
+    """Up to 32 labels, more than 2^30 entries per array: a batch of 64 equal images against one of them (same sums in
+    double, other order: a float rounding apart), and the sweep that has 64-bit offsets."""
+    import torch
+    import paper_1910_10892_amd as mrf
+    print("case large batch", algo, L, H, W, flush=True)
+    B, K, dirs, dev = 64, 2, ((0, 1), (1, 0)), "cuda:0"
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(5)
+    rand = lambda *s: torch.rand(s, generator=gen, device=dev)  # noqa: E731
+    unary, V, w, gc = rand(1, H, W, L), rand(L, L), rand(2, 1, H, W) + 0.5, rand(1, H, W, L) - 0.5
+    code = mrf.MRF_ISGMR if algo == "isgmr" else mrf.MRF_TRWP
+    forward = mrf.mrf_isgmr_forward if algo == "isgmr" else mrf.mrf_trwp_forward
+    backward = mrf.mrf_isgmr_backward if algo == "isgmr" else mrf.mrf_trwp_backward
+
+    def replay(n, p, q):
+        batch = lambda x, axis: x.repeat_interleave(n, dim=axis)  # noqa: E731
+        prob = mrf.MrfProblem(None, V, dirs, K, batch(w, 1), rho=(0.4, 0.7), shape=(n, H, W, L))
+        g = [torch.empty(s, device=dev) for s in ((n, H, W, L), (2, n, H, W), (L, L))]
+        ws = torch.empty(mrf.mrf_workspace_bytes(prob, code, True), dtype=torch.uint8, device=dev)
+        backward(prob, batch(gc, 0), batch(p, 2), batch(q, 2), *g, ws)
+        return g
+
+    prob = mrf.MrfProblem(unary, V, dirs, K, w, rho=(0.4, 0.7))
+    p = torch.empty((K, 2, 1, H, W, L), dtype=torch.uint8, device=dev)
+    q = torch.empty((K, 2, 1, H, W), dtype=torch.uint8, device=dev)
+    ws = torch.empty(mrf.mrf_workspace_bytes(prob, code, False), dtype=torch.uint8, device=dev)
+    forward(prob, torch.empty_like(unary), None, p, q, None, ws)
+    one = replay(1, p, q)
+    many = replay(B, p, q)
+    assert mrf.mrf_last_sweep_launch(True).startswith("mrf_bwd_sweep_packed<%d," % (16 if L <= 16 else 32))
+    for b in range(B):
+        torch.testing.assert_close(many[0][b], one[0][0], rtol=1e-6, atol=1e-6)
+        torch.testing.assert_close(many[1][:, b], one[1][:, 0], rtol=1e-6, atol=1e-6)
+    # (a sum of 64 times as many terms, rounded once: the same relative bar as everywhere)
+    torch.testing.assert_close(many[2], B * one[2], rtol=RTOL, atol=B * ATOL)
 
 
 GV_APART_CASES = [
