@@ -1286,9 +1286,13 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
             const size_t tile = sizeof(double) * (size_t)L * L, both = tile + sizeof(float) * (size_t)L * L;
             G.v_lds = both <= 156 * 1024 ? 1 : 0;
             const size_t glds = G.v_lds ? both : tile;
-            // (a workgroup per compute unit at most; for few nodes fewer, so that the table's flush stays small)
-            long long gblocks = P.g.N / 256;
-            gblocks = gblocks < 1 ? 1 : (gblocks > MRF_GV_BLOCKS ? MRF_GV_BLOCKS : gblocks);
+            // (a workgroup per compute unit at most.  Its sixteen wavefronts take four nodes each at a time: one such turn
+            // per workgroup while there are few workgroups, then two, so that clearing and flushing the tables does not
+            // outweigh the turns.  Backward pass, 8 directions, K = 2, with one / two / four turns: 37 x 53 nodes, 70 labels
+            // 0.41 / 0.44 / 0.54 ms; 64 x 96, 96 labels 0.62 / 0.62 / 0.70; 128 x 128, 128 labels 1.21 / 1.07 / 1.10)
+            const long long one = (P.g.N + 63) / 64, two = P.g.N / 128;
+            long long gblocks = one < 96 ? one : (two > 96 ? two : 96);
+            if (gblocks > MRF_GV_BLOCKS) gblocks = MRF_GV_BLOCKS;
             const void *fn = LP == 1 ? reinterpret_cast<const void *>(&mrf_bwd_pairwise_from_g<1>) : reinterpret_cast<const void *>(&mrf_bwd_pairwise_from_g<2>);
             if (glds > 64 * 1024) {
                 const hipError_t ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)glds);
