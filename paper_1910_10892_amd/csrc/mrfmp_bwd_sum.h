@@ -68,7 +68,8 @@ __global__ void __launch_bounds__(1024) mrf_bwd_pairwise_from_g(const MrfGvParam
                 const int pc = at[u][s] < L ? at[u][s] : L - 1;
                 const int e = __mul24(pc, L) + lc[s];
                 if (live) __hip_atomic_fetch_add(&tile[e], (double)w[u] * g[u][s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (P.gw) acc = __builtin_fma(live ? g[u][s] : 0.0, (double)V[e], acc);
+                // (both operands selected: V may be infinite where no update was replayed)
+                if (P.gw) acc = __builtin_fma(live ? g[u][s] : 0.0, live ? (double)V[e] : 0.0, acc);
             }
             if (P.gw) {
                 acc = mrf_wave_sum_f64(acc);

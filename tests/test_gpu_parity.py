@@ -504,6 +504,19 @@ def test_pairwise_gradient_added_up_behind_the_chain_sweep(oracle, case):
     check_grad("grad_pairwise (two layouts)", a.grad_pairwise, None, b.grad_pairwise.astype(np.float64))
 
 
+def test_forbidden_transitions_leave_first_nodes_alone(oracle):
+    """Infinite entries of V that no update selects: the edge-weight gradient of nodes without a predecessor stays 0
+    (their p is 0, which may point at such an entry)."""
+    import paper_1910_10892_amd as mrf
+    print("case infinite entries of V", flush=True)
+    pr = random_problem(755, "trwp", 1, 6, 9, 70, DIRS4, 2, symmetric=False)
+    pr.pairwise[0, 3] = pr.pairwise[0, 66] = np.inf
+    g = full_check(oracle, pr)
+    assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_chain", mrf.mrf_last_sweep_launch(True)
+    assert (g.p[..., 3] != 0)[:, 0, :, :, 1:].all()            # (no update selects a forbidden transition)
+    assert (g.grad_edge_weight[0, :, :, 0] == 0).all()
+
+
 def truncated_problem(seed, algo, H, W, L, dirs, K, kind, trunc, integer_valued, weights):
     """Truncated linear (kind 1) / quadratic (kind 2) pairwise with the kind announced, so the
     library may take its window path.  weights: 'pos' | 'zero_mix' | 'neg_mix'."""
