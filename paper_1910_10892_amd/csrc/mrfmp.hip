@@ -1061,7 +1061,7 @@ hipError_t launch_bwd_narrow(MrfBwdParams &P, int ns, long long packs, hipStream
     // add to the same slots one after the other
     const long long most = gv && blocks > grad_slots(L) ? grad_slots(L) : blocks;
     const size_t lds = sizeof(double) * ((size_t)waves * (nseg * mrf_bwd_narrow_row<SEG, NL>() + 64) + (gv ? (size_t)mrf_bwd_narrow_tables(nseg, L) * mrf_bwd_narrow_table<SEG, NL>(L) : 0)) +
-                       sizeof(float) * (size_t)L * mrf_bwd_narrow_pitch(L);
+                       sizeof(float) * ((size_t)L * mrf_bwd_narrow_pitch(L) + 1);
     if (lds > 64 * 1024) return hipErrorInvalidValue;
     const dim3 block(64u * (unsigned)waves);
     // (one source, no grad theta and several directions: ISGMR, every coefficient 1)

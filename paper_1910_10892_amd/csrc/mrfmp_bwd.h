@@ -1363,7 +1363,7 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
     const int ntab = GV ? mrf_bwd_narrow_tables(NSEG, L) : 0, tsize = mrf_bwd_narrow_table<SEG, NL>(L), pitch = mrf_bwd_narrow_pitch(L);
     double *rows = reinterpret_cast<double *>(mrf_bsmem) + wv * (NSEG * RS + 64);            // [waves]{[NSEG][RS], 64 spare}
     double *tabs = reinterpret_cast<double *>(mrf_bsmem) + waves * (NSEG * RS + 64);         // [ntab][tsize]
-    float *vl = reinterpret_cast<float *>(tabs + ntab * tsize);                              // [L][pitch] V
+    float *vl = reinterpret_cast<float *>(tabs + ntab * tsize);                              // [L][pitch] V, then a 0
     double *sb = rows + seg * RS;
     double *spare = rows + NSEG * RS + lane;                  // where a lane with nothing to add adds
 
@@ -1371,6 +1371,7 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
         const int mu = e / pitch, lam = e - mu * pitch;
         vl[e] = lam < L ? P.V[mu * L + lam] : 0.0f;
     }
+    if (threadIdx.x == 0) vl[L * pitch] = 0.0f;
     for (int e = threadIdx.x; e < waves * (NSEG * RS + 64) + ntab * tsize; e += blockDim.x) reinterpret_cast<double *>(mrf_bsmem)[e] = 0.0;
     __syncthreads();
 
@@ -1493,7 +1494,8 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
     auto pairwise = [&](int slot) {
         int at[NL];
 #pragma unroll
-        for (int s = 0; s < NL; ++s) at[s] = __mul24(pP[s], pitch) + (FULL && NL > 1 ? (any ? lam0 + s : 0) : (lam0 + s < L ? lam0 + s : 0));
+        // (where there is no label p is 0, and the 0 behind V is met there: an infinite V[0][0] must not be)
+        for (int s = 0; s < NL; ++s) at[s] = __mul24(pP[s], pitch) + ((FULL ? any : lam0 + s < L) ? lam0 + s : L * pitch);
         // (formed whether it is wanted or not: the view of an array that is not there holds nothing)
         double acc = gP[0] * (double)vl[at[0]];
 #pragma unroll

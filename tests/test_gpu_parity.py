@@ -517,6 +517,25 @@ def test_forbidden_transitions_leave_first_nodes_alone(oracle):
     assert (g.grad_edge_weight[0, :, :, 0] == 0).all()
 
 
+@pytest.mark.parametrize("L", [5, 13, 21, 23, 25, 32])
+@pytest.mark.parametrize("algo", ["isgmr", "trwp"])
+def test_neighbours_that_must_differ(oracle, algo, L):
+    """V with an infinite diagonal (no update selects it): nothing of it reaches a gradient, also where a wavefront
+    has lanes without a label."""
+    import paper_1910_10892_amd as mrf
+    print("case infinite diagonal", algo, L, flush=True)
+    pr = random_problem(756 + L, algo, 2, 6, 9, L, DIRS8, 2, symmetric=False)
+    np.fill_diagonal(pr.pairwise, np.inf)
+    try:
+        assert mrf.mrf_tune(3, 2) == 0 and mrf.mrf_tune(6, 1) == 0 and mrf.mrf_tune(20, 1) == 0
+        for want_V in (True, False):
+            full_check(oracle, pr, want_V=want_V)
+            assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_narrow", mrf.mrf_last_sweep_launch(True)
+    finally:
+        for knob in (3, 6, 20):
+            mrf.mrf_tune(knob, 0)
+
+
 def truncated_problem(seed, algo, H, W, L, dirs, K, kind, trunc, integer_valued, weights):
     """Truncated linear (kind 1) / quadratic (kind 2) pairwise with the kind announced, so the
     library may take its window path.  weights: 'pos' | 'zero_mix' | 'neg_mix'."""
