@@ -1051,7 +1051,7 @@ hipError_t run_bwd_packed(MrfBwdParams &P, int seg, int ns, hipStream_t st)
 template <int SEG, int NL>
 hipError_t launch_bwd_narrow(MrfBwdParams &P, int ns, long long packs, hipStream_t st)
 {
-    // four wavefronts per workgroup share V and the V-gradient tables, but a launch that does not fill the machine
+    // four wavefronts per workgroup share V and a V-gradient slot, but a launch that does not fill the machine
     // spreads its wavefronts over the compute units
     const int waves = packs >= 1024 ? 4 : (packs >= 512 ? 2 : 1);
     const long long blocks = (packs + waves - 1) / waves;
@@ -1060,7 +1060,7 @@ hipError_t launch_bwd_narrow(MrfBwdParams &P, int ns, long long packs, hipStream
     // a workgroup has a V-gradient slot of its own: what is more than there are slots goes into further launches, which
     // add to the same slots one after the other
     const long long most = gv && blocks > grad_slots(L) ? grad_slots(L) : blocks;
-    const size_t lds = sizeof(double) * ((size_t)waves * (nseg * mrf_bwd_narrow_row<SEG, NL>() + 64) + (gv ? (size_t)mrf_bwd_narrow_tables(nseg, L) * mrf_bwd_narrow_table<SEG, NL>(L) : 0)) +
+    const size_t lds = sizeof(double) * (size_t)waves * (nseg * mrf_bwd_narrow_row<SEG, NL>() + 64 + (gv ? mrf_bwd_narrow_tables(nseg, L, waves) * mrf_bwd_narrow_table<SEG, NL>(L) : 0)) +
                        sizeof(float) * ((size_t)L * mrf_bwd_narrow_pitch(L) + 1);
     if (lds > 64 * 1024) return hipErrorInvalidValue;
     const dim3 block(64u * (unsigned)waves);

@@ -1326,7 +1326,8 @@ __global__ void __launch_bounds__(64) mrf_bwd_sweep_packed(const MrfBwdParams P)
 // chain is one add per label, the scatter into the segment's row in LDS and its read; the pairwise gradients of
 // a node are formed behind the scatter of the next one, while that is under way.
 // FULL: L is a multiple of NL, so that a lane's labels are one access of NL floats.
-// GV: every segment position has a table of its own in LDS, shared by the workgroup's wavefronts (LDS adds).
+// GV: every wavefront has V-gradient tables of its own in LDS, summed in a fixed order at the end: the order of all
+// additions, and with it every bit of the result, is the same in every run.
 template <int SEG, int NL>
 __host__ __device__ constexpr int mrf_bwd_narrow_row()
 {
@@ -1345,7 +1346,16 @@ __host__ __device__ inline int mrf_bwd_narrow_table(int L)
     return n + (want - n % 32 + 32) % 32;
 }
 
-__host__ __device__ inline int mrf_bwd_narrow_tables(int nseg, int L) { return L <= 22 || nseg < 4 ? nseg : nseg / 2; }
+// V-gradient tables of one wavefront: one for each of its segments where a workgroup has one wavefront and room (half
+// as many from 23 labels on), else as many as leave the workgroup's LDS what it is with one wavefront, at least one.
+// Segments that share a table add to it by the lanes of one instruction.  (Backward pass, ISGMR, four wavefronts sharing
+// the tables / with tables of their own: 4 x 512 x 512, 21 labels, 4 directions 1.10 / 1.09 ms; 256 x 512, 32 labels, 16
+// directions 1.06 / 1.05; TRWP 4 x 512 x 512, 32 labels 1.78 / 1.81)
+__host__ __device__ inline int mrf_bwd_narrow_tables(int nseg, int L, int waves)
+{
+    const int n = (L <= 22 || nseg < 4 ? nseg : nseg / 2) / waves;
+    return n > 0 ? n : 1;
+}
 
 template <int SEG, int NL, int NS, int D, bool UNARY, bool GV, bool FULL>
 __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P)
@@ -1360,10 +1370,10 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
     const int waves = (int)(blockDim.x >> 6);
     const int seg = lane / SEG, li = lane % SEG;
     const int lam0 = li * NL;                                 // the lane's first label
-    const int ntab = GV ? mrf_bwd_narrow_tables(NSEG, L) : 0, tsize = mrf_bwd_narrow_table<SEG, NL>(L), pitch = mrf_bwd_narrow_pitch(L);
+    const int ntab = GV ? mrf_bwd_narrow_tables(NSEG, L, waves) : 0, tsize = mrf_bwd_narrow_table<SEG, NL>(L), pitch = mrf_bwd_narrow_pitch(L);
     double *rows = reinterpret_cast<double *>(mrf_bsmem) + wv * (NSEG * RS + 64);            // [waves]{[NSEG][RS], 64 spare}
-    double *tabs = reinterpret_cast<double *>(mrf_bsmem) + waves * (NSEG * RS + 64);         // [ntab][tsize]
-    float *vl = reinterpret_cast<float *>(tabs + ntab * tsize);                              // [L][pitch] V, then a 0
+    double *tabs = reinterpret_cast<double *>(mrf_bsmem) + waves * (NSEG * RS + 64);         // [waves][ntab][tsize]
+    float *vl = reinterpret_cast<float *>(tabs + waves * ntab * tsize);                      // [L][pitch] V, then a 0
     double *sb = rows + seg * RS;
     double *spare = rows + NSEG * RS + lane;                  // where a lane with nothing to add adds
 
@@ -1372,7 +1382,7 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
         vl[e] = lam < L ? P.V[mu * L + lam] : 0.0f;
     }
     if (threadIdx.x == 0) vl[L * pitch] = 0.0f;
-    for (int e = threadIdx.x; e < waves * (NSEG * RS + 64) + ntab * tsize; e += blockDim.x) reinterpret_cast<double *>(mrf_bsmem)[e] = 0.0;
+    for (int e = threadIdx.x; e < waves * (NSEG * RS + 64 + ntab * tsize); e += blockDim.x) reinterpret_cast<double *>(mrf_bsmem)[e] = 0.0;
     __syncthreads();
 
     // this wavefront's scanlines: NSEG consecutive ones of direction r
@@ -1490,7 +1500,7 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
     float gwkeep = 0.0f;
     int gwleft = 0;                                           // lane's node of the group counts if positive
     unsigned gwat = 0;
-    double *tab = tabs + (ntab > 0 ? (seg % ntab) * tsize : 0);
+    double *tab = tabs + (GV ? (wv * ntab + seg % ntab) * tsize : 0);
     auto pairwise = [&](int slot) {
         int at[NL];
 #pragma unroll
@@ -1627,7 +1637,7 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
         for (int e = threadIdx.x; e < L * L; e += blockDim.x) {
             const int mu = e / L, at = mu * pitch + (e - mu * L);
             double v = tabs[at];
-            for (int k = 1; k < ntab; ++k) v += tabs[k * tsize + at];
+            for (int k = 1; k < waves * ntab; ++k) v += tabs[k * tsize + at];
             mrf_slot_add(&slot[e], v);
         }
     }

@@ -898,6 +898,39 @@ def test_backward_is_reproducible_run_to_run():
             np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
 
 
+@pytest.mark.parametrize("algo,B,L", [("isgmr", 32, 21), ("isgmr", 32, 16), ("isgmr", 16, 32), ("isgmr", 48, 8), ("trwp", 64, 25)])
+def test_pairwise_gradient_of_few_labels_is_reproducible(algo, B, L):
+    """Images in pairs with opposite gradients of the costs: every entry of grad_pairwise is a sum that cancels, so what
+    is left is the rounding of its additions, which shows any change of their order.  Launches with several wavefronts
+    per workgroup."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import GpuProblem
+    print("case reproducible few labels", algo, B, L, flush=True)
+    pr = random_problem(797 + L, algo, B, 24, 32, L, DIRS8, 2, symmetric=False)
+    for x in (pr.unary, pr.grad_cost):
+        x[B // 2:] = x[:B // 2]
+    pr.edge_weight[:, B // 2:] = pr.edge_weight[:, :B // 2]
+    pr.grad_cost[B // 2:] *= -1.0
+    g = GpuProblem(pr)
+    try:
+        assert mrf.mrf_tune(3, 2) == 0 and mrf.mrf_tune(20, 1) == 0
+        g.forward()
+        runs = []
+        for _ in range(4):
+            g.workspace.fill_(0xFF)
+            g.backward()
+            runs.append(g.results())
+        launch = mrf.mrf_last_sweep_launch(True)
+    finally:
+        mrf.mrf_tune(3, 0)
+        mrf.mrf_tune(20, 0)
+    assert launch.startswith("mrf_bwd_sweep_narrow") and int(launch.split("block=")[1].split()[0]) > 64, launch
+    assert (runs[0].grad_pairwise != 0).any()                  # (the order matters)
+    for r in runs[1:]:
+        for name in ("grad_unary", "grad_edge_weight", "grad_pairwise"):
+            np.testing.assert_array_equal(getattr(r, name), getattr(runs[0], name), err_msg=name)
+
+
 def test_waits_between_wavefronts_are_bounded(oracle):
     """The layouts that spread a scanline over several wavefronts give every wait a budget.  With a
     budget of one turn (set from the host) their first unmet wait gives up: every kernel still ends
