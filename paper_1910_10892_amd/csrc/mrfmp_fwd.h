@@ -573,6 +573,7 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
     constexpr int LH = LA / 2;                    // source labels per half
     constexpr int PT = LA + 4;                    // pitch of the transposed table (16-byte rows on different banks)
     constexpr int NCH = LH / 8;                   // chunks per half
+    constexpr int none = 256;                     // above any label; as a byte 0, which p and q are where no candidate is below infinity
     extern __shared__ __align__(16) unsigned char mrf_smem[];
     float *vt = reinterpret_cast<float *>(mrf_smem);             // [LA][PT] V transposed: row lambda
     __shared__ __align__(16) float hrow[2][LA];                  // h of the node, by step parity
@@ -634,7 +635,7 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
         plain = plain && !(Vr[i] < 0.0f) && !(mu == lam && Vr[i] != 0.0f);
         vt[lam * PT + mu] = Vr[i];
     }
-    if (threadIdx.x < 8) { (&hmin_w[0][0])[threadIdx.x] = INFINITY; (&q_w[0][0])[threadIdx.x] = 255; }
+    if (threadIdx.x < 8) { (&hmin_w[0][0])[threadIdx.x] = INFINITY; (&q_w[0][0])[threadIdx.x] = none; }
     if (threadIdx.x < 4) tmin_w[threadIdx.x] = INFINITY;
     // sign bit set: some node step may not take the minimum of h for that of the new message
     const int slow = __syncthreads_and(plain ? 1 : 0) != 0 ? 0 : (int)0x80000000;
@@ -722,7 +723,9 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
                 float d[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) d[j] = __builtin_fmaf(wgt, Vr[8 * ch + j], hq[8 * ch + j]);
-                const float m = mrf_min3(mrf_min3(d[0], d[1], d[2]), mrf_min3(d[3], d[4], d[5]), mrf_min(d[6], d[7]));
+                // (a running minimum starts below NaN: eight of them in the first chunk must not hide the others)
+                const float d67 = ch == 0 ? mrf_min3(d[6], d[7], INFINITY) : mrf_min(d[6], d[7]);
+                const float m = mrf_min3(mrf_min3(d[0], d[1], d[2]), mrf_min3(d[3], d[4], d[5]), d67);
                 if constexpr (ch == 0) {
                     best = m;
                 } else {
@@ -747,12 +750,12 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
             }
             carry = tv - tq;
             const unsigned qb = (unsigned)__ballot((int)valid & (int)(tv == tq));
-            q_w[par][wv] = qb != 0u ? 32 * wv + __ffs((int)qb) - 1 : 255;
+            q_w[par][wv] = qb != 0u ? 32 * wv + __ffs((int)qb) - 1 : none;
 
             // ---- p: the lowest source label of the winning chunk that attains the minimum, four per half ----
             const int m4 = mu0 + 4 * hf;
             const float4 va = *reinterpret_cast<const float4 *>(&vt[lam * PT + m4]), hv = *reinterpret_cast<const float4 *>(&hrow[par][m4]);
-            int pf = 255;
+            int pf = none;
             pf = __builtin_fmaf(wgt, va.w, hv.w) == tv ? m4 + 3 : pf;
             pf = __builtin_fmaf(wgt, va.z, hv.z) == tv ? m4 + 2 : pf;
             pf = __builtin_fmaf(wgt, va.y, hv.y) == tv ? m4 + 1 : pf;
@@ -764,7 +767,7 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
             ob += step_lb;
             on += step_n;
             store_f32(bmo, moff, ob, carry);
-            store_u8(bp, poff, ob >> 2, (int)min(px[0], px[1]));
+            store_u8(bp, poff, ob >> 2, tv < INFINITY ? (int)min(px[0], px[1]) : none);
         }
     };
 #pragma unroll

@@ -209,6 +209,38 @@ def test_dense_sweep_with_chunk_minima(oracle, case):
         np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("L", [33, 40, 64, 70, 96, 128])
+@pytest.mark.parametrize("algo", ["isgmr", "trwp"])
+def test_chunk_minima_where_no_label_is_possible(algo, L):
+    """Infinite or NaN unaries for all labels of a pixel, and masks with transitions between equal labels only, make
+    messages NaN: the argmins are still labels, those of the sweep with a running argmin."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    for kind in ("infinite", "nan", "masks"):
+        print("case no possible label", algo, L, kind, flush=True)
+        pr = random_problem(620 + L, algo, 1, 6, 9, L, DIRS8, 2, symmetric=False)
+        np.fill_diagonal(pr.pairwise, 0.0)
+        if kind == "masks":
+            mask = np.random.default_rng(L).random(pr.unary.shape) < 0.3
+            mask[..., L // 2] = False
+            pr.unary[mask] = np.inf
+            pr.pairwise[~np.eye(L, dtype=bool)] = np.inf
+        else:
+            pr.unary[:, 3, 4, :] = np.inf if kind == "infinite" else np.nan
+        try:
+            a = run_gpu(pr, backward=False)
+            assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_halves", mrf.mrf_last_sweep_launch(False)
+            assert mrf.mrf_tune(16, 1) == 0
+            b = run_gpu(pr, backward=False)
+            assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep"
+        finally:
+            mrf.mrf_tune(16, 0)
+        assert a.p.max() < L and a.q.max() < L
+        for name in ("p", "q", "labels", "cost", "messages"):
+            np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
+
+
 PRESUM_CASES = [
     # seed, B, H, W, L, dirs, K, integer_valued, truncated
     (701, 1, 6, 7, 40, DIRS8, 3, False, False), (702, 2, 5, 6, 21, DIRS8, 3, True, False),
