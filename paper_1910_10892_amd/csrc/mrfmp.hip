@@ -112,7 +112,7 @@ inline size_t gradv_bytes(const mrf_problem *pr)
     return align_up((size_t)grad_slots(pr->L) * pr->L * pr->L * sizeof(double));
 }
 
-// room for the node gradients that mrf_bwd_pairwise_from_g reads (33..128 labels)
+// room for the node gradients that mrf_bwd_pairwise_* reads (33..128 labels)
 inline size_t gstore_bytes(const mrf_problem *pr)
 {
     if (pr->L <= 32 || pr->L > 128) return 0;
@@ -1163,7 +1163,7 @@ int narrow_lanes(const MrfBwdParams &P, int L)
     return L <= 24 ? 8 : (P.gV ? 32 : 16);
 }
 
-#define MRF_GV_BLOCKS 256      // workgroups (and slots) of mrf_bwd_pairwise_from_g
+#define MRF_GV_BLOCKS 256      // workgroups (and slots) of mrf_bwd_pairwise_*
 
 hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
 {
@@ -1197,7 +1197,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     }
     const bool gv_any = P.gV != nullptr;
     // 33..128 labels, one direction per launch: the chain layout has no room for V-gradient tables, so its
-    // helpers store the node gradients and a streaming pass forms both pairwise gradients (mrf_bwd_pairwise_from_g)
+    // helpers store the node gradients and a streaming pass forms both pairwise gradients (mrf_bwd_pairwise_*)
     // (backward pass per iteration with all gradients, 256 x 512, 8 directions: 96 labels 3.6 -> 1.3 ms, 64 labels 2.1 ->
     // 0.9, 40 labels 1.0 -> 0.75; 16 directions on 128 x 256, 96 labels, 3.8 -> 1.35.  Up to 48 labels a launch of one
     // scanline per compute unit has room for eight helpers with tables of their own: 64 x 96, 40 labels, 4 directions,
@@ -1283,24 +1283,28 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
             G.w = P.w + (P.w_mul ? (size_t)P.r_first * P.g.N : 0); G.w_mul = P.w_mul;
             G.V = P.V; G.gw = P.gw ? P.gw + (size_t)P.r_first * P.g.N : nullptr;
             G.gV = slots;
-            const size_t tile = sizeof(double) * (size_t)L * L, both = tile + sizeof(float) * (size_t)L * L;
-            G.v_lds = both <= 156 * 1024 ? 1 : 0;
-            const size_t glds = G.v_lds ? both : tile;
-            // (a workgroup per compute unit at most.  Its sixteen wavefronts take four nodes each at a time: one such turn
-            // per workgroup while there are few workgroups, then two, so that clearing and flushing the tables does not
+            // (up to 64 labels: as many tables, eight or four, as 156 KB hold next to V)
+            const size_t vsize = sizeof(float) * (size_t)L * L, tsize = sizeof(double) * (size_t)L * L;
+            const int tables = LP == 1 ? (8 * tsize + vsize <= 156 * 1024 ? 8 : 4) : 1;
+            G.v_lds = tables * tsize + vsize <= 156 * 1024 ? 1 : 0;
+            const size_t glds = tables * tsize + (G.v_lds ? vsize : 0);
+            // (a workgroup per compute unit at most.  Its sixteen wavefronts take 64 nodes at a time: one such turn per
+            // workgroup while there are few workgroups, then two, so that clearing and flushing the tables does not
             // outweigh the turns.  Backward pass, 8 directions, K = 2, with one / two / four turns: 37 x 53 nodes, 70 labels
             // 0.41 / 0.44 / 0.54 ms; 64 x 96, 96 labels 0.62 / 0.62 / 0.70; 128 x 128, 128 labels 1.21 / 1.07 / 1.10)
             const long long one = (P.g.N + 63) / 64, two = P.g.N / 128;
             long long gblocks = one < 96 ? one : (two > 96 ? two : 96);
             if (gblocks > MRF_GV_BLOCKS) gblocks = MRF_GV_BLOCKS;
-            const void *fn = LP == 1 ? reinterpret_cast<const void *>(&mrf_bwd_pairwise_from_g<1>) : reinterpret_cast<const void *>(&mrf_bwd_pairwise_from_g<2>);
-            if (glds > 64 * 1024) {
-                const hipError_t ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)glds);
-                if (ea != hipSuccess) return ea;
-            }
-            if (LP == 1) hipLaunchKernelGGL(mrf_bwd_pairwise_from_g<1>, dim3((unsigned)gblocks), dim3(1024), glds, st, G);
-            else hipLaunchKernelGGL(mrf_bwd_pairwise_from_g<2>, dim3((unsigned)gblocks), dim3(1024), glds, st, G);
-            return hipGetLastError();
+            const auto go = [&](void (*kernel)(MrfGvParams)) {
+                if (glds > 64 * 1024) {
+                    const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)glds);
+                    if (ea != hipSuccess) return ea;
+                }
+                hipLaunchKernelGGL(kernel, dim3((unsigned)gblocks), dim3(1024), glds, st, G);
+                return hipGetLastError();
+            };
+            if (LP == 1) return tables == 8 ? go(mrf_bwd_pairwise_own<8>) : go(mrf_bwd_pairwise_own<4>);
+            return go(mrf_bwd_pairwise_shared);
         }
         return run_bwd_chain(P, ns, ni, vg, st);
     }
@@ -1341,7 +1345,7 @@ hipError_t fill(float *dst, long long n, float v, hipStream_t st)
 }
 
 // Slots that the sweeps of a backward call can add to: a layout has at most one per scanline of a launch (the
-// last workgroup of mrf_bwd_sweep may hold up to three wavefronts without one), mrf_bwd_pairwise_from_g one per workgroup.
+// last workgroup of mrf_bwd_sweep may hold up to three wavefronts without one), mrf_bwd_pairwise_* one per workgroup.
 long long slots_in_use(const mrf_problem *pr, const MrfGeom &g, int algo)
 {
     long long most = 0, all = 0;
@@ -1386,7 +1390,7 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     P.rho_e = (algo == MRF_TRWP) ? pr->rho_edge : nullptr;
     const size_t pk = (size_t)R * N * L, qk = (size_t)R * N;
 
-    // workspace: [scalars 256 B][buf0][buf1 (ISGMR only)][V-gradient slots][node gradients for mrf_bwd_pairwise_from_g (65..128 labels)]
+    // workspace: [scalars 256 B][buf0][buf1 (ISGMR only)][V-gradient slots][node gradients for mrf_bwd_pairwise_* (65..128 labels)]
     char *ws = (char *)workspace;
     float *scal = (float *)ws;
     float *buf0 = (float *)(ws + kAlign);                   // ISGMR: grad m-hat   TRWP: s per direction

@@ -79,7 +79,7 @@ struct MrfBwdParams {
     int force_plain;                       // the problem has no V: only mrf_bwd_sweep may run
     double *gstore_buf;                    // [N][L] room for gstore (workspace), or NULL
     double *gstore;                        // mrf_bwd_sweep_chain: if not NULL, its helpers store the gradient vector g of
-                                           // every node here (0 where no update is replayed) for mrf_bwd_pairwise_from_g,
+                                           // every node here (0 where no update is replayed) for mrf_bwd_pairwise_*,
                                            // which forms both pairwise gradients from it
     int *fault;                            // launch-wide word raised when a wait between wavefronts is given up (mrf_wait_turn)
     int spin_limit;                        // microseconds after which a wait is given up
@@ -484,7 +484,7 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
 // GV without VG (L <= 64, as far as LDS has room): the launch also wants the V gradient; every helper keeps an
 // accumulator of its own in LDS, lane lambda owning column lambda; their sum goes to the workgroup's slot at the end.
 // GV with VG (33..128 labels): there is no room for the tables; the helpers store the gradient vector g of every node
-// in P.gstore (0 where no update is replayed) and leave both pairwise gradients to mrf_bwd_pairwise_from_g, a streaming
+// in P.gstore (0 where no update is replayed) and leave both pairwise gradients to mrf_bwd_pairwise_*, a streaming
 // pass that has all of LDS for V and the table.  What is left for a helper is short enough that four of them keep
 // up with the chain, so the layout stays ahead to 1,536 scanlines per launch (it did to 512 while the helpers
 // gathered from V).
@@ -507,7 +507,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
     double *sbuf = b_sv + NR * LL;                               // [LL] scatter target of the chain
     double *gvacc = sbuf + LL;                                   // [NI][L*L] V-gradient accumulators (GV)
     constexpr bool GVT = GV && !VG;          // V-gradient tables in LDS
-    constexpr bool GS = GV && VG;            // node gradients stored for mrf_bwd_pairwise_from_g
+    constexpr bool GS = GV && VG;            // node gradients stored for mrf_bwd_pairwise_*
     static_assert(!GVT || LP == 1, "V-gradient tables");
     float *a_extT = reinterpret_cast<float *>(gvacc + (GVT ? NI * P.g.L * P.g.L : 0));   // [NR][LL] pre -> post (launches that form grad theta)
     int *pre_done = reinterpret_cast<int *>(a_extT + (P.unary_dir >= 0 ? NR * LL : 0));   // [MRF_CHAIN_MAX_HELPERS] per helper: last step published

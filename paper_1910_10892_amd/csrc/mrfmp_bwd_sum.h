@@ -8,10 +8,11 @@
 // Eq. supp-gradient-smoothness and Eq. supp-gradient-edge: at every replayed update, entry (p(lambda), lambda) of the
 // table receives theta_{i-r,i} g(lambda), and theta_{i-r,i} receives sum_lambda g(lambda) V(p(lambda), lambda).
 // Nothing of them depends on the order of the nodes, so where the chain layout has no room for the tables its
-// helpers store g per node and this streaming pass does the rest: lanes over lambda, one node after the other per
-// wavefront, the L x L table of a workgroup and V in LDS, the table added to the workgroup's slot at the end.
-// Bound by HBM (9 bytes per label); with a single node in flight per wavefront it was bound by the latency of the
-// loads, 129 us at 256 x 512, 96 labels.
+// helpers store g per node and a streaming pass does the rest: lanes over lambda, V and the table in LDS, the table
+// added to the workgroup's slot at the end.  Bound by HBM (9 bytes per label); with a single node in flight per
+// wavefront it was bound by the latency of the loads, 129 us at 256 x 512, 96 labels.
+//   mrf_bwd_pairwise_own     33..64 labels: the wavefronts that add have a table each
+//   mrf_bwd_pairwise_shared  65..128 labels: one table, to which all wavefronts add in the order they arrive
 struct MrfGvParams {
     long long N;
     int L;
@@ -20,17 +21,91 @@ struct MrfGvParams {
     const float *w;          // [N] edge weights of this direction, or the scalar at w[0] when w_mul == 0
     int w_mul;
     const float *V;          // [L][L]
-    int v_lds;               // V fits in LDS next to the table
+    int v_lds;               // V fits in LDS next to the table (it does next to mrf_bwd_pairwise_own's)
     float *gw;               // [N] edge-weight gradient of this direction, accumulated, or NULL
     double *gV;              // [gridDim.x][L][L] slots
 };
 
-template <int LP>
-__global__ void __launch_bounds__(1024) mrf_bwd_pairwise_from_g(const MrfGvParams P)
+// V gradient and edge-weight gradient on wavefronts of their own: NA = 4 (49..64 labels) or 8 wavefronts add to tables
+// of their own, which a workgroup sums in wavefront order, so the order of every addition is fixed; the others form the
+// edge-weight gradient of the same 64 nodes, and find g and p in the cache.  (With both on NA wavefronts the label sums
+// set the pace there.)
+template <int NA>
+__global__ void __launch_bounds__(1024) mrf_bwd_pairwise_own(const MrfGvParams P)
+{
+    extern __shared__ __align__(16) unsigned char mrf_gvsmem[];
+    double *tabs = reinterpret_cast<double *>(mrf_gvsmem);
+    constexpr int CH = 64;                               // nodes of a turn
+    constexpr int UA = CH / NA, UG = (CH + 15 - NA) / (16 - NA);      // of which a wavefront has
+    const int L = P.L;
+    float *vl = reinterpret_cast<float *>(tabs + NA * L * L);
+    for (int e = threadIdx.x; e < NA * L * L; e += blockDim.x) tabs[e] = 0.0;
+    for (int e = threadIdx.x; e < L * L; e += blockDim.x) vl[e] = P.V[e];
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lc = lane < L ? lane : 0;
+    if (wv < NA) {
+        double *tile = tabs + wv * L * L;
+        for (long long i0 = (long long)blockIdx.x * CH + wv * UA; i0 < P.N; i0 += (long long)gridDim.x * CH) {
+            double g[UA];
+            int pv[UA];
+            float w[UA];
+#pragma unroll
+            for (int u = 0; u < UA; ++u) {
+                const long long i = i0 + u < P.N ? i0 + u : P.N - 1;
+                w[u] = P.w[(size_t)(i * P.w_mul)];
+                g[u] = P.g[(size_t)i * L + lc];
+                pv[u] = P.p[(size_t)i * L + lc];
+            }
+#pragma unroll
+            for (int u = 0; u < UA; ++u) {
+                const int pc = pv[u] < L ? pv[u] : L - 1;
+                if (lane < L && i0 + u < P.N && g[u] != 0.0)
+                    __hip_atomic_fetch_add(&tile[__mul24(pc, L) + lc], (double)w[u] * g[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+    } else if (P.gw) {
+        const int first = (wv - NA) * UG, count = CH - first < UG ? CH - first : UG;
+        for (long long i0 = (long long)blockIdx.x * CH + first; count > 0 && i0 < P.N; i0 += (long long)gridDim.x * CH) {
+            double g[UG];
+            int pv[UG];
+#pragma unroll
+            for (int u = 0; u < UG; ++u) {
+                const long long i = i0 + u < P.N ? i0 + u : P.N - 1;
+                g[u] = P.g[(size_t)i * L + lc];
+                pv[u] = P.p[(size_t)i * L + lc];
+            }
+            float mine = 0.0f;           // lane u: edge-weight gradient of node i0 + u
+#pragma unroll
+            for (int u = 0; u < UG; ++u) {
+                const bool live = lane < L && g[u] != 0.0;
+                const int pc = pv[u] < L ? pv[u] : L - 1;
+                const float v = vl[__mul24(pc, L) + lc];
+                const double acc = mrf_wave_sum_f64(live ? g[u] * (double)v : 0.0);
+                if (lane == u) mine = (float)acc;
+            }
+            // one writer per entry and launch: a no-return atomic is a plain accumulate
+            if (lane < count && i0 + lane < P.N)
+                __hip_atomic_fetch_add(&P.gw[(size_t)(i0 + lane)], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __syncthreads();
+    double *slot = P.gV + (size_t)blockIdx.x * L * L;
+    for (int e = threadIdx.x; e < L * L; e += blockDim.x) {     // (no-return atomics as in mrf_slot_add)
+        double v = tabs[e];
+#pragma unroll
+        for (int k = 1; k < NA; ++k) v += tabs[k * L * L + e];
+        __hip_atomic_fetch_add(&slot[e], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+__global__ void __launch_bounds__(1024) mrf_bwd_pairwise_shared(const MrfGvParams P)
 {
     extern __shared__ __align__(16) unsigned char mrf_gvsmem[];
     double *tile = reinterpret_cast<double *>(mrf_gvsmem);
     float *vl = reinterpret_cast<float *>(tile + P.L * P.L);
+    constexpr int LP = 2;
     constexpr int U = 4;                 // nodes in flight per wavefront
     const int L = P.L;
     for (int e = threadIdx.x; e < L * L; e += blockDim.x) tile[e] = 0.0;

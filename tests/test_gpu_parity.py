@@ -930,37 +930,56 @@ def test_backward_is_reproducible_run_to_run():
             np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
 
 
-@pytest.mark.parametrize("algo,B,L", [("isgmr", 32, 21), ("isgmr", 32, 16), ("isgmr", 16, 32), ("isgmr", 48, 8), ("trwp", 64, 25)])
-def test_pairwise_gradient_of_few_labels_is_reproducible(algo, B, L):
+def cancelling_problem(seed, algo, B, H, W, L):
     """Images in pairs with opposite gradients of the costs: every entry of grad_pairwise is a sum that cancels, so what
-    is left is the rounding of its additions, which shows any change of their order.  Launches with several wavefronts
-    per workgroup."""
-    import paper_1910_10892_amd as mrf
-    from gpu_harness import GpuProblem
-    print("case reproducible few labels", algo, B, L, flush=True)
-    pr = random_problem(797 + L, algo, B, 24, 32, L, DIRS8, 2, symmetric=False)
+    is left is the rounding of its additions, which shows any change of their order."""
+    pr = random_problem(seed, algo, B, H, W, L, DIRS8, 2, symmetric=False)
     for x in (pr.unary, pr.grad_cost):
         x[B // 2:] = x[:B // 2]
     pr.edge_weight[:, B // 2:] = pr.edge_weight[:, :B // 2]
     pr.grad_cost[B // 2:] *= -1.0
-    g = GpuProblem(pr)
+    return pr
+
+
+def check_reproducible(g):
+    """Four backward passes of a problem of the kind above, bit for bit."""
+    g.forward()
+    runs = []
+    for _ in range(4):
+        g.workspace.fill_(0xFF)
+        g.backward()
+        runs.append(g.results())
+    assert (runs[0].grad_pairwise != 0).any()                  # (the order matters)
+    for r in runs[1:]:
+        for name in ("grad_unary", "grad_edge_weight", "grad_pairwise"):
+            np.testing.assert_array_equal(getattr(r, name), getattr(runs[0], name), err_msg=name)
+
+
+@pytest.mark.parametrize("algo,B,L", [("isgmr", 32, 21), ("isgmr", 32, 16), ("isgmr", 16, 32), ("isgmr", 48, 8), ("trwp", 64, 25)])
+def test_pairwise_gradient_of_few_labels_is_reproducible(algo, B, L):
+    """Launches with several wavefronts per workgroup."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import GpuProblem
+    print("case reproducible few labels", algo, B, L, flush=True)
+    g = GpuProblem(cancelling_problem(797 + L, algo, B, 24, 32, L))
     try:
         assert mrf.mrf_tune(3, 2) == 0 and mrf.mrf_tune(20, 1) == 0
-        g.forward()
-        runs = []
-        for _ in range(4):
-            g.workspace.fill_(0xFF)
-            g.backward()
-            runs.append(g.results())
+        check_reproducible(g)
         launch = mrf.mrf_last_sweep_launch(True)
     finally:
         mrf.mrf_tune(3, 0)
         mrf.mrf_tune(20, 0)
     assert launch.startswith("mrf_bwd_sweep_narrow") and int(launch.split("block=")[1].split()[0]) > 64, launch
-    assert (runs[0].grad_pairwise != 0).any()                  # (the order matters)
-    for r in runs[1:]:
-        for name in ("grad_unary", "grad_edge_weight", "grad_pairwise"):
-            np.testing.assert_array_equal(getattr(r, name), getattr(runs[0], name), err_msg=name)
+
+
+@pytest.mark.parametrize("L", [33, 40, 46, 50, 64])
+def test_pairwise_gradient_behind_the_chain_sweep_is_reproducible(L):
+    """33..64 labels, TRWP: the pass behind the chain sweep keeps a table per wavefront (sixteen to four of them)."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import GpuProblem
+    print("case reproducible behind the chain", L, flush=True)
+    check_reproducible(GpuProblem(cancelling_problem(798 + L, "trwp", 16, 24, 32, L)))
+    assert mrf.mrf_last_sweep_launch(True).startswith("mrf_bwd_sweep_chain<1,") and "true,true" in mrf.mrf_last_sweep_launch(True)
 
 
 def test_waits_between_wavefronts_are_bounded(oracle):
