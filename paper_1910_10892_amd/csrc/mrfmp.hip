@@ -112,11 +112,17 @@ inline size_t gradv_bytes(const mrf_problem *pr)
     return align_up((size_t)grad_slots(pr->L) * pr->L * pr->L * sizeof(double));
 }
 
-// room for the node gradients that mrf_bwd_pairwise_* reads (33..128 labels)
-inline size_t gstore_bytes(const mrf_problem *pr)
+// Most scanlines of a launch whose node gradients are stored for mrf_bwd_pairwise_* (33..128 labels, one direction per
+// launch), and room for them.  (By shape, directions and algorithm only, so that problems which agree in these can share
+// a workspace.)
+constexpr long long kApartMost = 1536;
+inline size_t gstore_bytes(const mrf_problem *pr, int algo)
 {
-    if (pr->L <= 32 || pr->L > 128) return 0;
-    return align_up((size_t)pr->B * pr->H * pr->W * pr->L * sizeof(double));
+    if (pr->L <= 32 || pr->L > 128 || (algo == MRF_ISGMR && pr->R > 1)) return 0;
+    bool any = false;
+    for (int r = 0; r < pr->R; ++r)
+        any = any || pr->B * mrf_geom_scanlines(pr->H, pr->W, pr->dirs[2 * r], pr->dirs[2 * r + 1]) <= kApartMost;
+    return any ? align_up((size_t)pr->B * pr->H * pr->W * pr->L * sizeof(double)) : 0;
 }
 
 // ---- process-global state: defined in the translation unit of the entry points ----------
@@ -1203,7 +1209,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // scanline per compute unit has room for eight helpers with tables of their own: 64 x 96, 40 labels, 4 directions,
     // 0.10 against 0.13 ms)
     const bool gv_apart = gv_any && L > 32 && LP <= 2 && P.gstore_buf && P.r_count == 1 && !P.rho_e && !P.force_plain &&
-                          P.total_scanlines <= 1536 && !(L <= 48 && P.total_scanlines <= 256) && g_tune_gv_apart != 1;
+                          P.total_scanlines <= kApartMost && !(L <= 48 && P.total_scanlines <= 256) && g_tune_gv_apart != 1;
     const bool gv = gv_any && !gv_apart;      // the V gradient inside the sweep that runs
     // as many helpers as keep up with the chain while the machine and the LDS have room
     // (measured per launch shape at L = 96: 256 scanlines 165 / 121 / 98 / 90 us with 4 / 6 / 8 / 12
@@ -1355,7 +1361,7 @@ long long slots_in_use(const mrf_problem *pr, const MrfGeom &g, int algo)
         if (n > most) most = n;
     }
     long long n = (algo == MRF_ISGMR ? all : most) + MRF_BWD_WAVES - 1;
-    if (gstore_bytes(pr) > 0 && n < MRF_GV_BLOCKS) n = MRF_GV_BLOCKS;
+    if (gstore_bytes(pr, algo) > 0 && n < MRF_GV_BLOCKS) n = MRF_GV_BLOCKS;
     return n < grad_slots(g.L) ? n : grad_slots(g.L);
 }
 
@@ -1390,7 +1396,7 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     P.rho_e = (algo == MRF_TRWP) ? pr->rho_edge : nullptr;
     const size_t pk = (size_t)R * N * L, qk = (size_t)R * N;
 
-    // workspace: [scalars 256 B][buf0][buf1 (ISGMR only)][V-gradient slots][node gradients for mrf_bwd_pairwise_* (65..128 labels)]
+    // workspace: [scalars 256 B][buf0][buf1 (ISGMR only)][V-gradient slots][node gradients for mrf_bwd_pairwise_* (gstore_bytes)]
     char *ws = (char *)workspace;
     float *scal = (float *)ws;
     float *buf0 = (float *)(ws + kAlign);                   // ISGMR: grad m-hat   TRWP: s per direction
@@ -1406,7 +1412,7 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     if (grad_V && !edge_tables) {
         P.gV = gvslots;
         slots = slots_in_use(pr, P.g, algo);
-        if (gstore_bytes(pr) > 0) P.gstore_buf = (double *)((char *)gvslots + gradv_bytes(pr));
+        if (gstore_bytes(pr, algo) > 0) P.gstore_buf = (double *)((char *)gvslots + gradv_bytes(pr));
     }
     if (grad_w || slots > 0) {
         const long long n_gw = grad_w ? (long long)R * N : 0, n_slots = slots * L * L;
@@ -1584,7 +1590,7 @@ size_t mrf_workspace_bytes(const mrf_problem *prob, int algo, int backward)
 {
     if (check_problem(prob, algo, false) != MRF_OK) return 0;
     if (!backward) return kAlign + (algo == MRF_ISGMR ? 2 : 1) * msg_bytes(prob);
-    return kAlign + (algo == MRF_ISGMR ? 2 : 1) * msg_bytes(prob) + gradv_bytes(prob) + gstore_bytes(prob);
+    return kAlign + (algo == MRF_ISGMR ? 2 : 1) * msg_bytes(prob) + gradv_bytes(prob) + gstore_bytes(prob, algo);
 }
 
 int mrf_validate(const mrf_problem *prob, int algo) { return check_problem(prob, algo, true); }

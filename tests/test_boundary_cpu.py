@@ -133,6 +133,23 @@ def test_entry_points_reject_before_any_gpu_work():
         assert f(ctypes.byref(c), fake, fake, fake, fake, None, None, fake, needb - 1, None) == -6
 
 
+def test_room_for_node_gradients_only_where_a_launch_stores_them():
+    """33..128 labels: one direction per launch (TRWP, or a single direction) and few enough scanlines in it."""
+    lib = mrf.load_library()
+
+    def room(algo, L, H=64, W=64, **kw):
+        c = _cprob(L=L, H=H, W=W, **kw)
+        fixed = lib.mrf_workspace_bytes(ctypes.byref(c), algo, 0)
+        slots = (16384 if L <= 32 else 1024) * L * L * 8
+        return lib.mrf_workspace_bytes(ctypes.byref(c), algo, 1) - fixed - (slots + 255) // 256 * 256
+
+    for L, algo, kw, want in ((64, 1, {}, True), (128, 1, {}, True), (32, 1, {}, False), (129, 1, {}, False), (64, 0, {}, False),
+                              (96, 0, {}, False), (64, 0, {"dirs": [(0, 1)]}, True), (64, 1, {"H": 1536, "W": 1536}, True),
+                              (64, 1, {"H": 1537, "W": 1537}, False), (64, 1, {"H": 1537, "W": 8}, True)):
+        nodes = kw.get("H", 64) * kw.get("W", 64)
+        assert room(algo, L, **kw) == (8 * nodes * L if want else 0), (L, algo, kw)
+
+
 def test_workspace_fault_query_rejects_null():
     lib = mrf.load_library()
     assert lib.mrf_workspace_fault(None, None) == -1
