@@ -433,6 +433,31 @@ def test_backward_with_several_labels_per_lane(oracle, case):
             check_grad("%s (%d lanes)" % (name, seg), getattr(g, name), None, getattr(plain, name).astype(np.float64))
 
 
+NARROW_WAVES_CASES = [
+    # seed, images, L, lanes, block: two and four wavefronts per workgroup, the last one with idle wavefronts
+    (801, 75, 5, 8, 64), (802, 301, 5, 8, 128), (803, 153, 13, 16, 128), (804, 303, 16, 16, 256), (805, 601, 23, 8, 256),
+    (806, 77, 25, 32, 128), (807, 151, 32, 32, 256), (808, 153, 32, 16, 128), (809, 601, 32, 8, 256),
+]
+
+
+@pytest.mark.parametrize("case", NARROW_WAVES_CASES, ids=lambda c: "seed%d" % c[0])
+def test_narrow_backward_with_several_wavefronts_per_workgroup(oracle, case):
+    """Batches of small images that take several wavefronts per workgroup: a V, its gradient's slot and the LDS behind
+    them shared, with and without grad_pairwise."""
+    import paper_1910_10892_amd as mrf
+    print("case narrow wavefronts", case, flush=True)
+    seed, B, L, lanes, block = case
+    pr = random_problem(seed, "isgmr", B, 3, 5, L, DIRS4, 2, symmetric=False)
+    try:
+        assert mrf.mrf_tune(3, lanes) == 0
+        for want_V in (True, False):
+            full_check(oracle, pr, want_V=want_V)
+            launch = mrf.mrf_last_sweep_launch(True)
+            assert launch.startswith("mrf_bwd_sweep_narrow<%d," % lanes) and "block=%d" % block in launch, launch
+    finally:
+        mrf.mrf_tune(3, 0)
+
+
 MANY_SMALL_IMAGES = [
     # seed, algo, images, L: more workgroups of the narrow sweep than there are V-gradient slots (16,384)
     (791, "isgmr", 6600, 25), (792, "isgmr", 13200, 12), (793, "isgmr", 26400, 5),
@@ -517,7 +542,7 @@ GV_APART_CASES = [
 @pytest.mark.parametrize("case", GV_APART_CASES, ids=lambda c: "seed%d" % c[0])
 def test_pairwise_gradient_added_up_behind_the_chain_sweep(oracle, case):
     """TRWP with 65..128 labels and grad_pairwise: the chain sweep stores the node gradients and a streaming
-    pass forms the table (Eq. supp-gradient-smoothness); against the oracle, and against the sweep that
+    pass forms both pairwise gradients (Eq. supp-gradient-smoothness, Eq. supp-gradient-edge); against the oracle, and against the sweep that
     accumulates the table itself."""
     import paper_1910_10892_amd as mrf
     print("case grad V apart", case[:5], len(case[5]), case[6:], flush=True)
@@ -531,6 +556,40 @@ def test_pairwise_gradient_added_up_behind_the_chain_sweep(oracle, case):
         assert mrf.mrf_tune(19, 1) == 0
         b = full_check(oracle, pr, want_V=True)
         assert mrf.mrf_last_sweep_kernel(True) != "mrf_bwd_sweep_chain"
+    finally:
+        mrf.mrf_tune(19, 0)
+    check_grad("grad_pairwise (two layouts)", a.grad_pairwise, None, b.grad_pairwise.astype(np.float64))
+
+
+GV_APART_FEW_CASES = [
+    # seed, B, H, W, L, dirs, K, kind: 33..64 labels; eight or four tables; sixteen sources; a pre-reduced scatter target
+    (761, 50, 6, 9, 33, DIRS4, 2, 0), (762, 1, 7, 9, 49, DIRS8, 2, 0), (763, 1, 5, 8, 64, DIRS16, 2, 0), (764, 3, 11, 7, 55, DIRS4, 3, 0),
+    (765, 130, 9, 6, 40, DIRS4, 2, 1), (766, 130, 9, 5, 64, DIRS4, 1, 1), (767, 130, 9, 6, 70, DIRS4, 1, 1), (768, 60, 5, 6, 48, DIRS16, 1, 0),
+    (769, 1, 5, 7, 96, DIRS16, 2, 0),
+]
+
+
+@pytest.mark.parametrize("case", GV_APART_FEW_CASES, ids=lambda c: "seed%d" % c[0])
+def test_pairwise_gradients_from_stored_node_gradients(oracle, case):
+    """The same for 33..64 labels, for sixteen directions and for launches whose chain wavefront sums the lanes of the
+    most popular scatter target (truncated models, more than 1,024 scanlines)."""
+    import paper_1910_10892_amd as mrf
+    print("case node gradients", case[:5], len(case[5]), case[6:], flush=True)
+    seed, B, H, W, L, dirs, K, kind = case
+    if kind:
+        from mrf_inputs import truncated_linear
+    pr = random_problem(seed, "trwp", B, H, W, L, dirs, K, symmetric=False, rho=np.linspace(0.3, 0.9, len(dirs)))
+    if kind:
+        pr.pairwise = truncated_linear(L, 20.0, 0.37)
+        pr.pairwise_kind, pr.trunc, pr.scale = 1, 20.0, 0.37
+    pr.grad_cost = (pr.grad_cost * (0.02 if len(dirs) > 8 else 0.2)).astype(np.float32)
+    a = full_check(oracle, pr)
+    launch = mrf.mrf_last_sweep_launch(True)
+    assert launch.startswith("mrf_bwd_sweep_chain<%d," % ((L + 63) // 64)) and "true,true,%s" % ("true" if kind else "false") in launch, launch
+    try:
+        assert mrf.mrf_tune(19, 1) == 0
+        b = full_check(oracle, pr)
+        assert "true,true," not in mrf.mrf_last_sweep_launch(True)
     finally:
         mrf.mrf_tune(19, 0)
     check_grad("grad_pairwise (two layouts)", a.grad_pairwise, None, b.grad_pairwise.astype(np.float64))
