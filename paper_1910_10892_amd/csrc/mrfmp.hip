@@ -1160,13 +1160,19 @@ hipError_t launch_bwd_split(const MrfBwdParams &P, long long blocks, size_t lds,
 // 1.87 ms with 8 / 16 / 32 lanes, TRWP 2.8 / 3.5 / 3.1 ms); two labels per lane are no faster than one (256 x 512, 16
 // labels, 16 directions 0.69 ms with 16 lanes, 0.77 with 8), and with four the V-gradient tables of eight scanlines
 // crowd LDS (32 labels, 16 directions 1.53 / 1.26 / 1.17 ms; without that gradient 16 lanes are ahead).
-int narrow_lanes(const MrfBwdParams &P, int L)
+// With several source arrays a lane's labels should be one access each: where they do not divide the label count, the
+// loads of a node cost more than the idle lanes of a wider segment (TRWP, K = 2, 5 x 512 x 512, 8 directions, 8 / 16 / 32
+// lanes: 20 labels 10.6 / 7.1 / 6.7 ms, 23 labels 10.8 / 9.9 / 7.2; 25 labels without grad V 12.5 / 9.1 / 6.7; 9 x 256 x 512,
+// 4 directions: 22 labels 2.63 / 2.08 / 2.21, 19 labels 2.54 / 2.49 / 2.41).
+int narrow_lanes(const MrfBwdParams &P, int L, int ns)
 {
     if (g_tune_narrow < 0 || P.g.N * L > MRF_BUF_MOST) return 0;
     if (g_tune_narrow == 8 || (g_tune_narrow == 16 && L > 8) || (g_tune_narrow == 32 && L > 16)) return g_tune_narrow;
     if (L <= 8) return 8;
     if (L <= 16) return 16;
-    return L <= 24 ? 8 : (P.gV ? 32 : 16);
+    if (L <= 24 && (ns == 1 || L % 3 == 0)) return 8;
+    if (ns > 1 && L % 2 != 0) return 32;
+    return L > 24 && P.gV ? 32 : 16;
 }
 
 #define MRF_GV_BLOCKS 256      // workgroups (and slots) of mrf_bwd_pairwise_*
@@ -1243,8 +1249,12 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // Few labels, one direction per launch (TRWP): the chain layout for one scanline per compute unit, two scanlines
     // around a chain wavefront beyond that, mrf_bwd_sweep_narrow for more than the machine holds that way.  (Backward
     // pass of 256 x 512 grids, 21 labels, 4 directions, K = 3, one / two / four images: 0.83 / 1.35 / 2.15 ms chain,
-    // 0.78 / 1.00 / 1.81 ms two scanlines, 2.1 ms narrow; 4 x 512 x 512: 3.4 ms two scanlines, 2.8 ms narrow.)
-    const long long pk_max = L <= 8 ? 1024 : 1536;
+    // 0.78 / 1.00 / 1.81 ms two scanlines, 2.1 ms narrow; 4 x 512 x 512: 3.4 ms two scanlines, 2.8 ms narrow.  The other label
+    // counts, two scanlines / narrow, K = 2: 7 x 256 x 256, 1,792 scanlines, 8 labels 0.95 / 0.59, 16 labels 0.97 / 0.73, 18
+    // labels 1.03 / 0.98, 32 labels 1.12 / 1.14.  17, 19 and 23 labels fill no segment: with up to four source arrays 1.59 /
+    // 1.80 at 1,640 scanlines, 2.03 / 2.19 at 2,048, 2.42 / 2.95 at 2,560, with eight 4.84 / 4.22 at 1,640)
+    const bool fills_none = L > 16 && L <= 24 && L % 2 != 0 && L % 3 != 0;
+    const long long pk_max = L <= 8 ? 1024 : (fills_none && ns == 4 ? 2560 : 1536);
     if (!generic && L <= 32 && P.r_count == 1 && ns <= 8 && g_tune_chain != 1 && g_tune_pack != 2 && g_tune_chain_pk != 1 &&
         (g_tune_chain_pk == 2 || (g_tune_chain != 2 && P.total_scanlines > 256 && P.total_scanlines <= pk_max)) &&
         !(gv_any && (P.total_scanlines + 1) / 2 > grad_slots(L))) {
@@ -1257,14 +1267,16 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // few labels: several scanlines per wavefront, once there are enough of them
     // (all directions in one launch, ISGMR, 1,536 scanlines: 0.47 against 0.56 ms for the chain with 16 labels, 0.63
     // against 0.74 with 32, but 0.66 against 0.59 with 21, where a lane's three labels make the node step long)
-    const long long chain_few = (P.r_count > 1 && L > 16 && L <= 24) ? 1536 : 1024;
+    // (without grad V the chain's helpers have less to do: 256 x 512, 4 directions, K = 2, 25 labels 0.38 against 0.40 ms, 31
+    // labels 0.38 against 0.43)
+    const long long chain_few = (P.r_count > 1 && L > 16 && (L <= 24 || !gv_any)) ? 1536 : 1024;
     if (!generic && L <= 32 && g_tune_pack != 1 && (g_tune_pack == 2 || P.total_scanlines >= 256) &&
         !(chain && g_tune_pack != 2 && (g_tune_chain == 2 || P.total_scanlines <= chain_few)))
     {
         // three scanlines per wavefront, one label per lane: on request only
         if (L > 16 && L <= 21 && g_tune_pack3 == 2)
             return run_bwd_packed(P, 21, ns, st);
-        const int seg = narrow_lanes(P, L);
+        const int seg = narrow_lanes(P, L, ns);
         if (seg > 0) return run_bwd_narrow(P, seg, ns, st);
         // arrays beyond 32-bit offsets: one label per lane, 64-bit addresses.  (Backward pass, ISGMR with grad V, eight
         // images, 2 directions, K = 1, N L = 1.08e9, against one wavefront per scanline: 20 / 58 ms with 8 labels, 15 / 31

@@ -458,6 +458,20 @@ def test_narrow_backward_with_several_wavefronts_per_workgroup(oracle, case):
         mrf.mrf_tune(3, 0)
 
 
+@pytest.mark.parametrize("L,B,want_V,kernel", [
+    (17, 1000, True, "chain_pk<4,"), (23, 1280, False, "chain_pk<4,"), (17, 1281, True, "narrow<32,1,4,"), (19, 1300, False, "narrow<32,1,4,"),
+    (20, 800, True, "narrow<16,2,4,"), (22, 800, False, "narrow<16,2,4,"), (21, 800, True, "narrow<8,3,4,"),
+    (25, 800, False, "narrow<32,1,4,"), (26, 800, False, "narrow<16,2,4,"), (26, 800, True, "narrow<32,1,4,")])
+def test_lanes_that_the_label_count_fills(oracle, L, B, want_V, kernel):
+    """TRWP launches of more than 1,536 scanlines with several source arrays: the segments whose lanes the label count
+    fills, two scanlines per workgroup to 2,560 scanlines where it fills none."""
+    import paper_1910_10892_amd as mrf
+    print("case lanes filled", L, B, want_V, flush=True)
+    pr = random_problem(810 + L, "trwp", B, 2, 3, L, DIRS4, 2, symmetric=False, rho=np.linspace(0.3, 0.9, 4))
+    full_check(oracle, pr, want_V=want_V)
+    assert mrf.mrf_last_sweep_launch(True).startswith("mrf_bwd_sweep_" + kernel), mrf.mrf_last_sweep_launch(True)
+
+
 MANY_SMALL_IMAGES = [
     # seed, algo, images, L: more workgroups of the narrow sweep than there are V-gradient slots (16,384)
     (791, "isgmr", 6600, 25), (792, "isgmr", 13200, 12), (793, "isgmr", 26400, 5),
