@@ -738,6 +738,7 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
             const auto cx = __builtin_amdgcn_permlane32_swap((unsigned)cid, (unsigned)cid, false, false);
             const float blo = __uint_as_float(bx[0]), bhi = __uint_as_float(bx[1]);
             const float tv = mrf_min(blo, bhi);
+            const float tp = mrf_min3(blo, bhi, 3.402823466e38f);       // what p looks for: no candidate if none is finite
             const int mu0 = bhi < blo ? LH + 8 * (int)cx[1] : 8 * (int)cx[0];
 
             // ---- minimum over the labels (Eq. isgmr-norm) ----
@@ -756,10 +757,10 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
             const int m4 = mu0 + 4 * hf;
             const float4 va = *reinterpret_cast<const float4 *>(&vt[lam * PT + m4]), hv = *reinterpret_cast<const float4 *>(&hrow[par][m4]);
             int pf = none;
-            pf = __builtin_fmaf(wgt, va.w, hv.w) == tv ? m4 + 3 : pf;
-            pf = __builtin_fmaf(wgt, va.z, hv.z) == tv ? m4 + 2 : pf;
-            pf = __builtin_fmaf(wgt, va.y, hv.y) == tv ? m4 + 1 : pf;
-            pf = __builtin_fmaf(wgt, va.x, hv.x) == tv ? m4 : pf;
+            pf = __builtin_fmaf(wgt, va.w, hv.w) == tp ? m4 + 3 : pf;
+            pf = __builtin_fmaf(wgt, va.z, hv.z) == tp ? m4 + 2 : pf;
+            pf = __builtin_fmaf(wgt, va.y, hv.y) == tp ? m4 + 1 : pf;
+            pf = __builtin_fmaf(wgt, va.x, hv.x) == tp ? m4 : pf;
             const auto px = __builtin_amdgcn_permlane32_swap((unsigned)pf, (unsigned)pf, false, false);
 
             // q of the node before (for the second node: of the first, whose q is 0 again)
@@ -767,7 +768,7 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
             ob += step_lb;
             on += step_n;
             store_f32(bmo, moff, ob, carry);
-            store_u8(bp, poff, ob >> 2, tv < INFINITY ? (int)min(px[0], px[1]) : none);
+            store_u8(bp, poff, ob >> 2, (int)min(px[0], px[1]));
         }
     };
 #pragma unroll
