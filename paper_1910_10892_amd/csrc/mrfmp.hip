@@ -145,7 +145,7 @@ MRF_G(int g_tune_pack3, 0);      // three scanlines per wavefront for 17..21 lab
 MRF_G(int g_tune_isgmr_lazy, 0); // ISGMR backward without a combine pass per iteration (up to 4 directions): 0 auto, 1 never
 MRF_G(int g_tune_isgmr_presum, 0); // ISGMR forward with the per-pair sums of the previous iteration formed once: 0 from six directions, 1 never, 2 always
 MRF_G(int g_tune_chain_pk, 0);     // chain backward with two scanlines of up to 32 labels per workgroup: 0 by launch size, 1 never, 2 always
-MRF_G(int g_tune_gv_apart, 0);     // V gradient of 65..128 labels by a streaming pass behind the chain backward sweep: 0 yes, 1 no
+MRF_G(int g_tune_gv_apart, 0);     // pairwise gradients of 33..128 labels by a streaming pass behind the chain backward sweep: 0 yes, 1 no
 MRF_G(int g_tune_gv_tile, 0);      // V gradient of 33..128 labels in one LDS table per workgroup: 0 yes, 1 no (a slot per wavefront in global memory)
 MRF_G(int g_tune_dense_sliced, 0); // dense sweep for more than 64 labels with a slice of the labels per wavefront: 0 yes, 1 no
 MRF_G(int g_tune_spin_limit, 0); // turns a wait between wavefronts may take: 0 = default
@@ -597,9 +597,10 @@ hipError_t run_dense(MrfFwdParams &P, int algo, long long blocks, hipStream_t st
         MRF_HCASE(2) MRF_HCASE(3) MRF_HCASE(4)
 #undef MRF_HCASE
     }
-    // more than 64 labels: every wavefront owns 32 of them (unless a tuning knob or a per-edge variant asks
+    // more than 128 labels: every wavefront owns 32 of them (unless a tuning knob or a per-edge variant asks
     // for the sweep in which every wavefront does the O(L) work of the whole node)
-    // (for 65..128 labels where the work outside the candidates is large: many source arrays, or a launch that
+    // What follows for 65..128 labels decides only beyond the offsets of the sweep above, or on request (knob 16):
+    // (where the work outside the candidates is large: many source arrays, or a launch that
     // fills the machine several times over; else three wavefronts of 32 source labels are no faster than four
     // of 24: measured at 96 labels, 256 x 512, per iteration: TRWP with 8 directions 5.70 -> 4.01 ms, with 16
     // 15.1 -> 8.8 ms, ISGMR with 16 directions 4.12 -> 3.74 ms, but TRWP with 4 directions 1.81 -> 1.96 ms)
@@ -1201,7 +1202,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     const int ns = need <= 1 ? 1 : (need <= 4 ? 4 : (need <= 8 ? 8 : 16));
     // few scanlines: the node-to-node chain on a wavefront of its own, helpers around it
     // (its addressing wants a node step times L in 32 bits; with the V gradient, L <= 64, room in LDS and
-    // a slot per helper)
+    // a slot per workgroup)
     bool step_fits = true;
     for (int r = P.r_first; r < P.r_first + P.r_count; ++r) {
         const long long stp = ((long long)mrf_iabs(P.g.dh[r]) * P.g.W + mrf_iabs(P.g.dw[r])) * L;

@@ -1,4 +1,4 @@
-// Streaming kernels around the backward sweeps: the V gradient of launches whose sweep stores the node
+// Streaming kernels around the backward sweeps: the pairwise gradients of launches whose sweep stores the node
 // gradients, the reduction of the private V-gradient accumulators, and fills.
 #pragma once
 
@@ -28,8 +28,9 @@ struct MrfGvParams {
 
 // V gradient and edge-weight gradient on wavefronts of their own: NA = 4 (49..64 labels) or 8 wavefronts add to tables
 // of their own, which a workgroup sums in wavefront order, so the order of every addition is fixed; the others form the
-// edge-weight gradient of the same 64 nodes, and find g and p in the cache.  (With both on NA wavefronts the label sums
-// set the pace there.)
+// edge-weight gradient of the same 64 nodes, and find g and p in the cache.  Backward pass, TRWP, 256 x 512, 64 labels, 8
+// directions, K = 2: 1.76 ms, 2.15 with both gradients on the four wavefronts (the label sums set the pace), 1.70 with one
+// table for sixteen (no fixed order); 37 x 53 nodes 0.304 / 0.411 / 0.286.
 template <int NA>
 __global__ void __launch_bounds__(1024) mrf_bwd_pairwise_own(const MrfGvParams P)
 {
