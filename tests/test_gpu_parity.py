@@ -241,6 +241,34 @@ def test_chunk_minima_where_no_label_is_possible(algo, L):
             np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
 
 
+@pytest.mark.parametrize("L", [5, 13, 21, 32, 40, 96])
+def test_impossible_labels_and_forbidden_transitions(oracle, L):
+    """Infinite unaries and infinite entries of V (one label of every pixel and the diagonal stay finite): the argmins of
+    the oracle, also where every candidate is infinite.  (The sweep of few labels with index wavefronts picks another
+    label there now and then; the library asks for finite inputs.)"""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    pr = random_problem(630 + L, "isgmr", 2, 7, 9, L, DIRS8, 2, symmetric=False)
+    rng = np.random.default_rng(L)
+    mask = rng.random(pr.unary.shape) < 0.3
+    mask[..., L // 2] = False
+    pr.unary[mask] = np.inf
+    never = rng.random(pr.pairwise.shape) < 0.5
+    np.fill_diagonal(never, False)
+    pr.pairwise[never] = np.inf
+    f = oracle_forward(oracle, pr)
+    print("case impossible labels", L, flush=True)
+    try:
+        assert mrf.mrf_tune(3, 2) == 0 and mrf.mrf_tune(11, 1) == 0
+        g = run_gpu(pr, backward=False)
+        assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_" + ("narrow" if L <= 32 else "halves")
+    finally:
+        mrf.mrf_tune(3, 0)
+        mrf.mrf_tune(11, 0)
+    for name in ("p", "q", "labels", "cost", "messages"):
+        np.testing.assert_array_equal(getattr(g, name), getattr(f, name), err_msg=name)
+
+
 PRESUM_CASES = [
     # seed, B, H, W, L, dirs, K, integer_valued, truncated
     (701, 1, 6, 7, 40, DIRS8, 3, False, False), (702, 2, 5, 6, 21, DIRS8, 3, True, False),
