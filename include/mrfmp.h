@@ -299,8 +299,8 @@ int mrf_set_sweep_events(void *start_event, void *stop_event);
  *           0 = for small problems (launch bound), 1 = never, 2 = always
  *   knob 16: dense forward sweep in which every wavefront owns 32 labels (loads, merge, normalisation and
  *           stores divided among the wavefronts) instead of doing that work for all labels (the layout knob 0
- *           tunes): 0 = for more than 128 labels (33..128 take the sweep with chunk minima), 1 = never, 2 = for more
- *           than 64 labels
+ *           tunes): 0 = by launch shape (33..128 labels: against the sweep with chunk minima too), 1 = never, 2 = for more
+ *           than 64 labels, 3 = as 0, but the sweep with chunk minima wherever it applies
  *   knob 17: ISGMR forward in which one streaming pass per iteration sums the unary and the previous
  *           iteration's messages once per pair of opposite directions, so that every sweep reads one array
  *           instead of R - 1: 0 = from six directions on, 1 = never, 2 = always (more than one iteration)

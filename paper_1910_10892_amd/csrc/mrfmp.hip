@@ -574,6 +574,31 @@ int pick_mch(int L, int LP, bool many_sources, long long blocks)
     return best;
 }
 
+// Whether mrf_fwd_sweep_halves is ahead of the better of the other two dense sweeps (33..128 labels; forward pass, K = 2,
+// others / halves).  Its barrier per node and its table in LDS cost more than they save where a launch neither reads
+// many arrays nor crowds the SIMDs, and up to 64 labels the other sweep has one or two wavefronts per SIMD to itself:
+// - up to 64 labels, TRWP: 128 x 128, 4 directions, 40 labels 0.68 / 0.74 ms, 64 labels 0.72 / 0.74; 8 directions 1.47 / 1.56;
+//   4 x 256 x 512, 4 directions 3.18 / 3.47, 8 directions 7.91 / 7.23; 2 x 300 x 300 (600 scanlines), 4 directions, 64 labels
+//   2.03 / 1.98
+// - up to 64 labels, ISGMR: 512 scanlines 0.20 / 0.22, 1,536 scanlines with 40 labels 0.74 / 0.85, with 64 0.97 / 0.86; 2,400
+//   scanlines 1.13 / 1.04; 6,144 scanlines 2.42 / 2.53
+// - 65..96 labels: ahead by 15 to 35 % (256 x 512, 96 labels, TRWP 2.9 / 2.2 with 4 directions, 5.5 / 3.9 with 8), but TRWP with 4
+//   directions and 65 labels 3.83 / 4.07 at 600 scanlines
+// - 97..128 labels: TRWP ahead by 10 to 20 %, ISGMR to 512 scanlines (128 x 128, 4 directions 12 %), behind beyond (128 x 128, 100
+//   labels, 8 directions 0.81 / 0.86, 16 directions 1.28 / 1.46); scanlines of 16 nodes do not pay for the table (0.22 / 0.24)
+bool chunk_minima_ahead(const MrfFwdParams &P, int algo, int rmax, long long blocks)
+{
+    const int L = P.g.L;
+    const bool middling = blocks > 512 && blocks < 1024;
+    if (L <= 64) {
+        if (rmax > 4) return blocks > 512;
+        if (algo == MRF_TRWP) return L > 48 && middling;
+        return blocks > (L > 48 ? 1024 : 2048) && blocks <= 3072;
+    }
+    if (L <= 96) return !(algo == MRF_TRWP && rmax <= 4 && L <= 72 && middling);
+    return (P.g.H > 32 || P.g.W > 32) && (algo == MRF_TRWP || blocks <= 512);
+}
+
 hipError_t run_dense(MrfFwdParams &P, int algo, long long blocks, hipStream_t st)
 {
     const bool generic = P.rho_e != nullptr;
@@ -583,11 +608,9 @@ hipError_t run_dense(MrfFwdParams &P, int algo, long long blocks, hipStream_t st
     for (int r = P.r_first; r < P.r_first + P.r_count; ++r)
         if (P.n_src[r] > max_src) max_src = P.n_src[r];
     const int rmax = (max_src + 1 <= 4) ? 4 : ((max_src + 1 <= 8) ? 8 : 16);
-    // 33..128 labels: chunk minima (any launch size, as far as its 32-bit offsets reach)
-    // (256 x 512, K = 2, against the better of the other two sweeps: 96 labels TRWP 3.6 -> 2.3 ms with 4 directions, 7.9 ->
-    // 4.7 with 8, ISGMR 2.1 -> 1.2; 64 labels 2.1 -> 1.8, 4.0 -> 3.3, 0.91 -> 0.69; 128 labels 4.0 -> 2.9, 8.2 -> 6.0, 2.3 ->
-    // 2.0; ahead at every size tried from 64 x 96 to 4 x 256 x 512)
-    if (L > 32 && L <= 128 && P.g.N * L * P.g.R <= MRF_BUF_MOST && !generic && !P.sgm_std && g_tune_mch == 0 && g_tune_dense_sliced == 0) {
+    // 33..128 labels: chunk minima where they are ahead, as far as the 32-bit offsets reach
+    const bool halves_fit = L > 32 && L <= 128 && P.g.N * L * P.g.R <= MRF_BUF_MOST && !generic && !P.sgm_std && g_tune_mch == 0;
+    if (halves_fit && (g_tune_dense_sliced == 3 || (g_tune_dense_sliced == 0 && chunk_minima_ahead(P, algo, rmax, blocks)))) {
         const int nw = (L + 31) / 32;
         P.NW = nw;
 #define MRF_HCASE(n) \
@@ -599,7 +622,7 @@ hipError_t run_dense(MrfFwdParams &P, int algo, long long blocks, hipStream_t st
     }
     // more than 128 labels: every wavefront owns 32 of them (unless a tuning knob or a per-edge variant asks
     // for the sweep in which every wavefront does the O(L) work of the whole node)
-    // What follows for 65..128 labels decides only beyond the offsets of the sweep above, or on request (knob 16):
+    // What follows for 65..128 labels decides where the sweep above is not taken, by its rule, its offsets or knob 16:
     // (where the work outside the candidates is large: many source arrays, or a launch that
     // fills the machine several times over; else three wavefronts of 32 source labels are no faster than four
     // of 24: measured at 96 labels, 256 x 512, per iteration: TRWP with 8 directions 5.70 -> 4.01 ms, with 16

@@ -198,6 +198,7 @@ def test_dense_sweep_with_chunk_minima(oracle, case):
         sign = np.where(np.random.default_rng(seed).random(pr.edge_weight.shape) > 0.2, 1.0, -0.5)
         pr.edge_weight = (pr.edge_weight * sign).astype(np.float32)
     try:
+        assert mrf.mrf_tune(16, 3) == 0
         a = full_check(oracle, pr, want_V=False)
         assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_halves", mrf.mrf_last_sweep_launch(False)
         assert mrf.mrf_tune(16, 1) == 0
@@ -229,6 +230,7 @@ def test_chunk_minima_where_no_label_is_possible(algo, L):
         else:
             pr.unary[:, 3, 4, :] = np.inf if kind == "infinite" else np.nan
         try:
+            assert mrf.mrf_tune(16, 3) == 0
             a = run_gpu(pr, backward=False)
             assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_halves", mrf.mrf_last_sweep_launch(False)
             assert mrf.mrf_tune(16, 1) == 0
@@ -259,14 +261,29 @@ def test_impossible_labels_and_forbidden_transitions(oracle, L):
     f = oracle_forward(oracle, pr)
     print("case impossible labels", L, flush=True)
     try:
-        assert mrf.mrf_tune(3, 2) == 0 and mrf.mrf_tune(11, 1) == 0
+        assert mrf.mrf_tune(3, 2) == 0 and mrf.mrf_tune(11, 1) == 0 and mrf.mrf_tune(16, 3) == 0
         g = run_gpu(pr, backward=False)
         assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_" + ("narrow" if L <= 32 else "halves")
     finally:
-        mrf.mrf_tune(3, 0)
-        mrf.mrf_tune(11, 0)
+        for knob in (3, 11, 16):
+            mrf.mrf_tune(knob, 0)
     for name in ("p", "q", "labels", "cost", "messages"):
         np.testing.assert_array_equal(getattr(g, name), getattr(f, name), err_msg=name)
+
+
+@pytest.mark.parametrize("algo,B,H,W,L,dirs,halves", [
+    ("trwp", 1, 40, 6, 64, DIRS4, False), ("trwp", 100, 6, 7, 49, DIRS4, True), ("trwp", 100, 6, 7, 48, DIRS4, False), ("trwp", 171, 6, 7, 64, DIRS4, False),
+    ("trwp", 100, 6, 7, 40, DIRS8, True), ("isgmr", 40, 6, 7, 64, DIRS4, True), ("isgmr", 40, 6, 7, 48, DIRS4, False), ("isgmr", 90, 6, 7, 48, DIRS4, True),
+    ("isgmr", 130, 6, 7, 64, DIRS4, False), ("trwp", 100, 6, 7, 72, DIRS4, False), ("trwp", 100, 6, 7, 73, DIRS4, True),
+    ("trwp", 1, 6, 33, 97, DIRS4, True), ("trwp", 1, 6, 32, 97, DIRS4, False), ("isgmr", 1, 40, 33, 128, DIRS4, True), ("isgmr", 10, 33, 6, 97, DIRS4, False)])
+def test_which_dense_sweep_runs(oracle, algo, B, H, W, L, dirs, halves):
+    """Both sides of each bound between the sweep with chunk minima and the two others, against the oracle."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    print("case which dense sweep", algo, B, H, W, L, len(dirs), flush=True)
+    pr = random_problem(640 + L, algo, B, H, W, L, dirs, 2, symmetric=False, rho=np.linspace(0.3, 0.9, len(dirs)))
+    check_forward(run_gpu(pr, backward=False), oracle_forward(oracle, pr))
+    assert (mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_halves") == halves, mrf.mrf_last_sweep_launch(False)
 
 
 PRESUM_CASES = [
