@@ -582,7 +582,7 @@ int pick_mch(int L, int LP, bool many_sources, long long blocks)
 //   2.03 / 1.98
 // - up to 64 labels, ISGMR: 512 scanlines 0.20 / 0.22, 1,536 scanlines with 40 labels 0.74 / 0.85, with 64 0.97 / 0.86; 2,400
 //   scanlines 1.13 / 1.04; 6,144 scanlines 2.42 / 2.53
-// - 65..96 labels: ahead by 15 to 35 % (256 x 512, 96 labels, TRWP 2.9 / 2.2 with 4 directions, 5.5 / 3.9 with 8), but TRWP with 4
+// - 65..96 labels: ahead by 15 to 35 % (256 x 512, 96 labels, TRWP 3.57 / 2.73 with 4 directions, 7.93 / 5.64 with 8), but TRWP with 4
 //   directions and 65 labels 3.83 / 4.07 at 600 scanlines
 // - 97..128 labels: TRWP ahead by 10 to 20 %, ISGMR to 512 scanlines (128 x 128, 4 directions 12 %), behind beyond (128 x 128, 100
 //   labels, 8 directions 0.81 / 0.86, 16 directions 1.28 / 1.46); scanlines of 16 nodes do not pay for the table (0.22 / 0.24)
