@@ -660,7 +660,7 @@ hipError_t run_dense(MrfFwdParams &P, int algo, long long blocks, hipStream_t st
 #endif  // MRF_HAS_FWD_DENSE
 
 #if MRF_HAS_FWD
-// pairwise potentials per edge (L <= 64): the table is fetched in two halves of ceil(L/2) rows
+// pairwise potentials per edge (L <= 64): more than 32 labels fetch the table in two halves of ceil(L/2) rows
 // (rounded up to a multiple of four)
 hipError_t launch_edge(const MrfFwdParams &P, int algo, long long blocks, hipStream_t st)
 {
@@ -669,9 +669,24 @@ hipError_t launch_edge(const MrfFwdParams &P, int algo, long long blocks, hipStr
         if (P.n_src[r] > ms) ms = P.n_src[r];
     const int rmax = (ms + 1 <= 4) ? 4 : ((ms + 1 <= 8) ? 8 : 16);
     const int L = P.g.L;
+    const dim3 grid((unsigned)blocks), block(64);
+    // up to 32 labels: the lanes in groups that share the source labels
+    if (L <= 32) {
+        const int seg = L <= 16 ? 16 : 32, rows = L <= 8 ? 2 : (L <= 16 ? 4 : (L <= 24 ? 12 : 16));
+        note_launch(0, "mrf_fwd_sweep_edge_groups", blocks, 64, "%d,%d,%d,%s", seg, rows, rmax, algo == MRF_TRWP ? "true" : "false");
+#define MRF_E(sg, hr, rm) \
+        if (seg == sg && rows == hr && rmax == rm) { \
+            if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_edge_groups<sg, hr, rm, true>), grid, block, 0, st, P); \
+            else hipLaunchKernelGGL((mrf_fwd_sweep_edge_groups<sg, hr, rm, false>), grid, block, 0, st, P); \
+            return hipGetLastError(); \
+        }
+#define MRF_EH(sg, hr) MRF_E(sg, hr, 4) MRF_E(sg, hr, 8) MRF_E(sg, hr, 16)
+        MRF_EH(16, 2) MRF_EH(16, 4) MRF_EH(32, 12) MRF_EH(32, 16)
+#undef MRF_EH
+#undef MRF_E
+    }
     note_launch(0, "mrf_fwd_sweep_edge", blocks, 64, "%d,%d,%s", (L + 7) / 8 * 4, rmax, algo == MRF_TRWP ? "true" : "false");
     if (L > 64) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(64);
 #define MRF_E(half, rm) \
     if (L <= 2 * half && rmax == rm) { \
         if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_edge<half, rm, true>), grid, block, 0, st, P); \
@@ -679,7 +694,7 @@ hipError_t launch_edge(const MrfFwdParams &P, int algo, long long blocks, hipStr
         return hipGetLastError(); \
     }
 #define MRF_EH(half) MRF_E(half, 4) MRF_E(half, 8) MRF_E(half, 16)
-    MRF_EH(4) MRF_EH(8) MRF_EH(12) MRF_EH(16) MRF_EH(20) MRF_EH(24) MRF_EH(28) MRF_EH(32)
+    MRF_EH(20) MRF_EH(24) MRF_EH(28) MRF_EH(32)
 #undef MRF_EH
 #undef MRF_E
     return hipErrorInvalidValue;

@@ -21,7 +21,8 @@
 //   mrf_fwd_sweep_halves        dense, 33..128 labels: chunk minima, argmin by a second look at the winning chunk
 //   mrf_fwd_sweep_narrow        dense, L <= 32: several scanlines of one direction per wavefront, argmin in two levels
 //   mrf_fwd_sweep_packed        the same for launches of few scanlines, with index wavefronts; scanlines of any direction
-//   mrf_fwd_sweep_edge          pairwise potentials given per edge (L <= 64)
+//   mrf_fwd_sweep_edge          pairwise potentials given per edge, 33..64 labels
+//   mrf_fwd_sweep_edge_groups   the same for up to 32 labels, groups of lanes sharing the source labels
 //   mrf_aggregate               final costs and labels
 //   mrf_fwd_sweep_window        truncated models: window of 2 TW - 1 source labels per label
 //   mrf_fwd_sweep_window_duo    the same with the dependency chain (values) on one wavefront and
@@ -797,9 +798,9 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
 //
 // theta_{i-r,i}(mu,lambda) read from a table of its own per edge, [R][N][L][L] with entry
 // (r, i) the edge that arrives at node i (Eq. isgmr / Eq. trwp as written, before the
-// decomposition into edge weight times V); for L <= 64.  One wavefront per scanline, lanes
+// decomposition into edge weight times V); for 33..64 labels.  One wavefront per scanline, lanes
 // over lambda.  Row mu of a node's table is one coalesced load of L floats; the table is
-// fetched in two halves of HALF = 4, 8, ..., 32 rows into two register sets, each reloaded
+// fetched in two halves of HALF = 20, 24, 28 or 32 rows into two register sets, each reloaded
 // for the next node as soon as the current node is done with it, so that one half is always
 // in flight behind the evaluation of the other.  h(mu) comes from the lane that owns mu
 // (v_readlane with a constant lane).  The candidate is the plain sum h(mu) + theta(mu,lambda).
@@ -934,6 +935,185 @@ mrf_fwd_sweep_edge(const MrfFwdParams P)
         rcur = rnxt;
 #pragma unroll
         for (int c = 0; c < RMAX; ++c) cur[c] = nxt[c];
+    }
+}
+
+// ---- the same for up to 32 labels ---------------------------------------------------------------
+//
+// Bound by the bytes of the tables (4 L^2 per node and direction) as long as enough of them are in flight: a launch has
+// a wavefront per scanline only, so a wavefront has to keep several nodes' tables on the way, and the counter of loads
+// in flight ends at 63.  Rows of one label per lane would leave half of the lanes idle and spend a load on each source
+// label.  Here NG = 64 / SEG groups of SEG lanes (16 up to 16 labels, else 32) hold the same destination labels and
+// group k the source labels k HR .. k HR + HR - 1: a load brings NG rows, a node takes HR table loads, and D nodes
+// are in flight.  Every group forms all of h (same loads, same operations) and keeps it in LDS; a lane reads its group's
+// HR entries, finds their lowest argmin, and one or two lane swaps join the groups, the lower one first on a tie.
+// All addresses of a node are scalar bases; table rows beyond L read as 0 through the view of the node's table and meet
+// h = +inf.  256 x 256, 21 labels, 4 directions: ISGMR sweep 273 -> 155 us (462 MB of tables).
+template <int SEG, int HR, int RMAX, bool TRWP>
+__global__ void __launch_bounds__(64)
+mrf_fwd_sweep_edge_groups(const MrfFwdParams P)
+{
+    constexpr int NG = 64 / SEG;
+    constexpr int HP = (HR + 3) / 4 * 4;                // LDS row of a group, 16-byte aligned
+    // nodes in flight: their loads, and the stores of the nodes between, within the counter's 63
+    constexpr int D0 = 1 + 63 / (HR + RMAX + 4), D = D0 > 6 ? 6 : D0;
+    static_assert(NG == 2 || NG == 4, "lane groups");
+    __shared__ __align__(16) float hrow[NG * HP + 4];       // (the last entry: for lanes without a label to scribble in)
+    const int L = P.g.L;
+    const int lane = threadIdx.x & 63;
+    const int lam = lane % SEG, grp = lane / SEG;
+    const bool valid = lam < L;
+    const unsigned lamc = valid ? (unsigned)lam : 0u;
+
+    const long long blk = blockIdx.x;
+    const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
+    const int r = P.r_first + ri;
+    const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
+    const unsigned nsc = (unsigned)P.g.nscan[r];
+    const int b = __builtin_amdgcn_readfirstlane((int)(local / nsc));
+    const unsigned t = local - (unsigned)b * nsc;
+    const int dh = P.g.dh[r], dw = P.g.dw[r];
+    int y0, x0, len;
+    mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
+    y0 = __builtin_amdgcn_readfirstlane(y0);              // uniform, and known to be
+    x0 = __builtin_amdgcn_readfirstlane(x0);
+    len = __builtin_amdgcn_readfirstlane(len);
+    const long long N = P.g.N;
+    const long long head = ((long long)b * P.g.H + y0) * P.g.W + x0;
+    const long long nstep = (long long)dh * P.g.W + dw;
+    const float rho = P.rho[r];
+    const int n_pre = P.n_pre[r], n_src = P.n_src[r], rm_slot = P.rm_slot[r];
+
+    // sources of h as in mrf_fwd_sweep: unused slots read the unary with factor 0
+    const float *src[RMAX];
+    float use[RMAX], carry_at[RMAX + 1], is_rm[RMAX];
+    src[0] = P.unary + (size_t)P.unary_slab[r] * N * L;
+    use[0] = 1.0f;
+    is_rm[0] = 0.0f;
+#pragma unroll
+    for (int c = 1; c < RMAX; ++c) {
+        src[c] = (c <= n_src) ? P.m_in + (size_t)P.src_dir[r][c - 1] * N * L : src[0];
+        use[c] = (c <= n_src) ? 1.0f : 0.0f;
+        is_rm[c] = (c - 1 == rm_slot) ? 1.0f : 0.0f;
+    }
+#pragma unroll
+    for (int c = 1; c <= RMAX; ++c) carry_at[c] = (c == n_pre + 1) ? 1.0f : 0.0f;
+
+    // (a node's vectors are views of their own: lanes without a label, and the other groups', store nothing)
+    const unsigned st4 = grp == 0 && valid ? (unsigned)lam << 2 : MRF_BUF_NONE, st1 = grp == 0 && valid ? (unsigned)lam : MRF_BUF_NONE;
+    const unsigned stq = lane == 0 ? 0u : MRF_BUF_NONE;
+    auto store = [&](long long i, float m, int arg, int q) {
+        mrf_buf_store_f32(mrf_buffer(P.m_out + ((size_t)r * N + i) * L, (size_t)L * 4), st4, m);
+        mrf_buf_store_u8(mrf_buffer(P.p + ((size_t)r * N + i) * L, (size_t)L), st1, arg);
+        mrf_buf_store_u8(mrf_buffer(P.q + (size_t)r * N + i, 1), stq, q);
+    };
+    store(head, 0.0f, 0, 0);
+    if (len < 2) return;
+
+    for (int e = lane; e < NG * HP; e += 64) hrow[e] = INFINITY;       // entries without a source label stay +inf
+    const int hslot = valid ? (lam / HR) * HP + lam % HR : NG * HP;
+    mrf_wave_lds_fence();
+
+    const int vzero = mrf_opaque_zero();
+    // (without a rho per edge the load takes any word: no branch around a load that is prefetched)
+    const bool per_edge = TRWP && P.rho_e;
+    const float *rbase = per_edge ? P.rho_e + (size_t)r * N : P.unary;
+    const float *tbase = P.Te + (size_t)r * N * L * L;
+    const unsigned tsize = (unsigned)(L * L) * 4u;
+    const unsigned toff = valid ? (unsigned)(grp * HR * L + lam) * 4u : MRF_BUF_NONE;
+    struct In {
+        float t[HR], v[RMAX];
+        float rho;
+    };
+    In in[D];
+    // inputs of the update of node n: its edge's table, the vectors of node n - 1 (past the end: the last node again)
+    auto prefetch = [&](In &x, int n) {
+        n = n < len ? n : len - 1;
+        const long long i = head + (long long)n * nstep, j = i - nstep;
+        const mrf_buf tb = mrf_buffer(tbase + (size_t)i * L * L, tsize);
+#pragma unroll
+        for (int m = 0; m < HR; ++m) x.t[m] = mrf_buf_f32s(tb, toff, (unsigned)(m * L) * 4u);
+#pragma unroll
+        for (int c = 0; c < RMAX; ++c) x.v[c] = (src[c] + (size_t)j * L)[lamc];
+        x.rho = TRWP ? rbase[(size_t)i + vzero] : 1.0f;
+    };
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+        prefetch(in[u], 1 + u);
+        // (dropped stores: what is in flight at the loop's entry then looks like what is when it comes round)
+        for (int x = 0; x < 3; ++x) mrf_buf_store_u8(mrf_buffer(P.q, 1), MRF_BUF_NONE, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    float carry = 0.0f;
+    for (int n0 = 1; n0 < len; n0 += D) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            const int n = n0 + u;
+            float v = in[u].v[0];
+            if (TRWP) {
+                float mrm = 0.0f;
+#pragma unroll
+                for (int c = 1; c < RMAX; ++c) {
+                    v = __builtin_fmaf(carry_at[c], carry, v);
+                    v = __builtin_fmaf(use[c], in[u].v[c], v);
+                    mrm = __builtin_fmaf(is_rm[c], in[u].v[c], mrm);
+                }
+                v = __builtin_fmaf(carry_at[RMAX], carry, v);
+                v = (per_edge ? in[u].rho : rho) * v;
+                v = v - mrm;
+            } else {
+#pragma unroll
+                for (int c = 1; c < RMAX; ++c) v = __builtin_fmaf(use[c], in[u].v[c], v);
+                v = v + carry;
+            }
+            // (the groups write the same values to the same places)
+            hrow[hslot] = v;
+            mrf_wave_lds_fence();
+            float d[HP];
+#pragma unroll
+            for (int m4 = 0; m4 < HP; m4 += 4) {
+                const float4 hv = *reinterpret_cast<const float4 *>(&hrow[grp * HP + m4]);
+                const float hq[4] = { hv.x, hv.y, hv.z, hv.w };
+#pragma unroll
+                for (int c = 0; c < 4; ++c) d[m4 + c] = m4 + c < HR ? hq[c] + in[u].t[m4 + c < HR ? m4 + c : 0] : INFINITY;
+            }
+            mrf_wave_lds_fence();
+            float best = mrf_min(d[0], d[1]);
+#pragma unroll
+            for (int m = 2; m + 1 < HP; m += 2) best = mrf_min3(best, d[m], d[m + 1]);
+            int arg = 0;
+            mrf_static_for<HP / 4>([&](auto g4) {
+                constexpr int m0 = HP - 4 - 4 * decltype(g4)::value;      // from the top down: the lowest index lands last
+                mrf_first_equal4<m0>(arg, best, d[m0], d[m0 + 1], d[m0 + 2], d[m0 + 3]);
+            });
+            arg += grp * HR;
+            // join the groups: a strict '<' keeps the lower group's index on a tie
+            const auto join = [&](auto b2, auto a2) {
+                const float lo = __builtin_bit_cast(float, (unsigned)b2[0]), hi = __builtin_bit_cast(float, (unsigned)b2[1]);
+                arg = hi < lo ? (int)a2[1] : (int)a2[0];
+                best = mrf_min(lo, hi);
+            };
+            if constexpr (NG == 4) {
+                const unsigned ub = __builtin_bit_cast(unsigned, best);
+                join(__builtin_amdgcn_permlane16_swap(ub, ub, false, false), __builtin_amdgcn_permlane16_swap((unsigned)arg, (unsigned)arg, false, false));
+            }
+            {
+                const unsigned ub = __builtin_bit_cast(unsigned, best);
+                join(__builtin_amdgcn_permlane32_swap(ub, ub, false, false), __builtin_amdgcn_permlane32_swap((unsigned)arg, (unsigned)arg, false, false));
+            }
+            const float tv = valid ? best : INFINITY;
+            const float tq = mrf_wave_min(tv);                            // (every group holds every label)
+            const unsigned long long bal = __ballot(tv == tq);
+            const int qidx = __ffsll((long long)bal) - 1;
+            carry = tv - tq;
+            const bool act = n < len;
+            const long long i = head + (long long)(act ? n : 0) * nstep;
+            store(i, act ? carry : 0.0f, act ? arg : 0, act ? qidx : 0);  // (past the end: the first node's zeros again)
+            __builtin_amdgcn_sched_barrier(0);          // (a node's loads stay together: what is in flight is countable)
+            prefetch(in[u], n + D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
 }
 

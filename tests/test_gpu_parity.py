@@ -1510,6 +1510,27 @@ def test_pairwise_potentials_given_per_edge(oracle, case):
         check(True)
 
 
+# label counts around the sizes of the lane groups and of their shares of the source labels; 4, 8 and 16 directions (up to
+# 3, 7 and 15 source arrays); scanlines of 1 to 29 nodes (prefetches past the end)
+@pytest.mark.parametrize("case", [(L, R, algo) for L in (2, 7, 8, 9, 13, 16, 17, 20, 24, 25, 29, 32, 33)
+                                  for R, algo in ((4, "isgmr"), (4, "trwp"), (8, "trwp"), (16, "trwp"), (16, "isgmr"))
+                                  if R == 4 or L in (8, 16, 24, 32)], ids=lambda c: "%d_%d_%s" % c)
+def test_per_edge_tables_in_lane_groups(oracle, case):
+    """mrf_fwd_sweep_edge_groups: bit for bit the oracle's messages, indices and costs; integer data, so that ties cross the groups."""
+    from gpu_harness import run_gpu
+    print("case lane groups", case, flush=True)
+    L, R, algo = case
+    B, H, W = (2, 3, 29) if R == 4 else (1, 7, 13)
+    dirs = (DIRS16 if R == 16 else DIRS8 if R == 8 else DIRS4)
+    for iv in (False, True):
+        pr = random_problem(700 + L, algo, B, H, W, L, dirs, 2, integer_valued=iv, per_edge=False, rho=np.linspace(0.3, 0.9, R))
+        rng = np.random.default_rng(9000 + L)
+        Te = rng.integers(0, 3, (R, B, H, W, L, L)) if iv else rng.random((R, B, H, W, L, L))
+        pr.pairwise_edge = Te.astype(np.float32)
+        g = run_gpu(pr, want_V=False)
+        check_forward(g, oracle.forward(pr.algo, pr.unary, None, pr.dirs, pr.K, rho=pr.rho, pairwise_edge=pr.pairwise_edge))
+
+
 def test_per_edge_tables_argument_errors():
     import torch
     import paper_1910_10892_amd as mrf
