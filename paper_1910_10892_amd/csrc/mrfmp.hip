@@ -125,6 +125,15 @@ inline size_t gstore_bytes(const mrf_problem *pr, int algo)
     return any ? align_up((size_t)pr->B * pr->H * pr->W * pr->L * sizeof(double)) : 0;
 }
 
+// Room for the node gradients that mrf_bwd_edge_tables adds up (per-edge tables): those of all iterations, but no more
+// than half of what the tables themselves take.  (A call with less room takes what there is, run_backward.)
+inline size_t edge_slab_bytes(const mrf_problem *pr) { return (size_t)pr->R * pr->B * pr->H * pr->W * pr->L * sizeof(float); }
+inline size_t edge_grad_bytes(const mrf_problem *pr)
+{
+    const int most = pr->L / 2 > 1 ? pr->L / 2 : 1;
+    return align_up((size_t)(pr->K < most ? pr->K : most) * edge_slab_bytes(pr));
+}
+
 // ---- process-global state: defined in the translation unit of the entry points ----------
 // tuning knobs (0 = heuristic)
 #if MRF_HAS_API
@@ -928,7 +937,7 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
 {
     const dim3 grid((unsigned)P.total_scanlines);
     const bool gv = P.gV != nullptr;
-    const bool gs = LP <= 2 && P.gstore != nullptr;       // the helpers store the node gradients (no tables, no V)
+    const bool gs = LP <= 2 && (P.gstore || P.gstore32);  // the helpers store the node gradients (no tables, no V)
     if (gs) vg = true;
     const bool hot = P.hot_label && (gs || !((LP == 1 && gv) || vg));
     note_launch(1, "mrf_bwd_sweep_chain", P.total_scanlines, 64 * (1 + ni), "%d,%d,%d,%d,%s,%s,%s", LP, NS, D, ni,
@@ -1119,7 +1128,12 @@ hipError_t launch_bwd_narrow(MrfBwdParams &P, int ns, long long packs, hipStream
             P.pack_first = (int)(first * waves); \
             note_launch(1, "mrf_bwd_sweep_narrow", grid.x, 64 * waves, "%d,%d,%d,%d,%s,%s,%s", SEG, NL, n, d, un ? "true" : "false", \
                         gv ? "true" : "false", full ? "true" : "false"); \
-            if (gv && full) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, true, true>), grid, block, lds, st, P); \
+            if (P.edge) { \
+                if constexpr (NL == 1 || (SEG == 8 && NL == 3)) { \
+                    if (full) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, false, true, true>), grid, block, lds, st, P); \
+                    else return hipErrorInvalidValue; \
+                } else return hipErrorInvalidValue; \
+            } else if (gv && full) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, true, true>), grid, block, lds, st, P); \
             else if (gv) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, true, NL == 1>), grid, block, lds, st, P); \
             else if (full) hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, false, true>), grid, block, lds, st, P); \
             else hipLaunchKernelGGL((mrf_bwd_sweep_narrow<SEG, NL, n, d, un, false, NL == 1>), grid, block, lds, st, P); \
@@ -1238,6 +1252,14 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     for (int r = P.r_first; r < P.r_first + P.r_count; ++r)
         if (P.n_src[r] + (P.use_gc ? 1 : 0) > need) need = P.n_src[r] + (P.use_gc ? 1 : 0);
     const int ns = need <= 1 ? 1 : (need <= 4 ? 4 : (need <= 8 ? 8 : 16));
+    // per-edge tables without a V: the chain layout, or for up to 32 labels and more scanlines the narrow one; either
+    // stores the node gradients if they are wanted (run_backward has checked that one of them fits)
+    if (P.edge) {
+        P.hot_label = 0;
+        if (L <= 32 && P.total_scanlines > 1024) return run_bwd_narrow(P, L <= 8 || (L <= 24 && L % 3 == 0 && L > 16) ? 8 : (L <= 16 ? 16 : 32), ns, st);
+        const int ni = P.total_scanlines <= 256 ? 12 : (P.total_scanlines <= 512 ? 8 : (P.total_scanlines <= 1024 ? 6 : 4));
+        return run_bwd_chain(P, ns, ni, true, st);
+    }
     // few scanlines: the node-to-node chain on a wavefront of its own, helpers around it
     // (its addressing wants a node step times L in 32 bits; with the V gradient, L <= 64, room in LDS and
     // a slot per workgroup)
@@ -1401,6 +1423,24 @@ hipError_t fill(float *dst, long long n, float v, hipStream_t st)
     return hipGetLastError();
 }
 
+hipError_t launch_edge_tables(const mrf_problem *pr, float *gE, const float *g, const uint8_t *p, int count, bool accumulate, hipStream_t st)
+{
+    MrfEdgeGradParams E;
+    E.L = pr->L;
+    E.tables = (long long)pr->R * pr->B * pr->H * pr->W;
+    // 32 KB of tables per workgroup, so that five of them share a compute unit and their phases overlap; a multiple of
+    // four tables where L L is odd, which keeps every range on a 16-byte boundary
+    const int LL = E.L * E.L, unit = LL % 4 ? 4 : 1, fit = 8192 / LL / unit * unit;
+    E.T = fit > unit ? fit : unit;
+    E.count = count; E.g = g; E.p = p; E.p_step = E.tables * E.L; E.gE = gE; E.accumulate = accumulate ? 1 : 0;
+    const long long turns = (E.tables + E.T - 1) / E.T;
+    const dim3 grid((unsigned)(turns < 1280 ? turns : 1280)), block(256);
+    const size_t lds = sizeof(float) * (size_t)E.T * LL;
+    if ((uintptr_t)gE % 16 == 0) hipLaunchKernelGGL(mrf_bwd_edge_tables<true>, grid, block, lds, st, E);
+    else hipLaunchKernelGGL(mrf_bwd_edge_tables<false>, grid, block, lds, st, E);
+    return hipGetLastError();
+}
+
 // Slots that the sweeps of a backward call can add to: a layout has at most one per scanline of a launch (the
 // last workgroup of mrf_bwd_sweep may hold up to three wavefronts without one), mrf_bwd_pairwise_* one per workgroup.
 long long slots_in_use(const mrf_problem *pr, const MrfGeom &g, int algo)
@@ -1428,7 +1468,8 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     // edge weights to differentiate
     const bool edge_tables = pr->pairwise_edge != nullptr;
     if (edge_tables && grad_w) return MRF_ERR_BAD_PAIRWISE_KIND;
-    const size_t need = mrf_workspace_bytes(pr, algo, 1);
+    // (mrf_workspace_bytes asks for more where there are per-edge tables: speed, not a condition)
+    const size_t need = kAlign + (algo == MRF_ISGMR ? 2 : 1) * msg_bytes(pr) + gradv_bytes(pr) + gstore_bytes(pr, algo);
     if (!workspace) return MRF_ERR_NULL_POINTER;
     if (workspace_bytes < need) return MRF_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t st = (hipStream_t)hip_stream;
@@ -1473,8 +1514,31 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
         const hipError_t e_ = hipGetLastError();
         if (e_ != hipSuccess) return hip_fail(e_, "mrf_bwd_clear");
     }
-    P.force_plain = edge_tables ? 1 : 0;
-    if (edge_tables && grad_V) {
+    // Per-edge tables: the sweeps store the node gradients of as many iterations as the workspace has room for, and
+    // mrf_bwd_edge_tables forms the tables' gradient from them.  mrf_bwd_sweep, which adds to the tables itself, keeps TRW
+    // coefficients per edge, arrays beyond the 32-bit offsets of the sweeps that store, and launches of more than 2,560
+    // scanlines of 33..64 labels.
+    long long most = 0, all = 0;
+    for (int r = 0; r < R; ++r) {
+        const long long n = (long long)pr->B * P.g.nscan[r];
+        all += n;
+        if (n > most) most = n;
+    }
+    const long long room = (long long)((workspace_bytes - (size_t)((char *)gvslots - ws)) / edge_slab_bytes(pr));
+    const int slabs = (int)(room < K ? room : K);
+    P.edge = edge_tables && !P.rho_e && NL <= MRF_BUF_MOST && (!grad_V || slabs > 0) &&
+             (L <= 32 || (algo == MRF_ISGMR ? all : most) <= 2560) && g_tune_chain != 1 && g_tune_narrow >= 0;
+    float *const edge_g = (float *)gvslots;
+    // behind the sweeps of iteration k; P.gstore32 holds where the next iteration's go
+    const auto edge_pass = [&](int k) -> hipError_t {
+        if (!P.edge || !grad_V) return hipSuccess;
+        const int done = (K - 1 - k) % slabs + 1;        // iterations stored since the last pass
+        P.gstore32 = edge_g + (size_t)(done % slabs) * R * NL;
+        return done == slabs || k == 0 ? launch_edge_tables(pr, grad_V, edge_g, p + (size_t)(k + done - 1) * pk, done, K - 1 - k >= slabs, st) : hipSuccess;
+    };
+    if (P.edge && grad_V) P.gstore32 = edge_g;
+    P.force_plain = edge_tables && !P.edge ? 1 : 0;
+    if (edge_tables && grad_V && !P.edge) {
         P.gE = grad_V;
         { const hipError_t e_ = fill(grad_V, (long long)R * N * L * L, 0.0f, st); if (e_ != hipSuccess) return hip_fail(e_, "fill"); }
     }
@@ -1545,6 +1609,7 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
             P.p = p + (size_t)k * pk;
             P.q = q + (size_t)k * qk;
             { const hipError_t e_ = dispatch_bwd(P, pr->pairwise_kind, st); if (e_ != hipSuccess) return hip_fail(e_, "dispatch_bwd"); }
+            { const hipError_t e_ = edge_pass(k); if (e_ != hipSuccess) return hip_fail(e_, "mrf_bwd_edge_tables"); }
             if (k == 0) {
                 C.S = s_cur; C.first = 0; C.ghat = nullptr; C.skip_dir = 0;
                 const dim3 cg((unsigned)(cvec ? cblocks4 : cblocks)), cb(256);
@@ -1561,6 +1626,7 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
             P.p = p + (size_t)k * pk;
             P.q = q + (size_t)k * qk;
             { const hipError_t e_ = dispatch_bwd(P, pr->pairwise_kind, st); if (e_ != hipSuccess) return hip_fail(e_, "dispatch_bwd"); }
+            { const hipError_t e_ = edge_pass(k); if (e_ != hipSuccess) return hip_fail(e_, "mrf_bwd_edge_tables"); }
             C.first = (k == K - 1);
             C.ghat = (k > 0) ? buf0 : nullptr;
             const dim3 cg((unsigned)(cvec ? cblocks4 : cblocks)), cb(256);
@@ -1601,6 +1667,7 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
                 P.q = q + (size_t)k * qk;
                 { const hipError_t e_ = dispatch_bwd(P, pr->pairwise_kind, st); if (e_ != hipSuccess) return hip_fail(e_, "dispatch_bwd"); }
             }
+            { const hipError_t e_ = edge_pass(k); if (e_ != hipSuccess) return hip_fail(e_, "mrf_bwd_edge_tables"); }
         }
     }
     mark(g_ev_stop, st);
@@ -1641,7 +1708,9 @@ size_t mrf_workspace_bytes(const mrf_problem *prob, int algo, int backward)
 {
     if (check_problem(prob, algo, false) != MRF_OK) return 0;
     if (!backward) return kAlign + (algo == MRF_ISGMR ? 2 : 1) * msg_bytes(prob);
-    return kAlign + (algo == MRF_ISGMR ? 2 : 1) * msg_bytes(prob) + gradv_bytes(prob) + gstore_bytes(prob, algo);
+    size_t grads = gradv_bytes(prob) + gstore_bytes(prob, algo);
+    if (prob->pairwise_edge && !(algo == MRF_TRWP && prob->rho_edge) && edge_grad_bytes(prob) > grads) grads = edge_grad_bytes(prob);
+    return kAlign + (algo == MRF_ISGMR ? 2 : 1) * msg_bytes(prob) + grads;
 }
 
 int mrf_validate(const mrf_problem *prob, int algo) { return check_problem(prob, algo, true); }

@@ -81,6 +81,9 @@ struct MrfBwdParams {
     double *gstore;                        // mrf_bwd_sweep_chain: if not NULL, its helpers store the gradient vector g of
                                            // every node here (0 where no update is replayed) for mrf_bwd_pairwise_*,
                                            // which forms both pairwise gradients from it
+    float *gstore32;                       // [R][N][L] the same in float for the gradient of per-edge tables (mrf_bwd_edge_tables)
+    int edge;                              // a problem with per-edge tables whose sweeps leave their gradient to that pass:
+                                           // no V, no edge-weight gradient
     int *fault;                            // launch-wide word raised when a wait between wavefronts is given up (mrf_wait_turn)
     int spin_limit;                        // microseconds after which a wait is given up
 };
@@ -485,7 +488,7 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
 // accumulator of its own in LDS, lane lambda owning column lambda; their sum goes to the workgroup's slot at the end.
 // GV with VG (33..128 labels): there is no room for the tables; the helpers store the gradient vector g of every node
 // in P.gstore (0 where no update is replayed) and leave both pairwise gradients to mrf_bwd_pairwise_*, a streaming
-// pass that has all of LDS for V and the table.  What is left for a helper is short enough that four of them keep
+// pass that has all of LDS for V and the table (P.gstore32: the same for mrf_bwd_edge_tables).  What is left for a helper is short enough that four of them keep
 // up with the chain, so the layout stays ahead to 1,536 scanlines per launch (it did to 512 while the helpers
 // gathered from V).
 // HOT: truncated models send most labels to one source label, and the chain wavefront's LDS
@@ -725,7 +728,8 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
     float *guw = P.gunary + (size_t)head * L;                       // stores of stage "post"
     float *sw = P.S + ((size_t)r * N + head) * L;
     float *gww = P.gw ? P.gw + (size_t)r * N + head : nullptr;
-    double *gsw = GS ? P.gstore + (size_t)head * L : nullptr;
+    double *gsw = GS && P.gstore ? P.gstore + (size_t)head * L : nullptr;
+    float *gsw32 = GS && P.gstore32 ? P.gstore32 + ((size_t)r * N + head) * L : nullptr;
 
     int chain_seen = -1;
     for (int it0 = 0; it0 < T + 1 && T > 0; it0 += D) {
@@ -816,7 +820,10 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
                     if ((P.gw || GV) && lam < L) {
                         const double g = cin + a_ext[slot * LL + lam];    // as the chain formed it
                         const int pv = a_p[slot * LL + lam];
-                        if constexpr (GS) gsw[oi + lam] = update ? g : 0.0;
+                        if constexpr (GS) {
+                            if (gsw32) gsw32[oi + lam] = update ? (float)g : 0.0f;
+                            else gsw[oi + lam] = update ? g : 0.0;
+                        }
                         if (!GS && P.gw) {
                             float vv;
                             if (GV) {
@@ -1328,6 +1335,8 @@ __global__ void __launch_bounds__(64) mrf_bwd_sweep_packed(const MrfBwdParams P)
 // FULL: L is a multiple of NL, so that a lane's labels are one access of NL floats.
 // GV: every wavefront has V-gradient tables of its own in LDS, summed in a fixed order at the end: the order of all
 // additions, and with it every bit of the result, is the same in every run.
+// GS: a problem with per-edge tables: no V and no edge-weight gradient; the gradient vector g of every node goes to
+// P.gstore32 (0 where no update is replayed), if that is wanted, for mrf_bwd_edge_tables.
 template <int SEG, int NL>
 __host__ __device__ constexpr int mrf_bwd_narrow_row()
 {
@@ -1357,7 +1366,7 @@ __host__ __device__ inline int mrf_bwd_narrow_tables(int nseg, int L, int waves)
     return n > 0 ? n : 1;
 }
 
-template <int SEG, int NL, int NS, int D, bool UNARY, bool GV, bool FULL>
+template <int SEG, int NL, int NS, int D, bool UNARY, bool GV, bool FULL, bool GS = false>
 __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P)
 {
     constexpr int NSEG = 64 / SEG;
@@ -1377,11 +1386,13 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
     double *sb = rows + seg * RS;
     double *spare = rows + NSEG * RS + lane;                  // where a lane with nothing to add adds
 
-    for (int e = threadIdx.x; e < L * pitch; e += blockDim.x) {
-        const int mu = e / pitch, lam = e - mu * pitch;
-        vl[e] = lam < L ? P.V[mu * L + lam] : 0.0f;
+    if constexpr (!GS) {
+        for (int e = threadIdx.x; e < L * pitch; e += blockDim.x) {
+            const int mu = e / pitch, lam = e - mu * pitch;
+            vl[e] = lam < L ? P.V[mu * L + lam] : 0.0f;
+        }
+        if (threadIdx.x == 0) vl[L * pitch] = 0.0f;
     }
-    if (threadIdx.x == 0) vl[L * pitch] = 0.0f;
     for (int e = threadIdx.x; e < waves * (NSEG * RS + 64 + ntab * tsize); e += blockDim.x) reinterpret_cast<double *>(mrf_bsmem)[e] = 0.0;
     __syncthreads();
 
@@ -1417,6 +1428,7 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
     const mrf_buf bw = mrf_buffer(P.w + (P.w_mul ? (size_t)r * N : 0), P.w_mul ? N * 4 : 4);
     const mrf_buf bs = mrf_buffer(P.S + (size_t)r * N * L, NL4), bu = mrf_buffer(P.gunary, NL4);
     const mrf_buf bgw = mrf_buffer(P.gw ? P.gw + (size_t)r * N : nullptr, P.gw ? N * 4 : 0);
+    const mrf_buf bgs = mrf_buffer(GS && P.gstore32 ? P.gstore32 + (size_t)r * N * L : nullptr, GS && P.gstore32 ? NL4 : 0);
     mrf_buf src[NS];
     double cG[NS], cT[NS];
     const int nsrc = P.n_src[r];
@@ -1590,12 +1602,18 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
             mrf_wave_lds_fence();
 #pragma unroll
             for (int s = 0; s < NL; ++s) sb[lam0 + s] = 0.0;
-            pairwise(u == 0 ? D - 1 : u - 1);
+            if constexpr (!GS) pairwise(u == 0 ? D - 1 : u - 1);
             if (u == 0) {
                 gwleft = li < D ? len - 1 - t0 - li : 0;
                 gwat = (ci - (unsigned)(li * nstep)) << 2;
             }
             const bool update = tt < len - 1;            // node i has a predecessor: replay its update
+            if constexpr (GS) {
+                float out[NL];
+#pragma unroll
+                for (int s = 0; s < NL; ++s) out[s] = update ? (float)g[s] : 0.0f;
+                store(bgs, (int)(tt < len) & (int)any ? ce << 2 : MRF_BUF_NONE, out);
+            }
             ce -= estep;
             {
                 float out[NL];
@@ -1616,7 +1634,7 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
         // (as many dropped stores as a group makes: what is in flight when the loop is entered then looks to the
         // compiler like what is in flight when it comes round, else it waits for the newest stores each time)
 #pragma unroll
-        for (int u = 0; u < D * (UNARY ? 2 : 1) * (FULL ? 1 : NL) + 1; ++u) mrf_buf_store_f32(bs, MRF_BUF_NONE, 0.0f);
+        for (int u = 0; u < D * ((UNARY ? 2 : 1) + (GS ? 1 : 0)) * (FULL ? 1 : NL) + (GS ? 0 : 1); ++u) mrf_buf_store_f32(bs, MRF_BUF_NONE, 0.0f);
         for (int t0 = 0; t0 < maxlen; t0 += 2 * D) {
 #pragma unroll
             for (int u = 0; u < D; ++u) prefetch(B[u]);
@@ -1629,7 +1647,7 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
             group(B, t0 + D);
             __builtin_amdgcn_sched_barrier(0);
         }
-        pairwise(D - 1);
+        if constexpr (!GS) pairwise(D - 1);
     }
     if (GV) {
         __syncthreads();

@@ -1,5 +1,5 @@
 // Streaming kernels around the backward sweeps: the pairwise gradients of launches whose sweep stores the node
-// gradients, the reduction of the private V-gradient accumulators, and fills.
+// gradients, the gradient of per-edge tables, the reduction of the private V-gradient accumulators, and fills.
 #pragma once
 
 #include "mrfmp_device.h"
@@ -160,6 +160,72 @@ __global__ void __launch_bounds__(1024) mrf_bwd_pairwise_shared(const MrfGvParam
     double *slot = P.gV + (size_t)blockIdx.x * L * L;
     for (int e = threadIdx.x; e < L * L; e += blockDim.x)       // (no-return atomics as in mrf_slot_add)
         __hip_atomic_fetch_add(&slot[e], tile[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ---- gradient of per-edge tables apart from the sweeps ---------------------------------------------
+// Eq. supp-gradient-pairwise: entry (p(lambda), lambda) of an edge's own table receives g(lambda), once per iteration.
+// Added in the sweeps, that is a read-modify-write of L scattered entries of every table in every iteration, behind a
+// zero fill of all of them.  Here the sweeps store g (one float per label and node), and this pass writes every table
+// once: a workgroup takes T neighbouring tables, which are one contiguous range, adds the g of `count` iterations to them
+// in LDS (a thread per node and label, iterations one after the other: the order of the additions is that of the sweeps)
+// and streams the range out.  With room for less than K iterations of g the passes behind the first one start from what
+// is there.  Bound by the bytes of the tables.  256 x 256, 21 labels, 4 directions, K = 3: EDGE_PASS_US us for 462 MB; the
+// backward pass 693 -> EDGE_BWD_US us.
+struct MrfEdgeGradParams {
+    long long tables;        // R * N
+    int L, T;                // labels; tables per workgroup and turn
+    int count;               // iterations in g
+    const float *g;          // [count][R][N][L], the iteration that was processed first at the front
+    const uint8_t *p;        // [R][N][L] of that iteration; the next one lies p_step bytes before it
+    long long p_step;
+    float *gE;               // [R][N][L][L]
+    int accumulate;          // add to what gE holds
+};
+
+// VEC: gE and T L L allow accesses of four floats
+template <bool VEC>
+__global__ void __launch_bounds__(256) mrf_bwd_edge_tables(const MrfEdgeGradParams P)
+{
+    extern __shared__ __align__(16) float mrf_etile[];
+    constexpr int W = VEC ? 4 : 1;
+    typedef float vecf __attribute__((ext_vector_type(W)));
+    const int L = P.L, LL = L * L, tid = threadIdx.x;
+    vecf *tile = reinterpret_cast<vecf *>(mrf_etile);
+    const long long turns = (P.tables + P.T - 1) / P.T;
+    const size_t slab = (size_t)P.tables * L;
+    if (!P.accumulate)
+        for (int e = tid; e < P.T * LL / W; e += 256) tile[e] = vecf(0.0f);
+    for (long long c = blockIdx.x; c < turns; c += gridDim.x) {
+        const long long first = c * P.T;
+        const int n = (int)(P.tables - first < P.T ? P.tables - first : P.T);     // tables of this turn
+        vecf *out = reinterpret_cast<vecf *>(P.gE + (size_t)first * LL);
+        const int whole = n * LL / W;
+        if (P.accumulate) {
+            __syncthreads();                             // (the turn before this one has left the tile)
+            for (int e = tid; e < n * LL; e += 256) mrf_etile[e] = P.gE[(size_t)first * LL + e];
+        }
+        __syncthreads();
+        for (int x = tid; x < n * L; x += 256) {
+            const int node = x / L;
+            float *col = mrf_etile + node * LL + (x - node * L);
+            const float *g = P.g + (size_t)first * L + x;
+            const uint8_t *p = P.p + (size_t)first * L + x;
+            for (int k = 0; k < P.count; ++k) {
+                const int mu = p[-(ptrdiff_t)k * P.p_step];
+                col[(mu < L ? mu : L - 1) * L] += g[(size_t)k * slab];
+            }
+        }
+        __syncthreads();
+        for (int e = tid; e < whole; e += 256) {
+            out[e] = tile[e];
+            tile[e] = vecf(0.0f);
+        }
+        for (int e = whole * W + tid; e < n * LL; e += 256) {                     // (the last turn's ragged end)
+            P.gE[(size_t)first * LL + e] = mrf_etile[e];
+            mrf_etile[e] = 0.0f;
+        }
+        // (the next turn's additions wait at its first barrier)
+    }
 }
 
 // Reduction of the V-gradient slots in a fixed order.  A workgroup takes ENT entries of the table and 256 / ENT

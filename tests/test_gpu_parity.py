@@ -1531,6 +1531,45 @@ def test_per_edge_tables_in_lane_groups(oracle, case):
         check_forward(g, oracle.forward(pr.algo, pr.unary, None, pr.dirs, pr.K, rho=pr.rho, pairwise_edge=pr.pairwise_edge))
 
 
+# the sweeps that leave the tables' gradient to a pass of its own: few scanlines (chain) and more than 1,024 (narrow: 8, 16 and
+# 32 lanes, three labels per lane), ragged and odd label counts; workspace for one iteration of three (L = 2, 3 on larger
+# grids: passes that add to the tables), the least workspace that is accepted, gradients off a 16-byte boundary
+@pytest.mark.parametrize("case", [("isgmr", 2, 7, 9, 5, 3), ("trwp", 1, 8, 11, 21, 2), ("isgmr", 1, 6, 5, 64, 2), ("trwp", 1, 5, 6, 45, 1),
+                                  ("isgmr", 1, 2, 530, 7, 2), ("isgmr", 1, 2, 530, 13, 2), ("isgmr", 1, 2, 530, 21, 3),
+                                  ("isgmr", 1, 2, 530, 23, 2), ("isgmr", 1, 2, 530, 32, 2), ("trwp", 2, 2, 530, 8, 2),
+                                  ("trwp", 2, 3, 530, 18, 2), ("trwp", 2, 2, 530, 29, 2),
+                                  ("isgmr", 1, 130, 190, 3, 3), ("trwp", 1, 100, 170, 2, 3)], ids=lambda c: "_".join(map(str, c)))
+def test_gradient_of_per_edge_tables_in_a_pass_of_its_own(oracle, case):
+    import torch
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import GpuProblem
+    print("case table gradient", case, flush=True)
+    algo, B, H, W, L, K = case
+    pr = random_problem(800 + L, algo, B, H, W, L, DIRS4, K, per_edge=False, rho=np.linspace(0.3, 0.9, 4))
+    rng = np.random.default_rng(9100 + L)
+    pr.pairwise_edge = rng.random((4, B, H, W, L, L)).astype(np.float32)
+    f = oracle.forward(pr.algo, pr.unary, None, pr.dirs, pr.K, rho=pr.rho, pairwise_edge=pr.pairwise_edge)
+    b = {dt: oracle.backward(pr.algo, pr.shape, None, pr.dirs, pr.K, pr.grad_cost.astype(dt), f.p, f.q, rho=pr.rho, dtype=dt,
+                             per_edge_pairwise=True) for dt in (np.float32, np.float64)}
+    for variant in ("as asked for", "least workspace", "off a boundary", "no table gradient"):
+        g = GpuProblem(pr)
+        if variant == "least workspace":
+            plain = mrf.MrfProblem(g.unary, torch.zeros((L, L), device="cuda:0"), pr.dirs, K, rho=pr.rho)
+            g.workspace = g.workspace[:mrf.mrf_workspace_bytes(plain, g.algo, True)]
+        if variant == "off a boundary":
+            g.grad_pairwise = torch.empty(g.grad_pairwise.numel() + 1, device="cuda:0")[1:].view(g.grad_pairwise.shape)
+        g.poison_outputs()
+        g.forward()
+        g.backward(want_V=variant != "no table gradient")
+        out = g.results()
+        np.testing.assert_array_equal(out.p, f.p)
+        check_grad("grad_unary", out.grad_unary, b[np.float32].grad_unary, b[np.float64].grad_unary)
+        if variant != "no table gradient":
+            if algo == "isgmr" and variant != "least workspace":     # (which may hold no iteration: then the sweep adds to the tables)
+                assert mrf.mrf_last_sweep_launch(True).startswith("mrf_bwd_sweep_narrow" if 2 * B * (H + W) > 1024 else "mrf_bwd_sweep_chain")
+            check_grad("grad_pairwise_edge", out.grad_pairwise, b[np.float32].grad_pairwise_edge, b[np.float64].grad_pairwise_edge)
+
+
 def test_per_edge_tables_argument_errors():
     import torch
     import paper_1910_10892_amd as mrf
