@@ -681,16 +681,17 @@ hipError_t launch_edge(const MrfFwdParams &P, int algo, long long blocks, hipStr
     const dim3 grid((unsigned)blocks), block(64);
     // up to 32 labels: the lanes in groups that share the source labels
     if (L <= 32) {
-        const int seg = L <= 16 ? 16 : 32, rows = L <= 8 ? 2 : (L <= 16 ? 4 : (L <= 24 ? 12 : 16));
-        note_launch(0, "mrf_fwd_sweep_edge_groups", blocks, 64, "%d,%d,%d,%s", seg, rows, rmax, algo == MRF_TRWP ? "true" : "false");
-#define MRF_E(sg, hr, rm) \
-        if (seg == sg && rows == hr && rmax == rm) { \
-            if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_edge_groups<sg, hr, rm, true>), grid, block, 0, st, P); \
-            else hipLaunchKernelGGL((mrf_fwd_sweep_edge_groups<sg, hr, rm, false>), grid, block, 0, st, P); \
+        // (accesses of 1 KB per table: none for up to 8 labels, whose table is one of 256 bytes)
+        const int seg = L <= 16 ? 16 : 32, rows = L <= 8 ? 2 : (L <= 16 ? 4 : (L <= 24 ? 12 : 16)), nt = L <= 8 ? 0 : (L * L + 255) / 256;
+        note_launch(0, "mrf_fwd_sweep_edge_groups", blocks, 64, "%d,%d,%d,%d,%s", seg, rows, nt, rmax, algo == MRF_TRWP ? "true" : "false");
+#define MRF_E(sg, hr, n, rm) \
+        if (seg == sg && rows == hr && nt == n && rmax == rm) { \
+            if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_edge_groups<sg, hr, n, rm, true>), grid, block, 0, st, P); \
+            else hipLaunchKernelGGL((mrf_fwd_sweep_edge_groups<sg, hr, n, rm, false>), grid, block, 0, st, P); \
             return hipGetLastError(); \
         }
-#define MRF_EH(sg, hr) MRF_E(sg, hr, 4) MRF_E(sg, hr, 8) MRF_E(sg, hr, 16)
-        MRF_EH(16, 2) MRF_EH(16, 4) MRF_EH(32, 12) MRF_EH(32, 16)
+#define MRF_EH(sg, hr, n) MRF_E(sg, hr, n, 4) MRF_E(sg, hr, n, 8) MRF_E(sg, hr, n, 16)
+        MRF_EH(16, 2, 0) MRF_EH(16, 4, 1) MRF_EH(32, 12, 2) MRF_EH(32, 12, 3) MRF_EH(32, 16, 3) MRF_EH(32, 16, 4)
 #undef MRF_EH
 #undef MRF_E
     }

@@ -169,8 +169,8 @@ __global__ void __launch_bounds__(1024) mrf_bwd_pairwise_shared(const MrfGvParam
 // once: a workgroup takes T neighbouring tables, which are one contiguous range, adds the g of `count` iterations to them
 // in LDS (a thread per node and label, iterations one after the other: the order of the additions is that of the sweeps)
 // and streams the range out.  With room for less than K iterations of g the passes behind the first one start from what
-// is there.  Bound by the bytes of the tables.  256 x 256, 21 labels, 4 directions, K = 3: EDGE_PASS_US us for 462 MB; the
-// backward pass 693 -> EDGE_BWD_US us.
+// is there.  Bound by the bytes of the tables.  256 x 256, 21 labels, 4 directions, K = 3: 118 us for 462 MB; the
+// backward pass 693 -> 350 us.
 struct MrfEdgeGradParams {
     long long tables;        // R * N
     int L, T;                // labels; tables per workgroup and turn

@@ -940,24 +940,28 @@ mrf_fwd_sweep_edge(const MrfFwdParams P)
 
 // ---- the same for up to 32 labels ---------------------------------------------------------------
 //
-// Bound by the bytes of the tables (4 L^2 per node and direction) as long as enough of them are in flight: a launch has
-// a wavefront per scanline only, so a wavefront has to keep several nodes' tables on the way, and the counter of loads
-// in flight ends at 63.  Rows of one label per lane would leave half of the lanes idle and spend a load on each source
-// label.  Here NG = 64 / SEG groups of SEG lanes (16 up to 16 labels, else 32) hold the same destination labels and
-// group k the source labels k HR .. k HR + HR - 1: a load brings NG rows, a node takes HR table loads, and D nodes
-// are in flight.  Every group forms all of h (same loads, same operations) and keeps it in LDS; a lane reads its group's
-// HR entries, finds their lowest argmin, and one or two lane swaps join the groups, the lower one first on a tie.
-// All addresses of a node are scalar bases; table rows beyond L read as 0 through the view of the node's table and meet
-// h = +inf.  256 x 256, 21 labels, 4 directions: ISGMR sweep 273 -> 155 us (462 MB of tables).
-template <int SEG, int HR, int RMAX, bool TRWP>
+// Bound by the bytes of the tables (4 L^2 per node and direction) as long as enough of them are in flight: a launch has a
+// wavefront per scanline only, so a wavefront has to keep several nodes' tables on the way, and the counter of loads in
+// flight ends at 63.  A table is therefore loaded as it lies in memory, NT = 1..4 accesses of 16 bytes per lane (up to
+// eight labels: one of 4), up to seven nodes ahead, and goes through a tile in LDS, from which its rows are read.  (A load
+// per pair of rows, four nodes ahead, touches most cache lines twice: 155 us where this takes 131.)
+// NG = 64 / SEG groups of SEG lanes (16 up to 16 labels, else 32) hold the same destination labels and group k the source
+// labels k HR .. k HR + HR - 1, so no lane idles for want of labels.  Every group forms all of h (same loads, same
+// operations) and keeps it in LDS; a lane reads its group's HR entries, finds their lowest argmin, and one or two lane swaps
+// join the groups, the lower one first on a tie.  Entries without a source label are h = +inf.
+// 256 x 256, 21 labels, 4 directions, ISGMR sweep: 273 us with one label per lane and half a table in flight, now 131 (4.2 TB/s
+// of tables and messages).
+template <int SEG, int HR, int NT, int RMAX, bool TRWP>
 __global__ void __launch_bounds__(64)
 mrf_fwd_sweep_edge_groups(const MrfFwdParams P)
 {
     constexpr int NG = 64 / SEG;
     constexpr int HP = (HR + 3) / 4 * 4;                // LDS row of a group, 16-byte aligned
     // nodes in flight: their loads, and the stores of the nodes between, within the counter's 63
-    constexpr int D0 = 1 + 63 / (HR + RMAX + 4), D = D0 > 6 ? 6 : D0;
+    constexpr int NL = NT > 0 ? NT : 1, D0 = 1 + 63 / (NL + RMAX + 4), D = D0 > 7 ? 7 : D0;
+    constexpr int TILE = NT > 0 ? 256 * NT : 64;         // floats
     static_assert(NG == 2 || NG == 4, "lane groups");
+    __shared__ __align__(16) float tile[TILE + 256 + HR * 32];
     __shared__ __align__(16) float hrow[NG * HP + 4];       // (the last entry: for lanes without a label to scribble in)
     const int L = P.g.L;
     const int lane = threadIdx.x & 63;
@@ -999,15 +1003,23 @@ mrf_fwd_sweep_edge_groups(const MrfFwdParams P)
 #pragma unroll
     for (int c = 1; c <= RMAX; ++c) carry_at[c] = (c == n_pre + 1) ? 1.0f : 0.0f;
 
-    // (a node's vectors are views of their own: lanes without a label, and the other groups', store nothing)
+    // Bases of the vectors of the node that is being loaded and of the one that is being stored walk along the scanline by
+    // scalar additions.  A node's vectors are views of their own: lanes without a label, and the other groups', store
+    // nothing, and behind the scanline's end the views are empty.
+    const long long estep = nstep * L;
     const unsigned st4 = grp == 0 && valid ? (unsigned)lam << 2 : MRF_BUF_NONE, st1 = grp == 0 && valid ? (unsigned)lam : MRF_BUF_NONE;
     const unsigned stq = lane == 0 ? 0u : MRF_BUF_NONE;
-    auto store = [&](long long i, float m, int arg, int q) {
-        mrf_buf_store_f32(mrf_buffer(P.m_out + ((size_t)r * N + i) * L, (size_t)L * 4), st4, m);
-        mrf_buf_store_u8(mrf_buffer(P.p + ((size_t)r * N + i) * L, (size_t)L), st1, arg);
-        mrf_buf_store_u8(mrf_buffer(P.q + (size_t)r * N + i, 1), stq, q);
+    float *mo = P.m_out + ((size_t)r * N + head) * L;
+    uint8_t *po = P.p + ((size_t)r * N + head) * L, *qo = P.q + (size_t)r * N + head;
+    auto store = [&](bool act, float m, int arg, int q) {
+        mrf_buf_store_f32(mrf_buffer(mo, act ? (size_t)L * 4 : 0), st4, m);
+        mrf_buf_store_u8(mrf_buffer(po, act ? (size_t)L : 0), st1, arg);
+        mrf_buf_store_u8(mrf_buffer(qo, act ? (size_t)L : 0), stq, q);       // (lane 0 stores, its first byte)
+        mo += estep;
+        po += estep;
+        qo += nstep;
     };
-    store(head, 0.0f, 0, 0);
+    store(true, 0.0f, 0, 0);
     if (len < 2) return;
 
     for (int e = lane; e < NG * HP; e += 64) hrow[e] = INFINITY;       // entries without a source label stay +inf
@@ -1017,39 +1029,114 @@ mrf_fwd_sweep_edge_groups(const MrfFwdParams P)
     const int vzero = mrf_opaque_zero();
     // (without a rho per edge the load takes any word: no branch around a load that is prefetched)
     const bool per_edge = TRWP && P.rho_e;
-    const float *rbase = per_edge ? P.rho_e + (size_t)r * N : P.unary;
-    const float *tbase = P.Te + (size_t)r * N * L * L;
+    const float *rb = (per_edge ? P.rho_e + (size_t)r * N : P.unary) + head + nstep;
     const unsigned tsize = (unsigned)(L * L) * 4u;
-    const unsigned toff = valid ? (unsigned)(grp * HR * L + lam) * 4u : MRF_BUF_NONE;
+    // a table as it lies in memory: sixteen bytes per lane and access (up to eight labels: four), the last ones those that
+    // end the table; a lane without any keeps to a place of its own behind the tile
+    unsigned toff[NL], tput[NL];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const unsigned at = NT > 0 ? 1024u * k + 16u * lane : 4u * lane;
+        const bool live = at < tsize;
+        toff[k] = live ? (NT > 0 && at + 16u > tsize ? tsize - 16u : at) : MRF_BUF_NONE;
+        tput[k] = live ? toff[k] / 4u : (unsigned)(TILE + 4 * lane);
+    }
     struct In {
-        float t[HR], v[RMAX];
+        float f[NL][4], v[RMAX];
         float rho;
     };
     In in[D];
     // inputs of the update of node n: its edge's table, the vectors of node n - 1 (past the end: the last node again)
-    auto prefetch = [&](In &x, int n) {
-        n = n < len ? n : len - 1;
-        const long long i = head + (long long)n * nstep, j = i - nstep;
-        const mrf_buf tb = mrf_buffer(tbase + (size_t)i * L * L, tsize);
+    const float *tb = P.Te + ((size_t)r * N + head + nstep) * L * L;
+    const long long tstep = estep * L;
 #pragma unroll
-        for (int m = 0; m < HR; ++m) x.t[m] = mrf_buf_f32s(tb, toff, (unsigned)(m * L) * 4u);
+    for (int c = 0; c < RMAX; ++c) src[c] += (size_t)head * L;
+    int ahead = 1;                                       // node that the next prefetch is for
+    auto prefetch = [&](In &x) {
+        const mrf_buf tv = mrf_buffer(tb, tsize);
 #pragma unroll
-        for (int c = 0; c < RMAX; ++c) x.v[c] = (src[c] + (size_t)j * L)[lamc];
-        x.rho = TRWP ? rbase[(size_t)i + vzero] : 1.0f;
+        for (int k = 0; k < NL; ++k) {
+            if constexpr (NT > 0) mrf_buf_f32xn<4>(tv, toff[k], x.f[k]);
+            else x.f[k][0] = mrf_buf_f32(tv, toff[k]);
+        }
+#pragma unroll
+        for (int c = 0; c < RMAX; ++c) x.v[c] = src[c][lamc];
+        x.rho = TRWP ? rb[vzero] : 1.0f;
+        // (a mask instead of a choice, which would become a branch)
+        const long long more = ++ahead < len ? -1LL : 0LL;
+        const long long tinc = tstep & more, einc = estep & more;
+        rb += nstep & more;
+        tb += tinc;
+#pragma unroll
+        for (int c = 0; c < RMAX; ++c) src[c] += einc;
     };
 #pragma unroll
     for (int u = 0; u < D; ++u) {
-        prefetch(in[u], 1 + u);
+        prefetch(in[u]);
         // (dropped stores: what is in flight at the loop's entry then looks like what is when it comes round)
         for (int x = 0; x < 3; ++x) mrf_buf_store_u8(mrf_buffer(P.q, 1), MRF_BUF_NONE, 0);
         __builtin_amdgcn_sched_barrier(0);
     }
 
+    // the tile holds the table of the node whose rows are read next
+    float tr[HR];
+    auto put = [&](const In &x) {
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+#pragma unroll
+            for (int c = 0; c < (NT > 0 ? 4 : 1); ++c) tile[tput[k] + c] = x.f[k][c];
+    };
+    const int trow = valid ? grp * HR * L + lam : 0;
+    auto rows = [&]() {
+#pragma unroll
+        for (int m = 0; m < HR; ++m) tr[m] = tile[trow + m * L];      // (rows past L meet h = +inf)
+    };
+    for (int e = lane; e < TILE + 256; e += 64) tile[e] = 0.0f;
+    mrf_wave_lds_fence();
+    put(in[0]);
+    mrf_wave_lds_fence();
+    rows();
+    mrf_wave_lds_fence();
+
+    // lower group's (first) and upper group's value of what a lane holds, in both
+    const auto pair = [&](unsigned x, auto upper) {
+        if constexpr (decltype(upper)::value) return __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        else return __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    };
+    const auto bits = [](float x) { return __builtin_bit_cast(unsigned, x); };
+    const auto real = [](unsigned x) { return __builtin_bit_cast(float, x); };
+
+    // What is left of a node once its message is known (indices and stores) runs in the next node's step, where that
+    // waits for h to come back from LDS.
+    float dP[HP], bestP = 0.0f, tvP = 0.0f, tqP = 0.0f;
+    bool actP = false;
+#pragma unroll
+    for (int m = 0; m < HP; ++m) dP[m] = 0.0f;
+    auto finish = [&]() {
+        int arg = 0;
+        mrf_static_for<HP / 4>([&](auto g4) {
+            constexpr int m0 = HP - 4 - 4 * decltype(g4)::value;      // from the top down: the lowest index lands last
+            mrf_first_equal4<m0>(arg, bestP, dP[m0], dP[m0 + 1], dP[m0 + 2], dP[m0 + 3]);
+        });
+        arg += grp * HR;
+        // join the groups: a strict '<' keeps the lower group's index on a tie
+        float b = bestP;
+        if constexpr (NG == 4) {
+            const auto b2 = pair(bits(b), std::false_type{}), a2 = pair((unsigned)arg, std::false_type{});
+            arg = real(b2[1]) < real(b2[0]) ? (int)a2[1] : (int)a2[0];
+            b = mrf_min(real(b2[0]), real(b2[1]));
+        }
+        const auto b2 = pair(bits(b), std::true_type{}), a2 = pair((unsigned)arg, std::true_type{});
+        arg = real(b2[1]) < real(b2[0]) ? (int)a2[1] : (int)a2[0];
+        const unsigned long long bal = __ballot(tvP == tqP);
+        store(actP, tvP - tqP, arg, __ffsll((long long)bal) - 1);
+    };
+
     float carry = 0.0f;
+    mo -= estep; po -= estep; qo -= nstep;               // (the first turn finishes no node)
     for (int n0 = 1; n0 < len; n0 += D) {
 #pragma unroll
         for (int u = 0; u < D; ++u) {
-            const int n = n0 + u;
             float v = in[u].v[0];
             if (TRWP) {
                 float mrm = 0.0f;
@@ -1070,51 +1157,42 @@ mrf_fwd_sweep_edge_groups(const MrfFwdParams P)
             // (the groups write the same values to the same places)
             hrow[hslot] = v;
             mrf_wave_lds_fence();
-            float d[HP];
+            float4 hv[HP / 4];
 #pragma unroll
-            for (int m4 = 0; m4 < HP; m4 += 4) {
-                const float4 hv = *reinterpret_cast<const float4 *>(&hrow[grp * HP + m4]);
-                const float hq[4] = { hv.x, hv.y, hv.z, hv.w };
-#pragma unroll
-                for (int c = 0; c < 4; ++c) d[m4 + c] = m4 + c < HR ? hq[c] + in[u].t[m4 + c < HR ? m4 + c : 0] : INFINITY;
-            }
+            for (int k = 0; k < HP / 4; ++k) hv[k] = *reinterpret_cast<const float4 *>(&hrow[grp * HP + 4 * k]);
             mrf_wave_lds_fence();
-            float best = mrf_min(d[0], d[1]);
+            __builtin_amdgcn_sched_barrier(0);
+            finish();
+            put(in[(u + 1) % D]);
+            mrf_wave_lds_fence();
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int m = 2; m + 1 < HP; m += 2) best = mrf_min3(best, d[m], d[m + 1]);
-            int arg = 0;
-            mrf_static_for<HP / 4>([&](auto g4) {
-                constexpr int m0 = HP - 4 - 4 * decltype(g4)::value;      // from the top down: the lowest index lands last
-                mrf_first_equal4<m0>(arg, best, d[m0], d[m0 + 1], d[m0 + 2], d[m0 + 3]);
-            });
-            arg += grp * HR;
-            // join the groups: a strict '<' keeps the lower group's index on a tie
-            const auto join = [&](auto b2, auto a2) {
-                const float lo = __builtin_bit_cast(float, (unsigned)b2[0]), hi = __builtin_bit_cast(float, (unsigned)b2[1]);
-                arg = hi < lo ? (int)a2[1] : (int)a2[0];
-                best = mrf_min(lo, hi);
-            };
+            for (int m = 0; m < HP; ++m) {
+                const float hm = m % 4 == 0 ? hv[m / 4].x : (m % 4 == 1 ? hv[m / 4].y : (m % 4 == 2 ? hv[m / 4].z : hv[m / 4].w));
+                dP[m] = m < HR ? hm + tr[m < HR ? m : 0] : INFINITY;
+            }
+            rows();
+            mrf_wave_lds_fence();
+            bestP = mrf_min(dP[0], dP[1]);
+#pragma unroll
+            for (int m = 2; m + 1 < HP; m += 2) bestP = mrf_min3(bestP, dP[m], dP[m + 1]);
+            float b = bestP;
             if constexpr (NG == 4) {
-                const unsigned ub = __builtin_bit_cast(unsigned, best);
-                join(__builtin_amdgcn_permlane16_swap(ub, ub, false, false), __builtin_amdgcn_permlane16_swap((unsigned)arg, (unsigned)arg, false, false));
+                const auto b2 = pair(bits(b), std::false_type{});
+                b = mrf_min(real(b2[0]), real(b2[1]));
             }
-            {
-                const unsigned ub = __builtin_bit_cast(unsigned, best);
-                join(__builtin_amdgcn_permlane32_swap(ub, ub, false, false), __builtin_amdgcn_permlane32_swap((unsigned)arg, (unsigned)arg, false, false));
-            }
-            const float tv = valid ? best : INFINITY;
-            const float tq = mrf_wave_min(tv);                            // (every group holds every label)
-            const unsigned long long bal = __ballot(tv == tq);
-            const int qidx = __ffsll((long long)bal) - 1;
-            carry = tv - tq;
-            const bool act = n < len;
-            const long long i = head + (long long)(act ? n : 0) * nstep;
-            store(i, act ? carry : 0.0f, act ? arg : 0, act ? qidx : 0);  // (past the end: the first node's zeros again)
-            __builtin_amdgcn_sched_barrier(0);          // (a node's loads stay together: what is in flight is countable)
-            prefetch(in[u], n + D);
+            const auto b2 = pair(bits(b), std::true_type{});
+            b = mrf_min(real(b2[0]), real(b2[1]));
+            tvP = valid ? b : INFINITY;
+            tqP = mrf_wave_min(tvP);                     // (every group holds every label)
+            carry = tvP - tqP;
+            actP = n0 + u < len;
+            __builtin_amdgcn_sched_barrier(0);           // (a node's loads stay together: what is in flight is countable)
+            prefetch(in[u]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    finish();
 }
 
 // ---- final costs and labels: c_i = theta_i + sum_r m^r_i (direction order), x_i = argmin ----
