@@ -158,7 +158,8 @@ MRF_G(int g_tune_gv_apart, 0);     // pairwise gradients of 33..128 labels by a 
 MRF_G(int g_tune_gv_tile, 0);      // V gradient of 33..128 labels in one LDS table per workgroup: 0 yes, 1 no (a slot per wavefront in global memory)
 MRF_G(int g_tune_dense_sliced, 0); // dense sweep for more than 64 labels with a slice of the labels per wavefront: 0 yes, 1 no
 MRF_G(int g_tune_spin_limit, 0); // turns a wait between wavefronts may take: 0 = default
-MRF_G(int g_tune_pack_idx, 0);   // index wavefronts in the packed dense sweep: 0 by launch size, 1 never, 2 always, 3 never and 64-bit offsets
+MRF_G(int g_tune_pack_idx, 0);   // packed dense sweep divided among four wavefronts: 0 by launch size, 1 never, 2 always, 3 never and 64-bit offsets,
+                                 // 4 always and one scanline per wavefront, 5 always and several
 MRF_G(int g_tune_chain, 0);      // backward sweep with a chain wavefront: 0 auto, 1 never, 2 whenever possible
 MRF_G(int g_tune_chain_hot, 0);  // its pre-reduction of the most popular scatter target: 0 auto, 1 never, 2 whenever V is no dense table
 MRF_G(int g_tune_chain_ni, 0);   // its helpers per scanline: 0 auto, 2, 4, 6, 8
@@ -283,16 +284,39 @@ hipError_t launch_narrow_mu(MrfFwdParams P, int algo, int rmax, hipStream_t st)
     return hipErrorInvalidValue;
 }
 
+// the packed sweep divided among four wavefronts
+template <int SEG, int NG, int MU>
+hipError_t launch_packed_divided(MrfFwdParams P, int algo, int rmax, hipStream_t st)
+{
+    constexpr int NSEG = NG > 1 ? 1 : 64 / SEG;
+    P.pack_begin[0] = 0;
+    bool none = algo == MRF_ISGMR;
+    for (int ri = 0; ri < P.r_count; ++ri) {
+        P.pack_begin[ri + 1] = P.pack_begin[ri] + (int)((P.blk_begin[ri + 1] - P.blk_begin[ri] + NSEG - 1) / NSEG);
+        none = none && P.n_src[P.r_first + ri] == 0;
+    }
+    const unsigned blocks = (unsigned)P.pack_begin[P.r_count];
+    if (none) rmax = 1;
+    note_launch(0, "mrf_fwd_sweep_packed", blocks, 256, "%d,%d,%d,%d,%s", SEG, NG, MU, rmax, algo == MRF_TRWP ? "true" : "false");
+    const dim3 grid(blocks), block(256);
+#define MRF_P(rm) \
+    if (rmax == rm) { \
+        if (algo == MRF_TRWP) hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, NG, MU, rm, true>), grid, block, 0, st, P); \
+        else hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, NG, MU, rm, false>), grid, block, 0, st, P); \
+        return hipGetLastError(); \
+    }
+    MRF_P(4) MRF_P(8) MRF_P(16)
+#undef MRF_P
+    hipLaunchKernelGGL((mrf_fwd_sweep_packed<SEG, NG, MU, 1, false>), grid, block, 0, st, P);
+    return hipGetLastError();
+}
+
 template <int SEG, int MU>
 hipError_t launch_packed_mu(const MrfFwdParams &P, int algo, int rmax, long long scanlines, hipStream_t st)
 {
     const unsigned blocks = (unsigned)((scanlines + 64 / SEG - 1) / (64 / SEG));
-    // few wavefronts in the launch: further ones per workgroup for the argmin tables and the stores
-    // (two of them: an index wavefront has more to do per node than the value wavefront)
-    // (forward pass, K = 3, 4 directions, index wavefronts / mrf_fwd_sweep_narrow, at 1,024 wavefronts: TRWP 4 x 512 x 512 2.85 /
-    // 2.95 ms with 32 labels, 2.43 / 2.84 with 21; at half of that 1.98 / 2.89; at 2,048 6.37 / 4.09 with 32 labels, ISGMR 1.58 /
-    // 0.92)
-    const bool idx = g_tune_pack_idx == 2 || (g_tune_pack_idx == 0 && blocks <= 1024);
+    // (few wavefronts in a launch beyond the 32-bit offsets: two further ones per workgroup for the argmin tables and stores)
+    const bool idx = P.g.N * P.g.L > MRF_BUF_MOST && g_tune_pack_idx != 1 && g_tune_pack_idx != 3 && (g_tune_pack_idx == 2 || blocks <= 1024);
     // else one wavefront does all: mrf_fwd_sweep_narrow as far as its 32-bit offsets reach
     if (!idx && g_tune_pack_idx != 3 && P.g.N * P.g.L <= MRF_BUF_MOST) {
         bool none = true;
@@ -317,9 +341,49 @@ hipError_t launch_packed_mu(const MrfFwdParams &P, int algo, int rmax, long long
     return hipErrorInvalidValue;
 }
 
+// Whether a launch is for the sweep divided among four wavefronts, as far as its 32-bit offsets reach, or for
+// mrf_fwd_sweep_narrow (forward pass, divided / narrow, by wavefronts of scanlines):
+// - 1,024: TRWP, 4 directions, K = 2: 6 x 512 x 512, 21 labels 1.73 / 2.14 ms, 4 x 512 x 512, 32 labels 1.76 / 2.04, 8 x 512 x 512, 16
+//   labels 1.49 / 1.61, 8 labels 1.13 / 1.41; at 1,366 to 1,536 behind: 21 labels 2.86 / 2.62, 32 labels 2.91 / 2.36, 16 labels 2.49 / 2.29
+// - ISGMR, 4 directions, K = 3: 1,026 wavefronts (512 x 1024, 21 labels) 0.91 / 1.29, 1,368 0.90 / 0.86; 1,536 with 32 labels 1.16 / 1.36,
+//   with 16 0.71 / 0.70
+// - eight directions, TRWP: 1,364 wavefronts with 21 labels 1.84 / 2.36, 2,044 with 32 labels 2.40 / 2.68
+bool packed_divided(const MrfFwdParams &P, int seg, int algo, int rmax, long long scanlines)
+{
+    if (P.g.N * P.g.L > MRF_BUF_MOST) return false;
+    if (g_tune_pack_idx == 2 || g_tune_pack_idx == 4 || g_tune_pack_idx == 5) return true;
+    const long long waves = (scanlines + 64 / seg - 1) / (64 / seg);
+    return g_tune_pack_idx == 0 && waves <= (rmax > 4 ? 2048 : (algo == MRF_ISGMR ? 1280 : 1024));
+}
+
+// and then, whether a scanline has a wavefront's lanes to itself (forward pass, one / several scanlines per wavefront):
+// TRWP, 21 labels, K = 3: 256 scanlines 0.62 / 0.73 ms, 600 1.62 / 1.73, 768 0.75 / 0.80, 1,024 1.61 / 1.53; 16 labels 600 1.16 / 1.30,
+// 1,024 1.26 / 1.25; 8 labels, where half of the lanes have no source label, 600 1.30 / 1.19.  ISGMR, all directions in one launch:
+// 512 scanlines 0.127 / 0.138 with 16 labels, 1,024 0.178 / 0.160; 320 with 8 labels level
+bool packed_one(int L, long long scanlines)
+{
+    if (g_tune_pack_idx >= 4) return g_tune_pack_idx == 4;
+    return scanlines <= (L > 8 ? 768 : 320);
+}
+
 template <int SEG>
 hipError_t launch_packed(const MrfFwdParams &P, int algo, int rmax, long long scanlines, hipStream_t st)
 {
+    if (packed_divided(P, SEG, algo, rmax, scanlines)) {
+        const bool one = packed_one(P.g.L, scanlines);
+        const int mu = (P.g.L + 3) / 4 * 4;
+        if constexpr (SEG == 21) return launch_packed_divided<21, 1, 24>(P, algo, rmax, st);
+        if constexpr (SEG == 16) {
+            if (one) return launch_packed_divided<16, 4, 16>(P, algo, rmax, st);
+            if (mu <= 8) return launch_packed_divided<16, 1, 8>(P, algo, rmax, st);
+            return mu <= 12 ? launch_packed_divided<16, 1, 12>(P, algo, rmax, st) : launch_packed_divided<16, 1, 16>(P, algo, rmax, st);
+        }
+        if constexpr (SEG == 32) {
+            if (one) return mu <= 24 ? launch_packed_divided<32, 2, 24>(P, algo, rmax, st) : launch_packed_divided<32, 2, 32>(P, algo, rmax, st);
+            if (mu <= 24) return mu <= 20 ? launch_packed_divided<32, 1, 20>(P, algo, rmax, st) : launch_packed_divided<32, 1, 24>(P, algo, rmax, st);
+            return mu <= 28 ? launch_packed_divided<32, 1, 28>(P, algo, rmax, st) : launch_packed_divided<32, 1, 32>(P, algo, rmax, st);
+        }
+    }
     // three scanlines of up to 21 labels per wavefront: always 24 source labels
     if constexpr (SEG == 21) {
         return launch_packed_mu<21, 24>(P, algo, rmax, scanlines, st);
@@ -726,8 +790,9 @@ hipError_t dispatch_fwd(MrfFwdParams &P, int algo, int tw, long long blocks, hip
         const int rmax = (ms + 1 <= 4) ? 4 : ((ms + 1 <= 8) ? 8 : 16);
         P.NW = 1;
         // 17..21 labels (the 21 classes of the segmentation shape): three scanlines per wavefront once the
-        // launch has wavefronts to spare, else two (a latency-bound launch gains nothing from fewer wavefronts)
-        if (P.g.L > 16 && P.g.L <= 21 && g_tune_pack3 != 1 && (g_tune_pack3 == 2 || blocks >= 3072))
+        // launch has wavefronts to spare, else two or one (a latency-bound launch gains nothing from fewer wavefronts:
+        // TRWP, 512 x 512 images, K = 3, three / two scanlines per wavefront: 1,024 scanlines 1.64 / 1.53 ms, 1,536 1.69 / 1.80)
+        if (P.g.L > 16 && P.g.L <= 21 && g_tune_pack3 != 1 && (g_tune_pack3 == 2 || blocks >= 1280))
             return run_packed(P, 21, algo, rmax, blocks, st);
         return run_packed(P, P.g.L <= 16 ? 16 : 32, algo, rmax, blocks, st);
     }

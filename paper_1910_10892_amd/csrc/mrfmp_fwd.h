@@ -20,7 +20,8 @@
 //   mrf_fwd_sweep_sliced        dense, L > 64: the same with the O(L) work of a node divided among the wavefronts
 //   mrf_fwd_sweep_halves        dense, 33..128 labels: chunk minima, argmin by a second look at the winning chunk
 //   mrf_fwd_sweep_narrow        dense, L <= 32: several scanlines of one direction per wavefront, argmin in two levels
-//   mrf_fwd_sweep_packed        the same for launches of few scanlines, with index wavefronts; scanlines of any direction
+//   mrf_fwd_sweep_packed        the same for launches of few scanlines, the work of a node divided among four wavefronts (five
+//                               template parameters), or with 64-bit offsets and scanlines of any direction (six)
 //   mrf_fwd_sweep_edge          pairwise potentials given per edge, 33..64 labels
 //   mrf_fwd_sweep_edge_groups   the same for up to 32 labels, groups of lanes sharing the source labels
 //   mrf_aggregate               final costs and labels
@@ -2889,8 +2890,8 @@ __device__ inline int mrf_segment_first(unsigned long long bal, int lane)
 // 21-lane segments, whose LDS rows are padded to 28 entries).
 // IDX = 1, 2: that many further wavefronts per workgroup take the argmin tables and the stores (as in
 // mrf_fwd_sweep_window_duo): the first computes values only and hands each node's h and
-// weights over through a ring in LDS.  For launches that leave most issue slots idle; the host
-// uses two, because an index wavefront has more to do per node than the value wavefront.
+// weights over through a ring in LDS.  For launches that leave most issue slots idle, beyond the 32-bit offsets of
+// the sweep divided among four wavefronts (below); two, because an index wavefront has more to do per node.
 template <int SEG, int MU, int RMAX, int D, bool TRWP, int IDX>
 __global__ void __launch_bounds__(64 * (1 + IDX))
 mrf_fwd_sweep_packed(const MrfFwdParams P)
@@ -3160,6 +3161,433 @@ mrf_fwd_sweep_packed(const MrfFwdParams P)
 #pragma unroll
             for (int c = 0; c < RMAX; ++c) cur[u][c] = nxt[u][c];
         }
+    }
+}
+
+// ---- the packed sweep with its work divided among four wavefronts -------------------------------------
+//
+// For launches of few labels that do not fill the machine (thumbnails, crops, TRWP's one direction at a time), where the
+// time of a sweep is the number of nodes on a scanline times the time of one node step on one wavefront.  A lone wavefront
+// issues an instruction every four to five clocks, so what counts is how many instructions stand between two messages, and
+// what it waits for:
+//   loader   does all global loads, sums what does not depend on the running message, and hands a node over in a ring in LDS
+//   values   h, its exchange through LDS, candidates, minimum, normalisation; h and the new message go to the ring
+//   index    two of them, taking nodes in turn: the argmin tables (two levels as in mrf_fwd_sweep_narrow) and all stores
+// The minimum over the labels of the new message is that of h where V >= 0 with a zero diagonal and the weight is not
+// negative (the candidate mu = lambda is h(lambda) itself and no other is smaller), so it is taken while h is on its way
+// through LDS; other nodes take it from the message.  One scanline per wavefront: NG = 64 / SEG groups of lanes hold the
+// same labels and share the source labels (HR each), joined by lane swaps; NG = 1: 64 / SEG scanlines of one direction per
+// wavefront, as many as fit.  Directions, factors, counts and base addresses are scalars, an entry is one 32-bit offset
+// into buffer views (the host checks that N L fits).
+// Every wait is on a counter in LDS that only grows: values on the loader, index on the values, the loader on the index
+// wavefronts' step NR nodes back; none can depend on itself.
+// A node step of the value wavefront takes 43 (16 labels, one scanline, ISGMR) to 81 instructions (21 labels, three, TRWP) of four to
+// five clocks.  With a value wavefront that loads for itself and two index wavefronts, now: 32 x 48, 16 labels, ISGMR, K = 5, forward
+// pass 75 -> 58 us; 37 x 53, 21 labels, TRWP, K = 5, 331 -> 254 us; 4 x 512 x 512, 21 labels, TRWP, K = 5, sweeps 4.17 -> 3.3 ms.
+template <int SEG, int NG, int MU, int RMAX, bool TRWP>
+__global__ void __launch_bounds__(256) mrf_fwd_sweep_packed(const MrfFwdParams P)
+{
+    constexpr int NSEG = NG > 1 ? 1 : 64 / SEG;   // scanlines per wavefront (three segments of 21 lanes leave lane 63 idle)
+    constexpr int NROW = SEG == 21 ? 4 : NSEG;    // LDS rows of h: the idle lane gets one of its own to scribble in
+    constexpr int HR = MU / NG;                   // source labels per group of lanes
+    constexpr int HP = SEG == 21 ? 28 : SEG + 4;  // row stride: an entry per lane, 16-byte rows on different banks
+    constexpr int NCH = HR / 4;                   // groups of four candidates
+    constexpr int NR = 8;                         // ring slots
+    constexpr int NI = 2;                         // index wavefronts
+    constexpr int D = RMAX <= 4 ? 4 : (RMAX == 8 ? 2 : 1);
+    constexpr int NQ = TRWP ? RMAX / 4 : 0;       // TRWP: start term and what is added behind the running message, four by four
+    static_assert(HR % 4 == 0 && (NG == 1 || NG * SEG == 64), "lane groups");
+    __shared__ __align__(16) float hring[NR][NROW][HP];
+    __shared__ __align__(16) float4 inq[NQ > 0 ? NQ : 1][NQ > 0 ? NR : 1][64];
+    __shared__ __align__(16) float2 ind[NR][64];  // TRWP: message of r^-, weight; ISGMR: start term, weight
+    __shared__ float mring[NR][64];
+    // Three scanlines per wavefront, which many wavefronts share a SIMD with: the minima of a lane's groups of four candidates
+    // go to the index wavefronts as well.  (Else the value wavefront's step is what counts, and they form them again: 37 x 530
+    // nodes, 21 labels, TRWP, two scanlines per wavefront 1.36 ms, with the minima handed over 1.48.)
+    constexpr int NC = SEG == 21 ? (NCH + 3) / 4 : 0;
+    __shared__ __align__(16) float4 cring[NC > 0 ? NC : 1][NC > 0 ? NR : 1][64];     // minima of a lane's groups of four candidates
+    __shared__ __align__(16) float vt[SEG][MU + 4];   // V transposed: row lambda
+    __shared__ MrfWaitBlock wait_lds;             // for the waits below (mrf_wait_turn)
+    __shared__ int loaded, valued, indexed[NI];   // last step finished
+    const int L = P.g.L;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int grp = NG > 1 ? lane / SEG : 0, seg = NG > 1 ? 0 : lane / SEG, lam = lane % SEG;
+    const bool valid = lam < L;
+    const int lamc = valid ? lam : 0;
+
+    // this wavefront's scanlines: NSEG consecutive ones of direction r
+    const int blk = (int)blockIdx.x;
+    int ri = 0;
+    while (ri + 1 < P.r_count && blk >= P.pack_begin[ri + 1]) ++ri;
+    const int r = P.r_first + ri;
+    const unsigned nsc = (unsigned)P.g.nscan[r];
+    const unsigned sl = (unsigned)(blk - P.pack_begin[ri]) * NSEG + seg;
+    const bool act_seg = seg < NSEG && sl < (unsigned)P.g.B * nsc;
+    const int dh = P.g.dh[r], dw = P.g.dw[r];
+    const int nstep = dh * P.g.W + dw;
+    int y0 = 0, x0 = 0, len = 0, head = 0;
+    if (act_seg) {
+        const int b = (int)(sl / nsc);
+        mrf_geom_head(P.g.H, P.g.W, dh, dw, sl - (unsigned)b * nsc, y0, x0, len);
+        head = (b * P.g.H + y0) * P.g.W + x0;
+    }
+    // longest scanline of the wavefront bounds the loops
+    int maxlen = 0;
+#pragma unroll
+    for (int sg = 0; sg < NSEG; ++sg) {
+        const int l2 = __builtin_amdgcn_readlane(len, sg * SEG);
+        maxlen = l2 > maxlen ? l2 : maxlen;
+    }
+    const size_t N = (size_t)P.g.N, NL = N * L;
+    const unsigned estep = (unsigned)nstep * (unsigned)L;
+
+    if (threadIdx.x == 0) {
+        loaded = 0; valued = 0;
+        for (int j = 0; j < NI; ++j) indexed[j] = j + 1 - NI;      // "finished" starts one turn before
+        mrf_wait_init(&wait_lds, P.fault, P.spin_limit);
+    }
+    const MrfWaitBlock *const wait_block = &wait_lds;
+    const auto look = [](int *counter) {
+        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    };
+    const auto post = [](int *counter, int n) {          // (written by every lane: the same word, no exec-mask juggling)
+        __hip_atomic_store(counter, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    // Everyone but the loader, whose first loads are under way in the meantime, prepares the LDS: entries mu >= L of the rows
+    // of h stay +inf (they never win); V transposed, all of a thread's loads in one batch.
+    float Vr[HR];                                 // the candidates' column of V
+    if (wave != 1) {
+        constexpr int NT = 192, IT = (SEG * MU + NT - 1) / NT;
+        const int t = wave == 0 ? lane : (int)threadIdx.x - 64;
+        float x[IT];
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            const int e = t + NT * i, l2 = e % SEG, mu = e / SEG;
+            x[i] = (mu < L && l2 < L) ? P.V[(size_t)mu * L + l2] : 0.0f;
+        }
+        for (int e = t; e < NR * NROW * HP; e += NT) (&hring[0][0][0])[e] = INFINITY;
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            const int e = t + NT * i;
+            if (e < SEG * MU) vt[e % SEG][e / SEG] = x[i];
+        }
+        mrf_block_sync_lds();
+#pragma unroll
+        for (int k = 0; k < NCH; ++k) {
+            const float4 x = *reinterpret_cast<const float4 *>(&vt[lam][grp * HR + 4 * k]);
+            Vr[4 * k] = x.x; Vr[4 * k + 1] = x.y; Vr[4 * k + 2] = x.z; Vr[4 * k + 3] = x.w;
+        }
+    }
+    const auto bits = [](float x) { return __builtin_bit_cast(unsigned, x); };
+    const auto real = [](unsigned x) { return __builtin_bit_cast(float, x); };
+
+    if (wave == 0) {
+        // ---- values: step n forms the message of node n ------------------------------------------
+        __builtin_amdgcn_s_setprio(3);
+        bool plain = true;
+#pragma unroll
+        for (int m = 0; m < HR; ++m) plain = plain && !(Vr[m] < 0.0f) && !(grp * HR + m == lam && Vr[m] != 0.0f);
+        const unsigned long long slow = __all(plain) ? 0ull : ~0ull;
+        const float rho = P.rho[r];
+        const auto await = [&](int n) {
+            int turns = 0;
+            while (look(&loaded) < n) mrf_wait_turn(wait_block, turns);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        };
+        const auto label_min = [&](float x) {
+            if constexpr (NG == 2) return mrf_segment_min32_regs(x, 0);         // (both halves hold every label)
+            else if constexpr (SEG == 16) {
+                asm("s_nop 1\n\t"
+                    "v_min_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+                    "s_nop 1\n\t"
+                    "v_min_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+                    "s_nop 1\n\t"
+                    "v_min_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                    "s_nop 1\n\t"
+                    "v_min_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+                    : "+v"(x));
+                return x;
+            } else if constexpr (SEG == 32) return mrf_segment_min32_regs(x, lane);
+            else return mrf_segment_min<SEG>(x);
+        };
+        if (maxlen < 2) return;
+        float4 q4[NQ > 0 ? NQ : 1];
+        float2 d2;
+        const auto fetch = [&](int slot) {
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) q4[k] = inq[k][slot][lane];
+            d2 = ind[slot][lane];
+        };
+        const auto arrived = [&]() {
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) asm volatile("" : : "v"(q4[k].x), "v"(q4[k].y), "v"(q4[k].z), "v"(q4[k].w));
+            asm volatile("" : : "v"(d2.x), "v"(d2.y));
+        };
+        await(1);
+        fetch(0);
+        arrived();
+        float carry = 0.0f;
+        for (int n = 1;;) {
+#pragma unroll
+            for (int u = 0; u < NR; ++u, ++n) {          // step n uses slot u = (n - 1) % NR
+                float v, wgt = d2.y;
+                if constexpr (TRWP) {
+                    v = q4[0].x + carry;
+#pragma unroll
+                    for (int c = 1; c < RMAX; ++c) v = v + (c % 4 == 0 ? q4[c / 4].x : (c % 4 == 1 ? q4[c / 4].y : (c % 4 == 2 ? q4[c / 4].z : q4[c / 4].w)));
+                    v = rho * v;
+                    v = v - d2.x;
+                } else {
+                    v = d2.x + carry;
+                }
+                v = valid ? v : INFINITY;
+                hring[u][seg][lam] = v;                  // (groups write the same values to the same places)
+                mrf_wave_lds_fence();
+                float4 hv[NCH];
+#pragma unroll
+                for (int k = 0; k < NCH; ++k) hv[k] = *reinterpret_cast<const float4 *>(&hring[u][seg][grp * HR + 4 * k]);
+                // in the same batch: the loader's counter, then (LDS keeps this order) the next node
+                const int seen = __hip_atomic_load(&loaded, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                fetch((u + 1) & (NR - 1));
+                __builtin_amdgcn_sched_barrier(0);
+                float tq;
+                if constexpr (SEG != 21) tq = label_min(v);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (SEG == 21) {
+                    // (segments that do not line up with the rows of 16 lanes: a lane has all of h by now)
+                    tq = mrf_min3(hv[0].x, hv[0].y, mrf_min(hv[0].z, hv[0].w));
+#pragma unroll
+                    for (int k = 1; k < NCH; ++k) tq = mrf_min3(mrf_min3(tq, hv[k].x, hv[k].y), hv[k].z, hv[k].w);
+                }
+                float cm[NCH], best;
+#pragma unroll
+                for (int k = 0; k < NCH; ++k) {
+                    const float e0 = __builtin_fmaf(wgt, Vr[4 * k], hv[k].x), e1 = __builtin_fmaf(wgt, Vr[4 * k + 1], hv[k].y);
+                    const float e2 = __builtin_fmaf(wgt, Vr[4 * k + 2], hv[k].z), e3 = __builtin_fmaf(wgt, Vr[4 * k + 3], hv[k].w);
+                    if constexpr (NC > 0) {
+                        cm[k] = mrf_min(mrf_min3(e0, e1, e2), e3);
+                    } else {
+                        best = k == 0 ? mrf_min(e0, e1) : mrf_min3(best, e0, e1);
+                        best = mrf_min3(best, e2, e3);
+                    }
+                }
+                if constexpr (NC > 0) {
+                    best = cm[0];
+#pragma unroll
+                    for (int k = 1; k + 1 < NCH; k += 2) best = mrf_min3(best, cm[k], cm[k + 1]);
+                    if constexpr (NCH % 2 == 0) best = mrf_min(best, cm[NCH - 1]);
+                }
+                if constexpr (NG == 4) {
+                    const auto x = __builtin_amdgcn_permlane16_swap(bits(best), bits(best), false, false);
+                    best = mrf_min(real(x[0]), real(x[1]));
+                }
+                if constexpr (NG >= 2) {
+                    const auto x = __builtin_amdgcn_permlane32_swap(bits(best), bits(best), false, false);
+                    best = mrf_min(real(x[0]), real(x[1]));
+                }
+                if (__builtin_expect((__ballot(!(wgt >= 0.0f)) | slow) != 0, 0)) tq = label_min(valid ? best : INFINITY);
+                carry = best - tq;
+                // (the next node's values are waited for here, where only reads are under way: behind the writes below the
+                // wait would be for those)
+                arrived();
+                // (what is behind the last group repeats it)
+#pragma unroll
+                for (int k = 0; k < NC; ++k)
+                    cring[k][u][lane] = make_float4(cm[4 * k < NCH ? 4 * k : 0], cm[4 * k + 1 < NCH ? 4 * k + 1 : NCH - 1], cm[4 * k + 2 < NCH ? 4 * k + 2 : NCH - 1],
+                                                    cm[4 * k + 3 < NCH ? 4 * k + 3 : NCH - 1]);
+                mring[u][lane] = carry;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");      // (LDS keeps a wavefront's operations in order)
+                post(&valued, n);
+                if (n + 1 >= maxlen) return;             // (uniform)
+                if (__builtin_expect(__builtin_amdgcn_readfirstlane(seen) <= n, 0)) {
+                    await(n + 1);
+                    fetch((u + 1) & (NR - 1));
+                    arrived();
+                }
+            }
+        }
+    }
+
+    if (wave == 1) {
+        // ---- loader ------------------------------------------------------------------------------
+        // Sources of h in summation order: the unary, then message arrays; unused slots load 0 and enter with factor 0
+        // (fma(0, 0, v) = v and fma(1, x, v) = v + x exactly).  r^- once more by itself.
+        __builtin_amdgcn_s_setprio(3);
+        const int n_pre = P.n_pre[r], n_src = P.n_src[r], rm_slot = P.rm_slot[r];
+        mrf_buf src[RMAX];
+        float before[RMAX], after[RMAX];
+        src[0] = mrf_buffer(P.unary + (size_t)__builtin_amdgcn_readfirstlane((int)P.unary_slab[r]) * NL, NL * 4);
+#pragma unroll
+        for (int c = 1; c < RMAX; ++c) {
+            const bool live = c <= n_src;
+            const size_t d = (size_t)__builtin_amdgcn_readfirstlane(live ? (int)P.src_dir[r][c - 1] : 0);
+            src[c] = mrf_buffer(P.m_in + d * NL, live ? NL * 4 : 0);
+            before[c] = live && (!TRWP || c <= n_pre) ? 1.0f : 0.0f;
+            after[c] = live && TRWP && c > n_pre ? 1.0f : 0.0f;
+        }
+        const bool has_rm = TRWP && rm_slot >= 0;
+        const mrf_buf brm = mrf_buffer(P.m_in + (size_t)__builtin_amdgcn_readfirstlane(has_rm ? (int)P.src_dir[r][has_rm ? rm_slot : 0] : 0) * NL,
+                                       has_rm ? NL * 4 : 0);
+        const mrf_buf bw = mrf_buffer(P.w + (P.w_mul ? (size_t)r * N : 0), P.w_mul ? N * 4 : 4);
+        struct In {
+            float v[RMAX];
+            float rm, w;
+        };
+        In A[D], B[D];
+        // (what is loaded past a scanline's end is another node or 0, and never used)
+        unsigned pe = ((unsigned)head * (unsigned)L + (unsigned)lamc) << 2;
+        unsigned pw = P.w_mul ? (unsigned)(head + nstep) << 2 : 0u;
+        const unsigned pe_step = estep << 2, pw_step = P.w_mul ? (unsigned)nstep << 2 : 0u;
+        auto prefetch = [&](In &in) {
+#pragma unroll
+            for (int c = 0; c < RMAX; ++c) in.v[c] = mrf_buf_f32(src[c], pe);
+            in.rm = TRWP ? mrf_buf_f32(brm, pe) : 0.0f;
+            in.w = mrf_buf_f32(bw, pw);
+            pe += pe_step;
+            pw += pw_step;
+        };
+        int freed = 0;                           // steps up to this one have left the ring
+        auto group = [&](const In (&in)[D], int n0) {
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                const int n = n0 + u;
+                float base = in[u].v[0];
+#pragma unroll
+                for (int c = 1; c < RMAX; ++c) base = __builtin_fmaf(before[c], in[u].v[c], base);
+                if (n >= maxlen) break;          // (uniform)
+                int turns = 0;
+                while (freed < n - NR) {
+                    // the index wavefronts take the steps in turn: behind the slowest one's last step, the others have
+                    // finished theirs
+                    const int i0 = look(&indexed[0]), i1 = look(&indexed[1]);
+                    freed = (i0 < i1 ? i0 : i1) + NI - 1;
+                    if (freed < n - NR) mrf_wait_turn(wait_block, turns);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                }
+                const int slot = (n - 1) & (NR - 1);
+                if constexpr (TRWP) {
+                    float a[RMAX];
+                    a[0] = base;
+#pragma unroll
+                    for (int c = 1; c < RMAX; ++c) a[c] = after[c] * in[u].v[c];
+#pragma unroll
+                    for (int k = 0; k < NQ; ++k) inq[k][slot][lane] = make_float4(a[4 * k], a[4 * k + 1], a[4 * k + 2], a[4 * k + 3]);
+                    ind[slot][lane] = make_float2(in[u].rm, in[u].w);
+                } else {
+                    ind[slot][lane] = make_float2(base, in[u].w);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                post(&loaded, n);
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < D; ++u) prefetch(A[u]);
+        mrf_block_sync_lds();
+        for (int n0 = 1; n0 < maxlen; n0 += 2 * D) {
+#pragma unroll
+            for (int u = 0; u < D; ++u) prefetch(B[u]);
+            __builtin_amdgcn_sched_barrier(0);
+            group(A, n0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < D; ++u) prefetch(A[u]);
+            __builtin_amdgcn_sched_barrier(0);
+            group(B, n0 + D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return;
+    }
+
+    // ---- index: p, q and all stores; wavefront jw takes steps 1 + jw, 1 + jw + NI, ... -------------------
+    const int jw = wave - 2;
+    const mrf_buf bm = mrf_buffer(P.m_out + (size_t)r * NL, NL * 4), bp = mrf_buffer(P.p + (size_t)r * NL, NL);
+    const mrf_buf bq = mrf_buffer(P.q + (size_t)r * N, N);
+    const bool mine = act_seg && valid && grp == 0;
+    unsigned oe = (unsigned)head * (unsigned)L + (unsigned)lam, on = (unsigned)head;
+    if (jw == 0) {
+        // first node of the scanline: message 0, p = q = 0
+        mrf_buf_store_f32(bm, mine ? oe << 2 : MRF_BUF_NONE, 0.0f);
+        mrf_buf_store_u8(bp, mine ? oe : MRF_BUF_NONE, 0);
+        mrf_buf_store_u8(bq, mine && lam == 0 ? on : MRF_BUF_NONE, 0);
+    }
+    const int len_m = mine ? len : 0, len_q = mine && lam == 0 ? len : 0;
+    oe += (unsigned)jw * estep;
+    on += (unsigned)(jw * nstep);
+    int seen = 0;
+    oe += estep;
+    on += (unsigned)nstep;
+    for (int n = 1 + jw; n < maxlen; n += NI) {
+        int turns = 0;
+        while (seen < n) {
+            seen = look(&valued);
+            if (seen < n) mrf_wait_turn(wait_block, turns);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        const int slot = (n - 1) & (NR - 1);
+        const float wgt = ind[slot][lane].y, m = mring[slot][lane];
+        const float *hr = &hring[slot][seg][grp * HR], *vr = &vt[lam][grp * HR];
+        // lowest group of four that attains the minimum of all, then the lowest of its candidates, formed once more
+        float best = 0.0f;
+        int ck = NCH - 1;
+        if constexpr (NC > 0) {
+            float4 c4[NC];
+#pragma unroll
+            for (int k = 0; k < NC; ++k) c4[k] = cring[k][slot][lane];
+            best = mrf_min(mrf_min3(c4[0].x, c4[0].y, c4[0].z), c4[0].w);
+            if constexpr (NC > 1) best = mrf_min(mrf_min3(best, c4[NC - 1].x, c4[NC - 1].y), mrf_min(c4[NC - 1].z, c4[NC - 1].w));
+            // (of the repeated ones the lowest index, which is looked at last, is the one that stands)
+            if constexpr (NC > 1) mrf_first_equal4<4>(ck, best, c4[NC - 1].x, c4[NC - 1].y, c4[NC - 1].z, c4[NC - 1].w);
+            mrf_first_equal4<0>(ck, best, c4[0].x, c4[0].y, c4[0].z, c4[0].w);
+        } else if constexpr (NCH > 1) {
+            float cm[NCH];
+#pragma unroll
+            for (int k = 0; k < NCH; ++k) {
+                const float4 hk = *reinterpret_cast<const float4 *>(hr + 4 * k);
+                const float e0 = __builtin_fmaf(wgt, Vr[4 * k], hk.x), e1 = __builtin_fmaf(wgt, Vr[4 * k + 1], hk.y);
+                const float e2 = __builtin_fmaf(wgt, Vr[4 * k + 2], hk.z), e3 = __builtin_fmaf(wgt, Vr[4 * k + 3], hk.w);
+                cm[k] = mrf_min(mrf_min3(e0, e1, e2), e3);
+            }
+            best = cm[0];
+#pragma unroll
+            for (int k = 1; k + 1 < NCH; k += 2) best = mrf_min3(best, cm[k], cm[k + 1]);
+            if constexpr (NCH % 2 == 0) best = mrf_min(best, cm[NCH - 1]);
+            // (where there are not four or eight they overlap or repeat: the lowest index wins all the same)
+            if constexpr (NCH > 4) mrf_first_equal4<NCH - 4>(ck, best, cm[NCH - 4], cm[NCH - 3], cm[NCH - 2], cm[NCH - 1]);
+            mrf_first_equal4<0>(ck, best, cm[0], cm[1], cm[NCH > 2 ? 2 : NCH - 1], cm[NCH > 3 ? 3 : NCH - 1]);
+        }
+        const float4 va = *reinterpret_cast<const float4 *>(vr + 4 * ck), hv = *reinterpret_cast<const float4 *>(hr + 4 * ck);
+        const float d0 = __builtin_fmaf(wgt, va.x, hv.x), d1 = __builtin_fmaf(wgt, va.y, hv.y);
+        const float d2 = __builtin_fmaf(wgt, va.z, hv.z), d3 = __builtin_fmaf(wgt, va.w, hv.w);
+        if constexpr (NCH == 1) best = mrf_min(mrf_min3(d0, d1, d2), d3);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        post(&indexed[jw], n);
+        int arg = 3;
+        mrf_first_equal4<0>(arg, best, d0, d1, d2, d3);
+        arg += 4 * ck;
+        if constexpr (NG > 1) {
+            // join the groups: a strict '<' keeps the lower group's index on a tie
+            arg += grp * HR;
+            if constexpr (NG == 4) {
+                const auto x = __builtin_amdgcn_permlane16_swap(bits(best), bits(best), false, false);
+                const auto a = __builtin_amdgcn_permlane16_swap((unsigned)arg, (unsigned)arg, false, false);
+                arg = real(x[1]) < real(x[0]) ? (int)a[1] : (int)a[0];
+                best = mrf_min(real(x[0]), real(x[1]));
+            }
+            const auto x = __builtin_amdgcn_permlane32_swap(bits(best), bits(best), false, false);
+            const auto a = __builtin_amdgcn_permlane32_swap((unsigned)arg, (unsigned)arg, false, false);
+            arg = real(x[1]) < real(x[0]) ? (int)a[1] : (int)a[0];
+        }
+        arg = arg < L ? arg : L - 1;
+        // the message is 0 exactly where it attains its minimum
+        const unsigned long long zero = __ballot((int)valid & (int)(m == 0.0f));
+        const int qidx = mrf_segment_first<SEG>(zero, lane);
+        mrf_buf_store_f32(bm, n < len_m ? oe << 2 : MRF_BUF_NONE, m);
+        mrf_buf_store_u8(bp, n < len_m ? oe : MRF_BUF_NONE, arg);
+        mrf_buf_store_u8(bq, n < len_q ? on : MRF_BUF_NONE, qidx);
+        oe += NI * estep;
+        on += (unsigned)(NI * nstep);
     }
 }
 

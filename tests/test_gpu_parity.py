@@ -1470,6 +1470,43 @@ EDGE_TABLE_CASES = [
 ]
 
 
+# label counts around the multiples of four and the segments, one scanline per wavefront (knob value 4), several (5), three
+# (knob 13); rings that wrap, scanlines of one and two nodes, counts that fill no wavefront; 3, 7 and 15 source arrays
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(L, R, algo) for L in (1, 4, 5, 8, 9, 12, 13, 16, 17, 20, 21, 22, 24, 25, 28, 29, 31, 32)
+                                  for R, algo in ((4, "trwp"), (4, "isgmr"), (8, "trwp"), (16, "trwp"), (16, "isgmr"))
+                                  if R == 4 or L in (8, 16, 21, 32)], ids=lambda c: "%d_%d_%s" % c)
+def test_packed_sweep_divided_among_four_wavefronts(oracle, case):
+    """Against the oracle and bit for bit against the sweep with one wavefront: V >= 0 with a zero diagonal (the minimum of h
+    is taken for that of the message) and general V with negative weights (it is not), ties."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    print("case divided", case, flush=True)
+    L, R, algo = case
+    dirs = DIRS16 if R == 16 else DIRS8 if R == 8 else DIRS4
+    for plain, iv, (B, H, W) in ((True, False, (2, 3, 37)), (False, False, (1, 7, 19)), (True, True, (1, 1, 12)), (False, True, (3, 5, 2))):
+        pr = random_problem(600 + L, algo, B, H, W, L, dirs, 2, integer_valued=iv, per_edge=True, symmetric=False, rho=np.linspace(0.3, 0.9, R))
+        if plain:
+            pr.pairwise, pr.edge_weight = np.abs(pr.pairwise), np.abs(pr.edge_weight)
+            np.fill_diagonal(pr.pairwise, 0.0)
+        else:
+            sign = np.where(np.random.default_rng(L).random(pr.edge_weight.shape) > 0.1, 1.0, -0.5)
+            pr.edge_weight = (pr.edge_weight * sign).astype(np.float32)
+        f = oracle_forward(oracle, pr)
+        out = []
+        try:
+            for knobs in ((4, 1), (5, 1), (2, 2), (1, 1)) if 16 < L <= 21 else ((4, 1), (5, 1), (1, 1)):
+                assert mrf.mrf_tune(3, 2) == 0 and mrf.mrf_tune(11, knobs[0]) == 0 and mrf.mrf_tune(13, knobs[1]) == 0
+                out.append(run_gpu(pr, backward=False))
+                check_forward(out[-1], f)
+                assert mrf.mrf_last_sweep_kernel(False) == ("mrf_fwd_sweep_narrow" if knobs[0] == 1 else "mrf_fwd_sweep_packed")
+                for name in ("p", "q", "labels", "cost", "messages"):
+                    np.testing.assert_array_equal(getattr(out[0], name), getattr(out[-1], name), err_msg=name)
+        finally:
+            for k in (3, 11, 13):
+                mrf.mrf_tune(k, 0)
+
+
 @pytest.mark.parametrize("case", EDGE_TABLE_CASES, ids=lambda c: "seed%d" % c[0])
 def test_pairwise_potentials_given_per_edge(oracle, case):
     """Pairwise potentials as one L x L table per directed edge (Eq. isgmr / Eq. trwp as written)
