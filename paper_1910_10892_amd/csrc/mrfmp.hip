@@ -148,8 +148,8 @@ MRF_G(int g_tune_pack, 0);       // 0 auto, 1 never, 2 whenever L <= 32
 MRF_G(int g_tune_duo, 0);        // 0 auto, 1 never, 2 whenever the window applies
 MRF_G(int g_tune_duo_ni, 0);     // index wavefronts per scanline: 0 auto, 1, 2
 MRF_G(int g_tune_loader, 0);     // loader wavefront in the window sweep: 0 auto, 1 never, 2 whenever possible
-MRF_G(int g_tune_squad, 0);      // index wavefronts next to the split layout: 0 by launch size, 1 never, 2 always
-MRF_G(int g_tune_squad_ni, 0);   // how many: 0 auto, 4, 8
+MRF_G(int g_tune_squad, 0);      // loader and index wavefronts next to the split layout: 0 by launch size, 1 never, 2 always
+MRF_G(int g_tune_squad_ni, 0);   // how many of both: 0 auto, 4, 8
 MRF_G(int g_tune_pack3, 0);      // three scanlines per wavefront for 17..21 labels: 0 by launch size, 1 never, 2 always
 MRF_G(int g_tune_isgmr_lazy, 0); // ISGMR backward without a combine pass per iteration (up to 4 directions): 0 auto, 1 never
 MRF_G(int g_tune_isgmr_presum, 0); // ISGMR forward with the per-pair sums of the previous iteration formed once: 0 from six directions, 1 never, 2 always
@@ -803,20 +803,34 @@ hipError_t dispatch_fwd(MrfFwdParams &P, int algo, int tw, long long blocks, hip
             if (P.n_src[r] > ms) ms = P.n_src[r];
         // few scanlines in the launch and many labels: spread each node step over one
         // wavefront per 64 labels
-        // (wide windows over many labels only: otherwise the value/index pair below is faster)
         // (measured with four directions: window 16, 192 or 256 labels, ISGMR with 1,536 to 3,072 scanlines: 2.2
         // against 3.8 ms, 2.6 against 5.4 ms, 5.0 against 7.2 ms, 7.3 against 8.2 ms for the next best layout; window
-        // 8, 192 or 256 labels: the value/index pair is ahead, TRWP 2.3 against 3.9 ms, ISGMR 1.3 against 1.6 ms)
+        // 8, 192 or 256 labels: the value/index pair is ahead)
         const int tws = tw == 4 ? 8 : (tw == 12 ? 16 : tw);      // (these two layouts exist for windows 2, 8 and 16: a wider window is as exact)
-        const bool split = !generic && LPw > 1 && g_tune_split != 1 &&
-                           (g_tune_split == 2 || (LPw >= 3 && tws >= 16 && blocks * LPw <= 16384));
-        if (ms + 1 <= 8 && split && g_tune_squad != 1 && (g_tune_squad == 2 || blocks <= 512)) {
-            // the value wavefronts of the split layout, with the index work on wavefronts of their own
+        const bool split_ok = !generic && LPw > 1 && g_tune_split != 1 && ms + 1 <= 8;
+        const bool split = split_ok && (g_tune_split == 2 || (LPw >= 3 && tws >= 16 && blocks * LPw <= 16384));
+        // Those value wavefronts with a loader and index wavefronts beside them (forward pass, against the better of the
+        // value/index pair and the split layout):
+        // - window 16 (and 12 beyond 128 labels): TRWP 256 x 256, 256 labels, K = 2 1.16 / 1.65 ms with index wavefronts alone beside
+        //   them and every neighbour read by itself; K = 1: 600 scanlines 3.06 / 3.32, with 128 labels 2.27 / 2.92, 700 with 200 labels
+        //   4.28 / 4.11; ISGMR 512 scanlines, K = 2, 256 labels 0.25 / 0.34, 128 labels 0.16 / 0.20
+        // - window 8 beyond 128 labels: TRWP, K = 2, 256 scanlines 1.03 / 1.32, 512 1.76 / 2.17, 600 level; eight directions, K = 1, 655
+        //   scanlines 1.75 / 1.95; ISGMR 512 scanlines 0.185 / 0.223, 600 0.335 / 0.320
+        // - window 8, 65..128 labels: behind the pair with its loader (TRWP, up to three source arrays: 0.61 / 0.54), ahead with more
+        //   (eight directions: 499 scanlines 1.58 / 1.79, 767 1.32 / 1.17) and for ISGMR to 256 scanlines (65.6 / 68.2 us)
+        // (eight beside the values where a scanline has a compute unit to itself and more than 128 labels: 1.16 / 1.36 ms at 256
+        // scanlines of 256 labels, but 1.75 / 1.44 at 512 of 96)
+        const bool many = ms + 1 > 4;
+        const long long squad_max = tw == 16 || (tw == 12 && LPw >= 3) ? 640
+                                    : (tw != 8 ? 0 : (LPw >= 3 ? (many ? 656 : 512) : (many ? 512 : (algo == MRF_ISGMR ? 256 : 0))));
+        const bool squad = split_ok && g_tune_squad != 1 && (long long)P.g.H * P.g.W * P.g.L <= MRF_BUF_MOST &&
+                           ((g_tune_split == 2 && g_tune_squad == 2) || (g_tune_split == 0 && g_tune_duo == 0 && blocks <= squad_max));
+        if (squad) {
             P.NW = LPw;
-            const int ni = (g_tune_squad_ni == 4 || g_tune_squad_ni == 8) ? g_tune_squad_ni : 8;
+            const int ni = (g_tune_squad_ni == 4 || g_tune_squad_ni == 8) ? g_tune_squad_ni : (LPw >= 3 && blocks <= 256 ? 8 : 4);
             return run_window_squad(P, algo, tws, ni, ms, blocks, st);
         }
-        if (ms + 1 <= 8 && split) {
+        if (split) {
             P.NW = LPw;
             return run_window_split(P, algo, tws, ms, blocks, st);
         }

@@ -29,7 +29,7 @@
 //   mrf_fwd_sweep_window_duo    the same with the dependency chain (values) on one wavefront and
 //                               index / loader wavefronts beside it, connected by LDS rings
 //   mrf_fwd_sweep_window_split  the same, one wavefront per 64 labels in lock step
-//   mrf_fwd_sweep_window_squad  value wavefronts per 64 labels plus index wavefronts per node
+//   mrf_fwd_sweep_window_squad  value wavefronts per 64 labels, a loader, index wavefronts per node
 // Which one a launch gets is host arithmetic on the launch shape (dispatch_fwd).
 #pragma once
 
@@ -2440,32 +2440,50 @@ mrf_fwd_sweep_window_split(const MrfFwdParams P)
     }
 }
 
-// ---- window sweep: value wavefronts per 64 labels, index wavefronts per node -----------------
+// ---- window sweep: value wavefronts per 64 labels, a loader and index wavefronts ----------------------
 //
-// Both ideas above together, for wide windows over many labels in small launches.  NWV =
-// ceil(L/64) value wavefronts walk the scanline in lock step as in mrf_fwd_sweep_window_split
-// but compute the values of the new message only; NI index wavefronts take the nodes in
-// turn as in mrf_fwd_sweep_window_duo, each doing the argmin bookkeeping of a whole node (all
-// labels) and the stores.  The value wavefronts publish h through a ring; all of a node's
-// entries are written before the node's barrier, so the wavefront that raises the counter
-// after the barrier needs no further wait.
+// Both ideas above together, for launches of few scanlines: NWV = ceil(L/64) value wavefronts walk the scanline in lock step
+// and compute the values of the new message only; of the NI wavefronts beside them the first does all loads and the part
+// of h that does not wait for the running message, the others take the nodes in turn and do the argmin tables (all labels
+// of a node) and the stores.  What bounds the sweep is the value wavefronts' node step, so
+// - the window is shared among the lanes: the four lanes of a quad hold four neighbouring labels, each evaluates a quarter of
+//   the distances for all four of them and two exchanges inside the quad leave every lane with its own label's minimum.  A
+//   lane then reads 4 TW / 8 neighbours in wide reads instead of 2 TW - 2 single ones (31 reads of a node's 256 labels by
+//   every value and index wavefront took a quarter of the node step in LDS bandwidth alone),
+// - nothing waits for its own writes, and the wave-wide minimum of h runs while the neighbours are on their way,
+// - value wavefronts meet twice without waiting twice: a flag says that a wavefront's h is in the ring (needed for the
+//   neighbours), a post carries its minimum (needed behind the window).  The hardware barrier would also wait for the others.
+// LDS executes a wavefront's operations in order, so whoever sees a flag, a post or a counter also sees what that wavefront
+// wrote before it.  A value wavefront is at most one step ahead of the slowest, whose flag it needs: posts alternate between
+// two sets.  The loader fills a slot of the h ring's step once the index wavefronts have left it (NR steps back) and its own
+// once the value wavefronts have (NRL steps back); no wait can depend on itself.
+// TRWP, 256 x 256, 256 labels, window 16, K = 10: sweeps 8.27 ms with index wavefronts alone beside the values and every neighbour
+// read by itself, now 5.8; window 8, K = 2: 1.32 ms (mrf_fwd_sweep_window_duo), now 1.03.  What is left: a quarter of the step is the
+// value wavefronts waiting for each other (K = 2: 1.16 ms, 0.93 without looking at flags and posts).
+// (four wavefronts per SIMD with four beside the values, so that two scanlines share a compute unit)
 template <int RMAX, int D, bool TRWP, int TW, int NI>
-__global__ void __launch_bounds__(64 * (4 + NI))
+__global__ void __launch_bounds__(64 * (4 + NI), NI <= 4 ? 4 : 3)
 mrf_fwd_sweep_window_squad(const MrfFwdParams P)
 {
-    constexpr int HB = 256 + 2 * TW;
-    constexpr int NR = 8;                          // ring slots
-    constexpr int LPI = 4;                         // label slots of an index wavefront
-    static_assert(NR >= D && (NR & (NR - 1)) == 0 && NI >= 1 && NI <= 8, "ring depth");
-    __shared__ float ring[NR][HB];
-    __shared__ float ringw[NR];
+    constexpr int PAD = TW < 4 ? 4 : TW;           // +inf beside the labels
+    constexpr int HB = 256 + 2 * PAD;
+    constexpr int NR = 8;                          // slots of the rings of h and of the new message
+    constexpr int NRL = RMAX <= 4 ? 8 : 4;         // slots of the loader's ring
+    constexpr int NX = NI - 1;                     // index wavefronts
+    constexpr int NQ = TRWP ? RMAX / 4 : 0;        // TRWP: start term and what is added behind the running message, four by four
+    static_assert(NX >= 1 && NX <= 7, "index wavefronts");
+    __shared__ __align__(16) float hring[NR][HB];
+    __shared__ __align__(16) float tring[NR][256];           // the new message before normalisation
+    __shared__ __align__(16) float2 mring[NR];               // minimum of h, of the new message
+    __shared__ __align__(16) float4 inq[NQ > 0 ? NQ : 1][NQ > 0 ? NRL : 1][256];
+    __shared__ __align__(16) float inr[NRL][256];            // TRWP: message of r^-; ISGMR: start term
+    __shared__ float lw[NR];                                 // edge weight
     __shared__ float ftab[TW + 1];
-    // exchanges among the value wavefronts: {step, float} per wavefront, two sets by step parity
-    __shared__ __align__(16) unsigned long long hmx[2][4];     // local minima of h
-    __shared__ __align__(16) unsigned long long tmx[2][4];     // local minima of the new message (general path)
-    __shared__ int produced;
-    __shared__ MrfWaitBlock wait_lds;             // for the waits below (mrf_wait_turn)
-    __shared__ __align__(16) int consumed[8];
+    __shared__ __align__(16) unsigned long long hmx[2][4];   // posts {step, minimum} per value wavefront: of h
+    __shared__ __align__(16) unsigned long long tmx[2][4];   // of the new message (general path)
+    __shared__ __align__(16) int hflag[4], valued[4], indexed[8];    // last step done, per wavefront
+    __shared__ int loaded;
+    __shared__ MrfWaitBlock wait_lds;              // for the waits below (mrf_wait_turn)
     const int L = P.g.L;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -2481,328 +2499,481 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
+    len = __builtin_amdgcn_readfirstlane(len);               // uniform, and known to be
     const long long N = P.g.N;
-    const long long head = ((long long)b * P.g.H + y0) * P.g.W + x0;
-    const long long nstep = (long long)dh * P.g.W + dw;
-    const float vz = mrf_opaque_zero_f();     // keeps uniform constants in vector registers
+    const long long head = ((long long)__builtin_amdgcn_readfirstlane(b) * P.g.H + __builtin_amdgcn_readfirstlane(y0)) * P.g.W +
+                           __builtin_amdgcn_readfirstlane(x0);
+    const long long nstep = (long long)dh * P.g.W + dw, estep = nstep * L;
 
-    float f[TW];
-#pragma unroll
-    for (int d = 0; d < TW; ++d) f[d] = P.V[d < L ? d : L - 1] + vz;
-    const float fT = P.V[L - 1] + vz;
-    const bool f0zero = (P.V[0] == 0.0f);
-    if ((int)threadIdx.x <= TW) ftab[threadIdx.x] = (int)threadIdx.x < TW ? P.V[(int)threadIdx.x < L ? threadIdx.x : L - 1] : fT;
-    // padding and the entries of labels >= L are never written again: they never win a strict '<'
-    for (int i = threadIdx.x; i < NR * HB; i += blockDim.x) (&ring[0][0])[i] = INFINITY;
+    if ((int)threadIdx.x <= TW) ftab[threadIdx.x] = P.V[(int)threadIdx.x < TW && (int)threadIdx.x < L ? threadIdx.x : L - 1];
+    // padding and the entries of labels >= L are never anything else: they never win a strict '<'
+    for (int i = threadIdx.x; i < NR * HB; i += blockDim.x) (&hring[0][0])[i] = INFINITY;
     if (threadIdx.x < 8) {
-        (&hmx[0][0])[threadIdx.x] = 0ull;                      // step 0: no step waits for it
-        (&tmx[0][0])[threadIdx.x] = 0ull;
-        consumed[threadIdx.x] = (int)threadIdx.x + 1 - NI;     // "finished" starts one turn before
+        // wavefronts that are not there have always arrived, with nothing
+        const bool here = (int)(threadIdx.x & 3) < NWV;
+        const unsigned long long none = here ? 0ull : ((0x7fffffffull << 32) | 0x7f800000ull);
+        (&hmx[0][0])[threadIdx.x] = none;
+        (&tmx[0][0])[threadIdx.x] = none;
+        if (threadIdx.x < 4) { hflag[threadIdx.x] = here ? 0 : 0x7fffffff; valued[threadIdx.x] = here ? 0 : 0x7fffffff; }
+        indexed[threadIdx.x] = (int)threadIdx.x < NX ? (int)threadIdx.x + 1 - NX : 0x7fffffff;     // "finished" starts one turn before
     }
-    if (threadIdx.x == 0) { produced = 0; mrf_wait_init(&wait_lds, P.fault, P.spin_limit); }
+    if (threadIdx.x == 0) { loaded = 0; mrf_wait_init(&wait_lds, P.fault, P.spin_limit); }
     const MrfWaitBlock *const wait_block = &wait_lds;
     __syncthreads();
+    const auto look = [](const int *counter) {
+        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    };
+    const auto look4 = [&](const int *counter) {             // the least of four
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int4 x = *reinterpret_cast<const int4 *>(counter);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        return __builtin_amdgcn_readfirstlane(min(min(x.x, x.y), min(x.z, x.w)));
+    };
+    const auto post = [](int *counter, int n) {              // (written by every lane: the same word, no exec-mask juggling)
+        __hip_atomic_store(counter, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
 
-    // the value wavefronts go first wherever they share a SIMD with index wavefronts
-    if (wv < NWV) __builtin_amdgcn_s_setprio(3);
-    if (wv >= NWV) {
-        // ---- p, q and all stores: index wavefront jw takes steps 1 + jw, 1 + jw + NI, ... ------
-        const int jw = wv - NWV;
-        if (jw == 0) {
+    if (wv < NWV) {
+        // ---- values: wavefront wv owns labels 64 wv .. 64 wv + 63; step n forms the message of node n ----
+        __builtin_amdgcn_s_setprio(3);             // they and the loader go first wherever they share a SIMD with others
+        if (len < 2) return;
+        constexpr int QD = TW >= 8 ? TW / 4 : 0;   // distances of a lane (TW < 8: all of its own label's)
+        const int lam = 64 * wv + lane, quarter = lane & 3, quad = lam & ~3;
+        const bool valid = lam < L;
+        const float rho = P.rho[r], fT = ftab[TW];
+        const bool f0zero = ftab[0] == 0.0f;
+        float f[QD > 0 ? QD : TW];
 #pragma unroll
-            for (int s = 0; s < LPI; ++s) {
-                const int lam = lane + 64 * s;
-                if (lam < L) {
-                    P.m_out[((size_t)r * N + head) * L + lam] = 0.0f;
-                    P.p[((size_t)r * N + head) * L + lam] = 0;
+        for (int e = 0; e < (QD > 0 ? QD : TW); ++e) f[e] = ftab[QD * quarter + e];
+        const auto run = [&](auto several) {
+            constexpr bool MULTI = decltype(several)::value;
+            float4 q4[NQ > 0 ? NQ : 1];
+            float dr, wgt;
+            const auto fetch = [&](int ls, int slot) {
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) q4[k] = inq[k][ls][lam];
+                dr = inr[ls][lam];
+                wgt = lw[slot];
+            };
+            const auto arrived = [&]() {
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) asm volatile("" : : "v"(q4[k].x), "v"(q4[k].y), "v"(q4[k].z), "v"(q4[k].w));
+                asm volatile("" : : "v"(dr), "v"(wgt));
+            };
+            const auto await = [&](int n) {
+                int turns = 0;
+                while (look(&loaded) < n) mrf_wait_turn(wait_block, turns);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+            };
+            // posts {step n, x} and returns the least of all wavefronts' x once all have posted step n
+            const auto post_min = [&](unsigned long long (&box)[2][4], int n, float x) {
+                __hip_atomic_store(&box[n & 1][wv], ((unsigned long long)(unsigned)n << 32) | (unsigned)__float_as_int(x),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            };
+            int4 e4[2];                                      // {minimum, step} of wavefronts 0, 1 and of 2, 3
+            const auto read_posts = [&](unsigned long long (&box)[2][4], int n) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) e4[k] = *reinterpret_cast<const int4 *>(&box[n & 1][2 * k]);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            };
+            const auto missing = [&](int n) {
+                return __builtin_amdgcn_readfirstlane(min(min(e4[0].y, e4[0].w), min(e4[1].y, e4[1].w))) < n;
+            };
+            const auto least_post = [&](unsigned long long (&box)[2][4], int n) {
+                if (__builtin_expect(missing(n), 0)) {
+                    int looks = 0;
+                    do {
+                        // (the partners are a few instructions apart: look again at once, and at the clock now and then)
+                        if ((++looks & 4095) == 0) mrf_wait_check(wait_block);
+                        read_posts(box, n);
+                    } while (missing(n));
                 }
-            }
-            if (lane == 0) P.q[(size_t)r * N + head] = 0;
-        }
-        int seen = 0;
-        for (int n = 1 + jw; n < len; n += NI) {
-            int wait_turns = 0;
-            while (seen < n) {
-                seen = __builtin_amdgcn_readfirstlane(
-                    __hip_atomic_load(&produced, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-                if (seen < n) mrf_wait_turn(wait_block, wait_turns);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-            const int slot = n & (NR - 1);
-            const float *hbuf = &ring[slot][TW];
-            const float wgt = ringw[slot];
-            const long long i = head + (long long)n * nstep;
-
-            float hv[LPI];
-            float hm = INFINITY;
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                return mrf_min(mrf_min(__int_as_float(e4[0].x), __int_as_float(e4[0].z)), mrf_min(__int_as_float(e4[1].x), __int_as_float(e4[1].z)));
+            };
+            await(1);
+            fetch(0, 0);
+            arrived();
+            float carry = 0.0f;
+            for (int n = 1;;) {
 #pragma unroll
-            for (int s = 0; s < LPI; ++s) {
-                hv[s] = hbuf[lane + 64 * s];           // +inf for labels >= L
-                hm = mrf_min(hm, hv[s]);
-            }
-            const float hmin = mrf_wave_min(hm);
-
-            float tv[LPI];
-            int tp[LPI];
-            float tq;
-            if (__builtin_expect(__builtin_amdgcn_readfirstlane(__float_as_int(wgt)) >= 0, 1)) {
-                const float gmin = __builtin_fmaf(wgt, fT, hmin);
-                int mug = 0;
-                bool found = false;
+                for (int u = 0; u < NR; ++u, ++n) {          // step n uses slot u = (n - 1) % NR
+                    float v;
+                    if constexpr (TRWP) {
+                        v = q4[0].x + carry;
 #pragma unroll
-                for (int s = 0; s < LPI; ++s) {
-                    const int lam = lane + 64 * s;
-                    const float gfar = lam < L ? __builtin_fmaf(wgt, fT, hv[s]) : INFINITY;
-                    const unsigned long long bal = __ballot(gfar == gmin);
-                    if (!found && bal != 0ull) { found = true; mug = 64 * s + __ffsll((long long)bal) - 1; }
-                }
-#pragma unroll
-                for (int s = 0; s < LPI; ++s) {
-                    const int lam = lane + 64 * s;
-                    float dl[2 * TW - 1];
-#pragma unroll
-                    for (int o = 0; o < 2 * TW - 1; ++o) {
-                        const int dist = o < TW - 1 ? TW - 1 - o : o - (TW - 1);
-                        dl[o] = __builtin_fmaf(wgt, f[dist], hbuf[lam + o - (TW - 1)]);
+                        for (int c = 1; c < RMAX; ++c) v = v + (c % 4 == 0 ? q4[c / 4].x : (c % 4 == 1 ? q4[c / 4].y : (c % 4 == 2 ? q4[c / 4].z : q4[c / 4].w)));
+                        v = rho * v;
+                        v = v - dr;
+                    } else {
+                        v = dr + carry;
                     }
-                    float W = dl[0];
+                    const float w = wgt;
+                    v = valid ? v : INFINITY;
+                    hring[u][PAD + lam] = v;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    if constexpr (MULTI) post(&hflag[wv], n);
+                    mrf_wave_lds_fence();
+                    // one batch of reads: who has written h, the neighbours; the loader's counter, the next node's values
+                    float lo[QD > 0 ? QD + 4 : TW], hi[QD > 0 ? QD + 4 : TW];
+                    int4 fl;
+                    const auto neighbours = [&]() {
+                        if constexpr (MULTI) {
+                            fl = *reinterpret_cast<const int4 *>(hflag);
+                            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                        }
+                        if constexpr (QD == 0) {
 #pragma unroll
-                    for (int o = 1; o + 1 < 2 * TW - 1; o += 2) W = mrf_min3(W, dl[o], dl[o + 1]);
-                    int po = 2 * TW - 2;
+                            for (int d = 0; d < TW; ++d) { lo[d] = hring[u][PAD + lam - d]; hi[d] = hring[u][PAD + lam + d]; }
+                        } else if constexpr (QD == 4) {
+                            // label quad + s at distance 4 quarter + e: lo[s - e + 4], hi[s + e]
+                            const float4 *pl = reinterpret_cast<const float4 *>(&hring[u][PAD + quad - 4 * quarter - 4]);
+                            const float4 *ph = reinterpret_cast<const float4 *>(&hring[u][PAD + quad + 4 * quarter]);
 #pragma unroll
-                    for (int o = 2 * TW - 3; o >= 0; --o) po = (dl[o] == W) ? o : po;
-                    const int pW = lam + po - (TW - 1);
-                    const bool wlt = W < gmin, wgt_ = W > gmin;
-                    tv[s] = (lam < L) ? (wlt ? W : gmin) : INFINITY;
-                    const int tie = pW < mug ? pW : mug;
-                    tp[s] = wlt ? pW : (wgt_ ? mug : tie);
-                }
-                if (__builtin_expect(f0zero, 1)) {
-                    tq = hmin;
-                } else {
-                    float mn = INFINITY;
+                            for (int k = 0; k < 2; ++k) {
+                                const float4 a = pl[k], c = ph[k];
+                                lo[4 * k] = a.x; lo[4 * k + 1] = a.y; lo[4 * k + 2] = a.z; lo[4 * k + 3] = a.w;
+                                hi[4 * k] = c.x; hi[4 * k + 1] = c.y; hi[4 * k + 2] = c.z; hi[4 * k + 3] = c.w;
+                            }
+                        } else {
+                            static_assert(QD == 0 || QD == 2 || QD == 4, "window widths");
+                            const float2 *pl = reinterpret_cast<const float2 *>(&hring[u][PAD + quad - 2 * quarter - 2]);
+                            const float2 *ph = reinterpret_cast<const float2 *>(&hring[u][PAD + quad + 2 * quarter]);
 #pragma unroll
-                    for (int s = 0; s < LPI; ++s) mn = fminf(mn, tv[s]);
-                    tq = mrf_wave_min(mn);
-                }
-            } else {
-                // negative weight: the ordering argument does not hold, evaluate every mu
-#pragma unroll
-                for (int s = 0; s < LPI; ++s) {
-                    const int lam = lane + 64 * s;
-                    float best = INFINITY;
-                    int bi = 0;
-                    for (int mu = 0; mu < L; ++mu) {
-                        int dist = mu > lam ? mu - lam : lam - mu;
-                        dist = dist < TW ? dist : TW;
-                        const float dlt = __builtin_fmaf(wgt, ftab[dist], hbuf[mu]);
-                        if (dlt < best) { best = dlt; bi = mu; }
+                            for (int k = 0; k < 3; ++k) {
+                                const float2 a = pl[k], c = ph[k];
+                                lo[2 * k] = a.x; lo[2 * k + 1] = a.y;
+                                hi[2 * k] = c.x; hi[2 * k + 1] = c.y;
+                            }
+                        }
+                    };
+                    neighbours();
+                    const int seen = __hip_atomic_load(&loaded, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    fetch((u + 1) % NRL, (u + 1) % NR);
+                    __builtin_amdgcn_sched_barrier(0);
+                    float hmin = mrf_wave_min(v);
+                    if constexpr (MULTI) post_min(hmx, n, hmin);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (MULTI) {
+                        const auto absent = [&]() { return __builtin_amdgcn_readfirstlane(min(min(fl.x, fl.y), min(fl.z, fl.w))) < n; };
+                        if (__builtin_expect(absent(), 0)) {
+                            int looks = 0;
+                            do {
+                                if ((++looks & 4095) == 0) mrf_wait_check(wait_block);
+                                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                                neighbours();
+                            } while (absent());
+                        }
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                        read_posts(hmx, n);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
-                    tv[s] = (lam < L) ? best : INFINITY;
-                    tp[s] = bi;
+                    // window: the two candidates at a distance share f, and a correctly rounded fma is non-decreasing in its
+                    // addend, so the smaller of the two comes from the smaller h
+                    float W;
+                    if constexpr (QD == 0) {
+                        W = __builtin_fmaf(w, f[0], v);
+#pragma unroll
+                        for (int d = 1; d < TW; ++d) W = mrf_min(W, __builtin_fmaf(w, f[d], mrf_min(lo[d], hi[d])));
+                    } else {
+                        float x[4];
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) {
+                            float dl[QD];
+#pragma unroll
+                            for (int e = 0; e < QD; ++e) dl[e] = __builtin_fmaf(w, f[e], mrf_min(lo[s - e + QD], hi[s + e]));
+                            x[s] = QD == 4 ? mrf_min(mrf_min3(dl[0], dl[1], dl[QD > 2 ? 2 : 0]), dl[QD - 1]) : mrf_min(dl[0], dl[1]);
+                        }
+                        // every lane keeps two of the four labels and gives two to the lane two further, then one of two
+                        const bool up2 = quarter & 2, up1 = quarter & 1;
+                        float give0 = up2 ? x[0] : x[2], give1 = up2 ? x[1] : x[3];
+                        float keep0 = up2 ? x[2] : x[0], keep1 = up2 ? x[3] : x[1];
+                        keep0 = mrf_min(keep0, mrf_dpp_f32<0x4E>(give0));
+                        keep1 = mrf_min(keep1, mrf_dpp_f32<0x4E>(give1));
+                        const float give = up1 ? keep0 : keep1, keep = up1 ? keep1 : keep0;
+                        W = mrf_min(keep, mrf_dpp_f32<0xB1>(give));
+                    }
+                    if constexpr (MULTI) hmin = least_post(hmx, n);
+                    float tv = mrf_min(W, __builtin_fmaf(w, fT, hmin)), tq = hmin;
+                    const bool wneg = __builtin_amdgcn_readfirstlane(__float_as_int(w)) < 0;
+                    if (__builtin_expect(wneg, 0)) {
+                        // negative weight: the ordering argument does not hold, evaluate every mu
+                        float best = INFINITY;
+                        for (int mu = 0; mu < L; ++mu) {
+                            int dist = mu > lam ? mu - lam : lam - mu;
+                            dist = dist < TW ? dist : TW;
+                            const float dlt = __builtin_fmaf(w, ftab[dist], hring[u][PAD + mu]);
+                            if (dlt < best) best = dlt;
+                        }
+                        tv = best;
+                    }
+                    if (__builtin_expect((int)wneg | (int)!f0zero, 0)) {
+                        // the minimum of the new message is not that of h
+                        tq = mrf_wave_min(valid ? tv : INFINITY);
+                        if constexpr (MULTI) {
+                            post_min(tmx, n, tq);
+                            read_posts(tmx, n);
+                            tq = least_post(tmx, n);
+                        }
+                    }
+                    carry = tv - tq;
+                    arrived();                               // (in front of the writes below, behind which the wait would be for those)
+                    tring[u][lam] = tv;
+                    mring[u] = make_float2(hmin, tq);        // (every lane and value wavefront writes the same)
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    post(&valued[wv], n);
+                    if (n + 1 >= len) return;                // (uniform)
+                    if (__builtin_expect(__builtin_amdgcn_readfirstlane(seen) <= n, 0)) {
+                        await(n + 1);
+                        fetch((u + 1) % NRL, (u + 1) % NR);
+                        arrived();
+                    }
                 }
-                float mn = INFINITY;
-#pragma unroll
-                for (int s = 0; s < LPI; ++s) mn = fminf(mn, tv[s]);
-                tq = mrf_wave_min(mn);
             }
-            // this slot has been read: hand it back
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-            if (lane == 0) __hip_atomic_store(&consumed[jw], n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-
-            int qidx = -1;
-#pragma unroll
-            for (int s = 0; s < LPI; ++s) {
-                const unsigned long long bal = __ballot(tv[s] == tq);
-                if (qidx < 0 && bal != 0ull) qidx = 64 * s + __ffsll((long long)bal) - 1;
-            }
-#pragma unroll
-            for (int s = 0; s < LPI; ++s) {
-                const int lam = lane + 64 * s;
-                if (lam < L) {
-                    P.m_out[((size_t)r * N + i) * L + lam] = tv[s] - tq;
-                    P.p[((size_t)r * N + i) * L + lam] = (uint8_t)tp[s];
-                }
-            }
-            if (lane == 0) P.q[(size_t)r * N + i] = (uint8_t)qidx;
-        }
+        };
+        if (NWV > 1) run(std::true_type{});
+        else run(std::false_type{});
         return;
     }
 
-    // ---- values: wavefront wv owns labels 64 wv .. 64 wv + 63 ---------------------------------
-    const int lam = wv * 64 + lane;
-    const bool valid = lam < L;
-    const int lamc = valid ? lam : 0;
-    const float rho = P.rho[r];
-    const int n_pre = P.n_pre[r], n_src = P.n_src[r], rm_slot = P.rm_slot[r];
-    const float *src[RMAX];
-    float use[RMAX], carry_at[RMAX + 1], is_rm[RMAX];
-    src[0] = P.unary + (size_t)P.unary_slab[r] * N * L;
-    use[0] = 1.0f;
-    is_rm[0] = 0.0f;
+    if (wv == NWV) {
+        // ---- loader ------------------------------------------------------------------------------------
+        // NLL neighbouring labels per lane and access; the last lane's are the last ones of the node.  Sources of h in
+        // summation order; unused slots are empty views (they load 0 and enter with factor 0).
+        __builtin_amdgcn_s_setprio(3);
+        if (len < 2) return;
+        const int n_pre = P.n_pre[r], n_src = P.n_src[r], rm_slot = P.rm_slot[r];
+        const auto run = [&](auto labels) {
+            constexpr int NLL = decltype(labels)::value, DL = NLL == 4 ? (D + 1) / 2 : D;      // (the registers of two sets)
+            const bool live = NLL * lane < L;
+            const int at = live ? (NLL * lane + NLL > L ? L - NLL : NLL * lane) : 0;
+            // (views of one image: the host checks that their entries fit)
+            const size_t image = (size_t)P.g.H * P.g.W, base = (size_t)__builtin_amdgcn_readfirstlane(b) * image;
+            mrf_buf src[RMAX];
+            float before[RMAX], after[RMAX], is_rm[RMAX];
+            src[0] = mrf_buffer(P.unary + ((size_t)__builtin_amdgcn_readfirstlane((int)P.unary_slab[r]) * N + base) * L, image * L * 4);
 #pragma unroll
-    for (int c = 1; c < RMAX; ++c) {
-        src[c] = (c <= n_src) ? P.m_in + (size_t)P.src_dir[r][c - 1] * N * L : src[0];
-        use[c] = ((c <= n_src) ? 1.0f : 0.0f) + vz;
-        is_rm[c] = ((c - 1 == rm_slot) ? 1.0f : 0.0f) + vz;
-    }
-#pragma unroll
-    for (int c = 1; c <= RMAX; ++c) carry_at[c] = ((c == n_pre + 1) ? 1.0f : 0.0f) + vz;
-
-    const int vzero = mrf_opaque_zero();
-    const float *wbase = P.w + (P.w_mul ? (size_t)r * N : 0);
-    const int lastsrc = len - 2;
-    float cur[D][RMAX], nxt[D][RMAX];
-    float wcur[D], wnxt[D];
-    auto prefetch = [&](float (&dst)[RMAX], float &wdst, int nj) {
-        nj = nj < lastsrc ? nj : lastsrc;
-        const long long j = head + (long long)nj * nstep;
-#pragma unroll
-        for (int c = 0; c < RMAX; ++c) dst[c] = src[c][(size_t)j * L + lamc];
-        wdst = wbase[(size_t)((j + nstep) * P.w_mul) + vzero];
-    };
-    if (len >= 2) {
-#pragma unroll
-        for (int u = 0; u < D; ++u) prefetch(cur[u], wcur[u], u);
-    }
-
-    // Meeting point of the value wavefronts.  The hardware barrier would also wait for the index
-    // wavefronts, so each value wavefront posts {step, its value} and reads the others' until all
-    // carry this step; LDS keeps a wavefront's operations in order, so whoever sees the post also
-    // sees what that wavefront wrote to the ring before it.  Two sets by step parity: a wavefront
-    // can be at most one step ahead of the slowest, because it needs that one's post to go on.
-    auto exchange_min = [&](unsigned long long (&box)[2][4], int par, int step, float val) {
-        if (lane == 0)
-            __hip_atomic_store(&box[par][wv], ((unsigned long long)(unsigned)step << 32) | (unsigned)__float_as_int(val),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        float m;
-        bool all;
-        int looks = 0;
-        do {
-            // all four posts in one batch of LDS reads (those of absent wavefronts are ignored)
-            unsigned long long e[4];
-#pragma unroll
-            for (int w2 = 0; w2 < 4; ++w2)
-                e[w2] = __hip_atomic_load(&box[par][w2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            m = INFINITY;
-            all = true;
-#pragma unroll
-            for (int w2 = 0; w2 < 4; ++w2) {
-                const bool here = w2 < NWV;
-                all = all && (!here || (int)(e[w2] >> 32) == step);
-                m = mrf_min(m, here ? __int_as_float((int)(unsigned)e[w2]) : INFINITY);
+            for (int c = 1; c < RMAX; ++c) {
+                const bool there = c <= n_src;
+                src[c] = mrf_buffer(P.m_in + ((size_t)__builtin_amdgcn_readfirstlane(there ? (int)P.src_dir[r][c - 1] : 0) * N + base) * L,
+                                    (size_t)(unsigned)__builtin_amdgcn_readfirstlane(there ? 1 : 0) * image * L * 4);
+                before[c] = there && (!TRWP || c <= n_pre) ? 1.0f : 0.0f;
+                after[c] = there && TRWP && c > n_pre ? 1.0f : 0.0f;
+                is_rm[c] = TRWP && c - 1 == rm_slot ? 1.0f : 0.0f;
             }
-            all = __builtin_amdgcn_readfirstlane((int)all) != 0;
-            // (the partners are a few instructions apart: look again at once, and at the clock now and then)
-            if (!all && (++looks & 4095) == 0) mrf_wait_check(wait_block);
-        } while (!all);
+            const mrf_buf bw = mrf_buffer(P.w + (P.w_mul ? (size_t)r * N + base : 0), P.w_mul ? image * 4 : 4);
+            const unsigned first = (unsigned)(head - (long long)base);
+            unsigned at4 = live ? (first * (unsigned)L + (unsigned)at) * 4u : MRF_BUF_NONE, w4 = P.w_mul ? (first + (unsigned)(int)nstep) * 4u : 0u;
+            const unsigned step4 = live ? (unsigned)(int)estep * 4u : 0u, wstep4 = P.w_mul ? (unsigned)(int)nstep * 4u : 0u;
+            struct In {
+                float v[RMAX][NLL];
+                float w;
+            };
+            In A[DL], B[DL];
+            // (what is loaded past the scanline's end is another node or 0, and never used)
+            const auto prefetch = [&](In &in) {
+#pragma unroll
+                for (int c = 0; c < RMAX; ++c) mrf_buf_f32xn<NLL>(src[c], at4, in.v[c]);
+                in.w = mrf_buf_f32(bw, w4);
+                at4 += step4;
+                w4 += wstep4;
+            };
+            int freed = 0, left = 0;                         // steps up to these have left the rings
+            const auto group = [&](const In (&in)[DL], int n0) {
+#pragma unroll
+                for (int u = 0; u < DL; ++u) {
+                    const int n = n0 + u;
+                    float base[NLL], mrm[NLL];
+#pragma unroll
+                    for (int s = 0; s < NLL; ++s) {
+                        base[s] = in[u].v[0][s];
+                        mrm[s] = 0.0f;
+#pragma unroll
+                        for (int c = 1; c < RMAX; ++c) {
+                            base[s] = __builtin_fmaf(before[c], in[u].v[c][s], base[s]);
+                            if constexpr (TRWP) mrm[s] = __builtin_fmaf(is_rm[c], in[u].v[c][s], mrm[s]);
+                        }
+                    }
+                    if (n >= len) break;                     // (uniform)
+                    int turns = 0;
+                    while (freed < n - NR) {
+                        // the index wavefronts take the steps in turn: behind the slowest one's last step, the others have
+                        // finished theirs
+                        const int i0 = look4(&indexed[0]), i1 = look4(&indexed[4]);
+                        freed = (i0 < i1 ? i0 : i1) + NX - 1;
+                        if (freed < n - NR) mrf_wait_turn(wait_block, turns);
+                    }
+                    while (NRL < NR && left < n - NRL) {
+                        left = look4(valued);
+                        if (left < n - NRL) mrf_wait_turn(wait_block, turns);
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                    const int ls = (n - 1) & (NRL - 1);
+                    if (live) {
+#pragma unroll
+                        for (int s = 0; s < NLL; ++s) {
+                            if constexpr (TRWP) {
+#pragma unroll
+                                for (int k = 0; k < NQ; ++k) {
+                                    float a[4];
+#pragma unroll
+                                    for (int c = 0; c < 4; ++c) a[c] = 4 * k + c == 0 ? base[s] : after[4 * k + c > 0 ? 4 * k + c : 1] * in[u].v[4 * k + c][s];
+                                    inq[k][ls][at + s] = make_float4(a[0], a[1], a[2], a[3]);
+                                }
+                                inr[ls][at + s] = mrm[s];
+                            } else {
+                                inr[ls][at + s] = base[s];
+                            }
+                        }
+                    }
+                    lw[(n - 1) & (NR - 1)] = in[u].w;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    post(&loaded, n);
+                }
+            };
+#pragma unroll
+            for (int u = 0; u < DL; ++u) prefetch(A[u]);
+            for (int n0 = 1; n0 < len; n0 += 2 * DL) {
+#pragma unroll
+                for (int u = 0; u < DL; ++u) prefetch(B[u]);
+                __builtin_amdgcn_sched_barrier(0);
+                group(A, n0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < DL; ++u) prefetch(A[u]);
+                __builtin_amdgcn_sched_barrier(0);
+                group(B, n0 + DL);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if (L <= 64) run(std::integral_constant<int, 1>{});
+        else if (L <= 128) run(std::integral_constant<int, 2>{});
+        else run(std::integral_constant<int, 4>{});
+        return;
+    }
+
+    // ---- p, q and all stores: index wavefront jw takes steps 1 + jw, 1 + jw + NX, ... -----------------------
+    // A lane holds two neighbouring labels, or two pairs 128 labels apart, one after the other.
+    const int jw = wv - NWV - 1;
+    constexpr int NB = 2 * PAD + 2;                          // neighbours of a pair: labels first - PAD ..
+    const int pairs = L > 128 ? 2 : 1;
+    const bool whole = L % 2 == 0;                           // a lane has both labels of a pair or none
+    float f[TW];
+#pragma unroll
+    for (int d = 0; d < TW; ++d) f[d] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ftab[d])));
+    const float fT = ftab[TW];
+    const auto store = [&](long long i, int pair, float m0, float m1, int p0, int p1) {
+        const mrf_buf bm = mrf_buffer(P.m_out + ((size_t)r * N + i) * L, 4 * (size_t)L), bp = mrf_buffer(P.p + ((size_t)r * N + i) * L, (size_t)L);
+        const unsigned at = 2u * (unsigned)lane + 128u * (unsigned)pair;      // (offsets of labels past L are past the views)
+        if (whole) {
+            const float m[2] = { m0, m1 };
+            mrf_buf_store_f32xn<2>(bm, 4u * at, m);
+            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(p0 | p1 << 8), bp, at, 0, 0);
+        } else {
+            mrf_buf_store_f32(bm, 4u * at, m0);
+            mrf_buf_store_f32(bm, 4u * at + 4u, m1);
+            mrf_buf_store_u8(bp, at, p0);
+            mrf_buf_store_u8(bp, at + 1u, p1);
+        }
+    };
+    const auto store_q = [&](long long i, int q) {
+        mrf_buf_store_u8(mrf_buffer(P.q + (size_t)r * N + i, 1), lane == 0 ? 0u : MRF_BUF_NONE, q);
+    };
+    // the lower of `found` and the lowest label of the pairs' lanes in b0 (their first labels) and b1
+    const auto lowest = [&](int found, int pair, unsigned long long b0, unsigned long long b1) {
+        const int l0 = (b0 | b1) != 0ull ? __ffsll((long long)(b0 | b1)) - 1 : 64;
+        const int at = 128 * pair + 2 * l0 + (int)(1u - (unsigned)((b0 >> (l0 & 63)) & 1ull));
+        return l0 < 64 && at < found ? at : found;
+    };
+    if (jw == 0) {
+        for (int s = 0; s < pairs; ++s) store(head, s, 0.0f, 0.0f, 0, 0);
+        store_q(head, 0);
+    }
+    int seen = 0;
+    for (int n = 1 + jw; n < len; n += NX) {
+        int turns = 0;
+        while (seen < n) {
+            seen = look4(valued);
+            if (seen < n) mrf_wait_turn(wait_block, turns);
+        }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-        return m;
-    };
-
-    float carry = 0.0f;
-    int par = 0;
-    int freed = 0;          // every step <= freed is finished by the index wavefronts (possibly stale view)
-    for (int n0 = 1; n0 < len; n0 += D) {
+        const int slot = (n - 1) & (NR - 1);
+        const long long i = head + (long long)n * nstep;
+        const float wgt = lw[slot];
+        const float2 mm = mring[slot];
+        const float hmin = mm.x, tq = mm.y;
+        const bool positive = __builtin_amdgcn_readfirstlane(__float_as_int(wgt)) >= 0;
+        const float gmin = __builtin_fmaf(wgt, fT, hmin);
+        // lowest label that attains the far minimum, and the lowest one that attains that of the message
+        int mug = L, q = L;
 #pragma unroll
-        for (int u = 0; u < D; ++u) prefetch(nxt[u], wnxt[u], n0 - 1 + D + u);
+        for (int s = 0; s < 2; ++s) {
+            if (s >= pairs) break;                           // (uniform)
+            const int lam = 2 * lane + 128 * s;
+            const float2 h = *reinterpret_cast<const float2 *>(&hring[slot][PAD + lam]), t2 = *reinterpret_cast<const float2 *>(&tring[slot][lam]);
+            const bool v0 = lam < L, v1 = lam + 1 < L;
+            mug = lowest(mug, s, __ballot((int)v0 & (int)(__builtin_fmaf(wgt, fT, h.x) == gmin)), __ballot((int)v1 & (int)(__builtin_fmaf(wgt, fT, h.y) == gmin)));
+            q = lowest(q, s, __ballot((int)v0 & (int)(t2.x == tq)), __ballot((int)v1 & (int)(t2.y == tq)));
+        }
 #pragma unroll
-        for (int u = 0; u < D; ++u) {
-            const int nn = n0 + u;
-            const bool past = nn >= len;
-            const float wgt = wcur[u];
-            const int slot = nn & (NR - 1);
-            float *hb = &ring[slot][TW];
-
-            // the slot was last used by step nn - NR
-            int wait_turns = 0;
-            while (__builtin_expect(!past && freed < nn - NR, 0)) {
-                int lo = __builtin_amdgcn_readfirstlane(
-                    __hip_atomic_load(&consumed[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+        for (int s = 0; s < 2; ++s) {
+            if (s >= pairs) break;                           // (uniform)
+            const int lam = 2 * lane + 128 * s;
+            const float2 t2 = *reinterpret_cast<const float2 *>(&tring[slot][lam]);
+            const float tv[2] = { t2.x, t2.y };
+            int p[2];
+            if (__builtin_expect(positive, 1)) {
+                float nb[NB];
 #pragma unroll
-                for (int j = 1; j < NI; ++j) {
-                    const int cj = __builtin_amdgcn_readfirstlane(
-                        __hip_atomic_load(&consumed[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-                    lo = cj < lo ? cj : lo;
+                for (int k = 0; k < NB / 2; ++k) {
+                    const float2 x = reinterpret_cast<const float2 *>(&hring[slot][lam])[k];
+                    nb[2 * k] = x.x; nb[2 * k + 1] = x.y;
                 }
-                freed = lo + NI - 1;
-                if (freed < nn - NR) mrf_wait_turn(wait_block, wait_turns);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-
-            float v = cur[u][0];
-            if (TRWP) {
-                float mrm = 0.0f;
-#pragma unroll
-                for (int c = 1; c < RMAX; ++c) {
-                    v = __builtin_fmaf(carry_at[c], carry, v);
-                    v = __builtin_fmaf(use[c], cur[u][c], v);
-                    mrm = __builtin_fmaf(is_rm[c], cur[u][c], mrm);
+                if (s + 1 == pairs) {
+                    // the slot has been read (what follows is in registers): hand it back
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                    post(&indexed[jw], n);
                 }
-                v = __builtin_fmaf(carry_at[RMAX], carry, v);
-                v = rho * v;
-                v = v - mrm;
+#pragma unroll
+                for (int o2 = 0; o2 < 2; ++o2) {
+                    // lowest label of the window that attains the value, from the top down; the far minimiser if it does
+                    constexpr int C = (2 * TW - 1 + 3) / 4 * 4;
+                    float dl[C];
+#pragma unroll
+                    for (int o = 0; o < C; ++o) {
+                        const int d = o < TW - 1 ? TW - 1 - o : o - (TW - 1);
+                        dl[o] = o < 2 * TW - 1 ? __builtin_fmaf(wgt, f[d < TW ? d : 0], nb[PAD + o2 + (o < 2 * TW - 1 ? o : 0) - (TW - 1)]) : INFINITY;
+                    }
+                    int po = 2 * C;
+                    mrf_static_for<C / 4>([&](auto g4) {
+                        constexpr int o = C - 4 - 4 * decltype(g4)::value;
+                        mrf_first_equal4<o>(po, tv[o2], dl[o], dl[o + 1], dl[o + 2], dl[o + 3]);
+                    });
+                    const int pw = po < 2 * C ? lam + o2 + po - (TW - 1) : L - 1, pg = tv[o2] == gmin ? mug : L - 1;
+                    p[o2] = max(min(min(pw, pg), L - 1), 0);
+                }
             } else {
+                // negative weight: every mu
 #pragma unroll
-                for (int c = 1; c < RMAX; ++c) v = __builtin_fmaf(use[c], cur[u][c], v);
-                v = v + carry;
-            }
-            // (lanes past L rewrite the +inf their ring entries hold anyway: no divergence; what
-            // they carry from node to node is never looked at)
-            const float av = valid ? v : INFINITY;
-            if (!past) hb[lam] = av;
-            const float hloc = mrf_wave_min(av);
-            // (written by every lane of the first value wavefront: no divergent branch in the step)
-            if (wv == 0 && !past) ringw[slot] = wgt;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            const float hmin = exchange_min(hmx, par, nn, hloc);
-            // every entry of the node is in the ring: let the index wavefronts have it
-            if (wv == 0 && !past)
-                __hip_atomic_store(&produced, nn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            const bool wpos = __builtin_amdgcn_readfirstlane(__float_as_int(wgt)) >= 0;
-            float tv;
-            // (evaluated for every node, so that the usual case is straight-line code; replaced
-            // below for a negative weight)
-            {
-                const float gmin = __builtin_fmaf(wgt, fT, hmin);
-                // The two candidates at distance d share f(d), and a correctly rounded fma is
-                // non-decreasing in its addend: the smaller of the two comes from the smaller h.
-                float dl[TW];
-                dl[0] = __builtin_fmaf(wgt, f[0], v);
-#pragma unroll
-                for (int d = 1; d < TW; ++d)
-                    dl[d] = __builtin_fmaf(wgt, f[d], mrf_min(hb[lam - d], hb[lam + d]));
-                float W = mrf_min(dl[0], gmin);
-#pragma unroll
-                for (int d = 1; d + 1 < TW; d += 2) W = mrf_min3(W, dl[d], dl[d + 1]);
-                if ((TW & 1) == 0) W = mrf_min(W, dl[TW - 1]);
-                tv = W;
-            }
-            if (__builtin_expect(!wpos, 0)) {
-                float best = INFINITY;
-                for (int mu = 0; mu < L; ++mu) {
-                    int dist = mu > lam ? mu - lam : lam - mu;
-                    dist = dist < TW ? dist : TW;
-                    const float dlt = __builtin_fmaf(wgt, ftab[dist], hb[mu]);
-                    if (dlt < best) best = dlt;
+                for (int o2 = 0; o2 < 2; ++o2) {
+                    float best = INFINITY;
+                    p[o2] = 0;
+                    for (int mu = 0; mu < L; ++mu) {
+                        int dist = mu > lam + o2 ? mu - (lam + o2) : lam + o2 - mu;
+                        dist = dist < TW ? dist : TW;
+                        const float dlt = __builtin_fmaf(wgt, ftab[dist], hring[slot][PAD + mu]);
+                        if (dlt < best) { best = dlt; p[o2] = mu; }
+                    }
                 }
-                tv = best;
+                if (s + 1 == pairs) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                    post(&indexed[jw], n);
+                }
             }
-            float tq = hmin;
-            if (__builtin_expect(!(wpos && f0zero), 0)) {
-                // general case: the minimum of the new message needs its own exchange
-                const float tloc = mrf_wave_min(valid ? tv : INFINITY);
-                tq = exchange_min(tmx, par, nn, tloc);
-            }
-            carry = tv - tq;
-            par ^= 1;
+            store(i, s, tv[0] - tq, tv[1] - tq, p[0], p[1]);
         }
-#pragma unroll
-        for (int u = 0; u < D; ++u) {
-            wcur[u] = wnxt[u];
-#pragma unroll
-            for (int c = 0; c < RMAX; ++c) cur[u][c] = nxt[u][c];
-        }
+        store_q(i, q < L ? q : 0);
     }
 }
 

@@ -780,6 +780,37 @@ def test_window_path_is_exact(oracle, case):
             np.testing.assert_array_equal(getattr(g, name), getattr(d, name), err_msg="%s %s" % (layout, name))
 
 
+# label counts around the wavefronts and pairs of labels, odd ones; the widths that share the window among lanes and the one
+# that does not; rings that wrap; 3 and 7 source arrays; negative weights, V(0) != 0, integer data
+@pytest.mark.parametrize("case", [(L, width, algo, R) for L in (65, 67, 96, 127, 128, 129, 131, 192, 193, 255, 256)
+                                  for width, algo, R in ((8, "trwp", 4), (16, "isgmr", 4), (16, "trwp", 8), (2, "trwp", 4))
+                                  if R == 4 and width > 2 or L in (67, 129, 256)], ids=lambda c: "%d_%d_%s_%d" % c)
+def test_window_sweep_with_loader_value_and_index_wavefronts(oracle, case):
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    print("case squad", case, flush=True)
+    L, width, algo, R = case
+    for iv, first, sign in ((False, 0.0, 1.0), (True, 0.0, 1.0), (False, 0.0, -0.5), (False, 0.4, 1.0)):
+        B, H, W = (2, 3, 21) if R == 4 else (1, 4, 9)
+        pr = random_problem(500 + L, algo, B, H, W, L, DIRS8 if R == 8 else DIRS4, 2, integer_valued=iv, per_edge=True, rho=np.linspace(0.3, 0.9, R))
+        d = np.abs(np.arange(L)[:, None] - np.arange(L)[None, :]).astype(np.float32)
+        pr.pairwise = np.minimum(d, np.float32(width)) if first == 0.0 else np.minimum(d * np.float32(0.3) + np.float32(first), np.float32(0.3 * width + first))
+        pr.pairwise_kind, pr.trunc, pr.scale = (1, float(width), 1.0) if first == 0.0 else (3, float(width), 1.0)
+        pr.edge_weight = np.abs(pr.edge_weight)
+        if sign < 0:
+            pr.edge_weight = (pr.edge_weight * np.where(np.random.default_rng(L).random(pr.edge_weight.shape) > 0.2, 1.0, sign)).astype(np.float32)
+        f = oracle_forward(oracle, pr)
+        try:
+            assert mrf.mrf_tune(2, 2) == 0 and mrf.mrf_tune(9, 2) == 0
+            for beside in (4, 8):
+                assert mrf.mrf_tune(10, beside) == 0
+                check_forward(run_gpu(pr, backward=False), f)
+                assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_window_squad", mrf.mrf_last_sweep_launch(False)
+        finally:
+            for k in (2, 9, 10):
+                mrf.mrf_tune(k, 0)
+
+
 CHAIN_CASES = [
     # seed, algo, B, H, W, L, dirs, K, integer_valued, per_edge
     (81, "trwp", 1, 3, 70, 96, DIRS4, 2, False, True),      # scanlines many times the ring
