@@ -1825,12 +1825,21 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
             for (int u = 0; u < D; ++u) {
                 const int nn = n0 + u;
                 if (nn < len) {
-                    // the slot was last read for step nn - NRL, before that step was published
+                    // both rings' slots were last used by step nn - NR: the value wavefront, which takes what it finds
+                    // here, needs no wait of its own
+                    static_assert(NR == NRL, "ring depths");
                     int wait_turns = 0;
-                    while (pseen < nn - NRL) {
-                        pseen = __builtin_amdgcn_readfirstlane(
-                            __hip_atomic_load(&produced, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-                        if (pseen < nn - NRL) mrf_wait_turn(wait_block, wait_turns);
+                    while (pseen < nn - NR) {
+                        int lo = __builtin_amdgcn_readfirstlane(
+                            __hip_atomic_load(&consumed[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+#pragma unroll
+                        for (int j = 1; j < NI; ++j) {
+                            const int cj = __builtin_amdgcn_readfirstlane(
+                                __hip_atomic_load(&consumed[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+                            lo = cj < lo ? cj : lo;
+                        }
+                        pseen = lo + NI - 1;
+                        if (pseen < nn - NR) mrf_wait_turn(wait_block, wait_turns);
                     }
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
                     const int ls = nn & (NRL - 1);
@@ -1908,29 +1917,17 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
             return sn;
         };
         float in[5][LP], wgt = 0.0f;
-        int lseen = 0;
         if (len >= 2) {
-            lseen = await_loader(1);
+            await_loader(1);
             read_entry(in, 1);
             wgt = lw[1];
         }
-        for (int nn = 1; nn < len; ++nn) {
-            const int slot = nn & (NR - 1);
-            float *hbuf = &ring[slot][TW];
-            int wait_turns = 0;
-            while (__builtin_expect(freed < nn - NR, 0)) {
-                int lo = __builtin_amdgcn_readfirstlane(
-                    __hip_atomic_load(&consumed[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+        if (len < 2) return;
+        for (int nn = 1;;) {
 #pragma unroll
-                for (int j = 1; j < NI; ++j) {
-                    const int cj = __builtin_amdgcn_readfirstlane(
-                        __hip_atomic_load(&consumed[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-                    lo = cj < lo ? cj : lo;
-                }
-                freed = lo + NI - 1;
-                if (freed < nn - NR) mrf_wait_turn(wait_block, wait_turns);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+          for (int u = 1; u <= NR; ++u, ++nn) {   // (unrolled, so that ring addresses are constants)
+            const int slot = u & (NR - 1);        // = nn % NR
+            float *hbuf = &ring[slot][TW];
 
             float a[LP];
             float hm = 0.0f;
@@ -1979,15 +1976,15 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
             // the next node's entries, in the same batch of LDS reads; if the loader's counter
             // (read first: the LDS queue keeps the order) does not cover them yet, they are read
             // again after waiting
-            const bool more = nn + 1 < len;
-            const int lsn = (nn + 1) & (NRL - 1);
+            const int lsn = (u + 1) & (NRL - 1);
             const int flag = __hip_atomic_load(&loaded, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             float nin[5][LP];
             read_entry(nin, lsn);
             float nwgt = lw[lsn];
-
+            __builtin_amdgcn_sched_barrier(0);    // (the reads are under way while the minimum is formed)
             const float hmin = mrf_wave_min(hm);
+            __builtin_amdgcn_sched_barrier(0);
             // LDS executes a wavefront's operations in order: whoever sees the counter also sees the
             // node's ring entries written before it, so no wait is needed in between
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -2047,13 +2044,11 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
             }
             // the next node's entries were read above with the loader's counter in front of them;
             // looked at only now, so that everything before is one straight block
-            if (more) {
-                lseen = __builtin_amdgcn_readfirstlane(flag);
-                if (__builtin_expect(lseen < nn + 1, 0)) {
-                    lseen = await_loader(nn + 1);
-                    read_entry(nin, lsn);
-                    nwgt = lw[lsn];
-                }
+            if (__builtin_expect(nn + 1 >= len, 0)) return;            // (uniform)
+            if (__builtin_expect(__builtin_amdgcn_readfirstlane(flag) < nn + 1, 0)) {
+                await_loader(nn + 1);
+                read_entry(nin, lsn);
+                nwgt = lw[lsn];
             }
 #pragma unroll
             for (int s = 0; s < LP; ++s) carry[s] = tv[s] - tq;
@@ -2062,8 +2057,8 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
             for (int c = 0; c < 5; ++c)
 #pragma unroll
                 for (int s = 0; s < LP; ++s) in[c][s] = nin[c][s];
+          }
         }
-        return;
     }
 
     if (len >= 2) {
