@@ -163,6 +163,7 @@ MRF_G(int g_tune_pack_idx, 0);   // packed dense sweep divided among four wavefr
 MRF_G(int g_tune_chain, 0);      // backward sweep with a chain wavefront: 0 auto, 1 never, 2 whenever possible
 MRF_G(int g_tune_chain_hot, 0);  // its pre-reduction of the most popular scatter target: 0 auto, 1 never, 2 whenever V is no dense table
 MRF_G(int g_tune_chain_ni, 0);   // its helpers per scanline: 0 auto, 2, 4, 6, 8
+MRF_G(int g_tune_narrow_divided, 0); // narrow backward sweep divided among four wavefronts: 0 by launch size, 1 never, 2 whenever possible
 MRF_G(int g_tune_narrow, 0);     // lanes per scanline of the narrow backward sweep: 0 by launch size, 8, 16, 32; -1: not that sweep
 MRF_G(hipEvent_t g_ev_start, nullptr);
 MRF_G(hipEvent_t g_ev_stop, nullptr);
@@ -1182,6 +1183,32 @@ hipError_t run_bwd_packed(MrfBwdParams &P, int seg, int ns, hipStream_t st)
     return seg == 16 ? launch_bwd_packed<16>(P, ns, st) : launch_bwd_packed<32>(P, ns, st);
 }
 
+// the narrow sweep divided among four wavefronts
+template <int SEG, int NL>
+hipError_t launch_bwd_narrow_divided(MrfBwdParams &P, int ns, long long packs, hipStream_t st)
+{
+    const int L = P.g.L;
+    const bool gv = P.gV != nullptr, unary = P.unary_dir >= 0;
+    if (gv && packs > grad_slots(L)) return hipErrorInvalidValue;
+    note_launch(1, "mrf_bwd_sweep_narrow", packs, 256, "%d,%d,%d,%s,%s", SEG, NL, ns, unary ? "true" : "false", gv ? "true" : "false");
+#define MRF_D_GO(n, un, g) \
+    if (ns == n && unary == un && gv == g) { \
+        const size_t lds = mrf_bwd_narrow_divided_lds<SEG, NL, un, g>(L); \
+        void (*const kernel)(MrfBwdParams) = mrf_bwd_sweep_narrow<SEG, NL, n, un, g>; \
+        if (lds > 64 * 1024) { \
+            const hipError_t ea_ = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+            if (ea_ != hipSuccess) return ea_; \
+        } \
+        hipLaunchKernelGGL(kernel, dim3((unsigned)packs), dim3(256), lds, st, static_cast<const MrfBwdParams &>(P)); \
+        return hipGetLastError(); \
+    }
+#define MRF_D(n) MRF_D_GO(n, false, false) MRF_D_GO(n, false, true) MRF_D_GO(n, true, false) MRF_D_GO(n, true, true)
+    MRF_D(4) MRF_D(8)
+#undef MRF_D
+#undef MRF_D_GO
+    return hipErrorInvalidValue;
+}
+
 template <int SEG, int NL>
 hipError_t launch_bwd_narrow(MrfBwdParams &P, int ns, long long packs, hipStream_t st)
 {
@@ -1238,6 +1265,16 @@ hipError_t run_bwd_narrow(MrfBwdParams &P, int seg, int ns, hipStream_t st)
     }
     P.pack_begin[P.r_count] = (int)packs;
     const int nl = (L + seg - 1) / seg;
+    // the work of a node divided among four wavefronts while the launch leaves SIMDs idle (TRWP, 512 x 512 images, K = 2, one / four
+    // wavefronts: 256 wavefronts of scanlines, 21 labels 1.86 / 1.42 ms, 8 labels 1.11 / 0.92; 768 3.44 / 2.91, 1.77 / 1.20; 1,024 of 32 labels
+    // 1.82 / 1.50, of 16 labels 1.62 / 1.38; 1,536 of 32 labels 2.30 / 2.41)
+    const bool divided = P.r_count == 1 && (ns == 4 || ns == 8) && L % nl == 0 && !P.edge && g_tune_narrow_divided != 1 &&
+                         (g_tune_narrow_divided == 2 || packs <= 1024) && !(P.gV && packs > grad_slots(L));
+    if (divided && seg == 32 && nl == 1) return launch_bwd_narrow_divided<32, 1>(P, ns, packs, st);
+    if (divided && seg == 16 && nl == 1) return launch_bwd_narrow_divided<16, 1>(P, ns, packs, st);
+    if (divided && seg == 16 && nl == 2) return launch_bwd_narrow_divided<16, 2>(P, ns, packs, st);
+    if (divided && seg == 8 && nl == 1) return launch_bwd_narrow_divided<8, 1>(P, ns, packs, st);
+    if (divided && seg == 8 && nl == 3) return launch_bwd_narrow_divided<8, 3>(P, ns, packs, st);
     if (seg == 32 && nl == 1) return launch_bwd_narrow<32, 1>(P, ns, packs, st);
     if (seg == 16 && nl == 1) return launch_bwd_narrow<16, 1>(P, ns, packs, st);
     if (seg == 16 && nl == 2) return launch_bwd_narrow<16, 2>(P, ns, packs, st);
@@ -1395,7 +1432,12 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // labels 1.03 / 0.98, 32 labels 1.12 / 1.14.  17, 19 and 23 labels fill no segment: with up to four source arrays 1.59 /
     // 1.80 at 1,640 scanlines, 2.03 / 2.19 at 2,048, 2.42 / 2.95 at 2,560, with eight 4.84 / 4.22 at 1,640)
     const bool fills_none = L > 16 && L <= 24 && L % 2 != 0 && L % 3 != 0;
-    const long long pk_max = L <= 8 ? 1024 : (fills_none && ns == 4 ? 2560 : 1536);
+    // (the narrow sweep divided among four wavefronts, which several source arrays take, is ahead earlier; two scanlines / divided,
+    // 512 x 512 images, K = 2: 1,024 scanlines 8 labels 1.00 / 0.90 ms, 16 labels 1.03 / 0.98, 21 labels 1.08 / 1.39, 32 labels 1.14 /
+    // 1.22; 1,536 scanlines 16 labels 1.55 / 1.06, 21 labels 1.61 / 1.40, 32 labels 1.67 / 1.38; eight directions, 12 labels, 2 x 256 x 512
+    // 1.41 / 1.25)
+    const bool divided = ns > 1 && P.g.N * L <= MRF_BUF_MOST && g_tune_narrow == 0 && g_tune_narrow_divided != 1;
+    const long long pk_max = fills_none && ns == 4 ? 2560 : (divided ? (L <= 16 ? 896 : 1280) : (L <= 8 ? 1024 : 1536));
     if (!generic && L <= 32 && P.r_count == 1 && ns <= 8 && g_tune_chain != 1 && g_tune_pack != 2 && g_tune_chain_pk != 1 &&
         (g_tune_chain_pk == 2 || (g_tune_chain != 2 && P.total_scanlines > 256 && P.total_scanlines <= pk_max)) &&
         !(gv_any && (P.total_scanlines + 1) / 2 > grad_slots(L))) {
@@ -2065,7 +2107,12 @@ int mrf_tune(int knob, int value)
     if (knob == 17) { g_tune_isgmr_presum = value; return MRF_OK; }
     if (knob == 18) { g_tune_gv_tile = value; return MRF_OK; }
     if (knob == 19) { g_tune_gv_apart = value; return MRF_OK; }
-    if (knob == 20) { g_tune_chain_pk = value; return MRF_OK; }
+    if (knob == 20) {
+        // (3, 4: by launch size, and the narrow sweep never / whenever possible divided among four wavefronts)
+        g_tune_chain_pk = value <= 2 ? value : 0;
+        g_tune_narrow_divided = value == 3 ? 1 : (value == 4 ? 2 : 0);
+        return MRF_OK;
+    }
     if (knob == 7) { g_tune_chain_ni = (value == 2 || value == 4 || value == 6 || value == 8 || value == 12) ? value : 0; return MRF_OK; }
     return MRF_ERR_BAD_ALGORITHM;
 }

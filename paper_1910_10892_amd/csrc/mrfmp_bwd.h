@@ -32,7 +32,8 @@
 //                          for everything else (launches with few scanlines)
 //   mrf_bwd_sweep_split    one wavefront per 64 labels in lock step
 //   mrf_bwd_sweep_packed   L <= 32: several scanlines per wavefront, one label per lane; arrays of any size
-//   mrf_bwd_sweep_narrow   L <= 32: up to eight scanlines per wavefront, several labels per lane
+//   mrf_bwd_sweep_narrow   L <= 32: up to eight scanlines per wavefront, several labels per lane; with five template
+//                          parameters the work of a node divided among four wavefronts
 //   mrf_isgmr_bwd_combine  ISGMR's sums over directions between two iterations
 // Which sweep a launch gets is host arithmetic on the launch shape (dispatch_bwd).
 #pragma once
@@ -1656,6 +1657,360 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
             const int mu = e / L, at = mu * pitch + (e - mu * L);
             double v = tabs[at];
             for (int k = 1; k < waves * ntab; ++k) v += tabs[k * tsize + at];
+            mrf_slot_add(&slot[e], v);
+        }
+    }
+}
+
+// ---- the narrow replay with its work divided among four wavefronts ---------------------------------------
+//
+// One direction per launch (TRWP) leaves the wavefronts above, eight scanlines each, alone on a quarter of the SIMDs: 4 x 512 x
+// 512 is 256 of them, and a node step of theirs is 1,100 clocks.  Here a workgroup of four wavefronts, one per SIMD, walks the
+// same scanlines: two take the nodes in turn and do what does not wait for the chain (loads, the gradient arriving from
+// elsewhere with the correction at q), one does the chain (add, scatter through LDS, read, the stored s), one what is left (grad
+// theta, both pairwise gradients).  Rings in LDS as in mrf_bwd_sweep_chain: ext and p from the first two, the carry that entered a
+// node from the chain.  Same operations on the same values in the same order as mrf_bwd_sweep_narrow.
+// Every wait is on a counter that only grows: chain on pre, post on chain, pre on post NR steps back.
+// Several source arrays; label counts that the lanes' labels divide (the launches that the rule of narrow_lanes gives them).
+// Backward pass, 4 x 512 x 512, TRWP, 4 directions, K = 2: 21 labels 1.86 -> 1.42 ms, 16 labels 1.37 -> 1.07, 32 labels 1.82 -> 1.50.  What sets the
+// pace now is the chain's 80 instructions and two trips through LDS per node.
+template <int SEG, int NL, bool UNARY, bool GV>
+__host__ __device__ inline size_t mrf_bwd_narrow_divided_lds(int L)
+{
+    constexpr int NSEG = 64 / SEG, NR = 8;
+    return sizeof(double) * (NSEG * mrf_bwd_narrow_row<SEG, NL>() + 128 + (size_t)(UNARY ? 3 : 2) * NR * NL * 64 +
+                             (GV ? (size_t)mrf_bwd_narrow_tables(NSEG, L, 1) * mrf_bwd_narrow_table<SEG, NL>(L) : 0)) +
+           sizeof(float) * ((size_t)L * mrf_bwd_narrow_pitch(L) + 1 + 2 * NR * 64 + 8) + sizeof(MrfWaitBlock) + 8;
+}
+
+template <int SEG, int NL, int NS, bool UNARY, bool GV>
+__global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P)
+{
+    constexpr int NSEG = 64 / SEG, NR = 8, D = NS <= 4 ? 2 : 1;
+    constexpr int RS = mrf_bwd_narrow_row<SEG, NL>();
+    extern __shared__ __align__(16) unsigned char mrf_bsmem[];
+    const int L = P.g.L;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int seg = lane / SEG, li = lane % SEG;
+    const int lam0 = li * NL;                                 // the lane's first label
+    const int ntab = GV ? mrf_bwd_narrow_tables(NSEG, L, 1) : 0, tsize = mrf_bwd_narrow_table<SEG, NL>(L), pitch = mrf_bwd_narrow_pitch(L);
+    // carved in the order of mrf_bwd_narrow_divided_lds
+    double *rows = reinterpret_cast<double *>(mrf_bsmem);     // [NSEG][RS] scatter target, 64 spare, 64 spare of the tables
+    double *r_ext = rows + NSEG * RS + 128;                   // [NR][NL][64] pre -> chain, post
+    double *r_cin = r_ext + NR * NL * 64;                     // [NR][NL][64] chain -> post
+    double *r_all = r_cin + NR * NL * 64;                     // [NR][NL][64] pre -> post: grad theta's part (UNARY)
+    double *tabs = r_all + (UNARY ? NR * NL * 64 : 0);        // [ntab][tsize]
+    unsigned *r_p = reinterpret_cast<unsigned *>(tabs + ntab * tsize);        // [NR][64]
+    float *r_w = reinterpret_cast<float *>(r_p + NR * 64);    // [NR][64]
+    int *counters = reinterpret_cast<int *>(r_w + NR * 64);   // pre (two), chain, post: last step done
+    float *vl = reinterpret_cast<float *>(counters + 8);      // [L][pitch] V, then a 0
+    MrfWaitBlock &wait_lds = *reinterpret_cast<MrfWaitBlock *>(mrf_bsmem + (reinterpret_cast<unsigned char *>(vl + L * pitch + 1) - mrf_bsmem + 7) / 8 * 8);
+
+    for (int e = threadIdx.x; e < L * pitch; e += 256) {
+        const int mu = e / pitch, lam = e - mu * pitch;
+        vl[e] = lam < L ? P.V[mu * L + lam] : 0.0f;
+    }
+    for (int e = threadIdx.x; e < NSEG * RS + 128; e += 256) rows[e] = 0.0;
+    for (int e = threadIdx.x; e < ntab * tsize; e += 256) tabs[e] = 0.0;
+    if (threadIdx.x < 8) counters[threadIdx.x] = -1;
+    if (threadIdx.x == 0) { vl[L * pitch] = 0.0f; mrf_wait_init(&wait_lds, P.fault, P.spin_limit); }
+    __syncthreads();
+    const MrfWaitBlock *const wait_block = &wait_lds;
+    int *const pre_done = counters, *const chain_done = counters + 2, *const post_done = counters + 3;
+    const auto look = [](int *counter) {
+        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    };
+    const auto post = [](int *counter, int n) {               // (written by every lane: the same word)
+        __hip_atomic_store(counter, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+
+    // this workgroup's scanlines: NSEG consecutive ones of the launch's direction
+    const int r = P.r_first;
+    const unsigned nsc = (unsigned)P.g.nscan[r];
+    const unsigned sl = blockIdx.x * NSEG + seg;
+    const bool act = sl < (unsigned)P.g.B * nsc;
+    const int dh = P.g.dh[r], dw = P.g.dw[r];
+    int y0 = 0, x0 = 0, len = 0;
+    int last = 0;                                             // the scanline's last node, where the replay starts
+    const int nstep = dh * P.g.W + dw;
+    if (act) {
+        const int b = (int)(sl / nsc);
+        mrf_geom_head(P.g.H, P.g.W, dh, dw, sl - (unsigned)b * nsc, y0, x0, len);
+        last = (b * P.g.H + y0) * P.g.W + x0 + (len - 1) * nstep;
+    }
+    int maxlen = 0;
+#pragma unroll
+    for (int sg = 0; sg < NSEG; ++sg) {
+        const int l2 = __builtin_amdgcn_readlane(len, sg * SEG);
+        maxlen = l2 > maxlen ? l2 : maxlen;
+    }
+    const size_t N = (size_t)P.g.N, NL4 = N * L * 4;
+    const unsigned estep = (unsigned)(nstep * L);
+    const bool any = lam0 < L;
+    unsigned ce = (unsigned)last * (unsigned)L + (unsigned)lam0;      // first entry of the node at hand
+
+    if (wv == 0) {
+        // ---- the chain ---------------------------------------------------------------------------------
+        __builtin_amdgcn_s_setprio(3);
+        const mrf_buf bs = mrf_buffer(P.S + (size_t)r * N * L, NL4);
+        double *sb = rows + seg * RS;
+        double *spare = rows + NSEG * RS + lane;              // where a lane with nothing to add adds
+        const double cscale = (double)P.carry_scale[r];
+        float out[NL];
+#pragma unroll
+        for (int s = 0; s < NL; ++s) out[s] = 0.0f;
+        // the last node of a scanline has no successor in direction r
+        mrf_buf_store_f32xn<NL>(bs, (int)act & (int)any ? ce << 2 : MRF_BUF_NONE, out);
+        if (maxlen == 0) return;
+        const auto await = [&](int tt) {
+            int turns = 0;
+            while (look(&pre_done[tt & 1]) < tt) mrf_wait_turn(wait_block, turns);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        };
+        double ext[NL], carry[NL];
+        unsigned pk;
+        const auto fetch = [&](int slot) {
+#pragma unroll
+            for (int s = 0; s < NL; ++s) ext[s] = r_ext[(slot * NL + s) * 64 + lane];
+            pk = r_p[slot * 64 + lane];
+        };
+        await(0);
+        fetch(0);
+#pragma unroll
+        for (int s = 0; s < NL; ++s) carry[s] = 0.0;
+        for (int tt = 0;;) {
+#pragma unroll
+            for (int u = 0; u < NR; ++u, ++tt) {              // step tt uses slot u = tt % NR
+                double g[NL];
+                int pv[NL];
+#pragma unroll
+                for (int s = 0; s < NL; ++s) {
+                    r_cin[(u * NL + s) * 64 + lane] = carry[s];
+                    g[s] = carry[s] + ext[s];
+                    pv[s] = (int)((pk >> (8 * s)) & 255u);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                post(chain_done, tt);                         // (LDS keeps a wavefront's operations in order)
+                // (a lane merges its labels that go where its first one goes, and lanes whose first label goes where lane 0's
+                // does are summed by DPP for lane 0: mrf_bwd_sweep_narrow above)
+                double g0 = g[0];
+#pragma unroll
+                for (int s = 1; s < NL; ++s) g0 += pv[s] == pv[0] ? g[s] : 0.0;
+                const bool common = pv[0] == mrf_segment_lane0<SEG>(pv[0]);
+                const double gc0 = mrf_segment_sum_f64<SEG>(common ? g0 : 0.0);
+                __hip_atomic_fetch_add((int)!common | (int)(li == 0) ? &sb[pv[0]] : spare, common ? gc0 : g0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+                for (int s = 1; s < NL; ++s)
+                    __hip_atomic_fetch_add(pv[s] != pv[0] ? &sb[pv[s]] : spare, g[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                mrf_wave_lds_fence();
+                // in one batch behind the scatter: the counter of the next node's wavefront, then that node's ring entries, then
+                // the scattered vector
+                const int flag = __hip_atomic_load(&pre_done[(u + 1) & 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                fetch((u + 1) % NR);
+                double sv[NL];
+#pragma unroll
+                for (int s = 0; s < NL; ++s) sv[s] = sb[lam0 + s];
+                mrf_wave_lds_fence();
+#pragma unroll
+                for (int s = 0; s < NL; ++s) {
+                    out[s] = (float)sv[s];
+                    carry[s] = cscale * sv[s];
+                    sb[lam0 + s] = 0.0;
+                }
+                ce -= estep;
+                // node i has a predecessor: replay its update
+                mrf_buf_store_f32xn<NL>(bs, (int)(tt < len - 1) & (int)any ? ce << 2 : MRF_BUF_NONE, out);
+                if (__builtin_expect(tt + 1 >= maxlen, 0)) return;    // (uniform)
+                if (__builtin_expect(__builtin_amdgcn_readfirstlane(flag) < tt + 1, 0)) {
+                    await(tt + 1);
+                    fetch((u + 1) % NR);
+                }
+            }
+        }
+    }
+
+    if (wv <= 2) {
+        // ---- pre: step tt of wavefront jw = tt % 2 ----------------------------------------------------------
+        const int jw = wv - 1;
+        const bool own_unary = UNARY && r == P.unary_dir;
+        const unsigned no_old = own_unary && !P.unary_init ? 0u : MRF_BUF_NONE;
+        const mrf_buf bp = mrf_buffer(P.p + (size_t)r * N * L, N * L), bq = mrf_buffer(P.q + (size_t)r * N, N);
+        const mrf_buf bw = mrf_buffer(P.w + (P.w_mul ? (size_t)r * N : 0), P.w_mul ? N * 4 : 4), bu = mrf_buffer(P.gunary, NL4);
+        mrf_buf src[NS];
+        double cG[NS], cT[NS];
+        const int nsrc = P.n_src[r];
+#pragma unroll
+        for (int c = 0; c < NS; ++c) {
+            const bool live = c < nsrc, isgc = c == nsrc && P.use_gc;
+            // (empty slots are empty views: nothing is read for them)
+            src[c] = mrf_buffer(live ? P.src_base + (size_t)P.src_dir[r][c] * P.src_stride : P.gc, live || isgc ? NL4 : 0);
+            cG[c] = live ? (double)P.coefG[r][c] : (isgc ? 1.0 : 0.0);
+            cT[c] = live ? (double)P.coefT[r][c] : (isgc ? 1.0 : 0.0);
+        }
+        // p of the lane's labels: one access of 1, 2 or 4 bytes that stays inside the node's L bytes, and a shift
+        constexpr int PB = NL == 1 ? 1 : (NL == 2 ? 2 : 4);
+        const int p_at = any ? (lam0 < L - PB ? lam0 : L - PB) : 0, p_shift = any ? 8 * (lam0 - p_at) : 0;
+        const auto load_p = [&](unsigned at) {
+            if constexpr (PB == 1) return (unsigned)mrf_buf_u8(bp, at);
+            else if constexpr (PB == 2) return (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(bp, at, 0, 0);
+            else return (unsigned)__builtin_amdgcn_raw_buffer_load_b32(bp, at, 0, 0);
+        };
+        struct In {
+            float v[NS][NL];
+            float u[UNARY ? NL : 1];                          // old grad theta_i (0 unless accumulating)
+            unsigned p;
+            int q;
+            float w;
+        };
+        In A[D], B[D];
+        // (the prefetch walks on past the first node: what it then loads is another node or nothing, and never used)
+        unsigned pi = (unsigned)(last - jw * nstep), pe = (unsigned)(last - jw * nstep) * (unsigned)L;
+        const auto prefetch = [&](In &in) {
+            const unsigned at = any ? (pe + (unsigned)lam0) << 2 : MRF_BUF_NONE;
+#pragma unroll
+            for (int c = 0; c < NS; ++c) mrf_buf_f32xn<NL>(src[c], at, in.v[c]);
+            if constexpr (UNARY) mrf_buf_f32xn<NL>(bu, no_old ? MRF_BUF_NONE : at, in.u);
+            in.p = load_p(any ? pe + (unsigned)p_at : MRF_BUF_NONE);
+            in.q = mrf_buf_u8(bq, pi);
+            in.w = GV ? mrf_buf_f32(bw, P.w_mul ? pi * 4u : 0u) : 0.0f;
+            pe -= 2 * estep;
+            pi -= (unsigned)(2 * nstep);
+        };
+        int freed = -1;
+        const auto group = [&](const In (&in)[D], int it0) {
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                const int tt = jw + 2 * (it0 + u);
+                double ext[NL], part = 0.0;
+#pragma unroll
+                for (int s = 0; s < NL; ++s) {
+                    double e = cG[0] * (double)in[u].v[0][s];
+#pragma unroll
+                    for (int c = 1; c < NS; ++c) e = __builtin_fma(cG[c], (double)in[u].v[c][s], e);
+                    ext[s] = e;
+                    part = s == 0 ? e : part + e;
+                }
+                // back Eq. isgmr-norm: the entry at q loses the label sum
+                const double tot = mrf_segment_sum_f64<SEG>(part);
+                const int qv = in[u].q < L ? in[u].q : L - 1;
+                const unsigned pw = in[u].p >> p_shift;
+                unsigned pk = 0;
+#pragma unroll
+                for (int s = 0; s < NL; ++s) {
+                    if (lam0 + s == qv) ext[s] -= tot;
+                    const unsigned pr = (pw >> (8 * s)) & 255u;
+                    pk |= (pr < (unsigned)L ? pr : (unsigned)(L - 1)) << (8 * s);
+                }
+                double all[NL];
+                if constexpr (UNARY) {
+                    // grad theta_i: everything every direction passed back to node i, but for the carry
+#pragma unroll
+                    for (int s = 0; s < NL; ++s) {
+                        double a = (double)in[u].u[s];
+#pragma unroll
+                        for (int c = 0; c < NS; ++c) a = __builtin_fma(cT[c], (double)in[u].v[c][s], a);
+                        all[s] = a;
+                    }
+                }
+                if (tt >= maxlen) break;                      // (uniform)
+                int turns = 0;
+                while (freed < tt - NR) {
+                    freed = look(post_done);
+                    if (freed < tt - NR) mrf_wait_turn(wait_block, turns);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                const int slot = tt & (NR - 1);
+#pragma unroll
+                for (int s = 0; s < NL; ++s) {
+                    r_ext[(slot * NL + s) * 64 + lane] = ext[s];
+                    if constexpr (UNARY) r_all[(slot * NL + s) * 64 + lane] = all[s];
+                }
+                r_p[slot * 64 + lane] = pk;
+                if constexpr (GV) r_w[slot * 64 + lane] = in[u].w;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                post(&pre_done[jw], tt);
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < D; ++u) prefetch(A[u]);
+        for (int it0 = 0; jw + 2 * it0 < maxlen; it0 += 2 * D) {
+#pragma unroll
+            for (int u = 0; u < D; ++u) prefetch(B[u]);
+            __builtin_amdgcn_sched_barrier(0);
+            group(A, it0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < D; ++u) prefetch(A[u]);
+            __builtin_amdgcn_sched_barrier(0);
+            group(B, it0 + D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        // ---- post ----------------------------------------------------------------------------------------
+        const bool own_unary = UNARY && r == P.unary_dir;
+        const mrf_buf bu = mrf_buffer(P.gunary, NL4);
+        const mrf_buf bgw = mrf_buffer(P.gw ? P.gw + (size_t)r * N : nullptr, P.gw ? N * 4 : 0);
+        double *tab = tabs + (GV ? (seg % ntab) * tsize : 0), *spare = rows + NSEG * RS + 64 + lane;
+        // edge-weight gradients of eight nodes: lane li < 8 of a segment keeps that of the li-th, one access adds them all
+        static_assert(SEG >= 8, "lanes that keep edge-weight gradients");
+        float gwkeep = 0.0f;
+        int seen = -1;
+        for (int tt = 0; tt < maxlen; ++tt) {
+            int turns = 0;
+            while (seen < tt) {
+                seen = look(chain_done);
+                if (seen < tt) mrf_wait_turn(wait_block, turns);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+            const int slot = tt & (NR - 1);
+            double g[NL];
+            float out[NL];
+            const unsigned pk = r_p[slot * 64 + lane];
+            const double w = GV ? (double)r_w[slot * 64 + lane] : 0.0;
+#pragma unroll
+            for (int s = 0; s < NL; ++s) {
+                const double cin = r_cin[(slot * NL + s) * 64 + lane];
+                g[s] = cin + r_ext[(slot * NL + s) * 64 + lane];
+                if constexpr (UNARY) out[s] = (float)(cin + r_all[(slot * NL + s) * 64 + lane]);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            post(post_done, tt);
+            if constexpr (UNARY) mrf_buf_store_f32xn<NL>(bu, (int)(tt < len) & (int)any & (int)own_unary ? ce << 2 : MRF_BUF_NONE, out);
+            const bool update = tt < len - 1;                 // node i has a predecessor: its update is replayed
+            int at[NL];
+#pragma unroll
+            // (where there is no label p is 0, and the 0 behind V is met there: an infinite V[0][0] must not be)
+            for (int s = 0; s < NL; ++s) at[s] = __mul24((int)((pk >> (8 * s)) & 255u), pitch) + (any ? lam0 + s : L * pitch);
+            // (formed whether it is wanted or not: the view of an array that is not there holds nothing)
+            double acc = g[0] * (double)vl[any ? at[0] : L * pitch];
+#pragma unroll
+            for (int s = 1; s < NL; ++s) acc = __builtin_fma(g[s], (double)vl[any ? at[s] : L * pitch], acc);     // (g is 0 where there is no label)
+            acc = mrf_segment_sum_f64<SEG>(acc);
+            gwkeep = li == (tt & 7) ? (float)acc : gwkeep;
+            // one writer per entry and launch: a no-return atomic is a plain accumulate
+            if ((tt & 7) == 7 || tt + 1 == maxlen) {
+                const int t8 = (tt & ~7) + li;                // this lane's node counts if it has been passed and has a predecessor
+                mrf_buf_add_f32(bgw, (int)(li < 8) & (int)(t8 <= tt) & (int)(t8 < len - 1) ? (unsigned)(last - t8 * nstep) << 2 : MRF_BUF_NONE, gwkeep);
+            }
+            if constexpr (GV) {
+                // (no short-circuit in the conditions: it would become a branch)
+#pragma unroll
+                for (int s = 0; s < NL; ++s)
+                    __hip_atomic_fetch_add((int)update & (int)any ? &tab[at[s]] : spare, w * g[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            ce -= estep;
+        }
+    }
+    if constexpr (GV) {
+        // (the chain wavefront has ended or will; a barrier waits for the wavefronts that are left)
+        __syncthreads();
+        double *slot = P.gV + (size_t)blockIdx.x * L * L;
+        for (int e = (int)threadIdx.x - 64; e < L * L; e += 192) {
+            const int mu = e / L, at = mu * pitch + (e - mu * L);
+            double v = tabs[at];
+            for (int k = 1; k < ntab; ++k) v += tabs[k * tsize + at];
             mrf_slot_add(&slot[e], v);
         }
     }

@@ -517,6 +517,35 @@ def test_lanes_that_the_label_count_fills(oracle, L, B, want_V, kernel):
     assert mrf.mrf_last_sweep_launch(True).startswith("mrf_bwd_sweep_" + kernel), mrf.mrf_last_sweep_launch(True)
 
 
+# every segment of the narrow sweep that its lanes' labels fill, up to three and seven source arrays, scanlines of different
+# lengths in a workgroup (diagonals, images that fill none), rings that wrap
+@pytest.mark.parametrize("case", [(L, lanes, R) for L, lanes in ((1, 8), (5, 8), (8, 8), (9, 16), (16, 16), (18, 8), (21, 8), (24, 8), (20, 16), (32, 16), (17, 32), (23, 32), (32, 32))
+                                  for R in (4, 8)], ids=lambda c: "%d_%d_%d" % c)
+def test_narrow_backward_divided_among_four_wavefronts(oracle, case):
+    """Against the oracle, and against the sweep with one wavefront, which adds the same terms in the same order: the same floats
+    but for grad theta, whose sum starts elsewhere."""
+    import paper_1910_10892_amd as mrf
+    print("case narrow divided", case, flush=True)
+    L, lanes, R = case
+    B, H, W = (5, 3, 29) if R == 4 else (3, 7, 9)
+    pr = random_problem(840 + L, "trwp", B, H, W, L, DIRS8 if R == 8 else DIRS4, 2, symmetric=False, rho=np.linspace(0.3, 0.9, R))
+    pr.grad_cost = (pr.grad_cost * 0.2).astype(np.float32)
+    try:
+        for want_V in (True, False):
+            got = []
+            for divided in (4, 3):
+                assert mrf.mrf_tune(3, lanes) == 0 and mrf.mrf_tune(20, divided) == 0 and mrf.mrf_tune(6, 1) == 0
+                got.append(full_check(oracle, pr, want_V=want_V))
+                assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_narrow"
+                assert ("block=256" in mrf.mrf_last_sweep_launch(True)) == (divided == 4), mrf.mrf_last_sweep_launch(True)
+            for name in ("grad_edge_weight",) + (("grad_pairwise",) if want_V else ()):
+                np.testing.assert_array_equal(getattr(got[0], name), getattr(got[1], name), err_msg=name)
+            np.testing.assert_allclose(got[0].grad_unary, got[1].grad_unary, rtol=1e-6, atol=1e-6)
+    finally:
+        for k in (3, 6, 20):
+            mrf.mrf_tune(k, 0)
+
+
 MANY_SMALL_IMAGES = [
     # seed, algo, images, L: more workgroups of the narrow sweep than there are V-gradient slots (16,384)
     (791, "isgmr", 6600, 25), (792, "isgmr", 13200, 12), (793, "isgmr", 26400, 5),
