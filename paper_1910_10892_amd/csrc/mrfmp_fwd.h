@@ -3339,9 +3339,10 @@ mrf_fwd_sweep_packed(const MrfFwdParams P)
 //   loader   does all global loads, sums what does not depend on the running message, and hands a node over in a ring in LDS
 //   values   h, its exchange through LDS, candidates, minimum, normalisation; h and the new message go to the ring
 //   index    two of them, taking nodes in turn: the argmin tables (two levels as in mrf_fwd_sweep_narrow) and all stores
-// The minimum over the labels of the new message is that of h where V >= 0 with a zero diagonal and the weight is not
-// negative (the candidate mu = lambda is h(lambda) itself and no other is smaller), so it is taken while h is on its way
-// through LDS; other nodes take it from the message.  One scanline per wavefront: NG = 64 / SEG groups of lanes hold the
+// The minimum over the labels of the new message is that of h where V >= 0 with a zero diagonal and the weight is finite and
+// not negative (the candidate mu = lambda is h(lambda) itself and no other is smaller), so it is taken while h is on its way
+// through LDS; other nodes take it from the message.  Candidates that are NaN are passed over and a label without a finite
+// candidate has p = 0, as in a running argmin that starts from infinity.  One scanline per wavefront: NG = 64 / SEG groups of lanes hold the
 // same labels and share the source labels (HR each), joined by lane swaps; NG = 1: 64 / SEG scanlines of one direction per
 // wavefront, as many as fit.  Directions, factors, counts and base addresses are scalars, an entry is one 32-bit offset
 // into buffer views (the host checks that N L fits).
@@ -3535,7 +3536,8 @@ __global__ void __launch_bounds__(256) mrf_fwd_sweep_packed(const MrfFwdParams P
                     if constexpr (NC > 0) {
                         cm[k] = mrf_min(mrf_min3(e0, e1, e2), e3);
                     } else {
-                        best = k == 0 ? mrf_min(e0, e1) : mrf_min3(best, e0, e1);
+                        // (+inf where every candidate is NaN: here, or where the groups are joined)
+                        best = k > 0 ? mrf_min3(best, e0, e1) : (NG > 1 ? mrf_min(e0, e1) : mrf_min3(e0, e1, INFINITY));
                         best = mrf_min3(best, e2, e3);
                     }
                 }
@@ -3543,7 +3545,7 @@ __global__ void __launch_bounds__(256) mrf_fwd_sweep_packed(const MrfFwdParams P
                     best = cm[0];
 #pragma unroll
                     for (int k = 1; k + 1 < NCH; k += 2) best = mrf_min3(best, cm[k], cm[k + 1]);
-                    if constexpr (NCH % 2 == 0) best = mrf_min(best, cm[NCH - 1]);
+                    best = mrf_min3(best, cm[NCH - 1], INFINITY);
                 }
                 if constexpr (NG == 4) {
                     const auto x = __builtin_amdgcn_permlane16_swap(bits(best), bits(best), false, false);
@@ -3551,9 +3553,9 @@ __global__ void __launch_bounds__(256) mrf_fwd_sweep_packed(const MrfFwdParams P
                 }
                 if constexpr (NG >= 2) {
                     const auto x = __builtin_amdgcn_permlane32_swap(bits(best), bits(best), false, false);
-                    best = mrf_min(real(x[0]), real(x[1]));
+                    best = mrf_min3(real(x[0]), real(x[1]), INFINITY);
                 }
-                if (__builtin_expect((__ballot(!(wgt >= 0.0f)) | slow) != 0, 0)) tq = label_min(valid ? best : INFINITY);
+                if (__builtin_expect((__ballot(bits(wgt) >= 0x7f800000u) | slow) != 0, 0)) tq = label_min(valid ? best : INFINITY);
                 carry = best - tq;
                 // (the next node's values are waited for here, where only reads are under way: behind the writes below the
                 // wait would be for those)
@@ -3733,22 +3735,23 @@ __global__ void __launch_bounds__(256) mrf_fwd_sweep_packed(const MrfFwdParams P
         mrf_first_equal4<0>(arg, best, d0, d1, d2, d3);
         arg += 4 * ck;
         if constexpr (NG > 1) {
-            // join the groups: a strict '<' keeps the lower group's index on a tie
+            // join the groups: the lower one's index on a tie, never that of a group whose candidates are all NaN
             arg += grp * HR;
             if constexpr (NG == 4) {
                 const auto x = __builtin_amdgcn_permlane16_swap(bits(best), bits(best), false, false);
                 const auto a = __builtin_amdgcn_permlane16_swap((unsigned)arg, (unsigned)arg, false, false);
-                arg = real(x[1]) < real(x[0]) ? (int)a[1] : (int)a[0];
                 best = mrf_min(real(x[0]), real(x[1]));
+                arg = real(x[0]) == best ? (int)a[0] : (int)a[1];
             }
             const auto x = __builtin_amdgcn_permlane32_swap(bits(best), bits(best), false, false);
             const auto a = __builtin_amdgcn_permlane32_swap((unsigned)arg, (unsigned)arg, false, false);
-            arg = real(x[1]) < real(x[0]) ? (int)a[1] : (int)a[0];
+            best = mrf_min(real(x[0]), real(x[1]));
+            arg = real(x[0]) == best ? (int)a[0] : (int)a[1];
         }
-        arg = arg < L ? arg : L - 1;
-        // the message is 0 exactly where it attains its minimum
-        const unsigned long long zero = __ballot((int)valid & (int)(m == 0.0f));
-        const int qidx = mrf_segment_first<SEG>(zero, lane);
+        arg = best < INFINITY ? arg : 0;                 // (and with that below L: labels past it are +inf)
+        // the message is 0 exactly where it attains a finite minimum, NaN where it attains an infinite one
+        const unsigned long long least = __ballot((int)valid & (int)!(m > 0.0f));
+        const int qidx = mrf_segment_first<SEG>(least, lane);
         mrf_buf_store_f32(bm, n < len_m ? oe << 2 : MRF_BUF_NONE, m);
         mrf_buf_store_u8(bp, n < len_m ? oe : MRF_BUF_NONE, arg);
         mrf_buf_store_u8(bq, n < len_q ? on : MRF_BUF_NONE, qidx);

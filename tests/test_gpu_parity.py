@@ -246,8 +246,7 @@ def test_chunk_minima_where_no_label_is_possible(algo, L):
 @pytest.mark.parametrize("L", [5, 13, 21, 32, 40, 96])
 def test_impossible_labels_and_forbidden_transitions(oracle, L):
     """Infinite unaries and infinite entries of V (one label of every pixel and the diagonal stay finite): the argmins of
-    the oracle, also where every candidate is infinite.  (The sweep of few labels with index wavefronts picks another
-    label there now and then; the library asks for finite inputs.)"""
+    the oracle, also where every candidate is infinite."""
     import paper_1910_10892_amd as mrf
     from gpu_harness import run_gpu
     pr = random_problem(630 + L, "isgmr", 2, 7, 9, L, DIRS8, 2, symmetric=False)
@@ -269,6 +268,58 @@ def test_impossible_labels_and_forbidden_transitions(oracle, L):
             mrf.mrf_tune(knob, 0)
     for name in ("p", "q", "labels", "cost", "messages"):
         np.testing.assert_array_equal(getattr(g, name), getattr(f, name), err_msg=name)
+
+
+def not_finite(pr, kind, seed):
+    """Writes infinities or NaN into a problem: what the oracle makes of them is a running argmin from infinity, with NaN passed over."""
+    rng = np.random.default_rng(seed)
+    L = pr.unary.shape[-1]
+    if kind == "masks":                       # some labels of every pixel, and transitions, cannot be
+        mask = rng.random(pr.unary.shape) < 0.3
+        mask[..., L // 2] = False
+        pr.unary[mask] = np.inf
+        never = rng.random(pr.pairwise.shape) < 0.5
+        np.fill_diagonal(never, False)
+        pr.pairwise[never] = np.inf
+    elif kind == "infinite":                  # one pixel without a possible label, in the middle of scanlines
+        pr.unary[:, 3, 4, :] = np.inf
+    elif kind == "nan":                       # one pixel whose upper labels are not numbers, one with none that is
+        pr.unary[:, 3, 4, :L // 2] = np.nan
+        pr.unary[:, 2, 6, :] = np.nan
+    elif kind == "weight":
+        pr.edge_weight[:, :, 2, 5] = np.inf
+    return pr
+
+
+# (masks: TRWP forms 0 x inf and inf - inf from them, so that whole groups of candidates are NaN beside finite ones)
+@pytest.mark.parametrize("kind", ["masks", "infinite", "nan", "weight"])
+@pytest.mark.parametrize("algo", ["isgmr", "trwp"])
+@pytest.mark.parametrize("L", [3, 8, 13, 16, 17, 21, 24, 32])
+def test_few_labels_that_are_not_finite_by_the_default_rules(oracle, L, algo, kind):
+    """The packed sweep divided among four wavefronts, which small launches get: indices, costs and messages of the oracle where
+    labels are impossible, pixels have none, or a weight is infinite; one and several scanlines per wavefront."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    print("case not finite", L, algo, kind, flush=True)
+    for zero_diagonal in (True, False):
+        pr = random_problem(650 + L, algo, 2, 7, 9, L, DIRS4, 2, symmetric=False, rho=np.linspace(0.3, 0.9, 4))
+        if zero_diagonal:
+            np.fill_diagonal(pr.pairwise, 0.0)
+        not_finite(pr, kind, L)
+        with np.errstate(all="ignore"):
+            f = oracle_forward(oracle, pr)
+        try:
+            for knobs in ((0, 0), (4, 0), (5, 0), (2, 2)) if 16 < L <= 21 else ((0, 0), (4, 0), (5, 0)):
+                assert mrf.mrf_tune(11, knobs[0]) == 0 and mrf.mrf_tune(13, knobs[1]) == 0
+                g = run_gpu(pr, backward=False)
+                assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_packed"
+                for name in ("p", "q", "cost", "messages"):
+                    np.testing.assert_array_equal(getattr(g, name), getattr(f, name), err_msg="%s %s" % (name, knobs))
+                some = ~np.isnan(f.cost).any(-1)      # (mrf_aggregate names no label for a pixel whose costs are not numbers)
+                np.testing.assert_array_equal(g.labels[some], f.labels[some])
+        finally:
+            mrf.mrf_tune(11, 0)
+            mrf.mrf_tune(13, 0)
 
 
 @pytest.mark.parametrize("algo,B,H,W,L,dirs,halves", [
