@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <float.h>
 #include <limits.h>
 #ifdef __HIPCC__
 #include <utility>

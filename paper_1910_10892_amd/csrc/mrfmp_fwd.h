@@ -740,7 +740,7 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
             const auto cx = __builtin_amdgcn_permlane32_swap((unsigned)cid, (unsigned)cid, false, false);
             const float blo = __uint_as_float(bx[0]), bhi = __uint_as_float(bx[1]);
             const float tv = mrf_min(blo, bhi);
-            const float tp = mrf_min3(blo, bhi, 3.402823466e38f);       // what p looks for: no candidate if none is finite
+            const float tp = mrf_min3(blo, bhi, FLT_MAX);       // what p looks for: no candidate if none is finite
             const int mu0 = bhi < blo ? LH + 8 * (int)cx[1] : 8 * (int)cx[0];
 
             // ---- minimum over the labels (Eq. isgmr-norm) ----
@@ -949,7 +949,8 @@ mrf_fwd_sweep_edge(const MrfFwdParams P)
 // NG = 64 / SEG groups of SEG lanes (16 up to 16 labels, else 32) hold the same destination labels and group k the source
 // labels k HR .. k HR + HR - 1, so no lane idles for want of labels.  Every group forms all of h (same loads, same
 // operations) and keeps it in LDS; a lane reads its group's HR entries, finds their lowest argmin, and one or two lane swaps
-// join the groups, the lower one first on a tie.  Entries without a source label are h = +inf.
+// join the groups, the lower one first on a tie.  Entries without a source label are h = +inf.  Candidates that are NaN are
+// passed over and a label without a finite candidate has p = 0, as in a running argmin that starts from infinity.
 // 256 x 256, 21 labels, 4 directions, ISGMR sweep: 273 us with one label per lane and half a table in flight, now 131 (4.2 TB/s
 // of tables and messages).
 template <int SEG, int HR, int NT, int RMAX, bool TRWP>
@@ -1115,13 +1116,14 @@ mrf_fwd_sweep_edge_groups(const MrfFwdParams P)
     for (int m = 0; m < HP; ++m) dP[m] = 0.0f;
     auto finish = [&]() {
         int arg = 0;
+        const float least = mrf_min(bestP, FLT_MAX);                  // (nothing equals it where no candidate is finite)
         mrf_static_for<HP / 4>([&](auto g4) {
             constexpr int m0 = HP - 4 - 4 * decltype(g4)::value;      // from the top down: the lowest index lands last
-            mrf_first_equal4<m0>(arg, bestP, dP[m0], dP[m0 + 1], dP[m0 + 2], dP[m0 + 3]);
+            mrf_first_equal4<m0>(arg, least, dP[m0], dP[m0 + 1], dP[m0 + 2], dP[m0 + 3]);
         });
         arg += grp * HR;
         // join the groups: a strict '<' keeps the lower group's index on a tie
-        float b = bestP;
+        float b = least;
         if constexpr (NG == 4) {
             const auto b2 = pair(bits(b), std::false_type{}), a2 = pair((unsigned)arg, std::false_type{});
             arg = real(b2[1]) < real(b2[0]) ? (int)a2[1] : (int)a2[0];
@@ -1174,7 +1176,7 @@ mrf_fwd_sweep_edge_groups(const MrfFwdParams P)
             }
             rows();
             mrf_wave_lds_fence();
-            bestP = mrf_min(dP[0], dP[1]);
+            bestP = mrf_min3(dP[0], dP[1], INFINITY);    // (+inf where every candidate is NaN)
 #pragma unroll
             for (int m = 2; m + 1 < HP; m += 2) bestP = mrf_min3(bestP, dP[m], dP[m + 1]);
             float b = bestP;

@@ -1679,6 +1679,30 @@ def test_per_edge_tables_in_lane_groups(oracle, case):
         check_forward(g, oracle.forward(pr.algo, pr.unary, None, pr.dirs, pr.K, rho=pr.rho, pairwise_edge=pr.pairwise_edge))
 
 
+@pytest.mark.parametrize("kind", ["masks", "infinite", "nan"])
+@pytest.mark.parametrize("algo", ["isgmr", "trwp"])
+@pytest.mark.parametrize("L", [3, 8, 13, 16, 17, 24, 25, 32])
+def test_per_edge_tables_that_are_not_finite_in_lane_groups(oracle, L, algo, kind):
+    """Tables with forbidden transitions, impossible labels and pixels without one: the indices, costs and messages of the oracle."""
+    from gpu_harness import run_gpu
+    print("case tables not finite", L, algo, kind, flush=True)
+    pr = random_problem(680 + L, algo, 2, 7, 9, L, DIRS4, 2, per_edge=False, rho=np.linspace(0.3, 0.9, 4))
+    not_finite(pr, kind, L)
+    rng = np.random.default_rng(9200 + L)
+    pr.pairwise_edge = rng.random((4, 2, 7, 9, L, L)).astype(np.float32)
+    if kind != "nan":
+        never = rng.random(pr.pairwise_edge.shape) < 0.3
+        never[..., np.arange(L), np.arange(L)] = False
+        pr.pairwise_edge[never] = np.inf
+    with np.errstate(all="ignore"):
+        f = oracle.forward(pr.algo, pr.unary, None, pr.dirs, pr.K, rho=pr.rho, pairwise_edge=pr.pairwise_edge)
+    g = run_gpu(pr, backward=False)
+    for name in ("p", "q", "cost", "messages"):
+        np.testing.assert_array_equal(getattr(g, name), getattr(f, name), err_msg=name)
+    some = ~np.isnan(f.cost).any(-1)
+    np.testing.assert_array_equal(g.labels[some], f.labels[some])
+
+
 # the sweeps that leave the tables' gradient to a pass of its own: few scanlines (chain) and more than 1,024 (narrow: 8, 16 and
 # 32 lanes, three labels per lane), ragged and odd label counts; workspace for one iteration of three (L = 2, 3 on larger
 # grids: passes that add to the tables), the least workspace that is accepted, gradients off a 16-byte boundary
