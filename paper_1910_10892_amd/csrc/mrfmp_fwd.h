@@ -2900,7 +2900,9 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
         const float wgt = lw[slot];
         const float2 mm = mring[slot];
         const float hmin = mm.x, tq = mm.y;
-        const bool positive = __builtin_amdgcn_readfirstlane(__float_as_int(wgt)) >= 0;
+        // (a finite minimum of h makes every entry of the message finite)
+        const bool positive = (int)(__builtin_amdgcn_readfirstlane(__float_as_int(wgt)) >= 0) &
+                              (int)(((unsigned)__builtin_amdgcn_readfirstlane(__float_as_int(hmin)) & 0x7fffffffu) < 0x7f800000u);
         const float gmin = __builtin_fmaf(wgt, fT, hmin);
         // lowest label that attains the far minimum, and the lowest one that attains that of the message
         int mug = L, q = L;
@@ -2951,7 +2953,7 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                     p[o2] = max(min(min(pw, pg), L - 1), 0);
                 }
             } else {
-                // negative weight: every mu
+                // negative weight, or no finite candidate (p = 0): every mu
 #pragma unroll
                 for (int o2 = 0; o2 < 2; ++o2) {
                     float best = INFINITY;

@@ -278,9 +278,10 @@ def not_finite(pr, kind, seed):
         mask = rng.random(pr.unary.shape) < 0.3
         mask[..., L // 2] = False
         pr.unary[mask] = np.inf
-        never = rng.random(pr.pairwise.shape) < 0.5
-        np.fill_diagonal(never, False)
-        pr.pairwise[never] = np.inf
+        if pr.pairwise_kind == 0:
+            never = rng.random(pr.pairwise.shape) < 0.5
+            np.fill_diagonal(never, False)
+            pr.pairwise[never] = np.inf
     elif kind == "infinite":                  # one pixel without a possible label, in the middle of scanlines
         pr.unary[:, 3, 4, :] = np.inf
     elif kind == "nan":                       # one pixel whose upper labels are not numbers, one with none that is
@@ -782,6 +783,27 @@ def truncated_problem(seed, algo, H, W, L, dirs, K, kind, trunc, integer_valued,
         pr.edge_weight = pr.edge_weight * np.where(rng.random(pr.edge_weight.shape) > 0.2, 1.0, -0.5)
     pr.edge_weight = pr.edge_weight.astype(np.float32)
     return pr
+
+
+@pytest.mark.parametrize("kind", ["masks", "infinite", "nan"])
+@pytest.mark.parametrize("case", [("isgmr", 96, 200.0, 2, DIRS4), ("trwp", 192, 200.0, 2, DIRS4), ("trwp", 255, 16.0, 1, DIRS4),
+                                  ("isgmr", 130, 7.0, 1, DIRS4), ("isgmr", 97, 8.0, 1, DIRS4)], ids=lambda c: "%s_%d" % c[:2])
+def test_window_with_loader_and_index_wavefronts_where_labels_are_not_finite(oracle, case, kind):
+    """mrf_fwd_sweep_window_squad by the default rules: the indices, costs and messages of the oracle where labels are impossible
+    or pixels have none."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    print("case window not finite", case[:4], kind, flush=True)
+    algo, L, trunc, pk, dirs = case
+    pr = not_finite(truncated_problem(660 + L, algo, 7, 9, L, dirs, 2, pk, trunc, False, "pos"), kind, L)
+    with np.errstate(all="ignore"):
+        f = oracle_forward(oracle, pr)
+    g = run_gpu(pr, backward=False)
+    assert mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_window_squad", mrf.mrf_last_sweep_launch(False)
+    for name in ("p", "q", "cost", "messages"):
+        np.testing.assert_array_equal(getattr(g, name), getattr(f, name), err_msg=name)
+    some = ~np.isnan(f.cost).any(-1)
+    np.testing.assert_array_equal(g.labels[some], f.labels[some])
 
 
 WINDOW_CASES = [
