@@ -1018,13 +1018,15 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
 {
     const dim3 grid((unsigned)P.total_scanlines);
     const bool gv = P.gV != nullptr;
-    const bool gs = LP <= 2 && (P.gstore || P.gstore32);  // the helpers store the node gradients (no tables, no V)
+    const bool edge = P.edge != 0;                        // (per-edge tables: a kernel of its own)
+    const bool gs = edge || (LP <= 2 && P.gstore);        // the helpers store the node gradients (no tables, no V)
     if (gs) vg = true;
     const bool hot = P.hot_label && (gs || !((LP == 1 && gv) || vg));
-    note_launch(1, "mrf_bwd_sweep_chain", P.total_scanlines, 64 * (1 + ni), "%d,%d,%d,%d,%s,%s,%s", LP, NS, D, ni,
-                (!(LP == 1 && gv) && vg) ? "true" : "false", ((LP == 1 && gv) || gs) ? "true" : "false", hot ? "true" : "false");
+    note_launch(1, "mrf_bwd_sweep_chain", P.total_scanlines, 64 * (1 + ni), "%d,%d,%d,%d,%s,%s,%s%s", LP, NS, D, ni,
+                (!(LP == 1 && gv) && vg) ? "true" : "false", ((LP == 1 && gv) || gs) ? "true" : "false", hot ? "true" : "false",
+                edge ? ",true" : "");
     if (gv && (LP != 1 || P.total_scanlines > grad_slots(P.g.L))) return hipErrorInvalidValue;
-    const size_t lds = mrf_bwd_chain_lds_bytes(LP, ni, P.g.L, P.unary_dir >= 0, vg, gv);
+    const size_t lds = mrf_bwd_chain_lds_bytes(LP, ni, P.g.L, P.unary_dir >= 0, vg, gv, edge);
     if (lds > chain_lds_cap(P.total_scanlines)) return hipErrorInvalidValue;
     // (more than 64 KB of dynamic LDS has to be announced per kernel)
 #define MRF_CH_GO(...) \
@@ -1038,6 +1040,12 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
     } while (0)
 #define MRF_CH(n) \
     if (ni == n) { \
+        if constexpr (LP == 1 && n >= 4) { \
+            if (edge) { \
+                MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, true, true, false, true>); \
+                return hipGetLastError(); \
+            } \
+        } \
         if constexpr (LP == 1) { \
             if (gv) { \
                 MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, false, true, false>); \

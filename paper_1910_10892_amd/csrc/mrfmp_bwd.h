@@ -101,11 +101,11 @@ __device__ inline void mrf_slot_add(double *slot, double v)
 #define MRF_CHAIN_MAX_HELPERS 12
 
 // dynamic LDS of mrf_bwd_sweep_chain (host and device agree through this one expression)
-__host__ __device__ inline size_t mrf_bwd_chain_lds_bytes(int LP, int NI, int L, bool with_theta, bool vg, bool gv)
+__host__ __device__ inline size_t mrf_bwd_chain_lds_bytes(int LP, int NI, int L, bool with_theta, bool vg, bool gv, bool edge = false)
 {
     const size_t NR = 2 * (size_t)NI, LL = 64 * (size_t)LP;
     const size_t arrays = sizeof(double) * (3 * NR * LL + LL + ((gv && LP == 1) ? (size_t)NI * L * L : 0)) +
-                          sizeof(float) * (with_theta ? NR * LL : 0) + sizeof(int) * (3 * MRF_CHAIN_MAX_HELPERS + 1) +
+                          (edge ? sizeof(double) : sizeof(float)) * (with_theta ? NR * LL : 0) + sizeof(int) * (3 * MRF_CHAIN_MAX_HELPERS + 1) +
                           sizeof(float) * (gv ? (size_t)L * L : (vg ? 0 : (size_t)L)) + NR * LL;
     return (arrays + 7) / 8 * 8 + sizeof(MrfWaitBlock);      // the deadline of the waits sits behind the arrays
 }
@@ -489,15 +489,18 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
 // accumulator of its own in LDS, lane lambda owning column lambda; their sum goes to the workgroup's slot at the end.
 // GV with VG (33..128 labels): there is no room for the tables; the helpers store the gradient vector g of every node
 // in P.gstore (0 where no update is replayed) and leave both pairwise gradients to mrf_bwd_pairwise_*, a streaming
-// pass that has all of LDS for V and the table (P.gstore32: the same for mrf_bwd_edge_tables).  What is left for a helper is short enough that four of them keep
+// pass that has all of LDS for V and the table.  What is left for a helper is short enough that four of them keep
 // up with the chain, so the layout stays ahead to 1,536 scanlines per launch (it did to 512 while the helpers
 // gathered from V).
+// EDGE (GV and VG, 33..64 labels and fewer): a problem with per-edge tables: the helpers store g in P.gstore32, if that is
+// wanted, for mrf_bwd_edge_tables, and what arrives at theta from elsewhere waits for the carry in double, so that grad theta
+// is rounded once, as in mrf_bwd_sweep.
 // HOT: truncated models send most labels to one source label, and the chain wavefront's LDS
 // adds would queue at that one word; the helpers guess it (as in mrf_bwd_sweep) and the chain
 // sums its lanes with a DPP tree while the LDS round trip is under way.  Costs the chain some
 // twenty instructions per node: for launches that are bound by LDS throughput, not by the
 // latency of the chain.
-template <int LP, int NS, int D, int NI, bool VG, bool GV, bool HOT>
+template <int LP, int NS, int D, int NI, bool VG, bool GV, bool HOT, bool EDGE = false>
 __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBwdParams P)
 {
     constexpr int NR = 2 * NI;
@@ -513,7 +516,9 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
     constexpr bool GVT = GV && !VG;          // V-gradient tables in LDS
     constexpr bool GS = GV && VG;            // node gradients stored for mrf_bwd_pairwise_*
     static_assert(!GVT || LP == 1, "V-gradient tables");
-    float *a_extT = reinterpret_cast<float *>(gvacc + (GVT ? NI * P.g.L * P.g.L : 0));   // [NR][LL] pre -> post (launches that form grad theta)
+    static_assert(!EDGE || (GS && !HOT), "per-edge tables");
+    using theta_t = std::conditional_t<EDGE, double, float>;
+    theta_t *a_extT = reinterpret_cast<theta_t *>(gvacc + (GVT ? NI * P.g.L * P.g.L : 0));   // [NR][LL] pre -> post (launches that form grad theta)
     int *pre_done = reinterpret_cast<int *>(a_extT + (P.unary_dir >= 0 ? NR * LL : 0));   // [MRF_CHAIN_MAX_HELPERS] per helper: last step published
     int *chain_done = pre_done + MRF_CHAIN_MAX_HELPERS;          // last step the chain finished
     int *a_hot = chain_done + 1;                                 // [NR] pre -> chain: most popular scatter target, or -1
@@ -729,8 +734,8 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
     float *guw = P.gunary + (size_t)head * L;                       // stores of stage "post"
     float *sw = P.S + ((size_t)r * N + head) * L;
     float *gww = P.gw ? P.gw + (size_t)r * N + head : nullptr;
-    double *gsw = GS && P.gstore ? P.gstore + (size_t)head * L : nullptr;
-    float *gsw32 = GS && P.gstore32 ? P.gstore32 + ((size_t)r * N + head) * L : nullptr;
+    double *gsw = GS && !EDGE ? P.gstore + (size_t)head * L : nullptr;
+    float *gsw32 = EDGE && P.gstore32 ? P.gstore32 + ((size_t)r * N + head) * L : nullptr;
 
     int chain_seen = -1;
     for (int it0 = 0; it0 < T + 1 && T > 0; it0 += D) {
@@ -757,7 +762,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
                     }
                     ev[s] = lam < L ? e : 0.0;
                     part += ev[s];
-                    if (own_unary) a_extT[slot * LL + lam] = (float)eT;
+                    if (own_unary) a_extT[slot * LL + lam] = (theta_t)eT;
                     // (labels past L scatter their zeros to entries of their own)
                     a_p[slot * LL + lam] = (uint8_t)(lam < L ? (pcur[u][s] < L ? pcur[u][s] : L - 1) : lam);
                 }
@@ -821,9 +826,10 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
                     if ((P.gw || GV) && lam < L) {
                         const double g = cin + a_ext[slot * LL + lam];    // as the chain formed it
                         const int pv = a_p[slot * LL + lam];
-                        if constexpr (GS) {
+                        if constexpr (EDGE) {
                             if (gsw32) gsw32[oi + lam] = update ? (float)g : 0.0f;
-                            else gsw[oi + lam] = update ? g : 0.0;
+                        } else if constexpr (GS) {
+                            gsw[oi + lam] = update ? g : 0.0;
                         }
                         if (!GS && P.gw) {
                             float vv;

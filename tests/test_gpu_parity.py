@@ -1764,6 +1764,35 @@ def test_gradient_of_per_edge_tables_in_a_pass_of_its_own(oracle, case):
             check_grad("grad_pairwise_edge", out.grad_pairwise, b[np.float32].grad_pairwise_edge, b[np.float64].grad_pairwise_edge)
 
 
+# chain and narrow layout, TRWP (grad theta formed by one direction per iteration) and ISGMR on small grids (by the first one)
+@pytest.mark.parametrize("case", [("trwp", 2, 9, 24, 13), ("trwp", 1, 20, 30, 45), ("isgmr", 2, 12, 14, 21), ("isgmr", 1, 12, 17, 64),
+                                  ("trwp", 3, 4, 360, 21), ("isgmr", 1, 2, 530, 8)], ids=lambda c: "_".join(map(str, c)))
+@pytest.mark.parametrize("want_V", [True, False])
+def test_unary_gradient_of_per_edge_tables_is_rounded_once(oracle, case, want_V):
+    """What arrives at theta is summed in double and rounded to float once per pass over it, in every layout: so the layouts
+    agree in all bits but where two double sums of other orders, some 2^-50 apart, lie on two sides of a rounding boundary (of
+    few floats with few bits between them an exact tie now and then), or cancel to what is left of them (below 2^-40 of the
+    largest value, whose last place is 2^-24 of it).  What a scatter array rounds the other way reaches the entries of the scanlines
+    through its node that went to the same label: some tens of the 5,616 or more here, one in a hundred at most.  Summed in two
+    floats, 1.4 to 14 values in a hundred differ."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    print("case rounded once", case, want_V, flush=True)
+    algo, B, H, W, L = case
+    pr = random_problem(890 + L, algo, B, H, W, L, DIRS4, 3, per_edge=False, rho=np.linspace(0.3, 0.9, 4))
+    pr.pairwise_edge = np.random.default_rng(9300 + L).random((4, B, H, W, L, L)).astype(np.float32)
+    a = run_gpu(pr, want_V=want_V)
+    assert mrf.mrf_last_sweep_kernel(True) != "mrf_bwd_sweep"
+    try:
+        assert mrf.mrf_tune(6, 1) == 0
+        b = run_gpu(pr, want_V=want_V)
+        assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep"
+    finally:
+        mrf.mrf_tune(6, 0)
+    differ = np.count_nonzero(np.abs(a.grad_unary - b.grad_unary) > np.abs(b.grad_unary).max() * 2.0 ** -40)
+    assert differ <= a.grad_unary.size // 100, (differ, a.grad_unary.size)
+
+
 def test_per_edge_tables_argument_errors():
     import torch
     import paper_1910_10892_amd as mrf
