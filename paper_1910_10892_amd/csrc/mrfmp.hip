@@ -159,7 +159,7 @@ MRF_G(int g_tune_gv_tile, 0);      // V gradient of 33..128 labels in one LDS ta
 MRF_G(int g_tune_dense_sliced, 0); // dense sweep for more than 64 labels with a slice of the labels per wavefront: 0 yes, 1 no
 MRF_G(int g_tune_spin_limit, 0); // turns a wait between wavefronts may take: 0 = default
 MRF_G(int g_tune_pack_idx, 0);   // packed dense sweep divided among four wavefronts: 0 by launch size, 1 never, 2 always, 3 never and 64-bit offsets,
-                                 // 4 always and one scanline per wavefront, 5 always and several
+                                 // 4 always and one scanline per wavefront, 5 always and several, 6 as 3 with two index wavefronts
 MRF_G(int g_tune_chain, 0);      // backward sweep with a chain wavefront: 0 auto, 1 never, 2 whenever possible
 MRF_G(int g_tune_chain_hot, 0);  // its pre-reduction of the most popular scatter target: 0 auto, 1 never, 2 whenever V is no dense table
 MRF_G(int g_tune_chain_ni, 0);   // its helpers per scanline: 0 auto, 2, 4, 6, 8
@@ -317,7 +317,8 @@ hipError_t launch_packed_mu(const MrfFwdParams &P, int algo, int rmax, long long
 {
     const unsigned blocks = (unsigned)((scanlines + 64 / SEG - 1) / (64 / SEG));
     // (few wavefronts in a launch beyond the 32-bit offsets: two further ones per workgroup for the argmin tables and stores)
-    const bool idx = P.g.N * P.g.L > MRF_BUF_MOST && g_tune_pack_idx != 1 && g_tune_pack_idx != 3 && (g_tune_pack_idx == 2 || blocks <= 1024);
+    const bool idx = g_tune_pack_idx == 6 || (P.g.N * P.g.L > MRF_BUF_MOST && g_tune_pack_idx != 1 && g_tune_pack_idx != 3 &&
+                                              (g_tune_pack_idx == 2 || blocks <= 1024));
     // else one wavefront does all: mrf_fwd_sweep_narrow as far as its 32-bit offsets reach
     if (!idx && g_tune_pack_idx != 3 && P.g.N * P.g.L <= MRF_BUF_MOST) {
         bool none = true;

@@ -1122,11 +1122,11 @@ def test_packed_scanlines_layout(oracle, case):
         a = full_check(oracle, pr)
         assert mrf.mrf_tune(3, 2) == 0 and mrf.mrf_tune(11, 1) == 0      # packed, one wavefront does all
         b = full_check(oracle, pr)
-        assert mrf.mrf_tune(11, 2) == 0                                  # packed, value + index wavefront
+        assert mrf.mrf_tune(11, 2) == 0                                  # divided among four wavefronts
         c = full_check(oracle, pr)
         more = []
         if 16 < L <= 21:
-            # three scanlines per wavefront (segments of 21 lanes), with and without index wavefronts
+            # three scanlines per wavefront (segments of 21 lanes), divided and not
             assert mrf.mrf_tune(13, 2) == 0
             more.append(full_check(oracle, pr))
             assert "mrf_fwd_sweep_packed<21," in mrf.mrf_last_sweep_launch(False)
@@ -1143,6 +1143,35 @@ def test_packed_scanlines_layout(oracle, case):
         np.testing.assert_array_equal(getattr(a, name), getattr(c, name), err_msg=name)
         for m in more:
             np.testing.assert_array_equal(getattr(a, name), getattr(m, name), err_msg=name)
+
+
+@pytest.mark.parametrize("case", PACK_CASES, ids=lambda c: "seed%d" % c[0])
+def test_packed_scanlines_with_64_bit_offsets(oracle, case):
+    """What arrays beyond the 32-bit offsets get, on small ones: one wavefront that does all, and a value wavefront with two index
+    wavefronts (launches of few scanlines), also with three scanlines per wavefront; the same bits as mrf_fwd_sweep_narrow."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    print("case packed 64-bit", case[:8], flush=True)
+    seed, algo, B, H, W, L, dirs, K, iv, pe = case
+    pr = random_problem(seed, algo, B, H, W, L, dirs, K, integer_valued=iv, per_edge=pe, rho=np.linspace(0.3, 0.9, len(dirs)))
+    f = oracle_forward(oracle, pr)
+    out = []
+    try:
+        for form, three in ((1, 1), (3, 1), (6, 1), (3, 2), (6, 2)) if 16 < L <= 21 else ((1, 1), (3, 1), (6, 1)):
+            assert mrf.mrf_tune(3, 2) == 0 and mrf.mrf_tune(11, form) == 0 and mrf.mrf_tune(13, three) == 0
+            out.append(run_gpu(pr, backward=False))
+            check_forward(out[-1], f)
+            launch = mrf.mrf_last_sweep_launch(False)
+            if form == 1:
+                assert launch.startswith("mrf_fwd_sweep_narrow"), launch
+            else:
+                assert launch.startswith("mrf_fwd_sweep_packed<%d," % (21 if three == 2 else 16 if L <= 16 else 32)), launch
+                assert (",2>" if form == 6 else ",0>") in launch, launch
+            for name in ("p", "q", "labels", "cost", "messages"):
+                np.testing.assert_array_equal(getattr(out[0], name), getattr(out[-1], name), err_msg=name)
+    finally:
+        for k in (3, 11, 13):
+            mrf.mrf_tune(k, 0)
 
 
 def test_optional_outputs_may_be_null(oracle):
