@@ -963,7 +963,7 @@ mrf_fwd_sweep_edge_groups(const MrfFwdParams P)
     constexpr int NL = NT > 0 ? NT : 1, D0 = 1 + 63 / (NL + RMAX + 4), D = D0 > 7 ? 7 : D0;
     constexpr int TILE = NT > 0 ? 256 * NT : 64;         // floats
     static_assert(NG == 2 || NG == 4, "lane groups");
-    __shared__ __align__(16) float tile[TILE + 256 + HR * 32];
+    __shared__ __align__(16) float tile[TILE + 256];     // (rows past L end within it: NG HR L <= TILE + 256)
     __shared__ __align__(16) float hrow[NG * HP + 4];       // (the last entry: for lanes without a label to scribble in)
     const int L = P.g.L;
     const int lane = threadIdx.x & 63;
@@ -2542,8 +2542,8 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
         float f[QD > 0 ? QD : TW];
 #pragma unroll
         for (int e = 0; e < (QD > 0 ? QD : TW); ++e) f[e] = ftab[QD * quarter + e];
-        const auto run = [&](auto several) {
-            constexpr bool MULTI = decltype(several)::value;
+        // (written in place instead of as a function that is inlined, the node step gets two instructions more: 1.5 %)
+        const auto run = [&]() {
             float4 q4[NQ > 0 ? NQ : 1];
             float dr, wgt;
             const auto fetch = [&](int ls, int slot) {
@@ -2609,16 +2609,14 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                     v = valid ? v : INFINITY;
                     hring[u][PAD + lam] = v;
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    if constexpr (MULTI) post(&hflag[wv], n);
+                    post(&hflag[wv], n);
                     mrf_wave_lds_fence();
                     // one batch of reads: who has written h, the neighbours; the loader's counter, the next node's values
                     float lo[QD > 0 ? QD + 4 : TW], hi[QD > 0 ? QD + 4 : TW];
                     int4 fl;
                     const auto neighbours = [&]() {
-                        if constexpr (MULTI) {
-                            fl = *reinterpret_cast<const int4 *>(hflag);
-                            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        }
+                        fl = *reinterpret_cast<const int4 *>(hflag);
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                         if constexpr (QD == 0) {
 #pragma unroll
                             for (int d = 0; d < TW; ++d) { lo[d] = hring[u][PAD + lam - d]; hi[d] = hring[u][PAD + lam + d]; }
@@ -2650,22 +2648,20 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                     fetch((u + 1) % NRL, (u + 1) % NR);
                     __builtin_amdgcn_sched_barrier(0);
                     float hmin = mrf_wave_min(v);
-                    if constexpr (MULTI) post_min(hmx, n, hmin);
+                    post_min(hmx, n, hmin);
                     __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (MULTI) {
-                        const auto absent = [&]() { return __builtin_amdgcn_readfirstlane(min(min(fl.x, fl.y), min(fl.z, fl.w))) < n; };
-                        if (__builtin_expect(absent(), 0)) {
-                            int looks = 0;
-                            do {
-                                if ((++looks & 4095) == 0) mrf_wait_check(wait_block);
-                                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                                neighbours();
-                            } while (absent());
-                        }
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                        read_posts(hmx, n);
-                        __builtin_amdgcn_sched_barrier(0);
+                    const auto absent = [&]() { return __builtin_amdgcn_readfirstlane(min(min(fl.x, fl.y), min(fl.z, fl.w))) < n; };
+                    if (__builtin_expect(absent(), 0)) {
+                        int looks = 0;
+                        do {
+                            if ((++looks & 4095) == 0) mrf_wait_check(wait_block);
+                            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                            neighbours();
+                        } while (absent());
                     }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                    read_posts(hmx, n);
+                    __builtin_amdgcn_sched_barrier(0);
                     // window: the two candidates at a distance share f, and a correctly rounded fma is non-decreasing in its
                     // addend, so the smaller of the two comes from the smaller h
                     float W;
@@ -2691,7 +2687,7 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                         const float give = up1 ? keep0 : keep1, keep = up1 ? keep1 : keep0;
                         W = mrf_min(keep, mrf_dpp_f32<0xB1>(give));
                     }
-                    if constexpr (MULTI) hmin = least_post(hmx, n);
+                    hmin = least_post(hmx, n);
                     float tv = mrf_min(W, __builtin_fmaf(w, fT, hmin)), tq = hmin;
                     const bool wneg = __builtin_amdgcn_readfirstlane(__float_as_int(w)) < 0;
                     if (__builtin_expect(wneg, 0)) {
@@ -2708,11 +2704,9 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                     if (__builtin_expect((int)wneg | (int)!f0zero, 0)) {
                         // the minimum of the new message is not that of h
                         tq = mrf_wave_min(valid ? tv : INFINITY);
-                        if constexpr (MULTI) {
-                            post_min(tmx, n, tq);
-                            read_posts(tmx, n);
-                            tq = least_post(tmx, n);
-                        }
+                        post_min(tmx, n, tq);
+                        read_posts(tmx, n);
+                        tq = least_post(tmx, n);
                     }
                     carry = tv - tq;
                     arrived();                               // (in front of the writes below, behind which the wait would be for those)
@@ -2729,8 +2723,7 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                 }
             }
         };
-        if (NWV > 1) run(std::true_type{});
-        else run(std::false_type{});
+        run();
         return;
     }
 
@@ -2844,8 +2837,7 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        if (L <= 64) run(std::integral_constant<int, 1>{});
-        else if (L <= 128) run(std::integral_constant<int, 2>{});
+        if (L <= 128) run(std::integral_constant<int, 2>{});
         else run(std::integral_constant<int, 4>{});
         return;
     }
