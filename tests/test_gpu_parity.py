@@ -1793,6 +1793,48 @@ def test_gradient_of_per_edge_tables_in_a_pass_of_its_own(oracle, case):
             check_grad("grad_pairwise_edge", out.grad_pairwise, b[np.float32].grad_pairwise_edge, b[np.float64].grad_pairwise_edge)
 
 
+# (algo, B, H, W, L, directions, K, iterations whose node gradients the least workspace holds, whether a workgroup of the pass takes
+# more than one turn): passes of two and one iterations onto what the first one left, groups that come out even and not; several
+# turns in a pass that starts from nothing and in one that does not; 8 and 16 directions on the narrow sweep that stores
+@pytest.mark.parametrize("case", [("isgmr", 1, 110, 140, 5, 4, 5, 2, False), ("trwp", 1, 110, 140, 5, 4, 4, 2, False),
+                                  ("isgmr", 1, 41, 64, 32, 4, 1, 1, True), ("trwp", 1, 200, 222, 16, 4, 3, 2, True),
+                                  ("isgmr", 1, 3, 190, 13, 8, 2, 2, False), ("trwp", 1, 2, 1030, 8, 8, 2, 2, False),
+                                  ("isgmr", 1, 3, 150, 21, 16, 2, 2, False), ("trwp", 1, 2, 1030, 18, 16, 2, 2, True)],
+                         ids=lambda c: "_".join(map(str, c[:7])))
+def test_passes_over_the_gradient_of_per_edge_tables(oracle, case):
+    import torch
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import GpuProblem
+    print("case table passes", case, flush=True)
+    algo, B, H, W, L, R, K, slabs, turns = case
+    dirs = {4: DIRS4, 8: DIRS8, 16: DIRS16}[R]
+    pr = random_problem(830 + L, algo, B, H, W, L, dirs, K, per_edge=False, rho=np.linspace(0.3, 0.9, R))
+    rng = np.random.default_rng(9400 + L)
+    pr.pairwise_edge = rng.random((R, B, H, W, L, L), dtype=np.float32)
+    f = oracle.forward(pr.algo, pr.unary, None, pr.dirs, pr.K, rho=pr.rho, pairwise_edge=pr.pairwise_edge)
+    b = oracle.backward(pr.algo, pr.shape, None, pr.dirs, pr.K, pr.grad_cost.astype(np.float64), f.p, f.q, rho=pr.rho, dtype=np.float64,
+                        per_edge_pairwise=True)
+    for variant in ("as asked for", "least workspace"):
+        g = GpuProblem(pr)
+        if variant == "least workspace":
+            plain = mrf.MrfProblem(g.unary, torch.zeros((L, L), device="cuda:0"), pr.dirs, K, rho=pr.rho)
+            g.workspace = g.workspace[:mrf.mrf_workspace_bytes(plain, g.algo, True)]
+            room = (g.workspace.numel() - mrf.mrf_workspace_bytes(plain, g.algo, False)) // (4 * R * B * H * W * L)
+            assert min(room, K) == slabs
+        unit = 1 if L % 2 == 0 else 4
+        per_turn = max(8192 // (L * L) // unit * unit, unit)
+        assert (R * B * H * W > 1280 * per_turn) == turns
+        g.poison_outputs()
+        g.forward()
+        g.backward()
+        if R > 4 and algo == "isgmr":                  # (TRWP: the directions across the grid, not the last one swept)
+            assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_narrow", mrf.mrf_last_sweep_launch(True)
+        out = g.results()
+        np.testing.assert_array_equal(out.p, f.p)
+        check_grad("grad_unary", out.grad_unary, None, b.grad_unary)
+        check_grad("grad_pairwise_edge", out.grad_pairwise, None, b.grad_pairwise_edge)
+
+
 # chain and narrow layout, TRWP (grad theta formed by one direction per iteration) and ISGMR on small grids (by the first one)
 @pytest.mark.parametrize("case", [("trwp", 2, 9, 24, 13), ("trwp", 1, 20, 30, 45), ("isgmr", 2, 12, 14, 21), ("isgmr", 1, 12, 17, 64),
                                   ("trwp", 3, 4, 360, 21), ("isgmr", 1, 2, 530, 8)], ids=lambda c: "_".join(map(str, c)))
