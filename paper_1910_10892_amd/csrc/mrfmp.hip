@@ -1461,7 +1461,9 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // against 0.74 with 32, but 0.66 against 0.59 with 21, where a lane's three labels make the node step long)
     // (without grad V the chain's helpers have less to do: 256 x 512, 4 directions, K = 2, 25 labels 0.38 against 0.40 ms, 31
     // labels 0.38 against 0.43)
-    const long long chain_few = (P.r_count > 1 && L > 16 && (L <= 24 || !gv_any)) ? 1536 : 1024;
+    // (and where two scanlines per workgroup have given way to the divided sweep, it is the next: 8 x 128 x 128, 1,024 scanlines,
+    // chain / two scanlines / divided: 8 labels 0.447 / 0.315 / 0.274 ms, 16 labels 0.456 / 0.323 / 0.293)
+    const long long chain_few = (P.r_count > 1 && L > 16 && (L <= 24 || !gv_any)) ? 1536 : (P.r_count == 1 && L <= 16 && divided ? pk_max : 1024);
     if (!generic && L <= 32 && g_tune_pack != 1 && (g_tune_pack == 2 || P.total_scanlines >= 256) &&
         !(chain && g_tune_pack != 2 && (g_tune_chain == 2 || P.total_scanlines <= chain_few)))
     {

@@ -323,6 +323,20 @@ def test_few_labels_that_are_not_finite_by_the_default_rules(oracle, L, algo, ki
             mrf.mrf_tune(13, 0)
 
 
+@pytest.mark.parametrize("B,H,L,dirs,kernel", [
+    (128, 7, 8, DIRS4, "mrf_bwd_sweep_chain_pk"), (100, 9, 8, DIRS4, "mrf_bwd_sweep_narrow"), (128, 8, 16, DIRS4, "mrf_bwd_sweep_narrow"),
+    (100, 9, 12, DIRS8, "mrf_bwd_sweep_narrow"), (128, 8, 17, DIRS4, "mrf_bwd_sweep_chain_pk"), (160, 8, 21, DIRS4, "mrf_bwd_sweep_chain_pk"),
+    (161, 8, 21, DIRS4, "mrf_bwd_sweep_narrow")])
+def test_which_backward_sweep_runs_for_few_labels(oracle, B, H, L, dirs, kernel):
+    """Both sides of the bounds between two scanlines per workgroup and the narrow sweep (TRWP; the last launch is that of the first
+    direction, B H scanlines): never the chain of one scanline between them."""
+    import paper_1910_10892_amd as mrf
+    print("case which backward sweep", B, H, L, len(dirs), flush=True)
+    pr = random_problem(645 + L, "trwp", B, H, 5, L, dirs, 2, symmetric=False, rho=np.linspace(0.3, 0.9, len(dirs)))
+    full_check(oracle, pr)
+    assert mrf.mrf_last_sweep_kernel(True) == kernel, mrf.mrf_last_sweep_launch(True)
+
+
 @pytest.mark.parametrize("algo,B,H,W,L,dirs,halves", [
     ("trwp", 1, 40, 6, 64, DIRS4, False), ("trwp", 100, 6, 7, 49, DIRS4, True), ("trwp", 100, 6, 7, 48, DIRS4, False), ("trwp", 171, 6, 7, 64, DIRS4, False),
     ("trwp", 100, 6, 7, 40, DIRS8, True), ("isgmr", 40, 6, 7, 64, DIRS4, True), ("isgmr", 40, 6, 7, 48, DIRS4, False), ("isgmr", 90, 6, 7, 48, DIRS4, True),
