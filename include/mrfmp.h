@@ -23,8 +23,8 @@
  *  - Ties in every argmin go to the lowest label.
  *  - Ownership: the caller owns every buffer, including the workspace; the library
  *    allocates no device memory and keeps no problem data between calls (the only state is
- *    the process-global settings of mrf_tune, mrf_set_sweep_events and the two report
- *    strings below).  Outputs are fully
+ *    the settings of mrf_tune and mrf_set_sweep_events and the report strings below, all of
+ *    them per calling thread).  Outputs are fully
  *    overwritten (gradients are assigned, not accumulated into what the caller passed).
  *  - Calls enqueue work on `hip_stream` (a hipStream_t, NULL = default stream) and return
  *    without synchronising.  Calls that share a workspace must be ordered by the caller.
@@ -113,10 +113,16 @@ typedef struct {
                                    entry points included, returns MRF_ERR_BAD_ALGORITHM); runs the dense sweep. */
 } mrf_problem;
 
-/* Bytes of DEVICE workspace (256-byte aligned base required) that the forward
- * (backward = 0) or backward (backward != 0) pass of `algo` needs for this problem;
- * 0 if the problem is invalid.  Pure host arithmetic.  The backward figure covers the
- * case that grad_pairwise is requested. */
+/* Bytes of DEVICE workspace (256-byte aligned base required) for the forward
+ * (backward = 0) or backward (backward != 0) pass of `algo` on this problem; 0 if the
+ * problem is invalid.  Pure host arithmetic.  The backward figure covers the case that
+ * grad_pairwise is requested.  A call with less returns MRF_ERR_WORKSPACE_TOO_SMALL, with one
+ * exception: for the backward pass of a problem with pairwise_edge the figure includes room for the
+ * node gradients of min(K, max(L/2, 1)) iterations (4 R B H W L bytes each, so up to half of what the tables
+ * take), from which the tables' gradient is formed.  There the least that is accepted is what the same
+ * problem with a pairwise table instead of pairwise_edge needs; with room for fewer iterations the pass over
+ * the tables runs more often, and without room for one the sweeps add to the tables themselves (slower, the
+ * same sums). */
 size_t mrf_workspace_bytes(const mrf_problem *prob, int algo, int backward);
 
 /* Checks a problem description the way the entry points do; no GPU work. */
@@ -266,8 +272,8 @@ int mrf_set_sweep_events(void *start_event, void *stop_event);
  * thread that made it (the library keeps these knobs, the hooks above and nothing else, per thread).
  *   knob 0: source labels per wavefront in the dense forward sweep (8, 12, 16, 24, 32, 48; 0 = heuristic)
  *   knob 1: non-zero = ignore pairwise_kind and always run the dense forward sweep
- *   knob 2: window sweep layout: 0 = by launch size, 1 = one wavefront per scanline,
- *           2 = one wavefront per 64 labels whenever L > 64
+ *   knob 2: window sweep layout: 0 = by launch size, 1 = not one wavefront per 64 labels,
+ *           2 = one wavefront per 64 labels whenever L > 64 (without or with others beside them: knob 9)
  *   knob 3: several scanlines per wavefront for L <= 32: 0 = by launch shape, 1 = never, 2 = always, 3 = always, the
  *           backward sweep with one label per lane and 64-bit offsets;
  *           8, 16 (more than 8 labels), 32 (more than 16 labels) = always, with that many lanes per
@@ -280,12 +286,17 @@ int mrf_set_sweep_events(void *start_event, void *stop_event);
  *   knob 7: helper wavefronts per scanline in that sweep: 0 = by launch size, 2, 4, 6, 8, 12
  *   knob 8: loader wavefront in front of the value wavefront (TRWP, window sweep, two index
  *           wavefronts): 0 = by launch size, 1 = never, 2 = whenever it applies
- *   knob 9: where knob 2 picks one wavefront per 64 labels, those wavefronts compute values only and
- *           index wavefronts of their own do the argmin tables and the stores: 0 = by launch size,
- *           1 = never, 2 = always
- *   knob 10: index wavefronts per scanline in that layout: 0 = default, 4, 8
- *   knob 11: two index wavefronts next to the value wavefront in the sweep of knob 3: 0 = by launch size,
- *           1 = never, 2 = always, 3 = never, with 64-bit offsets
+ *   knob 9: window sweep in which one wavefront per 64 labels computes values only, a loader beside them does the
+ *           loads and index wavefronts do the argmin tables and the stores (L > 64): 0 = by launch size (with knobs 2
+ *           and 4 at 0; otherwise not), 1 = never, 2 = always, together with knob 2 = 2 (with another setting of
+ *           knob 2 as 0)
+ *   knob 10: wavefronts beside the values in that layout, the loader and the index wavefronts together:
+ *           0 = by launch size, 4, 8
+ *   knob 11: forward sweep of knob 3 with the work of a node divided among four wavefronts (loader, values, two for the
+ *           indices): 0 = by launch size, 1 = never, 2 = always, 4 = always, one scanline per workgroup,
+ *           5 = always, several scanlines per workgroup; 3 = never, one wavefront with 64-bit offsets (what arrays
+ *           beyond 32-bit offsets get), 6 = the same with two index wavefronts (what they get in launches of few
+ *           scanlines).  Beyond 32-bit offsets 2 is as 6, and 4 and 5 as 0.
  *   knob 12: in the sweep of knob 6, sum the lanes of the most popular scatter target in registers
  *           (truncated models): 0 = by launch shape, 1 = never, 2 = whenever V is not a dense table
  *   knob 13: three scanlines per wavefront (segments of 21 lanes) in the sweeps of knob 3 for 17..21 labels:
@@ -309,8 +320,11 @@ int mrf_set_sweep_events(void *start_event, void *stop_event);
  *   knob 19: grad_pairwise for 33..128 labels where the sweep of knob 6 runs one direction of up to 1,536 scanlines per launch
  *           (TRWP): its helpers store the gradient vector of every node and a streaming pass forms both pairwise gradients
  *           afterwards: 0 = yes, 1 = no (then a sweep accumulates the table itself)
- *   knob 20: backward sweep of knob 6 with two scanlines of up to 32 labels per workgroup (one direction per
- *           launch, TRWP): 0 = by launch size, 1 = never, 2 = whenever it applies
+ *   knob 20: which backward sweep TRWP launches (one direction per launch) of up to 32 labels get.  The one of knob 6
+ *           with two scanlines per workgroup: 0 = by launch size, 1 = never, 2 = whenever it applies.  3 and 4 leave that
+ *           choice to the launch size and set another one: where the sweep with several scanlines per wavefront
+ *           runs (knob 3), the work of a node divided among four wavefronts 3 = never, 4 = whenever it applies (0, 1, 2:
+ *           by launch size).  (Knob 6 = 1 rules out the sweep with two scanlines beside any of them.)
  * Returns MRF_OK, or MRF_ERR_BAD_ALGORITHM for an unknown knob. */
 int mrf_tune(int knob, int value);
 
