@@ -1561,8 +1561,9 @@ hipError_t launch_edge_tables(const mrf_problem *pr, float *gE, const float *g, 
     MrfEdgeGradParams E;
     E.L = pr->L;
     E.tables = (long long)pr->R * pr->B * pr->H * pr->W;
-    // 32 KB of tables per workgroup, so that five of them share a compute unit and their phases overlap; a multiple of
-    // four tables where L L is odd, which keeps every range on a 16-byte boundary
+    // Up to 32 KB of tables per workgroup, so that five of them share a compute unit and their phases overlap; a multiple of
+    // four tables where L L is odd, which keeps every range on a 16-byte boundary.  Four tables of 47, 49, .. 63 labels are
+    // more than that (35 to 63.5 KB): four to two workgroups share a compute unit there.
     const int LL = E.L * E.L, unit = LL % 4 ? 4 : 1, fit = 8192 / LL / unit * unit;
     E.T = fit > unit ? fit : unit;
     E.count = count; E.g = g; E.p = p; E.p_step = E.tables * E.L; E.gE = gE; E.accumulate = accumulate ? 1 : 0;

@@ -1675,7 +1675,9 @@ __global__ void __launch_bounds__(256) mrf_bwd_sweep_narrow(const MrfBwdParams P
 // same scanlines: two take the nodes in turn and do what does not wait for the chain (loads, the gradient arriving from
 // elsewhere with the correction at q), one does the chain (add, scatter through LDS, read, the stored s), one what is left (grad
 // theta, both pairwise gradients).  Rings in LDS as in mrf_bwd_sweep_chain: ext and p from the first two, the carry that entered a
-// node from the chain.  Same operations on the same values in the same order as mrf_bwd_sweep_narrow.
+// node from the chain.  Same operations on the same values in the same order as mrf_bwd_sweep_narrow, but for grad theta: what
+// arrives from elsewhere is summed in front of the chain, from the old value on, and the carry is added last (there: the carry first,
+// the old value last; both in double, rounded once).
 // Every wait is on a counter that only grows: chain on pre, post on chain, pre on post NR steps back.
 // Several source arrays; label counts that the lanes' labels divide (the launches that the rule of narrow_lanes gives them).
 // Backward pass, 4 x 512 x 512, TRWP, 4 directions, K = 2: 21 labels 1.86 -> 1.42 ms, 16 labels 1.37 -> 1.07, 32 labels 1.82 -> 1.50.  What sets the
