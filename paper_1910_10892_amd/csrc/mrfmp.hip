@@ -816,15 +816,18 @@ hipError_t dispatch_fwd(MrfFwdParams &P, int algo, int tw, long long blocks, hip
         // - window 16 (and 12 beyond 128 labels): TRWP 256 x 256, 256 labels, K = 2 1.16 / 1.65 ms with index wavefronts alone beside
         //   them and every neighbour read by itself; K = 1: 600 scanlines 3.06 / 3.32, with 128 labels 2.27 / 2.92, 700 with 200 labels
         //   4.28 / 4.11; ISGMR 512 scanlines, K = 2, 256 labels 0.25 / 0.34, 128 labels 0.16 / 0.20
-        // - window 8 beyond 128 labels: TRWP, K = 2, 256 scanlines 1.03 / 1.32, 512 1.76 / 2.17, 600 level; eight directions, K = 1, 655
+        // - window 8 beyond 192 labels: TRWP, K = 2, 256 scanlines 1.03 / 1.32, 512 1.76 / 2.17, 600 level; eight directions, K = 1, 655
         //   scanlines 1.75 / 1.95; ISGMR 512 scanlines 0.185 / 0.223, 600 0.335 / 0.320
+        // - window 8, 129..192 labels, where the pair has a label slot less: level to 256 scanlines (TRWP, K = 2, 256 x 256: 0.962 / 0.972),
+        //   behind beyond (256 and 512 scanlines, 192 labels 1.67 / 1.59; 300 and 600 2.52 / 2.32; ISGMR 512 scanlines, 160 labels 0.187 /
+        //   0.165); ahead with more source arrays (eight directions, 160 labels: to 383 scanlines 1.45 / 1.62, to 629 2.95 / 3.14)
         // - window 8, 65..128 labels: behind the pair with its loader (TRWP, up to three source arrays: 0.61 / 0.54), ahead with more
         //   (eight directions: 499 scanlines 1.58 / 1.79, 767 1.32 / 1.17) and for ISGMR to 256 scanlines (65.6 / 68.2 us)
         // (eight beside the values where a scanline has a compute unit to itself and more than 128 labels: 1.16 / 1.36 ms at 256
         // scanlines of 256 labels, but 1.75 / 1.44 at 512 of 96)
         const bool many = ms + 1 > 4;
         const long long squad_max = tw == 16 || (tw == 12 && LPw >= 3) ? 640
-                                    : (tw != 8 ? 0 : (LPw >= 3 ? (many ? 656 : 512) : (many ? 512 : (algo == MRF_ISGMR ? 256 : 0))));
+                                    : (tw != 8 ? 0 : (LPw >= 3 ? (many ? 656 : (LPw >= 4 ? 512 : 256)) : (many ? 512 : (algo == MRF_ISGMR ? 256 : 0))));
         const bool squad = split_ok && g_tune_squad != 1 && (long long)P.g.H * P.g.W * P.g.L <= MRF_BUF_MOST &&
                            ((g_tune_split == 2 && g_tune_squad == 2) || (g_tune_split == 0 && g_tune_duo == 0 && blocks <= squad_max));
         if (squad) {

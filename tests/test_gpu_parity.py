@@ -927,6 +927,22 @@ def test_window_sweep_with_loader_value_and_index_wavefronts(oracle, case):
                 mrf.mrf_tune(k, 0)
 
 
+# both sides of the bounds of window 8: 129..192 labels to 256 scanlines (656 with more than three source arrays), more labels to 512
+@pytest.mark.parametrize("case", [("trwp", 32, 130, 4, True), ("trwp", 33, 130, 4, False), ("isgmr", 8, 192, 4, True), ("isgmr", 9, 192, 4, False),
+                                  ("trwp", 64, 193, 4, True), ("trwp", 65, 193, 4, False), ("trwp", 43, 160, 8, True)], ids=lambda c: "%s_%d_%d_%d" % c[:4])
+def test_which_window_sweep_runs_for_many_labels(oracle, case):
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    print("case which window sweep", case, flush=True)
+    algo, B, L, R, squad = case
+    pr = random_problem(670 + L, algo, B, 8, 8, L, DIRS8 if R == 8 else DIRS4, 2, symmetric=False, rho=np.linspace(0.3, 0.9, R))
+    pr.pairwise = np.minimum(np.abs(np.arange(L)[:, None] - np.arange(L)[None, :]), 8).astype(np.float32)
+    pr.pairwise_kind, pr.trunc, pr.scale = 1, 8.0, 1.0
+    check_forward(run_gpu(pr, backward=False), oracle_forward(oracle, pr))
+    kernel = mrf.mrf_last_sweep_kernel(False)
+    assert kernel == ("mrf_fwd_sweep_window_squad" if squad else "mrf_fwd_sweep_window_duo"), mrf.mrf_last_sweep_launch(False)
+
+
 CHAIN_CASES = [
     # seed, algo, B, H, W, L, dirs, K, integer_valued, per_edge
     (81, "trwp", 1, 3, 70, 96, DIRS4, 2, False, True),      # scanlines many times the ring
