@@ -1444,12 +1444,19 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // labels 1.03 / 0.98, 32 labels 1.12 / 1.14.  17, 19 and 23 labels fill no segment: with up to four source arrays 1.59 /
     // 1.80 at 1,640 scanlines, 2.03 / 2.19 at 2,048, 2.42 / 2.95 at 2,560, with eight 4.84 / 4.22 at 1,640)
     const bool fills_none = L > 16 && L <= 24 && L % 2 != 0 && L % 3 != 0;
-    // (the narrow sweep divided among four wavefronts, which several source arrays take, is ahead earlier; two scanlines / divided,
-    // 512 x 512 images, K = 2: 1,024 scanlines 8 labels 1.00 / 0.90 ms, 16 labels 1.03 / 0.98, 21 labels 1.08 / 1.39, 32 labels 1.14 /
-    // 1.22; 1,536 scanlines 16 labels 1.55 / 1.06, 21 labels 1.61 / 1.40, 32 labels 1.67 / 1.38; eight directions, 12 labels, 2 x 256 x 512
-    // 1.41 / 1.25)
-    const bool divided = ns > 1 && P.g.N * L <= MRF_BUF_MOST && g_tune_narrow == 0 && g_tune_narrow_divided != 1;
-    const long long pk_max = fills_none && ns == 4 ? 2560 : (divided ? (L <= 16 ? 896 : 1280) : (L <= 8 ? 1024 : 1536));
+    // The narrow sweep divided among four wavefronts, which several source arrays take, is ahead earlier.  The machine holds 256
+    // workgroups of two scanlines with a compute unit each, 512 with two on each, and the time of a sweep of equal scanlines goes up by
+    // a half and by a third where these are full.  (Backward pass, 4 directions, 64 x 64 images, K = 3, two scanlines / divided, at 512,
+    // 576, 1,024 and 1,088 scanlines: 5 labels 0.192 / 0.244, 0.299 / 0.247, 0.305 / 0.248, -; 16 labels 0.200 / 0.261, 0.321 / 0.262,
+    // 0.324 / 0.271, -; 21 labels 0.209 / 0.353, 0.334 / 0.356, 0.339 / 0.358, 0.464 / 0.359; 32 labels 0.223 / 0.305, 0.356 / 0.330,
+    // 0.366 / 0.337, 0.496 / 0.361.  1024 x 1024, 1,024 scanlines, K = 2: 16 labels 2.13 / 1.90, 21 labels 2.23 / 2.73.)
+    // The short scanlines of a diagonal direction leave room early (eight directions, 1 x 300 x 300, K = 2, launches of 300 and 599
+    // scanlines: 8 labels 0.80 / 0.90, 32 labels 0.90 / 1.05; 512 x 512, 512 and 1,023: 32 labels 1.69 / 1.80; 2 x 256 x 512, 12 labels 1.41 /
+    // 1.25).
+    const bool divided = (ns == 4 || ns == 8) && P.g.N * L <= MRF_BUF_MOST && g_tune_narrow == 0 && g_tune_narrow_divided != 1;
+    const bool even = P.g.dh[P.r_first] == 0 || P.g.dw[P.r_first] == 0;      // (every scanline is as long as the others)
+    const long long pk_max = fills_none && ns == 4 ? 2560 : (!divided ? (L <= 8 ? 1024 : 1536)
+                                                             : (ns == 4 && even ? (L > 16 && L <= 24 ? 1024 : 512) : (L <= 16 ? 896 : 1280)));
     if (!generic && L <= 32 && P.r_count == 1 && ns <= 8 && g_tune_chain != 1 && g_tune_pack != 2 && g_tune_chain_pk != 1 &&
         (g_tune_chain_pk == 2 || (g_tune_chain != 2 && P.total_scanlines > 256 && P.total_scanlines <= pk_max)) &&
         !(gv_any && (P.total_scanlines + 1) / 2 > grad_slots(L))) {
@@ -1466,7 +1473,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // labels 0.38 against 0.43)
     // (and where two scanlines per workgroup have given way to the divided sweep, it is the next: 8 x 128 x 128, 1,024 scanlines,
     // chain / two scanlines / divided: 8 labels 0.447 / 0.315 / 0.274 ms, 16 labels 0.456 / 0.323 / 0.293)
-    const long long chain_few = (P.r_count > 1 && L > 16 && (L <= 24 || !gv_any)) ? 1536 : (P.r_count == 1 && L <= 16 && divided ? pk_max : 1024);
+    const long long chain_few = (P.r_count > 1 && L > 16 && (L <= 24 || !gv_any)) ? 1536 : (P.r_count == 1 && divided && pk_max < 1024 ? pk_max : 1024);
     if (!generic && L <= 32 && g_tune_pack != 1 && (g_tune_pack == 2 || P.total_scanlines >= 256) &&
         !(chain && g_tune_pack != 2 && (g_tune_chain == 2 || P.total_scanlines <= chain_few)))
     {

@@ -324,12 +324,14 @@ def test_few_labels_that_are_not_finite_by_the_default_rules(oracle, L, algo, ki
 
 
 @pytest.mark.parametrize("B,H,L,dirs,kernel", [
-    (128, 7, 8, DIRS4, "mrf_bwd_sweep_chain_pk"), (100, 9, 8, DIRS4, "mrf_bwd_sweep_narrow"), (128, 8, 16, DIRS4, "mrf_bwd_sweep_narrow"),
-    (100, 9, 12, DIRS8, "mrf_bwd_sweep_narrow"), (128, 8, 17, DIRS4, "mrf_bwd_sweep_chain_pk"), (160, 8, 21, DIRS4, "mrf_bwd_sweep_chain_pk"),
-    (161, 8, 21, DIRS4, "mrf_bwd_sweep_narrow")])
+    (64, 8, 8, DIRS4, "mrf_bwd_sweep_chain_pk"), (65, 8, 8, DIRS4, "mrf_bwd_sweep_narrow"), (128, 8, 16, DIRS4, "mrf_bwd_sweep_narrow"),
+    (125, 8, 12, DIRS16, "mrf_bwd_sweep_chain"), (128, 8, 17, DIRS4, "mrf_bwd_sweep_chain_pk"),
+    (112, 8, 16, DIRS8, "mrf_bwd_sweep_chain_pk"), (113, 8, 16, DIRS8, "mrf_bwd_sweep_narrow"), (320, 8, 19, DIRS4, "mrf_bwd_sweep_chain_pk"),
+    (128, 8, 21, DIRS4, "mrf_bwd_sweep_chain_pk"), (129, 8, 21, DIRS4, "mrf_bwd_sweep_narrow"), (64, 8, 28, DIRS4, "mrf_bwd_sweep_chain_pk"),
+    (65, 8, 28, DIRS4, "mrf_bwd_sweep_narrow")])
 def test_which_backward_sweep_runs_for_few_labels(oracle, B, H, L, dirs, kernel):
     """Both sides of the bounds between two scanlines per workgroup and the narrow sweep (TRWP; the last launch is that of the first
-    direction, B H scanlines): never the chain of one scanline between them."""
+    direction, B H scanlines): never the chain of one scanline between them (sixteen directions have neither)."""
     import paper_1910_10892_amd as mrf
     print("case which backward sweep", B, H, L, len(dirs), flush=True)
     pr = random_problem(645 + L, "trwp", B, H, 5, L, dirs, 2, symmetric=False, rho=np.linspace(0.3, 0.9, len(dirs)))
