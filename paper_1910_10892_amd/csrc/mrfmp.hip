@@ -1385,6 +1385,11 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     // stores the node gradients if they are wanted (run_backward has checked that one of them fits)
     if (P.edge) {
         P.hot_label = 0;
+        // (backward pass with the tables' gradient, K = 2, chain / narrow: TRWP, 128 x 128 images, 768 scanlines 8 labels 0.278 / 0.287 ms, 16
+        // labels 0.372 / 0.410; 1,024 8 labels 0.372 / 0.294, 16 labels 0.515 / 0.460, 18 labels 0.590 / 0.610, 32 labels 0.863 / 0.900; 1,280 18
+        // labels 0.751 / 0.664, 32 labels level.  ISGMR, 1 : 3 images, where the chain stays ahead a little longer: 1,024 scanlines 5 labels
+        // 0.138 / 0.203, 32 labels 0.345 / 0.442; 1,280 0.200 / 0.247, 0.541 / 0.613; 1,536 level, 0.710 / 0.816; 2,048 0.355 / 0.313, 1.18 /
+        // 1.31.  One line for both.)
         if (L <= 32 && P.total_scanlines > 1024) return run_bwd_narrow(P, L <= 8 || (L <= 24 && L % 3 == 0 && L > 16) ? 8 : (L <= 16 ? 16 : 32), ns, st);
         const int ni = P.total_scanlines <= 256 ? 12 : (P.total_scanlines <= 512 ? 8 : (P.total_scanlines <= 1024 ? 6 : 4));
         return run_bwd_chain(P, ns, ni, true, st);
@@ -1660,8 +1665,10 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     }
     // Per-edge tables: the sweeps store the node gradients of as many iterations as the workspace has room for, and
     // mrf_bwd_edge_tables forms the tables' gradient from them.  mrf_bwd_sweep, which adds to the tables itself, keeps TRW
-    // coefficients per edge, arrays beyond the 32-bit offsets of the sweeps that store, and launches of more than 2,560
-    // scanlines of 33..64 labels.
+    // coefficients per edge, arrays beyond the 32-bit offsets of the sweeps that store, and launches of more than 8,192
+    // scanlines of 33..64 labels, the most that was measured (backward pass with the tables' gradient, storing / adding: TRWP, 64 x 64
+    // images, K = 2, 45 labels 2,560 scanlines 1.79 / 3.03 ms, 8,192 5.95 / 8.50; ISGMR, 64 x 192, 33 labels 2,560 0.46 / 0.74, 8,192 1.36 / 1.79,
+    // 64 labels, K = 1, 8,192 2.76 / 3.03).
     long long most = 0, all = 0;
     for (int r = 0; r < R; ++r) {
         const long long n = (long long)pr->B * P.g.nscan[r];
@@ -1671,7 +1678,7 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     const long long room = (long long)((workspace_bytes - (size_t)((char *)gvslots - ws)) / edge_slab_bytes(pr));
     const int slabs = (int)(room < K ? room : K);
     P.edge = edge_tables && !P.rho_e && NL <= MRF_BUF_MOST && (!grad_V || slabs > 0) &&
-             (L <= 32 || (algo == MRF_ISGMR ? all : most) <= 2560) && g_tune_chain != 1 && g_tune_narrow >= 0;
+             (L <= 32 || (algo == MRF_ISGMR ? all : most) <= 8192) && g_tune_chain != 1 && g_tune_narrow >= 0;
     float *const edge_g = (float *)gvslots;
     // behind the sweeps of iteration k; P.gstore32 holds where the next iteration's go
     const auto edge_pass = [&](int k) -> hipError_t {

@@ -1896,6 +1896,25 @@ def test_unary_gradient_of_per_edge_tables_is_rounded_once(oracle, case, want_V)
     assert differ <= a.grad_unary.size // 100, (differ, a.grad_unary.size)
 
 
+@pytest.mark.parametrize("algo", ["isgmr", "trwp"])
+def test_per_edge_tables_of_33_labels_and_many_scanlines(oracle, algo):
+    """More than 2,560 scanlines of 33..64 labels in a launch: the chain layout that stores the node gradients."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    B, H, W, L = (330, 2, 2, 33) if algo == "isgmr" else (1300, 2, 2, 33)
+    print("case tables, many scanlines", algo, flush=True)
+    pr = random_problem(895, algo, B, H, W, L, DIRS4, 2, per_edge=False, rho=np.linspace(0.3, 0.9, 4))
+    pr.pairwise_edge = np.random.default_rng(9500).random((4, B, H, W, L, L), dtype=np.float32)
+    f = oracle.forward(pr.algo, pr.unary, None, pr.dirs, pr.K, rho=pr.rho, pairwise_edge=pr.pairwise_edge)
+    b = oracle.backward(pr.algo, pr.shape, None, pr.dirs, pr.K, pr.grad_cost.astype(np.float64), f.p, f.q, rho=pr.rho, dtype=np.float64,
+                        per_edge_pairwise=True)
+    g = run_gpu(pr)
+    np.testing.assert_array_equal(g.p, f.p)
+    assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_chain", mrf.mrf_last_sweep_launch(True)
+    check_grad("grad_unary", g.grad_unary, None, b.grad_unary)
+    check_grad("grad_pairwise_edge", g.grad_pairwise, None, b.grad_pairwise_edge)
+
+
 def test_per_edge_tables_argument_errors():
     import torch
     import paper_1910_10892_amd as mrf
