@@ -12,7 +12,7 @@ HEADERS = ["mrfmp_device.h", "mrfmp_fwd.h", "mrfmp_bwd.h", "mrfmp_bwd_sum.h", "m
 
 # -ffp-contract=off: the only fused multiply-add is the explicit one of the message update,
 #   so that floating point decisions (argmins) match a plain C evaluation order.
-# packed-fp32 instructions are switched off for the test machines of machines.
+# packed-fp32 instructions are switched off: some of their forms have given wrong results now and then.
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off", "-munsafe-fp-atomics",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall"]
 
