@@ -1033,7 +1033,34 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
                 (!(LP == 1 && gv) && vg) ? "true" : "false", ((LP == 1 && gv) || gs) ? "true" : "false", hot ? "true" : "false",
                 edge ? ",true" : "");
     if (gv && (LP != 1 || P.total_scanlines > grad_slots(P.g.L))) return hipErrorInvalidValue;
-    const size_t lds = mrf_bwd_chain_lds_bytes(LP, ni, P.g.L, P.unary_dir >= 0, vg, gv, edge);
+    MrfChainParams C;
+    memset(&C, 0, sizeof(C));
+    C.H = P.g.H; C.W = P.g.W; C.L = P.g.L; C.w_mul = P.w_mul; C.r_first = P.r_first; C.r_count = P.r_count; C.N = P.g.N;
+    int most = 0;
+    for (int ri = 0; ri < P.r_count; ++ri) {
+        const int n = P.n_src[P.r_first + ri] + (P.use_gc ? 1 : 0);
+        most = n > most ? n : most;
+    }
+    C.src_pitch = P.r_count == 1 ? MRF_MAXR : most;
+    if (most > NS || most * P.r_count > MRF_MAXR) return hipErrorInvalidValue;
+    for (int ri = 0; ri < P.r_count; ++ri) {
+        const int r = P.r_first + ri, n = P.n_src[r];
+        C.begin[ri] = (int)P.blk_begin[ri];
+        C.dh[ri] = P.g.dh[r]; C.dw[ri] = P.g.dw[r]; C.nscan[ri] = P.g.nscan[r];
+        C.carry_scale[ri] = P.carry_scale[r];
+        for (int c = 0; c < n; ++c) {
+            const int k = ri * C.src_pitch + c;
+            C.src[k] = P.src_base + (size_t)P.src_dir[r][c] * P.src_stride;
+            C.cg[k] = (double)P.coefG[r][c];
+            C.cd[k] = (double)P.coefT[r][c] - (double)P.coefG[r][c];
+        }
+        if (P.use_gc) { C.src[ri * C.src_pitch + n] = P.gc; C.cg[ri * C.src_pitch + n] = 1.0; }
+        C.n_src[ri] = n + (P.use_gc ? 1 : 0);
+    }
+    C.begin[P.r_count] = (int)P.blk_begin[P.r_count];
+    C.V = P.V; C.w = P.w; C.p = P.p; C.q = P.q; C.S = P.S; C.gunary = P.gunary; C.gw = P.gw; C.gV = P.gV; C.gstore = P.gstore;
+    C.gstore32 = P.gstore32; C.unary_dir = P.unary_dir; C.unary_init = P.unary_init; C.fault = P.fault; C.spin_limit = P.spin_limit;
+    const size_t lds = mrf_bwd_chain_lds_bytes(LP, ni, P.g.L, hot, gv, !vg && !gv);
     if (lds > chain_lds_cap(P.total_scanlines)) return hipErrorInvalidValue;
     // (more than 64 KB of dynamic LDS has to be announced per kernel)
 #define MRF_CH_GO(...) \
@@ -1043,7 +1070,7 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
             if (ea_ != hipSuccess) return ea_; \
         } \
-        hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(64 * (1 + ni)), lds, st, P); \
+        hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(64 * (1 + ni)), lds, st, C); \
     } while (0)
 #define MRF_CH(n) \
     if (ni == n) { \
@@ -1081,7 +1108,7 @@ hipError_t run_bwd_chain(MrfBwdParams &P, int ns, int ni, bool vg, hipStream_t s
 {
     const int LP = (P.g.L + 63) / 64;
 #define MRF_CCASE(lp) \
-    if (LP == lp && ns == 1) return launch_bwd_chain<lp, 1, 2>(P, ni, vg, st); \
+    if (LP == lp && ns == 1) return launch_bwd_chain<lp, 1, (lp <= 2 ? 2 : 1)>(P, ni, vg, st); \
     if (LP == lp && ns == 4) return launch_bwd_chain<lp, 4, (lp <= 2 ? 2 : 1)>(P, ni, vg, st); \
     if (LP == lp && ns == 8) return launch_bwd_chain<lp, 8, 1>(P, ni, vg, st);
     if (LP == 1 && ns == 16) return launch_bwd_chain<1, 16, 1>(P, ni, vg, st);
@@ -1416,33 +1443,37 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
                           P.total_scanlines <= kApartMost && !(L <= 48 && P.total_scanlines <= 256) && g_tune_gv_apart != 1;
     const bool gv = gv_any && !gv_apart;      // the V gradient inside the sweep that runs
     // as many helpers as keep up with the chain while the machine and the LDS have room
-    // (measured per launch shape at L = 96: 256 scanlines 165 / 121 / 98 / 90 us with 4 / 6 / 8 / 12
-    // helpers; 512 scanlines, two workgroups per compute unit, 94 / 78 / 98 us with 4 / 6 / 8)
+    // (backward pass, ISGMR, 4 directions, K = 3, with 4 / 6 / 8 helpers: 96 labels 512 scanlines 181 / 174 / 167 us, 1,024 604 / 597 /
+    // 732, 1,388 924 / 787 / 949, 2,560 2.80 / 2.67 / 3.07 ms; 40 labels 512 112 / 104 / 100 us, 1,388 585 / 520 / 574; 160 labels 512
+    // 201 / 183 / 180, 1,388 1.25 / 1.18 / 1.34 ms; 256 labels 512 251 / 237 / 306 us.  TRWP, 256 x 512, 96 labels, K = 5, 256 and 512
+    // scanlines, with 6 / 8 / 12 of them 1.50 / 1.28 / 1.31 ms; 256 x 256, 256 labels, K = 10, 256 scanlines 3.18 / 3.17 / 4.44)
     int ni = g_tune_chain_ni ? g_tune_chain_ni
-                             : (P.total_scanlines <= 256 ? 12
-                                : (P.total_scanlines <= 512 ? (LP >= 2 ? 6 : 8) : (P.total_scanlines <= 1024 ? 6 : 4)));
+                             : (P.total_scanlines <= 256 ? (LP <= 2 ? 12 : 8) : (P.total_scanlines <= 512 && LP <= 3 ? 8 : 6));
     // (the helpers of many source arrays, and those that leave the pairwise gradients to a later pass: six. 128 x 256, 16
     // directions, 96 labels: 3.1 / 2.7 / 3.0 / 3.6 ms with 4 / 6 / 8 / 12; 256 x 512, 8 directions, 40 labels: 1.75 / 1.50 /
     // 1.66 / 1.80 ms)
-    if (!g_tune_chain_ni && gv_apart && (ns == 16 || LP == 1 || P.total_scanlines > 512)) ni = 6;
+    if (!g_tune_chain_ni && gv_apart && (ns == 16 || LP == 1 || P.total_scanlines > 256)) ni = 6;
     if (!g_tune_chain_ni && gv && P.total_scanlines > 384 && ni > 6) ni = 6;   // (the accumulators take LDS)
     const bool vg = P.gw && pairwise_kind == MRF_PAIRWISE_DENSE;
-    const bool vg_lds = vg || gv_apart, gv_lds = gv;
-    while (ni > 2 && (mrf_bwd_chain_lds_bytes(LP, ni, L, P.unary_dir >= 0, vg_lds, gv_lds) > chain_lds_cap(P.total_scanlines) ||
+    // truncated models: the lanes that go to the most popular scatter target are kept apart
+    const bool chain_hot = (pairwise_kind != MRF_PAIRWISE_DENSE || gv_apart) && !gv && g_tune_chain_hot != 1 &&
+                           (g_tune_chain_hot == 2 || L > 128 || P.total_scanlines > 1024);
+    const auto chain_lds = [&](int helpers) { return mrf_bwd_chain_lds_bytes(LP, helpers, L, chain_hot, gv, !vg && !gv_any); };
+    while (ni > 2 && (chain_lds(ni) > chain_lds_cap(P.total_scanlines) ||
                       (gv && P.total_scanlines > grad_slots(L)))) ni = (ni == 12) ? 8 : ni - 2;
     // TRW coefficients or pairwise tables per edge: mrf_bwd_sweep handles them (and is the one
     // sweep that never touches V when no edge-weight gradient is asked for)
     const bool generic = P.rho_e != nullptr || P.force_plain;
-    const bool chain_fits = !generic && step_fits && ns <= (LP <= 2 ? 16 : 8) && g_tune_chain != 1 &&
+    const bool chain_fits = !generic && step_fits && (long long)P.g.H * P.g.W * L <= MRF_BUF_MOST / (gv_apart ? 2 : 1) && ns <= (LP <= 2 ? 16 : 8) && g_tune_chain != 1 &&
                             (!gv || (LP == 1 && P.total_scanlines <= grad_slots(L))) &&
-                            mrf_bwd_chain_lds_bytes(LP, ni, L, P.unary_dir >= 0, vg_lds, gv_lds) <= chain_lds_cap(P.total_scanlines);
-    // (65..128 labels with several source arrays, TRWP: at 2,048 scanlines per launch the plain sweep is ahead,
-    // 5.1 against 7.5 ms on 4 x 512 x 512 with 96 labels; at 1,024 the chain, 2.3 against 3.6 ms)
-    // (more than 128 labels, one source array, ISGMR: at 1,536 scanlines the chain is ahead, 1.7 against 2.4 ms
-    // with 192 labels, at 2,048 the plain sweep, 3.1 against 3.6 ms; several source arrays: level at 1,024)
-    // (a launch of eight or more directions has many short diagonal scanlines: the chain stays ahead longer,
-    // 0.80 against 1.04 ms at 2,876 scanlines of a 160 x 320 grid, 0.81 against 0.89 ms at 3,452 of 192 x 384)
-    const long long chain_max = LP <= 2 ? ((LP == 2 && ns >= 4) ? 1536 : (P.r_count >= 8 ? 3584 : 2560)) : (ns == 1 ? 1536 : 512);
+                            chain_lds(ni) <= chain_lds_cap(P.total_scanlines);
+    // (backward pass, chain / the next best layout.  ISGMR, one source array, 4 directions, K = 3: 96 labels 2,048 scanlines 1.65 / 2.10
+    // ms, 2,560 2.67 / 2.95, 3,072 level; 160 labels 2,048 2.40 / 3.01, 3,072 2.86 / 2.65; 256 labels 1,388 1.63 / 1.91, 2,048 3.44 /
+    // 3.26.  Eight directions, whose launch has many short diagonal scanlines, K = 2, 4,196 scanlines: 96 labels 1.06 / 1.19, 40 labels 0.71 /
+    // 0.76, 160 labels level, 256 labels 2.13 / 1.75.  TRWP, several source arrays, K = 2: 2,048 scanlines 40 labels 1.55 / 1.77, 96 labels 2.09 /
+    // 2.69, 160 labels 2.86 / 3.59, 256 labels 4.28 / 4.83; eight directions, 512 scanlines 160 labels 2.53 / 4.71, 256 labels 3.62 / 5.80)
+    const long long chain_max = ns >= 4 ? (LP == 1 ? 2560 : 2048)
+                                        : (LP == 4 ? 1536 : (P.r_count >= 8 ? (LP <= 2 ? 4224 : 3584) : 2560));
     const bool chain = chain_fits && (g_tune_chain == 2 || P.total_scanlines <= chain_max);
     // Few labels, one direction per launch (TRWP): the chain layout for one scanline per compute unit, two scanlines
     // around a chain wavefront beyond that, mrf_bwd_sweep_narrow for more than the machine holds that way.  (Backward

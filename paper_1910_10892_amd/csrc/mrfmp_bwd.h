@@ -100,13 +100,13 @@ __device__ inline void mrf_slot_add(double *slot, double v)
 }
 #define MRF_CHAIN_MAX_HELPERS 12
 
-// dynamic LDS of mrf_bwd_sweep_chain (host and device agree through this one expression)
-__host__ __device__ inline size_t mrf_bwd_chain_lds_bytes(int LP, int NI, int L, bool with_theta, bool vg, bool gv, bool edge = false)
+// dynamic LDS of mrf_bwd_sweep_chain (host and device agree through these two expressions)
+__host__ __device__ constexpr int mrf_bwd_chain_pitch(int LP, bool hot) { return 64 * LP + (hot ? 8 : 0); }
+__host__ __device__ inline size_t mrf_bwd_chain_lds_bytes(int LP, int NI, int L, bool hot, bool tables, bool row)
 {
     const size_t NR = 2 * (size_t)NI, LL = 64 * (size_t)LP;
-    const size_t arrays = sizeof(double) * (3 * NR * LL + LL + ((gv && LP == 1) ? (size_t)NI * L * L : 0)) +
-                          (edge ? sizeof(double) : sizeof(float)) * (with_theta ? NR * LL : 0) + sizeof(int) * (3 * MRF_CHAIN_MAX_HELPERS + 1) +
-                          sizeof(float) * (gv ? (size_t)L * L : (vg ? 0 : (size_t)L)) + NR * LL;
+    const size_t arrays = sizeof(double) * (NR * (size_t)mrf_bwd_chain_pitch(LP, hot) + NR * LL + (row ? (size_t)L : 0) + (tables ? (size_t)NI * L * L : 0)) +
+                          sizeof(int) * (3 * MRF_CHAIN_MAX_HELPERS + 1) + sizeof(float) * (tables ? (size_t)L * L : 0) + sizeof(uint16_t) * NR * LL;
     return (arrays + 7) / 8 * 8 + sizeof(MrfWaitBlock);      // the deadline of the waits sits behind the arrays
 }
 
@@ -462,6 +462,29 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
     }
 }
 
+// Arguments of mrf_bwd_sweep_chain, laid out by the host so that a wavefront has little to work out before its first
+// loads (a launch on a small image is mostly that): per direction of the launch, not of the problem, and the sources as pointers.
+struct MrfChainParams {
+    int H, W, L, w_mul, r_first, r_count;
+    long long N;
+    int begin[MRF_MAXR + 1];               // prefix sums of B*nscan over the launch's directions
+    int dh[MRF_MAXR], dw[MRF_MAXR], nscan[MRF_MAXR];
+    float carry_scale[MRF_MAXR];
+    // direction ri reads src[ri * src_pitch + c], c < n_src[ri]; cg: coefficient in the message gradient, cd: that in
+    // grad theta less cg.  (Twice as long as they can be filled: a kernel reads as many entries as it has slots.)
+    int src_pitch, n_src[MRF_MAXR];
+    const float *src[2 * MRF_MAXR];
+    double cg[2 * MRF_MAXR], cd[2 * MRF_MAXR];
+    const float *V, *w;
+    const uint8_t *p, *q;
+    float *S, *gunary, *gw;
+    double *gV, *gstore;
+    float *gstore32;
+    int unary_dir, unary_init;
+    int *fault;
+    int spin_limit;
+};
+
 // ---- index replay with the node-to-node chain on a wavefront of its own ----------------------
 //
 // For launches with few scanlines, where the time of a sweep is the length of a scanline
@@ -474,16 +497,27 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
 // correction at q can be applied to ext before the carry is known.
 //
 // A scanline gets 1 + NI wavefronts.  The helpers take the nodes in turn: they load, form
-// ext with the correction at q, and publish it with p through a ring in LDS (stage "pre");
-// the chain wavefront touches only LDS: one add per label, the scatter, one read, one
-// multiply; the same helpers later pick up what the chain left for a node (incoming carry
-// and scattered vector) and do the rest: grad theta (Alg. 4 line 8), the stored s, the
-// edge-weight gradient (Eq. supp-gradient-edge) (stage "post").  A helper runs pre(t) then
-// post(t - NI), with a ring of 2 NI slots: every slot is free again exactly when its owner
-// comes round to it, so only two kinds of wait exist (chain on pre, post on chain), each on
-// a counter that only grows.  The chain reads one node ahead and frees a node for post one
-// step late; with NI >= 2 no wait can depend on itself: post(t - 2 NI), which precedes
-// pre(t) in its helper, needs the chain to have passed step t - 2 NI + 1 only.
+// ext with the correction at q, and publish it with the scatter targets through a ring in LDS
+// (stage "pre"), next to a target vector of the node that they have cleared; the chain wavefront
+// touches only LDS: per label one add, the scatter, one read, one multiply, and off the way
+// to the next node it leaves g in the place of ext; the same helpers later pick up g and the
+// scattered vector and do the rest: grad theta (Alg. 4 line 8), the stored s, the edge-weight
+// gradient (Eq. supp-gradient-edge) (stage "post").  A helper runs pre(t) then post(t - NI),
+// with a ring of 2 NI slots: every slot is free again exactly when its owner comes round to
+// it, so only two kinds of wait exist (chain on pre, post on chain), each on a counter that
+// only grows.  The chain reads one node ahead; with NI >= 2 no wait can depend on itself:
+// post(t - 2 NI), which precedes pre(t) in its helper, needs the chain to have passed step
+// t - 2 NI only.
+// What a helper knows of a node when it runs pre stays in its registers until post: p, V's
+// entries, grad theta less g.  Loads and stores go through buffer views of the image: a lane's
+// offset is its label, the node's is a scalar, and what must not be stored gets the offset
+// at which the view ends; so a turn is one straight piece of code.  Label sums are formed by
+// the matrix unit (mrf_wave_sum_mat_f64).  A turn of a helper is some 95 vector instructions at 96 labels and three sources and
+// a step of the chain 26, where exec-masked stores, 64-bit addresses and sums by DPP took 300 and 50: those bounded launches of two and
+// more workgroups per compute unit, the chain's own writes (carry, scattered vector, clearing) the others.  256 x 512, 96 labels, TRWP,
+// K = 5: 1.66 -> 1.19 ms (65 us for the 265 MB of a launch, 4.1 TB/s); 256 x 256, 256 labels, TRWP, K = 10 4.51 -> 3.16 ms; 283 x 411, 70
+// labels, ISGMR, K = 5 1.52 -> 1.22 ms; 32 x 48, 16 labels, ISGMR, K = 5 65 -> 51 us, where half of a launch was the way to its first loads
+// (arguments per direction, no 64-bit products, no division for steps of one, loads in front of the preparation of LDS).
 //
 // GV without VG (L <= 64, as far as LDS has room): the launch also wants the V gradient; every helper keeps an
 // accumulator of its own in LDS, lane lambda owning column lambda; their sum goes to the workgroup's slot at the end.
@@ -493,76 +527,74 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
 // up with the chain, so the layout stays ahead to 1,536 scanlines per launch (it did to 512 while the helpers
 // gathered from V).
 // EDGE (GV and VG, 33..64 labels and fewer): a problem with per-edge tables: the helpers store g in P.gstore32, if that is
-// wanted, for mrf_bwd_edge_tables, and what arrives at theta from elsewhere waits for the carry in double, so that grad theta
-// is rounded once, as in mrf_bwd_sweep.
-// HOT: truncated models send most labels to one source label, and the chain wavefront's LDS
-// adds would queue at that one word; the helpers guess it (as in mrf_bwd_sweep) and the chain
-// sums its lanes with a DPP tree while the LDS round trip is under way.  Costs the chain some
-// twenty instructions per node: for launches that are bound by LDS throughput, not by the
-// latency of the chain.
+// wanted, for mrf_bwd_edge_tables.
+// HOT: truncated models send most labels to one source label, and the chain wavefront's LDS adds would queue at that
+// one word (64 lanes of one instruction that meet on a word take 170 clocks more than 64 that do not).  The helpers guess it
+// (as in mrf_bwd_sweep) and send its lanes to eight words of their own by lane, which leaves next to no queue (9
+// clocks); the chain adds the eight up.
 template <int LP, int NS, int D, int NI, bool VG, bool GV, bool HOT, bool EDGE = false>
-__global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBwdParams P)
+__global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfChainParams P)
 {
+    static_assert(D == 1 || D == 2, "sets of registers");
     constexpr int NR = 2 * NI;
     constexpr int LL = 64 * LP;
-    static_assert(NI >= 2 && NI <= MRF_CHAIN_MAX_HELPERS, "helpers per scanline");
+    constexpr int LH = mrf_bwd_chain_pitch(LP, HOT);              // a target vector and, with HOT, the eight words behind it
+    static_assert(NI >= 2 && NI <= MRF_CHAIN_MAX_HELPERS && NI % 2 == 0, "helpers per scanline");
     extern __shared__ __align__(16) unsigned char mrf_bsmem[];
-    // carved in the order of mrf_bwd_chain_lds_bytes
-    double *a_ext = reinterpret_cast<double *>(mrf_bsmem);       // [NR][LL] pre -> chain, post
-    double *b_cin = a_ext + NR * LL;                             // [NR][LL] chain -> post: carry that entered the node
-    double *b_sv = b_cin + NR * LL;                              // [NR][LL]                scattered vector that left it
-    double *sbuf = b_sv + NR * LL;                               // [LL] scatter target of the chain
-    double *gvacc = sbuf + LL;                                   // [NI][L*L] V-gradient accumulators (GV)
     constexpr bool GVT = GV && !VG;          // V-gradient tables in LDS
     constexpr bool GS = GV && VG;            // node gradients stored for mrf_bwd_pairwise_*
+    constexpr bool VROW = !VG && !GV;        // first row of V in LDS
     static_assert(!GVT || LP == 1, "V-gradient tables");
     static_assert(!EDGE || (GS && !HOT), "per-edge tables");
-    using theta_t = std::conditional_t<EDGE, double, float>;
-    theta_t *a_extT = reinterpret_cast<theta_t *>(gvacc + (GVT ? NI * P.g.L * P.g.L : 0));   // [NR][LL] pre -> post (launches that form grad theta)
-    int *pre_done = reinterpret_cast<int *>(a_extT + (P.unary_dir >= 0 ? NR * LL : 0));   // [MRF_CHAIN_MAX_HELPERS] per helper: last step published
+    const int L = P.L;
+    // carved in the order of mrf_bwd_chain_lds_bytes
+    double *svr = reinterpret_cast<double *>(mrf_bsmem);         // [NR][LH] scatter targets: cleared by pre, chain -> post
+    double *er = svr + NR * LH;                                  // [NR][LL] ext, pre -> chain; then g, chain -> post
+    double *vd = er + NR * LL;                                   // [L] first row of V (VROW)
+    double *gvacc = vd + (VROW ? L : 0);                     // [NI][L*L] V-gradient accumulators (GVT)
+    int *pre_done = reinterpret_cast<int *>(gvacc + (GVT ? NI * L * L : 0));   // [MRF_CHAIN_MAX_HELPERS] per helper: last step published
     int *chain_done = pre_done + MRF_CHAIN_MAX_HELPERS;          // last step the chain finished
     int *a_hot = chain_done + 1;                                 // [NR] pre -> chain: most popular scatter target, or -1
-    float *vl = reinterpret_cast<float *>(a_hot + 2 * MRF_CHAIN_MAX_HELPERS);   // [L] first row of V (unless VG), all of V (tables)
-    uint8_t *a_p = reinterpret_cast<uint8_t *>(vl + (GVT ? P.g.L * P.g.L : (VG ? 0 : P.g.L)));   // [NR][LL]
+    float *vl = reinterpret_cast<float *>(a_hot + 2 * MRF_CHAIN_MAX_HELPERS);   // [L*L] V (GVT)
+    uint16_t *tgr = reinterpret_cast<uint16_t *>(vl + (GVT ? L * L : 0));   // [NR][LL] pre -> chain: LDS address of a label's target, less the slot's offset
+    typedef __attribute__((address_space(3))) double *mrf_lds_f64;
+    const unsigned sv_base = (unsigned)(uintptr_t)(mrf_lds_f64)svr;                 // (0: nothing lies in front of the dynamic LDS)
     MrfWaitBlock &wait_lds = *reinterpret_cast<MrfWaitBlock *>(
-        mrf_bsmem + ((a_p + NR * LL - mrf_bsmem) + 7) / 8 * 8);  // for the waits below (mrf_wait_turn)
-    const int L = P.g.L;
+        mrf_bsmem + (((unsigned char *)(tgr + NR * LL) - mrf_bsmem) + 7) / 8 * 8);  // for the waits below (mrf_wait_turn)
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // uniform, and known to be
-    const long long N = P.g.N;
 
-    if (GVT) {
-        for (int e = threadIdx.x; e < L * L; e += blockDim.x) vl[e] = P.V[e];
-        for (int e = threadIdx.x; e < NI * L * L; e += blockDim.x) gvacc[e] = 0.0;
-    } else if (!VG) {
-        for (int e = threadIdx.x; e < L; e += blockDim.x) vl[e] = P.V[e];
-    }
-    if (threadIdx.x < MRF_CHAIN_MAX_HELPERS) pre_done[threadIdx.x] = (int)threadIdx.x - NI;
-    if (threadIdx.x == 0) { *chain_done = -1; mrf_wait_init(&wait_lds, P.fault, P.spin_limit); }
-    for (int e = threadIdx.x; e < LL; e += blockDim.x) sbuf[e] = 0.0;
-    __syncthreads();
-
-    const long long sl = blockIdx.x;       // one scanline per workgroup
-    const int ri = mrf_direction_of(P.blk_begin, P.r_count, sl);
-    const int r = P.r_first + ri;
-    const unsigned local = (unsigned)(sl - P.blk_begin[ri]);
-    const unsigned nsc = (unsigned)P.g.nscan[r];
-    const int b = (int)(local / nsc);
-    const unsigned t = local - (unsigned)b * nsc;
-    const int dh = P.g.dh[r], dw = P.g.dw[r];
+    const int sl = (int)blockIdx.x;        // one scanline per workgroup
+    int ri = 0;
+    while (ri + 1 < P.r_count && sl >= P.begin[ri + 1]) ++ri;
+    const unsigned local = (unsigned)(sl - P.begin[ri]), nsc = (unsigned)P.nscan[ri];
+    const int b = local < nsc ? 0 : (int)(local / nsc);
+    const int dh = P.dh[ri], dw = P.dw[ri];
     int y0, x0, len;
-    mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
-    const long long head = ((long long)b * P.g.H + y0) * P.g.W + x0;
-    const long long nstep = (long long)dh * P.g.W + dw;
+    mrf_geom_head(P.H, P.W, dh, dw, local - (unsigned)b * nsc, y0, x0, len);
+
+    // LDS, by all wavefronts together; those of the helpers have their first loads under way
+    auto prepare = [&]() {
+        if (GVT) {
+            for (int e = threadIdx.x; e < L * L; e += 64 * (1 + NI)) vl[e] = P.V[e];
+            for (int e = threadIdx.x; e < NI * L * L; e += 64 * (1 + NI)) gvacc[e] = 0.0;
+        } else if (VROW) {
+            for (int e = threadIdx.x; e < L; e += 64 * (1 + NI)) vd[e] = (double)P.V[e];
+        }
+        if (threadIdx.x < MRF_CHAIN_MAX_HELPERS) pre_done[threadIdx.x] = (int)threadIdx.x - NI;
+        if (threadIdx.x == 0) { *chain_done = -1; mrf_wait_init(&wait_lds, P.fault, P.spin_limit); }
+        __syncthreads();
+    };
 
     if (wv == 0) {
         // ---- the chain: step tt handles node len-1-tt ---------------------------------------
         // One wait per step: the read of the scattered vector.  What the step needs from the
-        // ring is read one step ahead, and the counter that frees a step for the helpers is
-        // written one step late, when the LDS queue is known to have drained past it.
-        const double cscale = (double)P.carry_scale[r];
+        // ring is read one step ahead.
+        __builtin_amdgcn_s_setprio(3);
+        const double cscale = (double)P.carry_scale[ri];
         double carry[LP], ext[LP];
-        int pv[LP];
+        int tg[LP];
+        int hot = -1;
         auto await = [&](int u, int tt) {
             int sn;
             int wait_turns = 0;
@@ -573,301 +605,296 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfBw
             } while (sn < tt);
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
         };
-        await(0, 0);
+        auto entries = [&](int slot) {
+            if (HOT) hot = a_hot[slot];
 #pragma unroll
-        for (int s = 0; s < LP; ++s) {
-            carry[s] = 0.0;
-            ext[s] = a_ext[lane + 64 * s];
-            pv[s] = a_p[lane + 64 * s];
-        }
-        int hot = -1;
-        if (HOT) hot = __builtin_amdgcn_readfirstlane(a_hot[0]);
-        int sb = 0;                         // slot of step t0 (t0 is a multiple of NI)
-        for (int t0 = 0; t0 < len; t0 += NI) {
-#pragma unroll
-            for (int u = 0; u < NI; ++u) {
-                const int tt = t0 + u;
-                if (tt < len) {
-                    const int slot = sb + u;
-                    const int un = (u + 1 == NI) ? 0 : u + 1;
-                    const int slotn = (u + 1 == NI) ? (sb == 0 ? NI : 0) : slot + 1;
-                    const bool more = tt + 1 < len;
-                    // index scatter: s(mu) = sum over lambda with p(lambda) = mu (labels past L
-                    // carry zeros to entries of their own)
-                    double hpart = 0.0;
-#pragma unroll
-                    for (int s = 0; s < LP; ++s) {
-                        const int lam = lane + 64 * s;
-                        const double g = carry[s] + ext[s];
-                        b_cin[slot * LL + lam] = carry[s];
-                        const bool ishot = HOT && pv[s] == hot;
-                        if (!ishot)
-                            __hip_atomic_fetch_add(&sbuf[pv[s]], g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        if (HOT) hpart += ishot ? g : 0.0;
-                    }
-                    mrf_wave_lds_fence();
-                    // In one batch behind the scatter: the counter of the next node's helper, then
-                    // (the LDS queue keeps this order) that node's ring entries, then the scattered
-                    // vector.  If the counter turns out not to cover the node, its entries are read
-                    // again after waiting.
-                    const int flag = __hip_atomic_load(&pre_done[un], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    double sv[LP];
-                    int hotn = -1;
-                    if (HOT) hotn = a_hot[slotn];
-#pragma unroll
-                    for (int s = 0; s < LP; ++s) {
-                        ext[s] = a_ext[slotn * LL + lane + 64 * s];
-                        pv[s] = a_p[slotn * LL + lane + 64 * s];
-                        sv[s] = sbuf[lane + 64 * s];
-                    }
-                    double hsum = 0.0;
-                    if (HOT) hsum = mrf_wave_sum_f64(hpart);
-                    if (__builtin_expect(more && __builtin_amdgcn_readfirstlane(flag) < tt + 1, 0)) {
-                        await(un, tt + 1);
-                        if (HOT) hotn = a_hot[slotn];
-#pragma unroll
-                        for (int s = 0; s < LP; ++s) {
-                            ext[s] = a_ext[slotn * LL + lane + 64 * s];
-                            pv[s] = a_p[slotn * LL + lane + 64 * s];
-                        }
-                    }
-                    // everything this wavefront sent to LDS before the reads above has landed
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                    __builtin_amdgcn_wave_barrier();
-                    // (written by every lane: the same word, and no exec-mask juggling in the step)
-                    if (tt > 0)
-                        __hip_atomic_store(chain_done, tt - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-#pragma unroll
-                    for (int s = 0; s < LP; ++s) {
-                        if (HOT && lane + 64 * s == hot) sv[s] += hsum;
-                        sbuf[lane + 64 * s] = 0.0;
-                        b_sv[slot * LL + lane + 64 * s] = sv[s];
-                        carry[s] = cscale * sv[s];
-                    }
-                    if (HOT) hot = __builtin_amdgcn_readfirstlane(hotn);
-                }
+            for (int s = 0; s < LP; ++s) {
+                ext[s] = er[slot * LL + lane + 64 * s];
+                tg[s] = tgr[slot * LL + lane + 64 * s];
             }
-            sb = (sb == 0) ? NI : 0;
+        };
+        prepare();
+        await(0, 0);
+        entries(0);
+#pragma unroll
+        for (int s = 0; s < LP; ++s) carry[s] = 0.0;
+        for (int t0 = 0;; t0 += NR) {
+#pragma unroll
+            for (int u = 0; u < NR; ++u) {          // (unrolled, so that ring addresses are constants)
+                const int tt = t0 + u;
+                constexpr int rn = NR;
+                const int un = (u + 1) % rn;
+                const bool last = tt + 1 >= len;
+                // index scatter: s(mu) = sum over lambda with p(lambda) = mu (labels past L
+                // carry zeros to entries of their own)
+                double g[LP];
+#pragma unroll
+                for (int s = 0; s < LP; ++s) {
+                    g[s] = carry[s] + ext[s];
+                    __hip_atomic_fetch_add((mrf_lds_f64)((unsigned)tg[s] + (unsigned)(u * LH) * 8u), g[s], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                mrf_wave_lds_fence();
+                // In one batch behind the scatter: the counter of the next node's helper, then
+                // (the LDS queue keeps this order) that node's ring entries, then the scattered
+                // vector.  If the counter turns out not to cover the node, its entries are read
+                // again after waiting.
+                const int flag = __hip_atomic_load(&pre_done[un % NI], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const int hot_now = hot;
+                entries(un);
+                double sv[LP], hc[8];
+#pragma unroll
+                for (int s = 0; s < LP; ++s) sv[s] = svr[u * LH + lane + 64 * s];
+                if (HOT) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) hc[j] = svr[u * LH + LL + j];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                // (behind the reads: nobody waits for these)
+#pragma unroll
+                for (int s = 0; s < LP; ++s) er[u * LL + lane + 64 * s] = g[s];
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                // (written by every lane: the same word, and no exec-mask juggling in the step.  LDS executes a
+                // wavefront's operations in order: whoever sees the counter sees what was sent before it)
+                if (!HOT) __hip_atomic_store(chain_done, tt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (__builtin_expect(!last && __builtin_amdgcn_readfirstlane(flag) < tt + 1, 0)) {
+                    await(un % NI, tt + 1);
+                    entries(un);
+                    __builtin_amdgcn_s_waitcnt(0xC07F);      // (lgkmcnt(0): the way past this branch is counted as if it had not been taken)
+                }
+                if (HOT) {
+                    const double hsum = ((hc[0] + hc[1]) + (hc[2] + hc[3])) + ((hc[4] + hc[5]) + (hc[6] + hc[7]));
+#pragma unroll
+                    for (int s = 0; s < LP; ++s) {
+                        sv[s] += lane + 64 * s == hot_now ? hsum : 0.0;
+                        svr[u * LH + lane + 64 * s] = sv[s];
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __hip_atomic_store(chain_done, tt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+#pragma unroll
+                for (int s = 0; s < LP; ++s) carry[s] = cscale * sv[s];
+                if (last) return;                   // (uniform)
+            }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_wave_barrier();
-        if (lane == 0) __hip_atomic_store(chain_done, len - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        return;
     }
 
     // ---- helpers ---------------------------------------------------------------------------
-    const int jw = wv - 1;
+    const int jw = wv - 1, r = P.r_first + ri;
     const bool own_unary = (r == P.unary_dir);
     const bool unary_old = own_unary && !P.unary_init;
-    const size_t umul = unary_old ? 1 : 0;
-    const uint8_t *pbase = P.p + (size_t)r * N * L;
-    const uint8_t *qbase = P.q + (size_t)r * N;
-    const int vzero = mrf_opaque_zero();
-
-    // source slots; unused ones re-read grad c / the first source with coefficient 0
-    const float *src[NS];
-    double cG[NS], cT[NS];
-    const int nsrc = P.n_src[r];
+    // views of the image (the host has checked that they fit 32-bit offsets); node n of the scanline lies
+    // at hn + n * step
+    const unsigned HW = (unsigned)P.H * (unsigned)P.W, HWL = HW * (unsigned)L, endb = HWL * 4u;
+    const size_t ibn = (size_t)((unsigned)b * HW), ib = ibn * (unsigned)L;
+    const size_t dibn = (size_t)(unsigned)r * (unsigned)P.N + ibn, dib = dibn * (unsigned)L;      // in arrays with an image per direction
+    const unsigned hn = (unsigned)y0 * (unsigned)P.W + (unsigned)x0, step = (unsigned)(dh * P.W + dw);
+    // a lane's offsets; past every view for labels past L
+    const unsigned lane4 = 4u * (unsigned)lane;
+    const bool in_last = lane + 64 * (LP - 1) < L;
+    const unsigned end4 = in_last ? lane4 + 256u * (LP - 1) : MRF_BUF_NONE, end1 = in_last ? (unsigned)lane + 64u * (LP - 1) : MRF_BUF_NONE;
+    auto vo = [&](int s) { return s < LP - 1 ? lane4 + 256u * (unsigned)s : end4; };
+    auto vp = [&](int s) { return s < LP - 1 ? (unsigned)lane + 64u * (unsigned)s : end1; };
+    mrf_buf bs[NS];
+    const int nsrc = P.n_src[ri], src0 = ri * P.src_pitch;
 #pragma unroll
     for (int c = 0; c < NS; ++c) {
-        const bool live = c < nsrc;
-        const bool isgc = (c == nsrc) && P.use_gc;
-        src[c] = live ? P.src_base + (size_t)P.src_dir[r][c] * P.src_stride : P.gc;
-        cG[c] = live ? (double)P.coefG[r][c] : (isgc ? 1.0 : 0.0);
-        cT[c] = live ? (double)P.coefT[r][c] : (isgc ? 1.0 : 0.0);
+        bs[c] = mrf_buffer(P.src[src0 + c] + ib, c < nsrc ? endb : 0);      // (a slot that is not in use reads zeros)
     }
-
-    // the last node of the scanline has no successor in direction r
-    if (jw == 0) {
-        const long long last = head + (long long)(len - 1) * nstep;
-#pragma unroll
-        for (int s = 0; s < LP; ++s) {
-            const int lam = lane + 64 * s;
-            if (lam < L) P.S[((size_t)r * N + last) * L + lam] = 0.0f;
-        }
-    }
+    const mrf_buf bp = mrf_buffer(P.p + dib, HWL), bq = mrf_buffer(P.q + dibn, HW);
+    const mrf_buf bgo = mrf_buffer(P.gunary + ib, unary_old ? endb : 0);
+    const mrf_buf bw = mrf_buffer(P.w + (P.w_mul ? dibn : 0), P.w_mul ? HW * 4u : 4u);
+    auto store_f32 = [](mrf_buf bb, unsigned off, unsigned soff, float x) { __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), bb, off, soff, 0); };
 
     // own steps: tt = jw + it * NI, it = 0 .. T-1; one more turn for the last post
     const int T = len > jw ? (len - jw + NI - 1) / NI : 0;
-    float cur[D][NS][LP], nxt[D][NS][LP];
-    float ucur[D][LP], unxt[D][LP];
-    int pcur[D][LP], pnxt[D][LP];
-    int qcur[D], qnxt[D];
-    float wcur[D], wnxt[D];                 // edge weight of the node's incoming edge (GV)
-    // addresses relative to the head of the scanline: one 32 x 32 bit product per node (the
-    // host has checked that a node step times L fits 32 bits)
-    const int step_l = (int)nstep * L;
-    const int step_n = (int)nstep;
-    const float *srcb[NS];
-#pragma unroll
-    for (int c = 0; c < NS; ++c) srcb[c] = src[c] + (size_t)head * L;
-    const float *gub = P.gunary + (size_t)head * L * umul;
-    const int step_u = unary_old ? step_l : 0;
-    const uint8_t *pb = pbase + (size_t)head * L;
-    const uint8_t *qb = qbase + (size_t)head;
-    const float *wb = P.w + (P.w_mul ? (size_t)r * N + head : 0);
-    const int step_w = P.w_mul ? step_n : 0;
-    auto prefetch = [&](float (&dst)[NS][LP], float (&udst)[LP], int (&pdst)[LP], int &qdst, float &wdst, int it) {
+    struct In {
+        float x[NS][LP], gu[LP], w;
+        int p[LP], q;
+    };
+    In in[D];                                   // a turn's loads are issued D turns before it, as soon as its registers are free
+    auto prefetch = [&](In &d, int it) {
         int n = len - 1 - (jw + it * NI);
         n = n > 0 ? n : 0;
-        const long long o = (long long)n * step_l;
-        const long long ou = (long long)n * step_u;
+        const unsigned node = hn + (unsigned)n * step, ob = node * (unsigned)L * 4u;
 #pragma unroll
         for (int s = 0; s < LP; ++s) {
-            const int lam = lane + 64 * s;
-            const int lc = lam < L ? lam : 0;
 #pragma unroll
-            for (int c = 0; c < NS; ++c) dst[c][s] = srcb[c][o + lc];
-            udst[s] = gub[ou + (unary_old ? lc : 0)];      // one cached word unless it is needed
-            pdst[s] = pb[o + lc];
+            for (int c = 0; c < NS; ++c) d.x[c][s] = mrf_buf_f32s(bs[c], vo(s), ob);
+            d.gu[s] = mrf_buf_f32s(bgo, vo(s), ob);
+            d.p[s] = (int)__builtin_amdgcn_raw_buffer_load_b8(bp, vp(s), ob >> 2, 0);
         }
-        qdst = qb[(long long)n * step_n + vzero];
-        wdst = GVT ? wb[(long long)n * step_w + vzero] : 0.0f;
+        d.q = (int)__builtin_amdgcn_raw_buffer_load_b8(bq, 0, node, 0);
+        d.w = GVT ? mrf_buf_f32s(bw, 0, P.w_mul ? node * 4u : 0u) : 0.0f;
     };
-    if (T > 0) {
 #pragma unroll
-        for (int u = 0; u < D; ++u) prefetch(cur[u], ucur[u], pcur[u], qcur[u], wcur[u], u);
+    for (int v = 0; v < D; ++v) prefetch(in[v], v);
+    prepare();
+    double cG[NS], cD[NS];
+#pragma unroll
+    for (int c = 0; c < NS; ++c) { cG[c] = P.cg[src0 + c]; cD[c] = P.cd[src0 + c]; }
+    const mrf_buf bgu = mrf_buffer(P.gunary + ib, own_unary ? endb : 0), bS = mrf_buffer(P.S + dib, endb);
+    const mrf_buf bgw = mrf_buffer(P.gw + dibn, P.gw ? HW * 4u : 0);
+    const mrf_buf bV = mrf_buffer(P.V, (size_t)L * L * 4);
+    const mrf_buf bg = mrf_buffer(EDGE ? (const void *)(P.gstore32 + dib) : (const void *)(P.gstore + ib),
+                                  EDGE ? (P.gstore32 ? endb : 0) : (P.gstore ? HWL * 8u : 0));
+    // the last node of the scanline has no successor in direction r
+    if (jw == 0) {
+        const unsigned last = (hn + (unsigned)(len - 1) * step) * (unsigned)L * 4u;
+#pragma unroll
+        for (int s = 0; s < LP; ++s) store_f32(bS, vo(s), last, 0.0f);
     }
-    double *gvl = gvacc + (GVT ? jw * L * L : 0);
-    float wlast = 0.0f;                     // weight of the node whose post stage comes next
-    float *guw = P.gunary + (size_t)head * L;                       // stores of stage "post"
-    float *sw = P.S + ((size_t)r * N + head) * L;
-    float *gww = P.gw ? P.gw + (size_t)r * N + head : nullptr;
-    double *gsw = GS && !EDGE ? P.gstore + (size_t)head * L : nullptr;
-    float *gsw32 = EDGE && P.gstore32 ? P.gstore32 + ((size_t)r * N + head) * L : nullptr;
 
+    // what a turn leaves for the next one, where the same node's post stage is
+    struct Kept {
+        double th[LP];                          // grad theta less g
+        float vv[LP];                           // V(p, lambda) (VG)
+        int p[LP];
+        float w;
+    };
+    Kept kept = {};
+    double *gvl = gvacc + (GVT ? jw * L * L : 0);
     int chain_seen = -1;
-    for (int it0 = 0; it0 < T + 1 && T > 0; it0 += D) {
-#pragma unroll
-        for (int u = 0; u < D; ++u) prefetch(nxt[u], unxt[u], pnxt[u], qnxt[u], wnxt[u], it0 + D + u);
-#pragma unroll
-        for (int u = 0; u < D; ++u) {
-            const int tt = jw + (it0 + u) * NI;
-            if (tt < len) {
-                // ---- pre(tt): everything of node len-1-tt that does not need the carry -------
-                const int slot = tt % NR;
-                double part = 0.0;
-                double ev[LP];
-#pragma unroll
-                for (int s = 0; s < LP; ++s) {
-                    const int lam = lane + 64 * s;
-                    double e = 0.0, eT = 0.0;
-#pragma unroll
-                    for (int c = 0; c < NS; ++c) e = __builtin_fma(cG[c], (double)cur[u][c][s], e);
-                    if (own_unary) {
-#pragma unroll
-                        for (int c = 0; c < NS; ++c) eT = __builtin_fma(cT[c], (double)cur[u][c][s], eT);
-                        eT += unary_old ? (double)ucur[u][s] : 0.0;     // (the buffer may hold anything at first)
-                    }
-                    ev[s] = lam < L ? e : 0.0;
-                    part += ev[s];
-                    if (own_unary) a_extT[slot * LL + lam] = (theta_t)eT;
-                    // (labels past L scatter their zeros to entries of their own)
-                    a_p[slot * LL + lam] = (uint8_t)(lam < L ? (pcur[u][s] < L ? pcur[u][s] : L - 1) : lam);
-                }
-                // the commoner of p at the first and at the last label: for a truncated model one
-                // of the two is far from the far-field minimiser and points to it
-                if (HOT) {
-                    int hot = -1;
-                    const int c0 = __builtin_amdgcn_readlane(pcur[u][0], 0);
-                    int c1 = c0;
-#pragma unroll
-                    for (int s = 0; s < LP; ++s)
-                        if (((L - 1) >> 6) == s) c1 = __builtin_amdgcn_readlane(pcur[u][s], (L - 1) & 63);
-                    int n0 = 0, n1 = 0;
-#pragma unroll
-                    for (int s = 0; s < LP; ++s) {
-                        const bool vld = lane + 64 * s < L;
-                        n0 += __popcll(__ballot(vld && pcur[u][s] == c0));
-                        n1 += __popcll(__ballot(vld && pcur[u][s] == c1));
-                    }
-                    hot = n1 > n0 ? c1 : c0;
-                    hot = hot < L ? hot : -1;
-                    if (lane == 0) a_hot[slot] = hot;
-                }
-                // back Eq. isgmr-norm, on the part of g that is known here: the entry at q loses
-                // the label sum
-                const double tot = mrf_wave_sum_f64(part);
-                int qv = __builtin_amdgcn_readfirstlane(qcur[u]);
-                qv = qv < L ? qv : L - 1;
-#pragma unroll
-                for (int s = 0; s < LP; ++s) {
-                    const int lam = lane + 64 * s;
-                    a_ext[slot * LL + lam] = (lam == qv) ? ev[s] - tot : ev[s];
-                }
-                // (LDS keeps a wavefront's operations in order: the counter lands behind the entries)
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                if (lane == 0) __hip_atomic_store(&pre_done[jw], tt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-            const int tp = tt - NI;
-            if (tp >= 0 && tp < len) {
-                // ---- post(tp): what is left of node len-1-tp once the chain has passed --------
-                int wait_turns = 0;
-                while (chain_seen < tp) {
-                    chain_seen = __builtin_amdgcn_readfirstlane(
-                        __hip_atomic_load(chain_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-                    if (chain_seen < tp) mrf_wait_turn(&wait_lds, wait_turns);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                const int slot = tp % NR;
-                const int n = len - 1 - tp;
-                const bool update = n > 0;             // node i has a predecessor: its update is replayed
-                const long long oi = (long long)n * step_l;              // node i, in label entries from the head
-                const long long oj = oi - step_l;                        // node i - r
-                double acc = 0.0;
-#pragma unroll
-                for (int s = 0; s < LP; ++s) {
-                    const int lam = lane + 64 * s;
-                    const double cin = b_cin[slot * LL + lam];
-                    if (own_unary && lam < L)
-                        guw[oi + lam] = (float)(cin + (double)a_extT[slot * LL + lam]);
-                    if (update && lam < L) sw[oj + lam] = (float)b_sv[slot * LL + lam];
-                    if ((P.gw || GV) && lam < L) {
-                        const double g = cin + a_ext[slot * LL + lam];    // as the chain formed it
-                        const int pv = a_p[slot * LL + lam];
-                        if constexpr (EDGE) {
-                            if (gsw32) gsw32[oi + lam] = update ? (float)g : 0.0f;
-                        } else if constexpr (GS) {
-                            gsw[oi + lam] = update ? g : 0.0;
-                        }
-                        if (!GS && P.gw) {
-                            float vv;
-                            if (GV) {
-                                vv = vl[__mul24(pv, L) + lam];
-                            } else if (VG) {
-                                vv = P.V[(size_t)__mul24(pv, L) + lam];
-                            } else {
-                                const int dist = pv > lam ? pv - lam : lam - pv;
-                                vv = vl[dist];
-                            }
-                            acc = __builtin_fma(g, (double)vv, acc);
-                        }
-                        if (GVT && update)
-                            gvl[__mul24(pv, L) + lam] = __builtin_fma((double)wlast, g, gvl[__mul24(pv, L) + lam]);
-                    }
-                }
-                if (!GS && P.gw) {
-                    acc = mrf_wave_sum_f64(acc);
-                    // one writer per entry and launch: a no-return atomic is a plain accumulate
-                    if (update && lane == 0)
-                        __hip_atomic_fetch_add(&gww[(long long)n * step_n], (float)acc, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
-            wlast = wcur[u];
-        }
-#pragma unroll
-        for (int u = 0; u < D; ++u) {
-            qcur[u] = qnxt[u];
-            wcur[u] = wnxt[u];
+    const bool want_w = (P.gw || GVT) && !GS;
+
+    auto turn = [&](In &in_, int it, auto parity) {
+        constexpr int par = decltype(parity)::value;
+        const int tt = jw + it * NI;
+        Kept now;
+        {
+            // ---- pre(tt): everything of node len-1-tt that does not need the carry -------
+            // (in the last turn there is no such node: what is published then nobody reads)
+            const int slot = jw + par * NI;
+            double ev[LP], part = 0.0;
+            int pc[LP];
 #pragma unroll
             for (int s = 0; s < LP; ++s) {
-                ucur[u][s] = unxt[u][s];
-                pcur[u][s] = pnxt[u][s];
+                double e = cG[0] * (double)in_.x[0][s];
 #pragma unroll
-                for (int c = 0; c < NS; ++c) cur[u][c][s] = nxt[u][c][s];
+                for (int c = 1; c < NS; ++c) e = __builtin_fma(cG[c], (double)in_.x[c][s], e);
+                ev[s] = e;
+                part += e;
+                pc[s] = in_.p[s] < L ? in_.p[s] : L - 1;
             }
+            // the commoner of p at the first and at the last label: for a truncated model one
+            // of the two is far from the far-field minimiser and points to it
+            int hot = -1;
+            if (HOT) {
+                const int c0 = __builtin_amdgcn_readlane(pc[0], 0), c1 = __builtin_amdgcn_readlane(pc[LP - 1], (L - 1) & 63);
+                int n0 = 0, n1 = 0;
+#pragma unroll
+                for (int s = 0; s < LP; ++s) {
+                    const int pm = s < LP - 1 || lane + 64 * s < L ? pc[s] : -1;
+                    n0 += __popcll(__builtin_amdgcn_ballot_w64(pm == c0));
+                    n1 += __popcll(__builtin_amdgcn_ballot_w64(pm == c1));
+                }
+                hot = n1 > n0 ? c1 : c0;
+                a_hot[slot] = hot;              // (by every lane)
+            }
+#pragma unroll
+            for (int s = 0; s < LP; ++s) {
+                const int lam = lane + 64 * s;
+                now.p[s] = pc[s];
+                int target = HOT && pc[s] == hot ? LL + (lane & 7) : pc[s];
+                if (s == LP - 1) target = lam < L ? target : lam;      // (labels past L: zeros to entries of their own)
+                tgr[slot * LL + lam] = (uint16_t)(sv_base + 8u * (unsigned)target);
+                svr[slot * LH + lam] = 0.0;
+            }
+            if (HOT && lane < 8) svr[slot * LH + LL + lane] = 0.0;
+            // back Eq. isgmr-norm, on the part of g that is known here: the entry at q loses
+            // the label sum
+            const double tot = mrf_wave_sum_mat_f64(part);
+            const int qv = in_.q < L ? in_.q : L - 1;
+#pragma unroll
+            for (int s = 0; s < LP; ++s) {
+                const double corr = lane + 64 * s == qv ? tot : 0.0;
+                er[slot * LL + lane + 64 * s] = ev[s] - corr;
+                now.th[s] = 0.0;
+                if (own_unary) {
+                    asm volatile("");            // (a branch, not a selection)
+                    double d = corr + (double)in_.gu[s];
+#pragma unroll
+                    for (int c = 0; c < NS; ++c) d = __builtin_fma(cD[c], (double)in_.x[c][s], d);
+                    now.th[s] = d;
+                }
+                now.vv[s] = 0.0f;
+                if (VG && !GS) now.vv[s] = mrf_buf_f32s(bV, vo(s) + 4u * (unsigned)__mul24(pc[s], L), 0);
+            }
+            now.w = in_.w;
+            // (LDS keeps a wavefront's operations in order: the counter lands behind the entries)
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __hip_atomic_store(&pre_done[jw], tt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        prefetch(in_, it + D);
+        {
+            // ---- post(tp): what is left of node len-1-tp once the chain has passed --------
+            // (in the first turn there is no such node: nothing is stored)
+            const int tp = tt - NI;
+            int wait_turns = 0;
+            while (chain_seen < tp) {
+                chain_seen = __builtin_amdgcn_readfirstlane(
+                    __hip_atomic_load(chain_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+                if (chain_seen < tp) mrf_wait_turn(&wait_lds, wait_turns);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+            const int slot = jw + (1 - par) * NI;
+            const int n = len - 1 - tp;
+            const bool node = it > 0, update = node && n > 0;      // node i has a predecessor: its update is replayed
+            const unsigned on = hn + (unsigned)n * step, oi = on * (unsigned)L * 4u;
+            const unsigned oj = oi - step * (unsigned)L * 4u;      // node i - r
+            double g[LP], sv[LP], V[LP];
+#pragma unroll
+            for (int s = 0; s < LP; ++s) {
+                const int lam = lane + 64 * s;
+                sv[s] = svr[slot * LH + lam];
+                g[s] = er[slot * LL + lam];
+                V[s] = 0.0;
+                if (VROW) {
+                    unsigned dist;
+                    asm("v_sad_u32 %0, %1, %2, 0" : "=v"(dist) : "v"(kept.p[s]), "v"(lam));
+                    if (s == LP - 1) dist = lam < L ? dist : 0;
+                    V[s] = vd[dist];
+                } else if (GVT) {
+                    V[s] = (double)vl[lam < L ? __mul24(kept.p[s], L) + lam : 0];
+                } else if (!GS) {
+                    V[s] = (double)kept.vv[s];
+                }
+                if (s == LP - 1) V[s] = in_last ? V[s] : 0.0;
+            }
+#pragma unroll
+            for (int s = 0; s < LP; ++s) {
+                store_f32(bS, vo(s), update ? oj : endb, (float)sv[s]);
+                if constexpr (EDGE) {
+                    store_f32(bg, vo(s), node ? oi : endb, update ? (float)g[s] : 0.0f);
+                } else if constexpr (GS) {
+                    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, update ? g[s] : 0.0), bg, s < LP - 1 || in_last ? 2u * vo(s) : MRF_BUF_NONE,
+                                                          node ? 2u * oi : 2u * endb, 0);
+                }
+                store_f32(bgu, vo(s), node ? oi : endb, (float)(g[s] + kept.th[s]));
+            }
+            if (want_w) {
+                double acc = g[0] * V[0];
+#pragma unroll
+                for (int s = 1; s < LP; ++s) acc = __builtin_fma(g[s], V[s], acc);
+                acc = mrf_wave_sum_mat_f64(acc);
+                // one writer per entry and launch: a no-return atomic is a plain accumulate
+                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32((float)acc, bgw, lane == 0 ? 0u : MRF_BUF_NONE, update ? 4u * on : 4u * HW, 0);
+            }
+            if (GVT && update && lane < L) {
+                double *const e = &gvl[__mul24(kept.p[0], L) + lane];
+                *e = __builtin_fma((double)kept.w, g[0], *e);
+            }
+        }
+        kept = now;
+    };
+    if (T > 0) {
+        for (int it = 0;; it += 2) {
+            turn(in[0], it, std::integral_constant<int, 0>{});
+            if (it >= T) break;                 // (uniform)
+            turn(in[D - 1], it + 1, std::integral_constant<int, 1>{});
+            if (it + 1 >= T) break;
         }
     }
     if (GVT) {

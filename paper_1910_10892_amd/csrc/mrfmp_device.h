@@ -41,22 +41,24 @@ __host__ __device__ inline void mrf_geom_head(int H, int W, int dh, int dw, long
                                               int &y0, int &x0, int &len)
 {
     // (t counts scanlines of one image: it and every product below fit 32 bits, and a 32-bit division costs a
-    // fifth of a 64-bit one in the few microseconds a launch takes to start)
+    // fifth of a 64-bit one in the few microseconds a launch takes to start; a step of one needs none at all)
     const unsigned adh = (unsigned)mrf_imin(mrf_iabs(dh), H), adw = (unsigned)mrf_imin(mrf_iabs(dw), W);
     const unsigned band = adh * (unsigned)W, tu = (unsigned)t;
     if (tu < band) {
-        const unsigned yy = tu / (unsigned)W;
+        const unsigned yy = adh == 1 ? 0u : tu / (unsigned)W;
         x0 = (int)(tu - yy * (unsigned)W);
         y0 = dh > 0 ? (int)yy : H - (int)adh + (int)yy;
     } else {
         const unsigned tt = tu - band;
-        const unsigned ry = tt / adw;
+        const unsigned ry = adw == 1 ? tt : tt / adw;
         const int cx = (int)(tt - ry * adw);
         y0 = dh > 0 ? (int)(adh + ry) : (int)ry;
         x0 = dw > 0 ? cx : W - (int)adw + cx;
     }
-    int sy = dh > 0 ? (H - 1 - y0) / dh : (dh < 0 ? y0 / (-dh) : INT_MAX);
-    int sx = dw > 0 ? (W - 1 - x0) / dw : (dw < 0 ? x0 / (-dw) : INT_MAX);
+    const unsigned uh = (unsigned)mrf_iabs(dh), uw = (unsigned)mrf_iabs(dw);
+    const unsigned hy = (unsigned)(dh > 0 ? H - 1 - y0 : y0), hx = (unsigned)(dw > 0 ? W - 1 - x0 : x0);
+    const int sy = uh == 1 ? (int)hy : (uh == 0 ? INT_MAX : (int)(hy / uh));
+    const int sx = uw == 1 ? (int)hx : (uw == 0 ? INT_MAX : (int)(hx / uw));
     len = 1 + mrf_imin(sy, sx);
 }
 
@@ -312,6 +314,19 @@ __device__ inline double mrf_wave_sum_f64(double v)
     const double r0 = mrf_readlane_f64(v, 0), r1 = mrf_readlane_f64(v, 16);
     const double r2 = mrf_readlane_f64(v, 32), r3 = mrf_readlane_f64(v, 48);
     return (r0 + r1) + (r2 + r3);
+}
+
+// The same by the matrix unit: one product with a vector of ones adds the lanes in fours (lanes l, l + 16, l + 32, l + 48:
+// the four columns of the 16 x 4 operand), three additions those of the result that a lane holds, a second product the
+// rest.  Products with 1 are exact and the accumulation is that of fused multiply-adds, so it is a sum of doubles in a
+// fixed order like the one above; five instructions instead of 23, on a unit that is otherwise idle.
+__device__ inline double mrf_wave_sum_mat_f64(double v)
+{
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    const d4 zero = {0.0, 0.0, 0.0, 0.0};
+    const d4 a = __builtin_amdgcn_mfma_f64_16x16x4f64(v, 1.0, zero, 0, 0, 0);
+    const d4 b = __builtin_amdgcn_mfma_f64_16x16x4f64(1.0, (a[0] + a[1]) + (a[2] + a[3]), zero, 0, 0, 0);
+    return b[0];
 }
 
 // v[lane ^ 16] + v[lane] and v[lane ^ 32] + v[lane]: the swap instructions exchange the odd rows (upper half)

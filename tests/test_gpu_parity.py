@@ -751,6 +751,47 @@ def test_pairwise_gradients_from_stored_node_gradients(oracle, case):
     check_grad("grad_pairwise (two layouts)", a.grad_pairwise, None, b.grad_pairwise.astype(np.float64))
 
 
+CHAIN_EDGE_CASES = [
+    # seed, algo, B, H, W, L, dirs, K, truncated: label counts around 64 per lane slot; scanlines shorter than, as long as and longer
+    # than the helpers' ring; one node; images, directions and source slots
+    (771, "trwp", 1, 1, 1, 5, DIRS4, 1, False), (772, "trwp", 2, 3, 25, 63, DIRS4, 2, True), (773, "isgmr", 1, 5, 13, 64, DIRS8, 2, True),
+    (774, "trwp", 3, 12, 2, 65, DIRS8, 2, True), (775, "isgmr", 1, 24, 7, 128, DIRS4, 2, False), (776, "trwp", 1, 4, 26, 129, DIRS4, 3, True),
+    (777, "isgmr", 2, 2, 49, 192, DIRS4, 2, True), (778, "trwp", 1, 7, 11, 193, ((0, 1), (0, -1)), 2, True),
+    (779, "trwp", 1, 9, 5, 256, DIRS8, 2, True), (780, "trwp", 1, 5, 30, 37, DIRS16, 1, True),
+]
+
+
+@pytest.mark.parametrize("case", CHAIN_EDGE_CASES, ids=lambda c: "seed%d" % c[0])
+def test_chain_backward_with_every_number_of_helpers(oracle, case):
+    """The chain sweep with 2 to 12 helpers, with and without the words for the most popular scatter target, against the oracle;
+    the number of helpers changes who does a node, not what is done: the same bits."""
+    import paper_1910_10892_amd as mrf
+    from mrf_inputs import truncated_linear
+    print("case chain helpers", case[:6], len(case[6]), case[7:], flush=True)
+    seed, algo, B, H, W, L, dirs, K, truncated = case
+    pr = random_problem(seed, algo, B, H, W, L, dirs, K, symmetric=False, rho=np.linspace(0.3, 0.9, len(dirs)))
+    if truncated:
+        pr.pairwise = truncated_linear(L, 3.0, 0.37)
+        pr.pairwise_kind, pr.trunc, pr.scale = 1, 3.0, 0.37
+    pr.grad_cost = (pr.grad_cost * (0.02 if len(dirs) > 8 else 0.2)).astype(np.float32)
+    try:
+        assert mrf.mrf_tune(6, 2) == 0
+        for hot in ((1, 2) if truncated else (0,)):
+            assert mrf.mrf_tune(12, hot) == 0
+            first = None
+            for ni in (2, 4, 6, 8, 12):
+                assert mrf.mrf_tune(7, ni) == 0
+                g = full_check(oracle, pr, want_V=False)
+                assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_chain", mrf.mrf_last_sweep_launch(True)
+                got = (g.grad_unary, g.grad_edge_weight)
+                if first is None:
+                    first = got
+                assert all(np.array_equal(a, b) for a, b in zip(first, got)), ni
+    finally:
+        for knob in (6, 7, 12):
+            mrf.mrf_tune(knob, 0)
+
+
 def test_forbidden_transitions_leave_first_nodes_alone(oracle):
     """Infinite entries of V that no update selects: the edge-weight gradient of nodes without a predecessor stays 0
     (their p is 0, which may point at such an entry)."""
