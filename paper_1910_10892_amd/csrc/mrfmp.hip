@@ -1035,7 +1035,7 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
     if (gv && (LP != 1 || P.total_scanlines > grad_slots(P.g.L))) return hipErrorInvalidValue;
     MrfChainParams C;
     memset(&C, 0, sizeof(C));
-    C.H = P.g.H; C.W = P.g.W; C.L = P.g.L; C.w_mul = P.w_mul; C.r_first = P.r_first; C.r_count = P.r_count; C.N = P.g.N;
+    C.B = P.g.B; C.H = P.g.H; C.W = P.g.W; C.L = P.g.L; C.w_mul = P.w_mul; C.r_first = P.r_first; C.r_count = P.r_count; C.N = P.g.N;
     int most = 0;
     for (int ri = 0; ri < P.r_count; ++ri) {
         const int n = P.n_src[P.r_first + ri] + (P.use_gc ? 1 : 0);

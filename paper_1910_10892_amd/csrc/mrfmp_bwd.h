@@ -465,7 +465,7 @@ __global__ void __launch_bounds__(64 * WAVES) mrf_bwd_sweep(const MrfBwdParams P
 // Arguments of mrf_bwd_sweep_chain, laid out by the host so that a wavefront has little to work out before its first
 // loads (a launch on a small image is mostly that): per direction of the launch, not of the problem, and the sources as pointers.
 struct MrfChainParams {
-    int H, W, L, w_mul, r_first, r_count;
+    int B, H, W, L, w_mul, r_first, r_count;
     long long N;
     int begin[MRF_MAXR + 1];               // prefix sums of B*nscan over the launch's directions
     int dh[MRF_MAXR], dw[MRF_MAXR], nscan[MRF_MAXR];
@@ -567,11 +567,11 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
     const int sl = (int)blockIdx.x;        // one scanline per workgroup
     int ri = 0;
     while (ri + 1 < P.r_count && sl >= P.begin[ri + 1]) ++ri;
-    const unsigned local = (unsigned)(sl - P.begin[ri]), nsc = (unsigned)P.nscan[ri];
-    const int b = local < nsc ? 0 : (int)(local / nsc);
     const int dh = P.dh[ri], dw = P.dw[ri];
-    int y0, x0, len;
-    mrf_geom_head(P.H, P.W, dh, dw, local - (unsigned)b * nsc, y0, x0, len);
+    int b, y0, x0, len;
+    unsigned t;
+    mrf_geom_order(P.H, P.W, dh, dw, (unsigned)P.nscan[ri], (unsigned)P.B, (unsigned)(sl - P.begin[ri]), b, t);
+    mrf_geom_head(P.H, P.W, dh, dw, t, y0, x0, len);
 
     // LDS, by all wavefronts together; those of the helpers have their first loads under way
     auto prepare = [&]() {

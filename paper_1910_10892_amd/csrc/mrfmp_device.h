@@ -62,6 +62,42 @@ __host__ __device__ inline void mrf_geom_head(int H, int W, int dh, int dw, long
     len = 1 + mrf_imin(sy, sx);
 }
 
+// Image b and scanline t (as mrf_geom_head counts them) of the scanline that comes `local`-th among the count * images of a
+// direction.  Along the axes they are all of one length and come image by image.  Those of a diagonal have any length up to
+// the shorter side of the grid; they come by falling length, every second run of 256 turned round: the workgroups of a launch that
+// the machine holds at once go round its 256 compute units in turn, so a compute unit's scanlines then add up to much the same length
+// (counted along the border, one got three of the longest and another one of them and two of the shortest).  256 x 512, TRWP, eight
+// directions, 767 scanlines per diagonal: 96 labels, dense, K = 5 11.8 -> 10.6 ms forward, 5.87 -> 5.64 backward; truncated, K = 2 2.34 ->
+// 2.32, 1.67 -> 1.53; 256 x 256, 256 labels, K = 1 1.54 -> 1.36, 0.79 -> 0.74.  mrf_fwd_sweep_window, which runs launches of several
+// thousand scanlines, keeps the order of the border (1.02 against 1.05 ms).
+__host__ __device__ inline void mrf_geom_order(int H, int W, int dh, int dw, unsigned count, unsigned images, unsigned local, int &b, unsigned &t)
+{
+    if (mrf_iabs(dh) != 1 || mrf_iabs(dw) != 1) {
+        const unsigned bu = local < count ? 0u : local / count;
+        b = (int)bu;
+        t = local - bu * count;
+        return;
+    }
+    const unsigned total = count * images, run = local & ~255u, left = total - run;
+    const unsigned s = (local >> 8) & 1u ? run + ((left < 256u ? left : 256u) - 1u - (local - run)) : local;
+    const unsigned at = images == 1u ? s : s / images;
+    b = (int)(s - at * images);
+    const unsigned Hu = (unsigned)H, Wu = (unsigned)W, m = Hu < Wu ? Hu : Wu, full = Hu + Wu - 2u * m + 1u;     // scanlines of the full length m
+    unsigned x0, ry;
+    bool row;                                      // starts in the boundary row at x0, or in the boundary column, ry rows behind the first
+    if (at < full) {
+        row = Hu <= Wu || at == 0u;
+        x0 = dw > 0 ? at : Wu - 1u - at;
+        ry = dh > 0 ? at - 1u : Hu - 1u - at;
+    } else {
+        const unsigned k = at - full, l = m - 1u - (k >> 1);     // two of every shorter length
+        row = (k & 1u) == 0u;
+        x0 = dw > 0 ? Wu - l : l - 1u;
+        ry = dh > 0 ? Hu - 1u - l : l - 1u;
+    }
+    t = row ? x0 : Wu + ry;
+}
+
 #ifdef __HIPCC__
 // which of the launch's `count` directions scanline `sl` belongs to; begin[] holds prefix sums
 __device__ inline int mrf_direction_of(const long long (&begin)[MRF_MAXR + 1], int count, long long sl)

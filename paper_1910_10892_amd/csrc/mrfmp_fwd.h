@@ -85,9 +85,9 @@ mrf_fwd_sweep(const MrfFwdParams P)
     const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
     const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
-    const unsigned nsc = (unsigned)P.g.nscan[r];
-    const int b = (int)(local / nsc);
-    const unsigned t = local - (unsigned)b * nsc;
+    int b;
+    unsigned t;
+    mrf_geom_order(P.g.H, P.g.W, P.g.dh[r], P.g.dw[r], (unsigned)P.g.nscan[r], (unsigned)P.g.B, local, b, t);
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -374,9 +374,9 @@ mrf_fwd_sweep_sliced(const MrfFwdParams P)
     const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
     const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
-    const unsigned nsc = (unsigned)P.g.nscan[r];
-    const int b = (int)(local / nsc);
-    const unsigned t = local - (unsigned)b * nsc;
+    int b;
+    unsigned t;
+    mrf_geom_order(P.g.H, P.g.W, P.g.dh[r], P.g.dw[r], (unsigned)P.g.nscan[r], (unsigned)P.g.B, local, b, t);
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -594,9 +594,9 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
     const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
     const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
-    const unsigned nsc = (unsigned)P.g.nscan[r];
-    const int b = (int)(local / nsc);
-    const unsigned t = local - (unsigned)b * nsc;
+    int b;
+    unsigned t;
+    mrf_geom_order(P.g.H, P.g.W, P.g.dh[r], P.g.dw[r], (unsigned)P.g.nscan[r], (unsigned)P.g.B, local, b, t);
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -1609,9 +1609,9 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
     const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
     const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
-    const unsigned nsc = (unsigned)P.g.nscan[r];
-    const int b = (int)(local / nsc);
-    const unsigned t = local - (unsigned)b * nsc;
+    int b;
+    unsigned t;
+    mrf_geom_order(P.g.H, P.g.W, P.g.dh[r], P.g.dw[r], (unsigned)P.g.nscan[r], (unsigned)P.g.B, local, b, t);
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -2241,9 +2241,9 @@ mrf_fwd_sweep_window_split(const MrfFwdParams P)
     const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
     const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
-    const unsigned nsc = (unsigned)P.g.nscan[r];
-    const int b = (int)(local / nsc);
-    const unsigned t = local - (unsigned)b * nsc;
+    int b;
+    unsigned t;
+    mrf_geom_order(P.g.H, P.g.W, P.g.dh[r], P.g.dw[r], (unsigned)P.g.nscan[r], (unsigned)P.g.B, local, b, t);
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);
@@ -2490,9 +2490,9 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
     const int ri = mrf_direction_of(P.blk_begin, P.r_count, blk);
     const int r = P.r_first + ri;
     const unsigned local = (unsigned)(blk - P.blk_begin[ri]);
-    const unsigned nsc = (unsigned)P.g.nscan[r];
-    const int b = (int)(local / nsc);
-    const unsigned t = local - (unsigned)b * nsc;
+    int b;
+    unsigned t;
+    mrf_geom_order(P.g.H, P.g.W, P.g.dh[r], P.g.dw[r], (unsigned)P.g.nscan[r], (unsigned)P.g.B, local, b, t);
     const int dh = P.g.dh[r], dw = P.g.dw[r];
     int y0, x0, len;
     mrf_geom_head(P.g.H, P.g.W, dh, dw, t, y0, x0, len);

@@ -792,6 +792,29 @@ def test_chain_backward_with_every_number_of_helpers(oracle, case):
             mrf.mrf_tune(knob, 0)
 
 
+DIAGONAL_ORDER_CASES = [
+    # seed, algo, B, H, W, L, truncation (0: dense): diagonals of fewer than 256 scanlines, of one more, of a whole number of runs of
+    # 256 and of a remainder; grids higher than wide, wider than high, square, of one row and of one column
+    (781, "trwp", 17, 8, 8, 40, 0), (782, "trwp", 257, 1, 3, 70, 0), (783, "trwp", 32, 9, 8, 100, 6), (784, "trwp", 40, 6, 9, 70, 6),
+    (785, "isgmr", 33, 7, 10, 40, 0), (786, "trwp", 21, 10, 4, 200, 12), (787, "trwp", 100, 5, 1, 40, 6), (788, "isgmr", 30, 6, 5, 200, 12),
+    (789, "isgmr", 1, 40, 21, 140, 0),
+]
+
+
+@pytest.mark.parametrize("case", DIAGONAL_ORDER_CASES, ids=lambda c: "seed%d" % c[0])
+def test_order_of_a_diagonals_scanlines(oracle, case):
+    """Every scanline of a diagonal is swept once, whatever run of 256 it falls into (mrf_geom_order)."""
+    from mrf_inputs import truncated_linear
+    print("case diagonal order", case, flush=True)
+    seed, algo, B, H, W, L, trunc = case
+    pr = random_problem(seed, algo, B, H, W, L, DIRS8, 2, symmetric=False, rho=np.linspace(0.3, 0.9, 8))
+    if trunc:
+        pr.pairwise = truncated_linear(L, float(trunc), 0.37)
+        pr.pairwise_kind, pr.trunc, pr.scale = 1, float(trunc), 0.37
+    pr.grad_cost = (pr.grad_cost * 0.02).astype(np.float32)
+    full_check(oracle, pr)
+
+
 def test_forbidden_transitions_leave_first_nodes_alone(oracle):
     """Infinite entries of V that no update selects: the edge-weight gradient of nodes without a predecessor stays 0
     (their p is 0, which may point at such an entry)."""
