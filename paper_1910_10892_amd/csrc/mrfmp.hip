@@ -649,21 +649,21 @@ int pick_mch(int L, int LP, bool many_sources, long long blocks)
     return best;
 }
 
-// Whether mrf_fwd_sweep_halves is ahead of the better of the other two dense sweeps (33..128 labels; forward pass, K = 2,
-// others / halves).  Its barrier per node and its table in LDS cost more than they save where a launch neither reads
-// many arrays nor crowds the SIMDs, and up to 64 labels the other sweep has one or two wavefronts per SIMD to itself:
-// - up to 64 labels, TRWP: 128 x 128, 4 directions, 40 labels 0.68 / 0.74 ms, 64 labels 0.72 / 0.74; 8 directions 1.47 / 1.56;
-//   4 x 256 x 512, 4 directions 3.18 / 3.47, 8 directions 7.91 / 7.23; 2 x 300 x 300 (600 scanlines), 4 directions, 64 labels
-//   2.03 / 1.98
-// - up to 64 labels, ISGMR: 512 scanlines 0.20 / 0.22, 1,536 scanlines with 40 labels 0.74 / 0.85, with 64 0.97 / 0.86; 2,400
-//   scanlines 1.13 / 1.04; 6,144 scanlines 2.42 / 2.53
-// - 65..96 labels: ahead by 15 to 35 % (256 x 512, 96 labels, TRWP 3.57 / 2.73 with 4 directions, 7.93 / 5.64 with 8), but TRWP with 4
-//   directions and 65 labels 3.83 / 4.07 at 600 scanlines
-// - 97..128 labels: TRWP ahead by 10 to 20 %, ISGMR to 512 scanlines (128 x 128, 4 directions 12 %), behind beyond (128 x 128, 100
-//   labels, 8 directions 0.81 / 0.86, 16 directions 1.28 / 1.46); scanlines of 16 nodes do not pay for the table (0.22 / 0.24)
+// Whether mrf_fwd_sweep_halves is ahead of the better of the other two dense sweeps (33..128 labels; forward pass, K = 2 unless
+// noted, others / halves).  On scanlines of more than 40 nodes nearly always:
+// - up to 64 labels: TRWP 64 x 64, 4 directions, 48 labels 0.350 / 0.325 ms, 128 x 128 36 labels 0.668 / 0.597, 64 labels 0.703 /
+//   0.600, 8 directions 1.47 / 1.32, 256 x 512 64 labels 2.10 / 1.81, 6 x 256 x 256 3.15 / 1.84; ISGMR 128 x 128 48 labels 188 / 180 us, 256 x
+//   512 64 labels 0.92 / 0.69 ms, 4 x 512 x 512, K = 1, 64 labels 2.64 / 2.28.  Behind where TRWP fills the SIMDs: 4 x 512 x 512, K = 1
+//   (2,048 scanlines) 36 labels 2.79 / 2.88, 64 labels 2.93 / 3.03
+// - 65..128 labels: 300 x 600, 65 labels, TRWP 4.96 / 3.04; 4 x 512 x 512, K = 1, 100 labels TRWP 11.8 / 8.3, ISGMR 8.9 / 7.7; 128 x 128,
+//   100 labels, ISGMR, 8 directions 0.78 / 0.68; 128 x 256, 16 directions 2.34 / 2.27
+// On short ones its table in LDS is a good part of a launch (4 images of 16 x 16, ISGMR, K = 3: 36 labels 44 / 49 us, 128 labels level; 16
+// images, TRWP, 36 labels 175 / 193; 28 x 40, K = 3, level up to 64 labels): there as many scanlines as share its cost decide,
+// and 65..96 labels, where the others leave lanes idle (28 x 40, 80 labels, TRWP 0.50 / 0.37 ms).
 bool chunk_minima_ahead(const MrfFwdParams &P, int algo, int rmax, long long blocks)
 {
     const int L = P.g.L;
+    if (P.g.H > 40 || P.g.W > 40) return L > 64 || algo != MRF_TRWP || blocks < 2048;
     const bool middling = blocks > 512 && blocks < 1024;
     if (L <= 64) {
         if (rmax > 4) return blocks > 512;
@@ -688,10 +688,24 @@ hipError_t run_dense(MrfFwdParams &P, int algo, long long blocks, hipStream_t st
     if (halves_fit && (g_tune_dense_sliced == 3 || (g_tune_dense_sliced == 0 && chunk_minima_ahead(P, algo, rmax, blocks)))) {
         const int nw = (L + 31) / 32;
         P.NW = nw;
+        // 65..96 labels and more than 512 scanlines under way at once (a diagonal's are of any length: nodes by the longest): half the
+        // nodes loaded ahead, which leaves registers for four workgroups on a compute unit instead of two.  (Forward pass, TRWP, 96
+        // labels, four / two nodes ahead: 3 x 256 x 256, K = 2 2.91 / 2.06 ms, 2 x 256 x 512 3.37 / 2.80, 6 x 256 x 256, K = 1 2.58 / 1.97; eight
+        // directions, two / one, 2 x 256 x 512, K = 1 3.58 / 3.01, but 256 x 512, K = 5, whose diagonals are 767 scanlines, half of them short,
+        // 10.6 / 10.8.  ISGMR level to 2 % ahead.)
+        long long at_once = 0;
+        for (int r = P.r_first; r < P.r_first + P.r_count; ++r) {
+            const int ah = mrf_iabs(P.g.dh[r]), aw = mrf_iabs(P.g.dw[r]);
+            const int down = ah ? (P.g.H + ah - 1) / ah : INT_MAX, across = aw ? (P.g.W + aw - 1) / aw : INT_MAX;
+            at_once += P.g.N / (down < across ? down : across);
+        }
+        const bool crowded = nw == 3 && at_once > 512;
 #define MRF_HCASE(n) \
         if (nw == n && rmax == 4) return launch_fwd_halves<n, 4, 4>(P, algo, blocks, st); \
         if (nw == n && rmax == 8) return launch_fwd_halves<n, 8, 2>(P, algo, blocks, st); \
         if (nw == n && rmax == 16) return launch_fwd_halves<n, 16, 1>(P, algo, blocks, st);
+        if (crowded && rmax == 4) return launch_fwd_halves<3, 4, 2>(P, algo, blocks, st);
+        if (crowded && rmax == 8) return launch_fwd_halves<3, 8, 1>(P, algo, blocks, st);
         MRF_HCASE(2) MRF_HCASE(3) MRF_HCASE(4)
 #undef MRF_HCASE
     }

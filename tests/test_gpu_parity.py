@@ -354,6 +354,23 @@ def test_which_dense_sweep_runs(oracle, algo, B, H, W, L, dirs, halves):
     assert (mrf.mrf_last_sweep_kernel(False) == "mrf_fwd_sweep_halves") == halves, mrf.mrf_last_sweep_launch(False)
 
 
+@pytest.mark.parametrize("algo,B,H,W,L,dirs,launch", [
+    ("trwp", 1, 41, 6, 40, DIRS4, "halves<2,4,4"), ("trwp", 49, 5, 41, 33, DIRS4, "halves<2,4,4"), ("trwp", 50, 5, 41, 33, DIRS4, ""),
+    ("isgmr", 60, 5, 41, 64, DIRS4, "halves<2,4,4"), ("isgmr", 3, 41, 6, 100, DIRS8, "halves<4,4,4"),
+    ("trwp", 12, 5, 42, 70, DIRS4, "halves<3,4,4"), ("trwp", 13, 5, 42, 70, DIRS4, "halves<3,4,2"), ("trwp", 13, 5, 42, 96, DIRS8, "halves<3,8,1"),
+    ("isgmr", 2, 41, 70, 80, DIRS8, "halves<3,4,2")])
+def test_which_dense_sweep_runs_on_long_scanlines(oracle, algo, B, H, W, L, dirs, launch):
+    """The same where the sweep with chunk minima is ahead by the length of the scanlines, and its two depths of prefetch; the last
+    launch of a TRWP pass sweeps the columns or a diagonal."""
+    import paper_1910_10892_amd as mrf
+    from gpu_harness import run_gpu
+    print("case long scanlines", algo, B, H, W, L, len(dirs), flush=True)
+    pr = random_problem(660 + L, algo, B, H, W, L, dirs, 2, symmetric=False, rho=np.linspace(0.3, 0.9, len(dirs)))
+    check_forward(run_gpu(pr, backward=False), oracle_forward(oracle, pr))
+    ran = mrf.mrf_last_sweep_launch(False)
+    assert launch in ran if launch else "halves" not in ran, ran
+
+
 PRESUM_CASES = [
     # seed, B, H, W, L, dirs, K, integer_valued, truncated
     (701, 1, 6, 7, 40, DIRS8, 3, False, False), (702, 2, 5, 6, 21, DIRS8, 3, True, False),
