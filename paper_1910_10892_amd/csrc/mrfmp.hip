@@ -900,11 +900,11 @@ void fill_sources(MrfFwdParams &P, int algo, int r, unsigned live)
         if (algo == MRF_ISGMR && d == rm) continue;       // Eq. isgmr excludes r and r-
         if (algo == MRF_TRWP && d < r) ++npre;            // Eq. trwp sums all d in index order
         if (d == rm) rmslot = n;
-        P.src_dir[r][n++] = (signed char)d;
+        P.src_dir[r][n++] = d;
     }
-    P.n_pre[r] = (signed char)npre;
-    P.n_src[r] = (signed char)n;
-    P.rm_slot[r] = (signed char)rmslot;
+    P.n_pre[r] = npre;
+    P.n_src[r] = n;
+    P.rm_slot[r] = rmslot;
 }
 
 hipError_t fill(float *dst, long long n, float v, hipStream_t st);
@@ -971,7 +971,7 @@ int run_forward(const mrf_problem *pr, int algo, float *cost, uint8_t *labels, u
                 P.unary = (k == 0) ? pr->unary : bufB;
                 for (int r = 0; r < R; ++r) {
                     fill_sources(P, algo, r, 0u);
-                    P.unary_slab[r] = (signed char)((k == 0) ? 0 : ((P.g.opp[r] >= 0 && P.g.opp[r] < r) ? P.g.opp[r] : r));
+                    P.unary_slab[r] = (int)((k == 0) ? 0 : ((P.g.opp[r] >= 0 && P.g.opp[r] < r) ? P.g.opp[r] : r));
                 }
                 if (k > 0) {
                     const dim3 sg((unsigned)sblocks), sb(256);
@@ -1691,7 +1691,6 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
     float *buf0 = (float *)(ws + kAlign);                   // ISGMR: grad m-hat   TRWP: s per direction
     float *buf1 = (float *)(ws + kAlign + msg_bytes(pr));   // ISGMR: s per direction
     double *gvslots = (double *)(ws + kAlign + (algo == MRF_ISGMR ? 2 : 1) * msg_bytes(pr));
-    { const hipError_t e_ = init_header(workspace, pr->edge_weight_scalar, st); if (e_ != hipSuccess) return hip_fail(e_, "init_header"); }
     P.fault = (int *)(ws + kFaultOffset);
     P.spin_limit = spin_limit();
     if (pr->edge_weight) { P.w = pr->edge_weight; P.w_mul = 1; }
@@ -1707,9 +1706,13 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
         const long long n_gw = grad_w ? (long long)R * N : 0, n_slots = slots * L * L;
         long long blocks = ((n_gw > n_slots ? n_gw : n_slots) + 255) / 256;
         if (blocks > 16384) blocks = 16384;
-        hipLaunchKernelGGL(mrf_bwd_clear, dim3((unsigned)blocks), dim3(256), 0, st, grad_w, n_gw, gvslots, n_slots);
+        hipLaunchKernelGGL(mrf_bwd_clear, dim3((unsigned)blocks), dim3(256), 0, st, grad_w, n_gw, gvslots, n_slots, scal,
+                           (int *)(ws + kFaultOffset), pr->edge_weight_scalar);
         const hipError_t e_ = hipGetLastError();
         if (e_ != hipSuccess) return hip_fail(e_, "mrf_bwd_clear");
+    } else {
+        const hipError_t e_ = init_header(workspace, pr->edge_weight_scalar, st);
+        if (e_ != hipSuccess) return hip_fail(e_, "init_header");
     }
     // Per-edge tables: the sweeps store the node gradients of as many iterations as the workspace has room for, and
     // mrf_bwd_edge_tables forms the tables' gradient from them.  mrf_bwd_sweep, which adds to the tables itself, keeps TRW
@@ -2027,7 +2030,7 @@ static int energy_launch(const mrf_problem *prob, const uint8_t *labels, double 
     E.w_scalar = prob->edge_weight_scalar;
     hipLaunchKernelGGL(mrf_energy_partial, dim3((unsigned)blocks, (unsigned)prob->B), dim3(256), 0, st, E);
     { const hipError_t e_ = hipGetLastError(); if (e_ != hipSuccess) return hip_fail(e_, "mrf_energy_partial"); }
-    hipLaunchKernelGGL(mrf_sum_partials, dim3((unsigned)prob->B), dim3(64), 0, st, (const double *)E.partial, (int)blocks,
+    hipLaunchKernelGGL(mrf_sum_partials, dim3((unsigned)prob->B), dim3(1024), 0, st, (const double *)E.partial, (int)blocks,
                        energy, (const long long *)nullptr);
     { const hipError_t e_ = hipGetLastError(); if (e_ != hipSuccess) return hip_fail(e_, "mrf_sum_partials"); }
     return MRF_OK;
@@ -2123,9 +2126,13 @@ static int softmin_loss(int64_t n_pixels, int32_t L, const float *cost, const fl
     { const hipError_t e_ = hipGetLastError(); if (e_ != hipSuccess) return hip_fail(e_, "mrf_softmin_l1 count"); }
     long long blocks = (n_pixels + 3) / 4;
     if (blocks > MRF_HEAD_BLOCKS) blocks = MRF_HEAD_BLOCKS;
-    hipLaunchKernelGGL(mrf_softmin_l1_kernel, dim3((unsigned)blocks), dim3(256), 0, st, Q);
+    const int slots = (L + 63) / 64;
+    if (slots == 1) hipLaunchKernelGGL(mrf_softmin_l1_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, Q);
+    else if (slots == 2) hipLaunchKernelGGL(mrf_softmin_l1_kernel<2>, dim3((unsigned)blocks), dim3(256), 0, st, Q);
+    else if (slots == 3) hipLaunchKernelGGL(mrf_softmin_l1_kernel<3>, dim3((unsigned)blocks), dim3(256), 0, st, Q);
+    else hipLaunchKernelGGL(mrf_softmin_l1_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, st, Q);
     { const hipError_t e_ = hipGetLastError(); if (e_ != hipSuccess) return hip_fail(e_, "mrf_softmin_l1_kernel"); }
-    hipLaunchKernelGGL(mrf_sum_partials, dim3(1), dim3(64), 0, st, (const double *)Q.partial, (int)blocks, loss,
+    hipLaunchKernelGGL(mrf_sum_partials, dim3(1), dim3(1024), 0, st, (const double *)Q.partial, (int)blocks, loss,
                        (const long long *)Q.count);
     { const hipError_t e_ = hipGetLastError(); if (e_ != hipSuccess) return hip_fail(e_, "mrf_sum_partials"); }
     return MRF_OK;

@@ -261,9 +261,10 @@ __global__ void __launch_bounds__(256) mrf_reduce_slots(double *buf, float *dst,
 }
 
 // What a backward call sets to zero before its sweeps: the edge-weight gradient and the V-gradient slots its
-// sweeps add to.
-__global__ void __launch_bounds__(256) mrf_bwd_clear(float *gw, long long n_gw, double *slots, long long n_slots)
+// sweeps add to.  Writes the workspace's header as well (mrf_init_header): a launch less.
+__global__ void __launch_bounds__(256) mrf_bwd_clear(float *gw, long long n_gw, double *slots, long long n_slots, float *scalar, int *fault, float w)
 {
+    if (threadIdx.x == 0 && blockIdx.x == 0) { *scalar = w; *fault = 0; }
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x, stride = (long long)gridDim.x * blockDim.x;
     for (long long e = t; e < n_gw; e += stride) gw[e] = 0.0f;
     for (long long e = t; e < n_slots; e += stride) slots[e] = 0.0;

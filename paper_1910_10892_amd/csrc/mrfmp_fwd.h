@@ -52,13 +52,14 @@ struct MrfFwdParams {
     const float *Te;                       // [R][N][L][L] pairwise potentials per edge (mrf_fwd_sweep_edge), or NULL
     // per swept direction r: the message arrays that enter h, in summation order.  The first
     // n_pre[r] are added before this direction's own running message, the rest after it.
-    signed char src_dir[MRF_MAXR][MRF_MAXR];
-    signed char n_pre[MRF_MAXR], n_src[MRF_MAXR];
-    signed char rm_slot[MRF_MAXR];         // position of r^- in src_dir[r], or -1 (term absent / still 0)
+    // (whole words: those come through the scalar cache, a byte takes a vector load from memory that no cache holds yet)
+    int src_dir[MRF_MAXR][MRF_MAXR];
+    int n_pre[MRF_MAXR], n_src[MRF_MAXR];
+    int rm_slot[MRF_MAXR];                 // position of r^- in src_dir[r], or -1 (term absent / still 0)
     int NW;                                // wavefronts per workgroup = ceil(L / MCH)
     int *fault;                            // launch-wide word raised when a wait between wavefronts is given up (mrf_wait_turn)
     int spin_limit;                        // microseconds after which a wait is given up
-    signed char unary_slab[MRF_MAXR];      // direction r reads its lambda-independent start term at
+    int unary_slab[MRF_MAXR];              // direction r reads its lambda-independent start term at
                                            // unary + unary_slab[r] * N * L (0 unless mrf_isgmr_presum prepared them)
     int sgm_std;                           // standard single-pass SGM (Eq. sgm_old): the message carries the node's own
                                            // unary, m^r_i = theta_i + min_mu (m^r_{i-r} + theta_{i-r,i}); mrf_fwd_sweep only
@@ -3391,7 +3392,7 @@ __global__ void __launch_bounds__(256) mrf_fwd_sweep_packed(const MrfFwdParams P
     const int nstep = dh * P.g.W + dw;
     int y0 = 0, x0 = 0, len = 0, head = 0;
     if (act_seg) {
-        const int b = (int)(sl / nsc);
+        const int b = sl < nsc ? 0 : (int)(sl / nsc);
         mrf_geom_head(P.g.H, P.g.W, dh, dw, sl - (unsigned)b * nsc, y0, x0, len);
         head = (b * P.g.H + y0) * P.g.W + x0;
     }
@@ -3796,7 +3797,7 @@ __global__ void __launch_bounds__(64) mrf_fwd_sweep_narrow(const MrfFwdParams P)
     const int nstep = dh * P.g.W + dw;
     int y0 = 0, x0 = 0, len = 0, head = 0;
     if (act_seg) {
-        const int b = (int)(sl / nsc);
+        const int b = sl < nsc ? 0 : (int)(sl / nsc);
         mrf_geom_head(P.g.H, P.g.W, dh, dw, sl - (unsigned)b * nsc, y0, x0, len);
         head = (b * P.g.H + y0) * P.g.W + x0;
     }

@@ -77,13 +77,26 @@ __global__ void __launch_bounds__(256) mrf_energy_partial(const MrfEnergyParams 
 
 // out[b] = scale * sum of partial[b][0..n) in index order; one workgroup per b.
 // scale_from: if not NULL, scale = 1 / max(*scale_from, 1) (a count kept on the device)
-__global__ void __launch_bounds__(64) mrf_sum_partials(const double *partial, int n, double *out, const long long *scale_from)
+__global__ void __launch_bounds__(1024) mrf_sum_partials(const double *partial, int n, double *out, const long long *scale_from)
 {
+    static_assert(MRF_HEAD_BLOCKS % 1024 == 0, "a thread's partials");
+    __shared__ double waves[16];
     const int b = blockIdx.x;
+    double x[MRF_HEAD_BLOCKS / 1024];
+#pragma unroll
+    for (int i = 0; i < MRF_HEAD_BLOCKS / 1024; ++i) {
+        const int k = (int)threadIdx.x + 1024 * i;
+        x[i] = k < n ? partial[(size_t)b * n + k] : 0.0;
+    }
     double v = 0.0;
-    for (int k = threadIdx.x; k < n; k += 64) v += partial[(size_t)b * n + k];
+#pragma unroll
+    for (int i = 0; i < MRF_HEAD_BLOCKS / 1024; ++i) v += x[i];
     v = mrf_wave_sum_f64(v);
+    if ((threadIdx.x & 63) == 0) waves[threadIdx.x >> 6] = v;
+    __syncthreads();
     if (threadIdx.x == 0) {
+        v = 0.0;
+        for (int w = 0; w < 16; ++w) v += waves[w];
         if (scale_from) {
             const long long c = *scale_from;
             v = v / (double)(c > 0 ? c : 1);
@@ -138,6 +151,9 @@ __global__ void __launch_bounds__(64) mrf_count_mask_final(const MrfLossParams P
 // One wavefront per pixel, lanes over labels (label = lane + 64 s).
 //   f = exp(-(c - cmin)) / sum, d = sum_lambda lambda f(lambda),
 //   d loss / d c(lambda) = sign(d - g) / n * (-f(lambda)) (lambda - d)
+// LP label slots per lane: with four for any label count two of them did nothing at 96 labels but took their exponentials'
+// and double products' time (256 x 512 pixels 54 -> 44 us).
+template <int LP>
 __global__ void __launch_bounds__(256) mrf_softmin_l1_kernel(const MrfLossParams P)
 {
     __shared__ double scratch[4];
@@ -148,19 +164,31 @@ __global__ void __launch_bounds__(256) mrf_softmin_l1_kernel(const MrfLossParams
     const long long cnt = *P.count;
     const double inv_n = 1.0 / (double)(cnt > 0 ? cnt : 1);
     double acc = 0.0;                    // this wavefront's sum of |d - g| (same value in every lane)
+    float next[LP], target = 0.0f;
+    int mask = 1;
+    const auto fetch = [&](long long i) {
+#pragma unroll
+        for (int s = 0; s < LP; ++s) next[s] = lane + 64 * s < L ? P.cost[(size_t)i * L + lane + 64 * s] : INFINITY;
+        target = P.target[i];
+        if (P.mask) mask = P.mask[i];
+    };
+    if (wave < P.N) fetch(wave);
     for (long long i = wave; i < P.N; i += nwaves) {
-        float c[4];
+        float c[LP];
         float mn = INFINITY;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int lam = lane + 64 * s;
-            c[s] = lam < L ? P.cost[(size_t)i * L + lam] : INFINITY;
+        for (int s = 0; s < LP; ++s) {
+            c[s] = next[s];
             mn = fminf(mn, c[s]);
         }
+        const double g = (double)target;
+        const bool counts = mask != 0;
+        // (the next pixel's costs are on their way while this one is worked on)
+        if (i + nwaves < P.N) fetch(i + nwaves);
         mn = mrf_wave_min(mn);
-        double e[4], se = 0.0, sle = 0.0;
+        double e[LP], se = 0.0, sle = 0.0;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < LP; ++s) {
             const int lam = lane + 64 * s;
             // (the exponential in single precision, about 1e-7 relative; the sums below in double)
             e[s] = lam < L ? (double)expf(mn - c[s]) : 0.0;
@@ -170,8 +198,6 @@ __global__ void __launch_bounds__(256) mrf_softmin_l1_kernel(const MrfLossParams
         se = mrf_wave_sum_f64(se);
         sle = mrf_wave_sum_f64(sle);
         const double d = sle / se;
-        const double g = (double)P.target[i];
-        const bool counts = P.mask ? P.mask[i] != 0 : true;
         const double diff = d - g;
         // per-pixel loss l(d - g) and its slope: |x| and sign(x), or for smooth L1 x^2 / (2 beta) and
         // x / beta inside |x| < beta, |x| - beta / 2 and sign(x) outside
@@ -182,7 +208,7 @@ __global__ void __launch_bounds__(256) mrf_softmin_l1_kernel(const MrfLossParams
             const double sgn = counts ? (small ? diff / P.beta : (diff > 0.0 ? 1.0 : (diff < 0.0 ? -1.0 : 0.0))) : 0.0;
             const double k = sgn * inv_n / se;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < LP; ++s) {
                 const int lam = lane + 64 * s;
                 if (lam < L) P.grad_cost[(size_t)i * L + lam] = (float)(-k * e[s] * ((double)lam - d));
             }
