@@ -340,6 +340,32 @@ __device__ inline float mrf_wave_min(float v)
     return r;
 }
 
+// the same in two parts with something else between them
+__device__ inline void mrf_wave_min_first(float &v)
+{
+    asm("s_nop 1\n\t"
+        "v_min_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf"
+        : "+v"(v));
+}
+__device__ inline float mrf_wave_min_rest(float v)
+{
+    float r;
+    asm("s_nop 1\n\t"
+        "v_min_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_f32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_f32_dpp %1, %1, %1 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_readlane_b32 %0, %1, 63"
+        : "=s"(r), "+v"(v));
+    return r;
+}
+
 // sum over the 64 lanes in a fixed tree order, returned to every lane
 __device__ inline double mrf_wave_sum_f64(double v)
 {

@@ -2451,13 +2451,18 @@ mrf_fwd_sweep_window_split(const MrfFwdParams P)
 // - nothing waits for its own writes, and the wave-wide minimum of h runs while the neighbours are on their way,
 // - value wavefronts meet twice without waiting twice: a flag says that a wavefront's h is in the ring (needed for the
 //   neighbours), a post carries its minimum (needed behind the window).  The hardware barrier would also wait for the others.
+//   Who looks too early looks again, a whole trip through LDS: the wavefronts are some tens of clocks apart, so flags and neighbours
+//   are read half way through the minimum and not right behind the own h, and the posts half way through the window
+//   (256 x 256, 256 labels, window 16, K = 10 5.48 -> 5.17 ms; window 8, K = 2 1.06 -> 1.00; 200 x 300, 128 labels, 8 directions, K = 2 1.46 ->
+//   1.41).
 // LDS executes a wavefront's operations in order, so whoever sees a flag, a post or a counter also sees what that wavefront
 // wrote before it.  A value wavefront is at most one step ahead of the slowest, whose flag it needs: posts alternate between
 // two sets.  The loader fills a slot of the h ring's step once the index wavefronts have left it (NR steps back) and its own
 // once the value wavefronts have (NRL steps back); no wait can depend on itself.
 // TRWP, 256 x 256, 256 labels, window 16, K = 10: sweeps 8.27 ms with index wavefronts alone beside the values and every neighbour
-// read by itself, now 5.8; window 8, K = 2: 1.32 ms (mrf_fwd_sweep_window_duo), now 1.03.  What is left: a quarter of the step is the
-// value wavefronts waiting for each other (K = 2: 1.16 ms, 0.93 without looking at flags and posts).
+// read by itself, now 5.2; window 8, K = 2: 1.32 ms (mrf_fwd_sweep_window_duo), now 1.00.  What is left: a part of the step is the
+// value wavefronts waiting for each other (K = 2, before the looks were moved: 1.16 ms, 0.93 without looking at flags and posts), the rest
+// vector issue: 934 instructions of twelve wavefronts per node are 934 clocks of the four SIMDs.
 // (four wavefronts per SIMD with four beside the values, so that two scanlines share a compute unit)
 template <int RMAX, int D, bool TRWP, int TW, int NI>
 __global__ void __launch_bounds__(64 * (4 + NI), NI <= 4 ? 4 : 3)
@@ -2612,7 +2617,7 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     post(&hflag[wv], n);
                     mrf_wave_lds_fence();
-                    // one batch of reads: who has written h, the neighbours; the loader's counter, the next node's values
+                    // the loader's counter and the next node's values; then, in one batch, who has written h and the neighbours
                     float lo[QD > 0 ? QD + 4 : TW], hi[QD > 0 ? QD + 4 : TW];
                     int4 fl;
                     const auto neighbours = [&]() {
@@ -2643,12 +2648,16 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                             }
                         }
                     };
-                    neighbours();
                     const int seen = __hip_atomic_load(&loaded, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                     fetch((u + 1) % NRL, (u + 1) % NR);
                     __builtin_amdgcn_sched_barrier(0);
-                    float hmin = mrf_wave_min(v);
+                    float vm = v;
+                    mrf_wave_min_first(vm);
+                    __builtin_amdgcn_sched_barrier(0);
+                    neighbours();
+                    __builtin_amdgcn_sched_barrier(0);
+                    float hmin = mrf_wave_min_rest(vm);
                     post_min(hmx, n, hmin);
                     __builtin_amdgcn_sched_barrier(0);
                     const auto absent = [&]() { return __builtin_amdgcn_readfirstlane(min(min(fl.x, fl.y), min(fl.z, fl.w))) < n; };
@@ -2661,12 +2670,12 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                         } while (absent());
                     }
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                    read_posts(hmx, n);
-                    __builtin_amdgcn_sched_barrier(0);
                     // window: the two candidates at a distance share f, and a correctly rounded fma is non-decreasing in its
                     // addend, so the smaller of the two comes from the smaller h
                     float W;
                     if constexpr (QD == 0) {
+                        read_posts(hmx, n);
+                        __builtin_amdgcn_sched_barrier(0);
                         W = __builtin_fmaf(w, f[0], v);
 #pragma unroll
                         for (int d = 1; d < TW; ++d) W = mrf_min(W, __builtin_fmaf(w, f[d], mrf_min(lo[d], hi[d])));
@@ -2674,6 +2683,11 @@ mrf_fwd_sweep_window_squad(const MrfFwdParams P)
                         float x[4];
 #pragma unroll
                         for (int s = 0; s < 4; ++s) {
+                            if (s == 2) {
+                                __builtin_amdgcn_sched_barrier(0);
+                                read_posts(hmx, n);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
                             float dl[QD];
 #pragma unroll
                             for (int e = 0; e < QD; ++e) dl[e] = __builtin_fmaf(w, f[e], mrf_min(lo[s - e + QD], hi[s + e]));
