@@ -1580,7 +1580,7 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
     // label slot then fit the 8-bit offsets of ds_read2_b32 and need no address arithmetic.
     struct Shared {
         float ring[NR][HB];
-        float ringw[NR], ringhm[NR];
+        alignas(16) float2 ringwh[NR];            // weight and minimum of h (one write of the value wavefront: 256 x 512, 96 labels 2.56 -> 2.54 ms)
         float ftab[TW + 1];
         int produced;                             // last step published
         int loaded;                               // last step the loader has published
@@ -1591,8 +1591,7 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
     };
     __shared__ Shared sm;
     auto &ring = sm.ring;
-    auto &ringw = sm.ringw;
-    auto &ringhm = sm.ringhm;
+    auto &ringwh = sm.ringwh;
     auto &ftab = sm.ftab;
     int &produced = sm.produced;
     int &loaded = sm.loaded;
@@ -1668,8 +1667,8 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
             const int slot = n & (NR - 1);
             const float *hbuf = &ring[slot][TW];
-            const float wgt = ringw[slot];
-            const float hmin = ringhm[slot];
+            const float2 wh = ringwh[slot];
+            const float wgt = wh.x, hmin = wh.y;
             const long long ol = (long long)n * istep_l;
             // the window's h in one batch of LDS reads behind the two words above (entries of labels
             // >= L and the padding hold +inf, so no lane needs a condition)
@@ -1991,9 +1990,8 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
             // LDS executes a wavefront's operations in order: whoever sees the counter also sees the
             // node's ring entries written before it, so no wait is needed in between
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            // (every lane writes the same three words: no divergent branch in the node step)
-            ringw[slot] = wgt;
-            ringhm[slot] = hmin;
+            // (every lane writes the same words: no divergent branch in the node step)
+            ringwh[slot] = make_float2(wgt, hmin);
             __hip_atomic_store(&produced, nn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
@@ -2138,10 +2136,9 @@ mrf_fwd_sweep_window_duo(const MrfFwdParams P)
             // LDS executes a wavefront's operations in order: whoever sees the counter also sees the
             // node's ring entries written before it, so no wait is needed in between
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            // (every lane writes the same three words: no divergent branch in the node step)
+            // (every lane writes the same words: no divergent branch in the node step)
             if (!past) {
-                ringw[slot] = wgt;
-                ringhm[slot] = hmin;
+                ringwh[slot] = make_float2(wgt, hmin);
                 __hip_atomic_store(&produced, nn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
