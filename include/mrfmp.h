@@ -297,7 +297,7 @@ int mrf_set_sweep_events(void *start_event, void *stop_event);
  *           5 = always, several scanlines per workgroup; 3 = never, one wavefront with 64-bit offsets (what arrays
  *           beyond 32-bit offsets get), 6 = the same with two index wavefronts (what they get in launches of few
  *           scanlines).  Beyond 32-bit offsets 2 is as 6, and 4 and 5 as 0.
- *   knob 12: in the sweep of knob 6, sum the lanes of the most popular scatter target in registers
+ *   knob 12: in the sweep of knob 6, words of their own for the lanes of the most popular scatter target
  *           (truncated models): 0 = by launch shape, 1 = never, 2 = whenever V is not a dense table
  *   knob 13: three scanlines per wavefront (segments of 21 lanes) in the sweeps of knob 3 for 17..21 labels:
  *           0 = by launch size, 1 = never (two per wavefront), 2 = always
