@@ -756,7 +756,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
     Kept kept = {};
     double *gvl = gvacc + (GVT ? jw * L * L : 0);
     int chain_seen = -1;
-    const bool want_w = (P.gw || GVT) && !GS;
+    const bool want_w = P.gw && !GS;
 
     auto turn = [&](In &in_, int it, auto parity) {
         constexpr int par = decltype(parity)::value;

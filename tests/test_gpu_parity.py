@@ -1308,6 +1308,35 @@ def test_optional_outputs_may_be_null(oracle):
         np.testing.assert_allclose(g.grad_unary.cpu().numpy(), ref.grad_unary, rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("algo,B,H,W,L", [("isgmr", 1, 6, 9, 16), ("trwp", 1, 7, 8, 21), ("trwp", 1, 5, 9, 40), ("isgmr", 1, 6, 5, 48),
+                                          ("trwp", 1, 6, 7, 96), ("isgmr", 1, 4, 6, 100), ("trwp", 1, 4, 5, 200), ("trwp", 60, 6, 5, 12)])
+@pytest.mark.parametrize("per_edge", [True, False])
+def test_each_gradient_alone(oracle, algo, B, H, W, L, per_edge):
+    """Every combination of the optional gradients, with a scalar weight and with one per edge, on a workspace that holds garbage
+    when the backward pass starts: its header, what the sweeps add to and what nobody asked for."""
+    from gpu_harness import GpuProblem
+    print("case each gradient alone", algo, B, H, W, L, per_edge, flush=True)
+    pr = random_problem(820 + L, algo, B, H, W, L, DIRS4, 2, symmetric=False, per_edge=per_edge, rho=np.linspace(0.3, 0.9, 4))
+    pr.grad_cost = (pr.grad_cost * 0.2).astype(np.float32)
+    g = GpuProblem(pr)
+    g.forward()
+    f = g.results(False)
+    check_forward(f, oracle_forward(oracle, pr))
+    ref = oracle_backward(oracle, pr, f.p, f.q, np.float64)
+    for want_w, want_V in ((True, True), (True, False), (False, True), (False, False)):
+        for x in (g.grad_unary, g.grad_edge_weight, g.grad_pairwise):
+            x.fill_(float("nan"))
+        g.workspace.fill_(0xFF)
+        g.backward(want_w=want_w, want_V=want_V)
+        got = g.results()
+        check_grad("grad_unary", got.grad_unary, None, ref.grad_unary)
+        for name, want in (("grad_edge_weight", want_w), ("grad_pairwise", want_V)):
+            if want:
+                check_grad(name, getattr(got, name), None, getattr(ref, name))
+            else:
+                assert np.isnan(getattr(got, name)).all(), name
+
+
 def test_backward_is_reproducible_run_to_run():
     from gpu_harness import GpuProblem
     print("case reproducible", flush=True)
