@@ -649,21 +649,56 @@ int pick_mch(int L, int LP, bool many_sources, long long blocks)
     return best;
 }
 
+// nodes of the longest scanline of direction r
+long long longest_scanline(const MrfGeom &g, int r)
+{
+    const int ah = mrf_iabs(g.dh[r]), aw = mrf_iabs(g.dw[r]);
+    const int down = ah ? (g.H + ah - 1) / ah : INT_MAX, across = aw ? (g.W + aw - 1) / aw : INT_MAX;
+    return down < across ? down : across;
+}
+
 // Whether mrf_fwd_sweep_halves is ahead of the better of the other two dense sweeps (33..128 labels; forward pass, K = 2 unless
-// noted, others / halves).  On scanlines of more than 40 nodes nearly always:
-// - up to 64 labels: TRWP 64 x 64, 4 directions, 48 labels 0.350 / 0.325 ms, 128 x 128 36 labels 0.668 / 0.597, 64 labels 0.703 /
-//   0.600, 8 directions 1.47 / 1.32, 256 x 512 64 labels 2.10 / 1.81, 6 x 256 x 256 3.15 / 1.84; ISGMR 128 x 128 48 labels 188 / 180 us, 256 x
-//   512 64 labels 0.92 / 0.69 ms, 4 x 512 x 512, K = 1, 64 labels 2.64 / 2.28.  Behind where TRWP fills the SIMDs: 4 x 512 x 512, K = 1
-//   (2,048 scanlines) 36 labels 2.79 / 2.88, 64 labels 2.93 / 3.03
-// - 65..128 labels: 300 x 600, 65 labels, TRWP 4.96 / 3.04; 4 x 512 x 512, K = 1, 100 labels TRWP 11.8 / 8.3, ISGMR 8.9 / 7.7; 128 x 128,
-//   100 labels, ISGMR, 8 directions 0.78 / 0.68; 128 x 256, 16 directions 2.34 / 2.27
-// On short ones its table in LDS is a good part of a launch (4 images of 16 x 16, ISGMR, K = 3: 36 labels 44 / 49 us, 128 labels level; 16
-// images, TRWP, 36 labels 175 / 193; 28 x 40, K = 3, level up to 64 labels): there as many scanlines as share its cost decide,
-// and 65..96 labels, where the others leave lanes idle (28 x 40, 80 labels, TRWP 0.50 / 0.37 ms).
+// noted, others / halves in ms, or halves over others).  Its node step is the shorter one nearly everywhere, its start the longer one (a
+// table in LDS): so on grids with a side of more than 40 the mean length of the launch's scanlines decides, and the longest one where the
+// launch lasts about as long as that takes by itself.
+// - up to 64 labels, TRWP, up to four arrays, one direction; 16 / 24 / 40 / 64 nodes per scanline: 512 scanlines 1.10 / 1.05 / 1.01 / 1.0;
+//   1,024, 36 labels 1.0 / 0.98 / 0.99 / 0.97, 64 labels 0.93 / 0.91 / 0.90 / 0.86; 3,072 1.06 / 1.02 / 0.98 / 0.91; 4,096 1.09 / 1.06 / 1.04 / 0.98.
+//   1,536 are as many as the machine holds of it at once: 0.83 / 0.83 / 0.82 / 0.75, with 8 nodes 0.93; 1,792 1.02 / 1.01 / 0.98 / 0.92.  2,048
+//   are as many as it holds of the others, which take two wavefronts for each from there on: 1.2 / 1.18 / 1.15 / 1.11; 2,032 and 2,052
+//   scanlines of 64 nodes 0.94 and 0.91; 8 x 512 x 512 5.39 / 4.80
+// - the same with more arrays, 8 directions, K = 1: 8 x 256 x 256, 40 labels 3.04 / 2.81, 12 x 256 x 256 4.58 / 3.71, 64 labels 4.84 / 4.02, 4 x
+//   512 x 512 6.36 / 5.80; 32 x 64 x 64 level; 16 directions 7.71 / 6.74
+// - up to 64 labels, ISGMR: 256 x 256, 40 labels 0.461 / 0.386, 384 x 384 0.860 / 0.647, 512 x 512 level, 600 x 600 2.21 / 1.64, 64 labels 2.24 /
+//   1.66; images of 48 x 48, 8,064 scanlines 0.95, 8 directions 0.98; 64 images of 20 x 64 level, 8 directions (mean 20) 0.85 / 0.89; 30 of 8 x
+//   400 0.67 / 0.56, 8 directions 1.11 / 1.27; 50 of 5 x 41 0.090 / 0.098
+// - 65..96 labels: 0.65 to 0.8 from 24 nodes on, at 8 nodes 72 labels level, 96 labels 0.9; 492 columns of 5 nodes 72 labels 1.07, 96 labels
+//   0.93, diagonals of 5 x 41 0.114 / 0.178; 50 images of 5 x 41, ISGMR, 8 directions 0.351 / 0.362; 30 of 8 x 400, TRWP, diagonals 2.55 / 1.45
+// - 97..128 labels, TRWP: 8 / 16 / 24 / 64 nodes 1.15 / 1.0 / 0.92 / 0.83, whatever the number of scanlines.  ISGMR, where a compute unit holds
+//   two workgroups: images of 48 x 48, 960 / 3,072 / 8,064 scanlines 0.91 / 1.02 / 1.03, of 64 x 64 0.89 / 0.97 / 1.0, 8 directions (mean 43) 764 /
+//   3,056 / 9,168 scanlines 0.94 / 0.96 / 1.03, of 96 x 96 8,064 scanlines 0.96; 4 of 16 x 1000 2.30 / 1.61, 8 directions 2.41 / 2.86
+// On smaller grids as many scanlines as share the cost of its table decide (4 images of 16 x 16, ISGMR, K = 3: 36 labels 44 / 49 us, 128
+// labels level; 16 images, TRWP, 36 labels 175 / 193; 28 x 40, K = 3, level up to 64 labels), and 65..96 labels, where the others leave lanes
+// idle (28 x 40, 80 labels, TRWP 0.50 / 0.37 ms).
 bool chunk_minima_ahead(const MrfFwdParams &P, int algo, int rmax, long long blocks)
 {
     const int L = P.g.L;
-    if (P.g.H > 40 || P.g.W > 40) return L > 64 || algo != MRF_TRWP || blocks < 2048;
+    const bool trwp = algo == MRF_TRWP;
+    if (P.g.H > 40 || P.g.W > 40) {
+        const long long nodes = P.g.N * P.r_count, mean = nodes / blocks;
+        long long longest = 0;
+        for (int r = P.r_first; r < P.r_first + P.r_count; ++r) {
+            const long long len = longest_scanline(P.g, r);
+            longest = len > longest ? len : longest;
+        }
+        const long long beside = L > 96 ? 256 : (longest > 64 ? 1024 : 512);      // scanlines that the machine sweeps beside the longest
+        if (!trwp && longest > 40 && longest * beside >= nodes) return true;
+        if (L > 96) return mean >= (trwp ? 16 : (blocks <= 1024 ? 24 : (blocks <= 4096 ? 40 : 56)));
+        if (L > 64) return mean >= (trwp ? 5 : 7) || (trwp && blocks >= 4096);
+        if (!trwp || rmax > 4) return mean >= 24;
+        if (blocks == 2048) return false;
+        if (blocks <= 512 || blocks > 3072) return mean >= (blocks <= 512 ? 40 : 48);
+        return mean >= (blocks > 1024 && blocks <= 1536 ? 8 : (L > 48 && blocks < 2048 ? 16 : 24));
+    }
     const bool middling = blocks > 512 && blocks < 1024;
     if (L <= 64) {
         if (rmax > 4) return blocks > 512;
@@ -694,11 +729,7 @@ hipError_t run_dense(MrfFwdParams &P, int algo, long long blocks, hipStream_t st
         // directions, two / one, 2 x 256 x 512, K = 1 3.58 / 3.01, but 256 x 512, K = 5, whose diagonals are 767 scanlines, half of them short,
         // 10.6 / 10.8.  ISGMR level to 2 % ahead.)
         long long at_once = 0;
-        for (int r = P.r_first; r < P.r_first + P.r_count; ++r) {
-            const int ah = mrf_iabs(P.g.dh[r]), aw = mrf_iabs(P.g.dw[r]);
-            const int down = ah ? (P.g.H + ah - 1) / ah : INT_MAX, across = aw ? (P.g.W + aw - 1) / aw : INT_MAX;
-            at_once += P.g.N / (down < across ? down : across);
-        }
+        for (int r = P.r_first; r < P.r_first + P.r_count; ++r) at_once += P.g.N / longest_scanline(P.g, r);
         const bool crowded = nw == 3 && at_once > 512;
 #define MRF_HCASE(n) \
         if (nw == n && rmax == 4) return launch_fwd_halves<n, 4, 4>(P, algo, blocks, st); \

@@ -355,13 +355,20 @@ def test_which_dense_sweep_runs(oracle, algo, B, H, W, L, dirs, halves):
 
 
 @pytest.mark.parametrize("algo,B,H,W,L,dirs,launch", [
-    ("trwp", 1, 41, 6, 40, DIRS4, "halves<2,4,4"), ("trwp", 49, 5, 41, 33, DIRS4, "halves<2,4,4"), ("trwp", 50, 5, 41, 33, DIRS4, ""),
-    ("isgmr", 60, 5, 41, 64, DIRS4, "halves<2,4,4"), ("isgmr", 3, 41, 6, 100, DIRS8, "halves<4,4,4"),
-    ("trwp", 12, 5, 42, 70, DIRS4, "halves<3,4,4"), ("trwp", 13, 5, 42, 70, DIRS4, "halves<3,4,2"), ("trwp", 13, 5, 42, 96, DIRS8, "halves<3,8,1"),
+    ("trwp", 1, 41, 6, 40, DIRS4, "halves<2,4,4"), ("trwp", 1, 39, 41, 40, DIRS4, ""), ("trwp", 49, 5, 41, 33, DIRS4, ""), ("trwp", 50, 5, 41, 33, DIRS4, ""),
+    ("trwp", 9, 24, 57, 40, DIRS4, "halves<2,4,4"), ("trwp", 9, 23, 57, 48, DIRS4, ""), ("trwp", 9, 16, 57, 49, DIRS4, "halves<2,4,4"), ("trwp", 9, 15, 57, 49, DIRS4, ""),
+    ("trwp", 25, 8, 41, 36, DIRS4, "halves<2,4,4"), ("trwp", 25, 7, 41, 36, DIRS4, ""), ("trwp", 33, 8, 47, 36, DIRS4, ""),
+    ("trwp", 32, 24, 64, 33, DIRS4, ""), ("trwp", 32, 24, 65, 33, DIRS4, "halves<2,4,4"), ("trwp", 64, 24, 49, 33, DIRS4, ""),
+    ("trwp", 2, 47, 60, 40, DIRS8, "halves<2,8,2"), ("trwp", 2, 30, 60, 40, DIRS8, ""), ("trwp", 20, 47, 60, 33, DIRS8, "halves<2,8,2"),
+    ("isgmr", 60, 5, 41, 64, DIRS4, ""), ("isgmr", 12, 5, 41, 64, DIRS4, "halves<2,4,4"), ("isgmr", 1, 48, 41, 36, DIRS8, "halves<2,4,4"),
+    ("isgmr", 3, 41, 6, 100, DIRS8, "halves<4,4,4"), ("isgmr", 6, 41, 6, 100, DIRS8, ""), ("isgmr", 12, 48, 41, 97, DIRS4, "halves<4,4,4"),
+    ("isgmr", 7, 48, 41, 97, DIRS8, ""), ("trwp", 1, 16, 41, 128, DIRS4, "halves<4,4,4"), ("trwp", 1, 15, 41, 128, DIRS4, ""),
+    ("trwp", 1, 4, 41, 70, DIRS4, ""), ("trwp", 100, 4, 41, 70, DIRS4, "halves<3,4,2"), ("isgmr", 50, 5, 41, 72, DIRS8, ""),
+    ("trwp", 12, 5, 42, 70, DIRS4, "halves<3,4,4"), ("trwp", 13, 5, 42, 70, DIRS4, "halves<3,4,2"), ("trwp", 13, 7, 42, 96, DIRS8, "halves<3,8,1"),
     ("isgmr", 2, 41, 70, 80, DIRS8, "halves<3,4,2")])
 def test_which_dense_sweep_runs_on_long_scanlines(oracle, algo, B, H, W, L, dirs, launch):
-    """The same where the sweep with chunk minima is ahead by the length of the scanlines, and its two depths of prefetch; the last
-    launch of a TRWP pass sweeps the columns or a diagonal."""
+    """The same on grids with a side of more than 40, where the lengths of a launch's scanlines decide, and its two depths of prefetch;
+    the last launch of a TRWP pass sweeps the columns or a diagonal."""
     import paper_1910_10892_amd as mrf
     from gpu_harness import run_gpu
     print("case long scanlines", algo, B, H, W, L, len(dirs), flush=True)
