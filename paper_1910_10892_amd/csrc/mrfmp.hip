@@ -161,8 +161,8 @@ MRF_G(int g_tune_spin_limit, 0); // turns a wait between wavefronts may take: 0 
 MRF_G(int g_tune_pack_idx, 0);   // packed dense sweep divided among four wavefronts: 0 by launch size, 1 never, 2 always, 3 never and 64-bit offsets,
                                  // 4 always and one scanline per wavefront, 5 always and several, 6 as 3 with two index wavefronts
 MRF_G(int g_tune_chain, 0);      // backward sweep with a chain wavefront: 0 auto, 1 never, 2 whenever possible
-MRF_G(int g_tune_chain_hot, 0);  // its pre-reduction of the most popular scatter target: 0 auto, 1 never, 2 whenever V is no dense table
-MRF_G(int g_tune_chain_ni, 0);   // its helpers per scanline: 0 auto, 2, 4, 6, 8
+MRF_G(int g_tune_chain_hot, 0);  // its words for the lanes of the most popular scatter target: 0 auto, 1 never, 2 whenever V is no dense table
+MRF_G(int g_tune_chain_ni, 0);   // its helpers per scanline: 0 auto, 2, 4, 6, 8, 12
 MRF_G(int g_tune_narrow_divided, 0); // narrow backward sweep divided among four wavefronts: 0 by launch size, 1 never, 2 whenever possible
 MRF_G(int g_tune_narrow, 0);     // lanes per scanline of the narrow backward sweep: 0 by launch size, 8, 16, 32; -1: not that sweep
 MRF_G(hipEvent_t g_ev_start, nullptr);
@@ -1572,11 +1572,7 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
         return run_bwd_packed(P, L <= 16 ? 16 : 32, ns, st);
     }
     if (chain) {
-        // truncated models: the chain wavefront sums the lanes of the most popular scatter target
-        // in registers
-        // where LDS throughput, not the latency of the chain, bounds the launch
-        P.hot_label = ((pairwise_kind != MRF_PAIRWISE_DENSE || gv_apart) && !gv && g_tune_chain_hot != 1 &&
-                       (g_tune_chain_hot == 2 || L > 128 || P.total_scanlines > 1024)) ? 1 : 0;
+        P.hot_label = chain_hot ? 1 : 0;      // (what its LDS was sized for)
         if (gv_apart) {
             double *const slots = P.gV;
             P.gV = nullptr; P.gstore = P.gstore_buf;
