@@ -255,6 +255,14 @@ inline size_t chain_lds_cap(long long scanlines)
     return 64 * 1024;
 }
 
+// Whether an image's entries lie beyond what the chain sweep's views reach (node gradients are doubles): then its variant that makes
+// a view per access runs, with six helpers.
+inline bool chain_far(const MrfGeom &g, bool node_gradients)
+{
+    return (long long)g.H * g.W * g.L > MRF_BUF_MOST / (node_gradients ? 2 : 1);
+}
+#define MRF_CHAIN_FAR_HELPERS 6
+
 hipError_t run_bwd_chain(MrfBwdParams &P, int ns, int ni, bool vg, hipStream_t st);
 hipError_t run_bwd_chain_pk(MrfBwdParams &P, int ns, int ni, hipStream_t st);
 hipError_t run_bwd_packed(MrfBwdParams &P, int seg, int ns, hipStream_t st);
@@ -1074,9 +1082,10 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
     const bool gs = edge || (LP <= 2 && P.gstore);        // the helpers store the node gradients (no tables, no V)
     if (gs) vg = true;
     const bool hot = P.hot_label && (gs || !((LP == 1 && gv) || vg));
+    const bool far = chain_far(P.g, gs && !edge);
     note_launch(1, "mrf_bwd_sweep_chain", P.total_scanlines, 64 * (1 + ni), "%d,%d,%d,%d,%s,%s,%s%s", LP, NS, D, ni,
                 (!(LP == 1 && gv) && vg) ? "true" : "false", ((LP == 1 && gv) || gs) ? "true" : "false", hot ? "true" : "false",
-                edge ? ",true" : "");
+                edge ? ",true" : (far ? ",false,true" : ""));
     if (gv && (LP != 1 || P.total_scanlines > grad_slots(P.g.L))) return hipErrorInvalidValue;
     MrfChainParams C;
     memset(&C, 0, sizeof(C));
@@ -1117,6 +1126,22 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
         } \
         hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(64 * (1 + ni)), lds, st, C); \
     } while (0)
+    if (far) {
+        if constexpr (NS >= 4) {
+            if (ni != MRF_CHAIN_FAR_HELPERS || edge) return hipErrorInvalidValue;
+            constexpr int n = MRF_CHAIN_FAR_HELPERS;
+            if constexpr (LP == 1) {
+                if (gv) { MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, false, true, false, false, true>); return hipGetLastError(); }
+            }
+            if constexpr (LP <= 2) {
+                if (gs) { MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, true, true, true, false, true>); return hipGetLastError(); }
+            }
+            if (vg) MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, true, false, false, false, true>);
+            else MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, false, false, (LP >= 3), false, true>);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
 #define MRF_CH(n) \
     if (ni == n) { \
         if constexpr (LP == 1 && n >= 4) { \
@@ -1152,6 +1177,7 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
 hipError_t run_bwd_chain(MrfBwdParams &P, int ns, int ni, bool vg, hipStream_t st)
 {
     const int LP = (P.g.L + 63) / 64;
+    if (ns == 1 && !P.edge && chain_far(P.g, P.gstore != nullptr)) ns = 4;
 #define MRF_CCASE(lp) \
     if (LP == lp && ns == 1) return launch_bwd_chain<lp, 1, (lp <= 2 ? 2 : 1)>(P, ni, vg, st); \
     if (LP == lp && ns == 4) return launch_bwd_chain<lp, 4, (lp <= 2 ? 2 : 1)>(P, ni, vg, st); \
@@ -1470,8 +1496,8 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
         return run_bwd_chain(P, ns, ni, true, st);
     }
     // few scanlines: the node-to-node chain on a wavefront of its own, helpers around it
-    // (its addressing wants a node step times L in 32 bits; with the V gradient, L <= 64, room in LDS and
-    // a slot per workgroup)
+    // (its addressing wants a node step times L in 32 bits, and a variant of its own where an image is beyond that; with the
+    // V gradient, L <= 64, room in LDS and a slot per workgroup)
     bool step_fits = true;
     for (int r = P.r_first; r < P.r_first + P.r_count; ++r) {
         const long long stp = ((long long)mrf_iabs(P.g.dh[r]) * P.g.W + mrf_iabs(P.g.dw[r])) * L;
@@ -1500,16 +1526,19 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     if (!g_tune_chain_ni && gv_apart && (ns == 16 || LP == 1 || P.total_scanlines > 256)) ni = 6;
     if (!g_tune_chain_ni && gv && P.total_scanlines > 384 && ni > 6) ni = 6;   // (the accumulators take LDS)
     const bool vg = P.gw && pairwise_kind == MRF_PAIRWISE_DENSE;
+    const bool far = chain_far(P.g, gv_apart);
+    if (far) ni = MRF_CHAIN_FAR_HELPERS;
     // truncated models: the lanes that go to the most popular scatter target are kept apart
-    const bool chain_hot = (pairwise_kind != MRF_PAIRWISE_DENSE || gv_apart) && !gv && g_tune_chain_hot != 1 &&
-                           (g_tune_chain_hot == 2 || L > 128 || P.total_scanlines > 1024);
+    const bool chain_hot = far ? !gv && (gv_apart || (!vg && LP >= 3))
+                               : (pairwise_kind != MRF_PAIRWISE_DENSE || gv_apart) && !gv && g_tune_chain_hot != 1 &&
+                                     (g_tune_chain_hot == 2 || L > 128 || P.total_scanlines > 1024);
     const auto chain_lds = [&](int helpers) { return mrf_bwd_chain_lds_bytes(LP, helpers, L, chain_hot, gv, !vg && !gv_any); };
     while (ni > 2 && (chain_lds(ni) > chain_lds_cap(P.total_scanlines) ||
                       (gv && P.total_scanlines > grad_slots(L)))) ni = (ni == 12) ? 8 : ni - 2;
     // TRW coefficients or pairwise tables per edge: mrf_bwd_sweep handles them (and is the one
     // sweep that never touches V when no edge-weight gradient is asked for)
     const bool generic = P.rho_e != nullptr || P.force_plain;
-    const bool chain_fits = !generic && step_fits && (long long)P.g.H * P.g.W * L <= MRF_BUF_MOST / (gv_apart ? 2 : 1) && ns <= (LP <= 2 ? 16 : 8) && g_tune_chain != 1 &&
+    const bool chain_fits = !generic && step_fits && !(far && ni != MRF_CHAIN_FAR_HELPERS) && ns <= (LP <= 2 ? 16 : 8) && g_tune_chain != 1 &&
                             (!gv || (LP == 1 && P.total_scanlines <= grad_slots(L))) &&
                             chain_lds(ni) <= chain_lds_cap(P.total_scanlines);
     // (backward pass, chain / the next best layout.  ISGMR, one source array, 4 directions, K = 3: 96 labels 2,048 scanlines 1.65 / 2.10

@@ -532,7 +532,12 @@ struct MrfChainParams {
 // one word (64 lanes of one instruction that meet on a word take 170 clocks more than 64 that do not).  The helpers guess it
 // (as in mrf_bwd_sweep) and send its lanes to eight words of their own by lane, which leaves next to no queue (9
 // clocks); the chain adds the eight up.
-template <int LP, int NS, int D, int NI, bool VG, bool GV, bool HOT, bool EDGE = false>
+// FAR: images whose entries lie beyond 32-bit offsets from the image's first one (more than 2^30, half of that where node
+// gradients are stored): every access makes a view of its node's entries alone, by scalar instructions.  TRWP, backward pass, K = 1, against the
+// sweeps with 64-bit addresses: 1024 x 16640, 64 labels, two directions 11.5 / 19.6 ms; 512 x 8400, 256 labels 7.4 / 16.1; 512 x 16800, 128
+// labels, four directions 16.0 / 40.2, with grad V 36 / 81.  Six helpers; HOT beyond 128 labels and with stored gradients (64 and 128
+// labels without: 12.9 -> 11.5, 18.8 -> 16.0 ms).
+template <int LP, int NS, int D, int NI, bool VG, bool GV, bool HOT, bool EDGE = false, bool FAR = false>
 __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfChainParams P)
 {
     static_assert(D == 1 || D == 2, "sets of registers");
@@ -545,7 +550,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
     constexpr bool GS = GV && VG;            // node gradients stored for mrf_bwd_pairwise_*
     constexpr bool VROW = !VG && !GV;        // first row of V in LDS
     static_assert(!GVT || LP == 1, "V-gradient tables");
-    static_assert(!EDGE || (GS && !HOT), "per-edge tables");
+    static_assert(!EDGE || (GS && !HOT && !FAR), "per-edge tables");
     const int L = P.L;
     // carved in the order of mrf_bwd_chain_lds_bytes
     double *svr = reinterpret_cast<double *>(mrf_bsmem);         // [NR][LH] scatter targets: cleared by pre, chain -> post
@@ -684,7 +689,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
     const int jw = wv - 1, r = P.r_first + ri;
     const bool own_unary = (r == P.unary_dir);
     const bool unary_old = own_unary && !P.unary_init;
-    // views of the image (the host has checked that they fit 32-bit offsets); node n of the scanline lies
+    // views of the image (the host has checked that they fit 32-bit offsets, or taken FAR); node n of the scanline lies
     // at hn + n * step
     const unsigned HW = (unsigned)P.H * (unsigned)P.W, HWL = HW * (unsigned)L, endb = HWL * 4u;
     const size_t ibn = (size_t)((unsigned)b * HW), ib = ibn * (unsigned)L;
@@ -697,11 +702,15 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
     auto vo = [&](int s) { return s < LP - 1 ? lane4 + 256u * (unsigned)s : end4; };
     auto vp = [&](int s) { return s < LP - 1 ? (unsigned)lane + 64u * (unsigned)s : end1; };
     mrf_buf bs[NS];
+    const float *first[NS];                     // FAR: the image in a source
     const int nsrc = P.n_src[ri], src0 = ri * P.src_pitch;
 #pragma unroll
     for (int c = 0; c < NS; ++c) {
-        bs[c] = mrf_buffer(P.src[src0 + c] + ib, c < nsrc ? endb : 0);      // (a slot that is not in use reads zeros)
+        first[c] = P.src[src0 + c] + ib;
+        bs[c] = mrf_buffer(first[c], c < nsrc ? endb : 0);      // (a slot that is not in use reads zeros)
     }
+    // FAR: the n entries of a node alone, or none of them
+    auto only = [&](auto *array, size_t entry, unsigned n, bool any) { return mrf_buffer(array + entry, any ? n * (unsigned)sizeof(*array) : 0u); };
     const mrf_buf bp = mrf_buffer(P.p + dib, HWL), bq = mrf_buffer(P.q + dibn, HW);
     const mrf_buf bgo = mrf_buffer(P.gunary + ib, unary_old ? endb : 0);
     const mrf_buf bw = mrf_buffer(P.w + (P.w_mul ? dibn : 0), P.w_mul ? HW * 4u : 4u);
@@ -717,7 +726,26 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
     auto prefetch = [&](In &d, int it) {
         int n = len - 1 - (jw + it * NI);
         n = n > 0 ? n : 0;
-        const unsigned node = hn + (unsigned)n * step, ob = node * (unsigned)L * 4u;
+        const unsigned node = hn + (unsigned)n * step;
+        if constexpr (FAR) {
+            const size_t e = (size_t)node * (unsigned)L;
+            const mrf_buf vgo = only(P.gunary, ib + e, L, unary_old), vp8 = only(P.p, dib + e, L, true);
+#pragma unroll
+            for (int c = 0; c < NS; ++c) {
+                const mrf_buf v = only(first[c], e, L, c < nsrc);
+#pragma unroll
+                for (int s = 0; s < LP; ++s) d.x[c][s] = mrf_buf_f32s(v, vo(s), 0);
+            }
+#pragma unroll
+            for (int s = 0; s < LP; ++s) {
+                d.gu[s] = mrf_buf_f32s(vgo, vo(s), 0);
+                d.p[s] = (int)__builtin_amdgcn_raw_buffer_load_b8(vp8, vp(s), 0, 0);
+            }
+            d.q = (int)__builtin_amdgcn_raw_buffer_load_b8(only(P.q, dibn + node, 1, true), 0, 0, 0);
+            d.w = GVT ? mrf_buf_f32s(only(P.w, P.w_mul ? dibn + node : 0, 1, true), 0, 0) : 0.0f;
+            return;
+        }
+        const unsigned ob = node * (unsigned)L * 4u;
 #pragma unroll
         for (int s = 0; s < LP; ++s) {
 #pragma unroll
@@ -741,9 +769,10 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
                                   EDGE ? (P.gstore32 ? endb : 0) : (P.gstore ? HWL * 8u : 0));
     // the last node of the scanline has no successor in direction r
     if (jw == 0) {
-        const unsigned last = (hn + (unsigned)(len - 1) * step) * (unsigned)L * 4u;
+        const unsigned at = hn + (unsigned)(len - 1) * step, last = FAR ? 0u : at * (unsigned)L * 4u;
+        const mrf_buf v = FAR ? only(P.S, dib + (size_t)at * (unsigned)L, L, true) : bS;
 #pragma unroll
-        for (int s = 0; s < LP; ++s) store_f32(bS, vo(s), last, 0.0f);
+        for (int s = 0; s < LP; ++s) store_f32(v, vo(s), last, 0.0f);
     }
 
     // what a turn leaves for the next one, where the same node's post stage is
@@ -841,8 +870,9 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
             const int slot = jw + (1 - par) * NI;
             const int n = len - 1 - tp;
             const bool node = it > 0, update = node && n > 0;      // node i has a predecessor: its update is replayed
-            const unsigned on = hn + (unsigned)n * step, oi = on * (unsigned)L * 4u;
+            const unsigned on = hn + (unsigned)(FAR && !node ? 0 : n) * step, oi = on * (unsigned)L * 4u;
             const unsigned oj = oi - step * (unsigned)L * 4u;      // node i - r
+            const size_t fi = FAR ? (size_t)on * (unsigned)L : 0, fj = FAR ? (size_t)(update ? on - step : on) * (unsigned)L : 0;
             double g[LP], sv[LP], V[LP];
 #pragma unroll
             for (int s = 0; s < LP; ++s) {
@@ -864,6 +894,16 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
             }
 #pragma unroll
             for (int s = 0; s < LP; ++s) {
+                if constexpr (FAR) {
+                    store_f32(only(P.S, dib + fj, L, update), vo(s), 0, (float)sv[s]);
+                    if constexpr (GS) {
+                        typedef unsigned u2 __attribute__((ext_vector_type(2)));
+                        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, update ? g[s] : 0.0), only(P.gstore, ib + fi, L, node && P.gstore),
+                                                              s < LP - 1 || in_last ? 2u * vo(s) : MRF_BUF_NONE, 0, 0);
+                    }
+                    store_f32(only(P.gunary, ib + fi, L, node && own_unary), vo(s), 0, (float)(g[s] + kept.th[s]));
+                    continue;
+                }
                 store_f32(bS, vo(s), update ? oj : endb, (float)sv[s]);
                 if constexpr (EDGE) {
                     store_f32(bg, vo(s), node ? oi : endb, update ? (float)g[s] : 0.0f);
@@ -880,7 +920,8 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
                 for (int s = 1; s < LP; ++s) acc = __builtin_fma(g[s], V[s], acc);
                 acc = mrf_wave_sum_mat_f64(acc);
                 // one writer per entry and launch: a no-return atomic is a plain accumulate
-                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32((float)acc, bgw, lane == 0 ? 0u : MRF_BUF_NONE, update ? 4u * on : 4u * HW, 0);
+                if constexpr (FAR) mrf_buf_add_f32(only(P.gw, dibn + on, 1, update), lane == 0 ? 0u : MRF_BUF_NONE, (float)acc);
+                else __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32((float)acc, bgw, lane == 0 ? 0u : MRF_BUF_NONE, update ? 4u * on : 4u * HW, 0);
             }
             if (GVT && update && lane < L) {
                 double *const e = &gvl[__mul24(kept.p[0], L) + lane];

@@ -711,6 +711,60 @@ def test_backward_of_arrays_beyond_32_bit_offsets(algo, L, H, W):
     torch.testing.assert_close(many[2], B * one[2], rtol=RTOL, atol=B * ATOL)
 
 
+FAR_ROW, FAR_COLUMN = ((0, 1), (0, -1)), ((1, 0), (-1, 0))
+FAR_CASES = [
+    # H, W, L, dirs, table, grad V: more than 2^30 entries in an image, or half of that with stored node gradients; a kernel each
+    (2100, 8200, 64, FAR_ROW, False, False, "<1,4,2,6,false,false,false,false,true>"),
+    (8400, 1000, 128, FAR_COLUMN, True, False, "<2,4,2,6,true,false,false,false,true>"),
+    (1500, 2900, 255, FAR_ROW + ((0, 2), (0, -2), (0, 3)), False, False, "<4,8,1,6,false,false,true,false,true>"),
+    (3000, 1500, 127, FAR_COLUMN, True, True, "<2,4,2,6,true,true,true,false,true>"),
+    (1400, 12000, 64, FAR_ROW, True, True, "<1,4,2,6,true,true,true,false,true>"),
+    (250, 215000, 20, FAR_ROW, True, True, "<1,4,2,6,false,true,false,false,true>"),
+]
+
+
+@pytest.mark.parametrize("case", FAR_CASES, ids=lambda c: "%dx%d_L%d" % c[:3])
+def test_chain_backward_of_images_beyond_32_bit_offsets(case):
+    """The chain sweep with a view per access against the sweeps with 64-bit addresses, on indices drawn at random: both sum in
+    double and round what they store to float, so a float rounding apart; an entry of grad V sums some 10^5 terms of that error."""
+    import torch
+    import paper_1910_10892_amd as mrf
+    H, W, L, dirs, table, want_V, launch = case
+    print("case far image", H, W, L, len(dirs), table, want_V, flush=True)
+    R, dev = len(dirs), "cuda:0"
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(7 + L)
+    lab = torch.arange(L, device=dev, dtype=torch.float32)
+    V = torch.rand((L, L), generator=gen, device=dev) if table else (lab[:, None] - lab[None, :]).abs().clamp(max=3.0).contiguous()
+    w = torch.rand((R, 1, H, W), generator=gen, device=dev) + 0.5
+    gc = torch.rand((1, H, W, L), generator=gen, device=dev) - 0.5
+    p = torch.randint(0, L, (1, R, 1, H, W, L), generator=gen, device=dev, dtype=torch.uint8)
+    q = torch.randint(0, L, (1, R, 1, H, W), generator=gen, device=dev, dtype=torch.uint8)
+    kind = {} if table else {"pairwise_kind": 1, "trunc": 3.0, "scale": 1.0}
+    prob = mrf.MrfProblem(None, V, dirs, 1, w, rho=np.linspace(0.3, 0.7, R), shape=(1, H, W, L), **kind)
+    ws = torch.empty(mrf.mrf_workspace_bytes(prob, mrf.MRF_TRWP, True), dtype=torch.uint8, device=dev)
+
+    def replay():
+        g = [torch.full((1, H, W, L), float("nan"), device=dev), torch.full((R, 1, H, W), float("nan"), device=dev),
+             torch.full((L, L), float("nan"), device=dev) if want_V else None]
+        ws.fill_(0xFF)
+        mrf.mrf_trwp_backward(prob, gc, p, q, *g, ws)
+        return g, mrf.mrf_last_sweep_launch(True)
+
+    far, ran = replay()
+    assert ran.startswith("mrf_bwd_sweep_chain" + launch), ran
+    try:
+        assert mrf.mrf_tune(6, 1) == 0
+        other, ran = replay()
+        assert "chain" not in ran, ran
+    finally:
+        mrf.mrf_tune(6, 0)
+    torch.testing.assert_close(far[0], other[0], rtol=RTOL, atol=1e-6)
+    torch.testing.assert_close(far[1], other[1], rtol=RTOL, atol=1e-5)
+    if want_V:
+        torch.testing.assert_close(far[2], other[2], rtol=RTOL, atol=1e-3)
+
+
 GV_APART_CASES = [
     # seed, B, H, W, L, dirs, K, integer_valued, per_edge
     (751, 1, 6, 9, 96, DIRS4, 3, False, True), (752, 2, 5, 7, 128, DIRS8, 2, True, True),
