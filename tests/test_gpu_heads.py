@@ -16,6 +16,7 @@ def _gpu_problem(pr):
 @pytest.mark.parametrize("case", [
     (1, 1, 5, 7, 9, DIRS4, True), (2, 3, 6, 5, 33, DIRS8, True), (3, 1, 1, 9, 4, DIRS4, False),
     (4, 2, 40, 70, 96, DIRS4, True), (5, 1, 7, 1, 256, [(0, 1), (1, 0), (-1, 0)], True),
+    (6, 1, 901, 903, 2, [(0, 1)], False),      # 3,179 partial sums: four for some threads of the last kernel
 ], ids=lambda c: "seed%d" % c[0])
 def test_energy_matches_oracle(case):
     import torch
@@ -107,7 +108,9 @@ def test_energy_minimisation_protocol_on_crops(oracle, index, crop, algo):
 
 
 @pytest.mark.parametrize("n,L,masked", [(1, 1, False), (37, 2, False), (1000, 96, True), (513, 200, True),
-                                        (4099, 21, False), (64, 256, True)])
+                                        (4099, 21, False), (64, 256, True),
+                                        # more pixels than wavefronts of a launch (16,384): two and three per wavefront, each number of label slots
+                                        (16385, 21, True), (40003, 21, False), (40003, 70, True), (20011, 130, False), (33000, 200, True)])
 def test_softmin_l1_matches_oracle(n, L, masked):
     import torch
     import paper_1910_10892_amd as mrf
@@ -127,10 +130,15 @@ def test_softmin_l1_matches_oracle(n, L, masked):
     d, l, gr = ho.softmin_l1(cost, target, mask)
     np.testing.assert_allclose(disp.cpu().numpy(), d, rtol=1e-5, atol=1e-4)
     np.testing.assert_allclose(loss.cpu().numpy()[0], l, rtol=1e-9, atol=1e-12)
-    np.testing.assert_allclose(grad.cpu().numpy(), gr, rtol=1e-5, atol=1e-7 / max(n, 1) + 1e-12)
+    # The weight of a label z above the lowest cost is off by 6e-8 z (z rounded to float) and 1.2e-7 (expf) relative, the mean of z
+    # under the weights is ln L at most: so d is off by (6e-8 ln L + 1.2e-7) L at most, and an entry of the gradient where lambda is next to
+    # d by 1 / n of that.  (Among the few entries of the small cases none lies so close.)
+    atol = 1e-7 / max(n, 1) + 1e-12 if n <= 16384 else (6e-8 * np.log(L) + 1.2e-7) * L / n
+    np.testing.assert_allclose(grad.cpu().numpy(), gr, rtol=1e-5, atol=atol)
 
 
-@pytest.mark.parametrize("n,L,masked,beta", [(1000, 96, True, 1.0), (513, 21, False, 0.25), (64, 256, True, 3.0)])
+@pytest.mark.parametrize("n,L,masked,beta", [(1000, 96, True, 1.0), (513, 21, False, 0.25), (64, 256, True, 3.0), (16387, 40, False, 0.5),
+                                             (33001, 100, True, 1.0), (20000, 190, True, 2.0), (17000, 256, False, 0.75)])
 def test_softmin_smooth_l1_matches_oracle(n, L, masked, beta):
     import torch
     import paper_1910_10892_amd as mrf
