@@ -4,6 +4,7 @@ geometry (Appendix C) enumerates exactly the maximal in-grid chains."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -221,3 +222,46 @@ def test_bench_refuses_more_than_one_gpu():
     res = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert res.returncode != 0
     assert "one GPU" in res.stderr and res.stdout.strip() == ""
+
+
+@pytest.fixture(scope="module")
+def scanline_order(tmp_path_factory):
+    """mrf_geom_order of the kernels' header as a host function: image and scanline of every place of a direction's launch."""
+    d = tmp_path_factory.mktemp("order")
+    src, so = d / "order.cpp", d / "order.so"
+    src.write_text('#include "mrfmp_device.h"\n'
+                   'extern "C" void order(int H, int W, int dh, int dw, unsigned count, unsigned images, int *b, unsigned *t) {\n'
+                   '  for (unsigned k = 0; k < count * images; ++k) mrf_geom_order(H, W, dh, dw, count, images, k, b[k], t[k]);\n}\n')
+    csrc = os.path.join(ROOT, "paper_1910_10892_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + csrc, str(src), "-o", str(so)],
+                   check=True)
+    lib = ctypes.CDLL(str(so))
+
+    def order(H, W, dh, dw, images):
+        n = mrf.mrf_scanline_count(H, W, dh, dw) * images
+        b, t = np.empty(n, np.int32), np.empty(n, np.uint32)
+        lib.order(H, W, dh, dw, ctypes.c_uint(n // images), ctypes.c_uint(images), b.ctypes.data_as(ctypes.c_void_p), t.ctypes.data_as(ctypes.c_void_p))
+        return b, t
+
+    return order
+
+
+@pytest.mark.parametrize("images", [1, 2, 3, 17, 64, 257])
+def test_a_launch_takes_every_scanline_once_and_those_of_a_diagonal_by_falling_length(scanline_order, images):
+    """Whatever run of 256 a scanline falls into; every second run is turned round.  Directions that are no diagonal with a step of
+    one come image by image in the order of the geometry."""
+    for H, W in [(1, 1), (1, 2), (2, 1), (1, 9), (9, 1), (2, 2), (3, 7), (7, 3), (8, 8), (13, 40), (40, 13), (5, 300), (130, 127)]:
+        for dh, dw in [(1, 1), (1, -1), (-1, 1), (-1, -1), (0, 1), (-1, 0), (1, 2), (-2, 1), (2, 2)]:
+            if images > 17 and H * W > 100:
+                continue
+            count = mrf.mrf_scanline_count(H, W, dh, dw)
+            b, t = scanline_order(H, W, dh, dw, images)
+            place = b.astype(np.int64) * count + t
+            np.testing.assert_array_equal(np.sort(place), np.arange(count * images), err_msg=str((H, W, dh, dw)))
+            if abs(dh) != 1 or abs(dw) != 1:
+                np.testing.assert_array_equal(place, np.arange(count * images))
+                continue
+            lengths = np.array([mrf.mrf_scanline_head(H, W, dh, dw, int(k))[2] for k in range(count)])[t]
+            for first in range(256, len(lengths), 512):
+                lengths[first:first + 256] = lengths[first:first + 256][::-1].copy()
+            assert (np.diff(lengths) <= 0).all(), (H, W, dh, dw)

@@ -796,7 +796,7 @@ def test_pairwise_gradient_added_up_behind_the_chain_sweep(oracle, case):
 
 
 GV_APART_FEW_CASES = [
-    # seed, B, H, W, L, dirs, K, kind: 33..64 labels; eight or four tables; sixteen sources; a pre-reduced scatter target
+    # seed, B, H, W, L, dirs, K, kind: 33..64 labels; eight or four tables; sixteen sources; a scatter target with words of its own
     (761, 50, 6, 9, 33, DIRS4, 2, 0), (762, 1, 7, 9, 49, DIRS8, 2, 0), (763, 1, 5, 8, 64, DIRS16, 2, 0), (764, 3, 11, 7, 55, DIRS4, 3, 0),
     (765, 130, 9, 6, 40, DIRS4, 2, 1), (766, 130, 9, 5, 64, DIRS4, 1, 1), (767, 130, 9, 6, 70, DIRS4, 1, 1), (768, 60, 5, 6, 48, DIRS16, 1, 0),
     (769, 1, 5, 7, 96, DIRS16, 2, 0),
@@ -805,8 +805,8 @@ GV_APART_FEW_CASES = [
 
 @pytest.mark.parametrize("case", GV_APART_FEW_CASES, ids=lambda c: "seed%d" % c[0])
 def test_pairwise_gradients_from_stored_node_gradients(oracle, case):
-    """The same for 33..64 labels, for sixteen directions and for launches whose chain wavefront sums the lanes of the
-    most popular scatter target (truncated models, more than 1,024 scanlines)."""
+    """The same for 33..64 labels, for sixteen directions and for launches that keep the lanes of the most popular scatter
+    target apart (truncated models, more than 1,024 scanlines)."""
     import paper_1910_10892_amd as mrf
     print("case node gradients", case[:5], len(case[5]), case[6:], flush=True)
     seed, B, H, W, L, dirs, K, kind = case
@@ -860,7 +860,10 @@ def test_chain_backward_with_every_number_of_helpers(oracle, case):
             for ni in (2, 4, 6, 8, 12):
                 assert mrf.mrf_tune(7, ni) == 0
                 g = full_check(oracle, pr, want_V=False)
-                assert mrf.mrf_last_sweep_kernel(True) == "mrf_bwd_sweep_chain", mrf.mrf_last_sweep_launch(True)
+                launch = mrf.mrf_last_sweep_launch(True)
+                assert launch.startswith("mrf_bwd_sweep_chain<"), launch
+                parts = launch[launch.index("<") + 1:launch.index(">")].split(",")       # LP, NS, D, NI, VG, GV, HOT
+                assert parts[3] == str(ni) and parts[6] == ("true" if hot == 2 else "false"), launch
                 got = (g.grad_unary, g.grad_edge_weight)
                 if first is None:
                     first = got
@@ -871,26 +874,31 @@ def test_chain_backward_with_every_number_of_helpers(oracle, case):
 
 
 DIAGONAL_ORDER_CASES = [
-    # seed, algo, B, H, W, L, truncation (0: dense): diagonals of fewer than 256 scanlines, of one more, of a whole number of runs of
-    # 256 and of a remainder; grids higher than wide, wider than high, square, of one row and of one column
-    (781, "trwp", 17, 8, 8, 40, 0), (782, "trwp", 257, 1, 3, 70, 0), (783, "trwp", 32, 9, 8, 100, 6), (784, "trwp", 40, 6, 9, 70, 6),
-    (785, "isgmr", 33, 7, 10, 40, 0), (786, "trwp", 21, 10, 4, 200, 12), (787, "trwp", 100, 5, 1, 40, 6), (788, "isgmr", 30, 6, 5, 200, 12),
-    (789, "isgmr", 1, 40, 21, 140, 0),
+    # seed, algo, B, H, W, L, truncation (0: dense), forward sweep, backward sweep: diagonals of fewer than 256 scanlines, of one more, of a whole
+    # number of runs of 256 and of a remainder; grids higher than wide, wider than high, square, of one row and of one column.  Every sweep
+    # that takes its scanlines from mrf_geom_order is among them; mrf_bwd_sweep and mrf_bwd_sweep_split take theirs as they come.
+    (781, "trwp", 17, 8, 8, 40, 0, "sweep", "sweep_chain"), (782, "trwp", 257, 1, 3, 70, 0, "sweep_halves", "sweep_chain"),
+    (783, "trwp", 32, 9, 8, 100, 6, "sweep_window_squad", "sweep_chain"), (784, "trwp", 40, 6, 9, 70, 6, "sweep_window_duo", "sweep_chain"),
+    (785, "isgmr", 33, 7, 10, 40, 0, "sweep", "sweep"), (786, "trwp", 21, 10, 4, 200, 12, "sweep_window_squad", "sweep_split"),
+    (787, "trwp", 100, 5, 1, 40, 6, "sweep_window_duo", "sweep_chain"), (788, "isgmr", 30, 6, 5, 200, 12, "sweep_window_split", "sweep"),
+    (789, "isgmr", 1, 40, 21, 140, 0, "sweep_sliced", "sweep_split"),
 ]
 
 
 @pytest.mark.parametrize("case", DIAGONAL_ORDER_CASES, ids=lambda c: "seed%d" % c[0])
 def test_order_of_a_diagonals_scanlines(oracle, case):
     """Every scanline of a diagonal is swept once, whatever run of 256 it falls into (mrf_geom_order)."""
+    import paper_1910_10892_amd as mrf
     from mrf_inputs import truncated_linear
     print("case diagonal order", case, flush=True)
-    seed, algo, B, H, W, L, trunc = case
+    seed, algo, B, H, W, L, trunc, forward, backward = case
     pr = random_problem(seed, algo, B, H, W, L, DIRS8, 2, symmetric=False, rho=np.linspace(0.3, 0.9, 8))
     if trunc:
         pr.pairwise = truncated_linear(L, float(trunc), 0.37)
         pr.pairwise_kind, pr.trunc, pr.scale = 1, float(trunc), 0.37
     pr.grad_cost = (pr.grad_cost * 0.02).astype(np.float32)
     full_check(oracle, pr)
+    assert (mrf.mrf_last_sweep_kernel(False), mrf.mrf_last_sweep_kernel(True)) == ("mrf_fwd_" + forward, "mrf_bwd_" + backward)
 
 
 def test_forbidden_transitions_leave_first_nodes_alone(oracle):
@@ -1141,7 +1149,7 @@ CHAIN_HOT_CASES = [
 @pytest.mark.parametrize("case", CHAIN_HOT_CASES, ids=lambda c: "seed%d" % c[0])
 def test_chain_wavefront_backward_hot_label(oracle, case):
     """The chain layout on truncated models, where most labels scatter to one source label: with
-    and without the register sum of that label's lanes, 2 and 8 helpers, against the oracle and
+    and without words of their own for that label's lanes, 2 to 12 helpers, against the oracle and
     against each other."""
     import paper_1910_10892_amd as mrf
     from mrf_inputs import truncated_linear, truncated_quadratic, sgm_penalties
