@@ -156,7 +156,7 @@ MRF_G(int g_tune_isgmr_presum, 0); // ISGMR forward with the per-pair sums of th
 MRF_G(int g_tune_chain_pk, 0);     // chain backward with two scanlines of up to 32 labels per workgroup: 0 by launch size, 1 never, 2 always
 MRF_G(int g_tune_gv_apart, 0);     // pairwise gradients of 33..128 labels by a streaming pass behind the chain backward sweep: 0 yes, 1 no
 MRF_G(int g_tune_gv_tile, 0);      // V gradient of 33..128 labels in one LDS table per workgroup: 0 yes, 1 no (a slot per wavefront in global memory)
-MRF_G(int g_tune_dense_sliced, 0); // dense sweep for more than 64 labels with a slice of the labels per wavefront: 0 yes, 1 no
+MRF_G(int g_tune_dense_sliced, 0); // dense sweep of 33 and more labels: 0 by launch shape, 1 every wavefront does the whole node, 2 a slice of the labels each, 3 chunk minima
 MRF_G(int g_tune_spin_limit, 0); // turns a wait between wavefronts may take: 0 = default
 MRF_G(int g_tune_pack_idx, 0);   // packed dense sweep divided among four wavefronts: 0 by launch size, 1 never, 2 always, 3 never and 64-bit offsets,
                                  // 4 always and one scanline per wavefront, 5 always and several, 6 as 3 with two index wavefronts
@@ -2213,7 +2213,7 @@ const char *mrf_last_sweep_kernel(int backward) { return g_last_sweep[backward ?
 
 const char *mrf_last_sweep_launch(int backward) { return g_last_launch[backward ? 1 : 0]; }
 
-const char *mrf_version(void) { return "0.3.9"; }
+const char *mrf_version(void) { return "0.3.10"; }
 
 int mrf_set_sweep_events(void *start_event, void *stop_event)
 {

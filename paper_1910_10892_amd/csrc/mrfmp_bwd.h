@@ -848,6 +848,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
                     now.th[s] = d;
                 }
                 now.vv[s] = 0.0f;
+                // (labels past L read p = 0, so their offset stays MRF_BUF_NONE)
                 if (VG && !GS) now.vv[s] = mrf_buf_f32s(bV, vo(s) + 4u * (unsigned)__mul24(pc[s], L), 0);
             }
             now.w = in_.w;

@@ -621,7 +621,7 @@ __global__ void __launch_bounds__(64 * NW) mrf_fwd_sweep_halves(const MrfFwdPara
     slab[0] = 0;
 #pragma unroll
     for (int c = 1; c < RMAX; ++c) {
-        // (what came through byte loads is uniform, which the compiler cannot know)
+        // (uniform as it is; but with plain indices the compiler holds more scalars at once and spills some where there are sixteen arrays)
         slab[c] = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)P.src_dir[r][c <= n_src ? c - 1 : 0] * NLb));
         before[c] = ((c <= n_src && (!TRWP || c <= n_pre)) ? 1.0f : 0.0f) + vz;
         after[c] = ((c <= n_src && TRWP && c > n_pre) ? 1.0f : 0.0f) + vz;

@@ -5,7 +5,7 @@
 //
 // Both stream over the grid once and are bound by HBM.  All sums are formed in double, in
 // an order that depends only on the launch shape (per wavefront in node order, per
-// workgroup in wavefront order, then over workgroups in index order), so results are
+// workgroup in wavefront order, then over workgroups as mrf_sum_partials says), so results are
 // reproducible run to run.
 #pragma once
 
@@ -75,7 +75,8 @@ __global__ void __launch_bounds__(256) mrf_energy_partial(const MrfEnergyParams 
     if (threadIdx.x == 0) P.partial[(size_t)b * gridDim.x + blockIdx.x] = t;
 }
 
-// out[b] = scale * sum of partial[b][0..n) in index order; one workgroup per b.
+// out[b] = scale * sum of partial[b][0..n); one workgroup per b: a thread adds every 1,024th, a wavefront its threads by a tree,
+// the first thread the wavefronts in order (one wavefront in index order: 17 us for the loss of 256 x 512 pixels, this 4.6).
 // scale_from: if not NULL, scale = 1 / max(*scale_from, 1) (a count kept on the device)
 __global__ void __launch_bounds__(1024) mrf_sum_partials(const double *partial, int n, double *out, const long long *scale_from)
 {
