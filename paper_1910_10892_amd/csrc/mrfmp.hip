@@ -1541,13 +1541,20 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
     const bool chain_fits = !generic && step_fits && !(far && ni != MRF_CHAIN_FAR_HELPERS) && ns <= (LP <= 2 ? 16 : 8) && g_tune_chain != 1 &&
                             (!gv || (LP == 1 && P.total_scanlines <= grad_slots(L))) &&
                             chain_lds(ni) <= chain_lds_cap(P.total_scanlines);
-    // (backward pass, chain / the next best layout.  ISGMR, one source array, 4 directions, K = 3: 96 labels 2,048 scanlines 1.65 / 2.10
-    // ms, 2,560 2.67 / 2.95, 3,072 level; 160 labels 2,048 2.40 / 3.01, 3,072 2.86 / 2.65; 256 labels 1,388 1.63 / 1.91, 2,048 3.44 /
-    // 3.26.  Eight directions, whose launch has many short diagonal scanlines, K = 2, 4,196 scanlines: 96 labels 1.06 / 1.19, 40 labels 0.71 /
-    // 0.76, 160 labels level, 256 labels 2.13 / 1.75.  TRWP, several source arrays, K = 2: 2,048 scanlines 40 labels 1.55 / 1.77, 96 labels 2.09 /
-    // 2.69, 160 labels 2.86 / 3.59, 256 labels 4.28 / 4.83; eight directions, 512 scanlines 160 labels 2.53 / 4.71, 256 labels 3.62 / 5.80)
-    const long long chain_max = ns >= 4 ? (LP == 1 ? 2560 : 2048)
-                                        : (LP == 4 ? 1536 : (P.r_count >= 8 ? (LP <= 2 ? 4224 : 3584) : 2560));
+    // (backward pass, chain / the next best layout, truncated models, K = 2.  ISGMR, one source array, 4 directions, 2,048 / 2,304 / 2,560
+    // scanlines: 160 labels 1.87 / 1.89, 2.31 / 2.41, 2.87 / 2.77 ms (a dense table ahead by 7 % at 2,560); up to 128 labels ahead to 2,560 (96 labels by 5 %); 256 labels 1,536
+    // 1.43 / 1.46, 2,048 behind by 16 %.  Label counts that fill the lanes of mrf_bwd_sweep, which has a variant for them: 64 labels 2,304 1.05 /
+    // 1.10, 2,560 1.33 / 1.25; 128 labels 1,792 1.04 / 1.06, 2,048 1.37 / 1.26; 192 labels 1,536 1.14 / 1.19, 1,792 1.53 / 1.46, 2,048 2.02 /
+    // 1.78.  Eight directions, whose launch has many short diagonal scanlines, 3,068 / 3,596 / 4,220 scanlines: 128 labels 0.693 / 0.696,
+    // 0.926 / 0.897, 1.25 / 1.18, 192 labels 0.99 / 0.95 (2,300 by 9 % ahead), 160 labels 0.92 / 1.00, 1.23 / 1.29, level; 96 labels ahead by
+    // 15 % at all of them.  TRWP, several source arrays: 2,048 scanlines 40 labels 1.55 / 1.77, 96 labels 2.09 / 2.69, 160
+    // labels 2.86 / 3.59, 256 labels 4.28 / 4.83; eight directions, 512 scanlines 160 labels 2.53 / 4.71, 256 labels 3.62 / 5.80)
+    const bool full = L == 64 * LP && pairwise_kind != MRF_PAIRWISE_DENSE && !P.gV;
+    long long chain_max;
+    if (ns >= 4) chain_max = LP == 1 ? 2560 : 2048;
+    else if (LP == 4) chain_max = 1536;
+    else if (P.r_count >= 8) chain_max = LP <= 2 ? (full && LP == 2 ? 3072 : 4224) : (full ? 2560 : 3584);
+    else chain_max = full ? (LP == 1 ? 2304 : (LP == 2 ? 2000 : 1536)) : (LP == 3 && pairwise_kind != MRF_PAIRWISE_DENSE ? 2304 : 2560);
     const bool chain = chain_fits && (g_tune_chain == 2 || P.total_scanlines <= chain_max);
     // Few labels, one direction per launch (TRWP): the chain layout for one scanline per compute unit, two scanlines
     // around a chain wavefront beyond that, mrf_bwd_sweep_narrow for more than the machine holds that way.  (Backward

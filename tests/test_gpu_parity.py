@@ -339,6 +339,24 @@ def test_which_backward_sweep_runs_for_few_labels(oracle, B, H, L, dirs, kernel)
     assert mrf.mrf_last_sweep_kernel(True) == kernel, mrf.mrf_last_sweep_launch(True)
 
 
+@pytest.mark.parametrize("B,L,dirs,kernel", [
+    (28, 64, DIRS4, "chain"), (29, 64, DIRS4, ""), (32, 63, DIRS4, "chain"), (33, 63, DIRS4, ""), (25, 128, DIRS4, "chain"), (26, 128, DIRS4, ""),
+    (32, 127, DIRS4, "chain"), (19, 192, DIRS4, "chain"), (20, 192, DIRS4, ""), (28, 191, DIRS4, "chain"), (29, 191, DIRS4, ""),
+    (13, 128, DIRS8, "chain"), (14, 128, DIRS8, ""), (10, 192, DIRS8, "chain"), (11, 192, DIRS8, ""), (15, 191, DIRS8, "chain"), (16, 191, DIRS8, "")])
+def test_which_backward_sweep_runs_with_one_source(oracle, B, L, dirs, kernel):
+    """ISGMR, truncated model, 16 x 24 images of 80 scanlines (236 with eight directions): both sides of the chain layout's bounds, which lie
+    lower for label counts that fill the lanes of the sweep that runs beyond."""
+    import paper_1910_10892_amd as mrf
+    from mrf_inputs import truncated_linear
+    print("case which backward sweep, one source", B, L, len(dirs), kernel, flush=True)
+    pr = random_problem(830 + L, "isgmr", B, 16, 24, L, dirs, 1)
+    pr.pairwise = truncated_linear(L, 4.0, 1.0)
+    pr.pairwise_kind, pr.trunc, pr.scale = 1, 4.0, 1.0
+    full_check(oracle, pr, want_V=False)
+    ran = mrf.mrf_last_sweep_kernel(True)
+    assert ran == ("mrf_bwd_sweep_chain" if kernel else "mrf_bwd_sweep"), mrf.mrf_last_sweep_launch(True)
+
+
 @pytest.mark.parametrize("algo,B,H,W,L,dirs,halves", [
     ("trwp", 1, 40, 6, 64, DIRS4, False), ("trwp", 100, 6, 7, 49, DIRS4, True), ("trwp", 100, 6, 7, 48, DIRS4, False), ("trwp", 171, 6, 7, 64, DIRS4, False),
     ("trwp", 100, 6, 7, 40, DIRS8, True), ("isgmr", 40, 6, 7, 64, DIRS4, True), ("isgmr", 40, 6, 7, 48, DIRS4, False), ("isgmr", 90, 6, 7, 48, DIRS4, True),
