@@ -102,6 +102,23 @@ inline void fill_geom(const mrf_problem *pr, MrfGeom &g)
     }
 }
 
+// nodes of the longest scanline of direction r
+inline long long longest_scanline(const MrfGeom &g, int r)
+{
+    const int ah = mrf_iabs(g.dh[r]), aw = mrf_iabs(g.dw[r]);
+    const int down = ah ? (g.H + ah - 1) / ah : INT_MAX, across = aw ? (g.W + aw - 1) / aw : INT_MAX;
+    return down < across ? down : across;
+}
+inline long long longest_scanline(const MrfGeom &g, int r_first, int r_count)
+{
+    long long most = 0;
+    for (int r = r_first; r < r_first + r_count; ++r) {
+        const long long n = longest_scanline(g, r);
+        most = n > most ? n : most;
+    }
+    return most;
+}
+
 inline size_t msg_bytes(const mrf_problem *pr)
 {
     return align_up((size_t)pr->R * pr->B * pr->H * pr->W * pr->L * sizeof(float));
@@ -657,14 +674,6 @@ int pick_mch(int L, int LP, bool many_sources, long long blocks)
     return best;
 }
 
-// nodes of the longest scanline of direction r
-long long longest_scanline(const MrfGeom &g, int r)
-{
-    const int ah = mrf_iabs(g.dh[r]), aw = mrf_iabs(g.dw[r]);
-    const int down = ah ? (g.H + ah - 1) / ah : INT_MAX, across = aw ? (g.W + aw - 1) / aw : INT_MAX;
-    return down < across ? down : across;
-}
-
 // Whether mrf_fwd_sweep_halves is ahead of the better of the other two dense sweeps (33..128 labels; forward pass, K = 2 unless
 // noted, others / halves in ms, or halves over others).  Its node step is the shorter one nearly everywhere, its start the longer one (a
 // table in LDS): so on grids with a side of more than 40 the mean length of the launch's scanlines decides, and the longest one where the
@@ -692,12 +701,7 @@ bool chunk_minima_ahead(const MrfFwdParams &P, int algo, int rmax, long long blo
     const int L = P.g.L;
     const bool trwp = algo == MRF_TRWP;
     if (P.g.H > 40 || P.g.W > 40) {
-        const long long nodes = P.g.N * P.r_count, mean = nodes / blocks;
-        long long longest = 0;
-        for (int r = P.r_first; r < P.r_first + P.r_count; ++r) {
-            const long long len = longest_scanline(P.g, r);
-            longest = len > longest ? len : longest;
-        }
+        const long long nodes = P.g.N * P.r_count, mean = nodes / blocks, longest = longest_scanline(P.g, P.r_first, P.r_count);
         const long long beside = L > 96 ? 256 : (longest > 64 ? 1024 : 512);      // scanlines that the machine sweeps beside the longest
         if (!trwp && longest > 40 && longest * beside >= nodes) return true;
         if (L > 96) return mean >= (trwp ? 16 : (blocks <= 1024 ? 24 : (blocks <= 4096 ? 40 : 56)));
@@ -1542,20 +1546,24 @@ hipError_t dispatch_bwd(MrfBwdParams &P, int pairwise_kind, hipStream_t st)
                             (!gv || (LP == 1 && P.total_scanlines <= grad_slots(L))) &&
                             chain_lds(ni) <= chain_lds_cap(P.total_scanlines);
     // (backward pass, chain / the next best layout, truncated models, K = 2.  ISGMR, one source array, 4 directions, 2,048 / 2,304 / 2,560
-    // scanlines: 160 labels 1.87 / 1.89, 2.31 / 2.41, 2.87 / 2.77 ms (a dense table ahead by 7 % at 2,560); up to 128 labels ahead to 2,560 (96 labels by 5 %); 256 labels 1,536
-    // 1.43 / 1.46, 2,048 behind by 16 %.  Label counts that fill the lanes of mrf_bwd_sweep, which has a variant for them: 64 labels 2,304 1.05 /
-    // 1.10, 2,560 1.33 / 1.25; 128 labels 1,792 1.04 / 1.06, 2,048 1.37 / 1.26; 192 labels 1,536 1.14 / 1.19, 1,792 1.53 / 1.46, 2,048 2.02 /
-    // 1.78.  Eight directions, whose launch has many short diagonal scanlines, 3,068 / 3,596 / 4,220 scanlines: 128 labels 0.693 / 0.696,
-    // 0.926 / 0.897, 1.25 / 1.18, 192 labels 0.99 / 0.95 (2,300 by 9 % ahead), 160 labels 0.92 / 1.00, 1.23 / 1.29, level; 96 labels ahead by
-    // 15 % at all of them.  TRWP, several source arrays: 2,048 scanlines 40 labels 1.55 / 1.77, 96 labels 2.09 / 2.69, 160
-    // labels 2.86 / 3.59, 256 labels 4.28 / 4.83; eight directions, 512 scanlines 160 labels 2.53 / 4.71, 256 labels 3.62 / 5.80)
-    const bool full = L == 64 * LP && pairwise_kind != MRF_PAIRWISE_DENSE && !P.gV;
-    long long chain_max;
-    if (ns >= 4) chain_max = LP == 1 ? 2560 : 2048;
-    else if (LP == 4) chain_max = 1536;
-    else if (P.r_count >= 8) chain_max = LP <= 2 ? (full && LP == 2 ? 3072 : 4224) : (full ? 2560 : 3584);
-    else chain_max = full ? (LP == 1 ? 2304 : (LP == 2 ? 2000 : 1536)) : (LP == 3 && pairwise_kind != MRF_PAIRWISE_DENSE ? 2304 : 2560);
-    const bool chain = chain_fits && (g_tune_chain == 2 || P.total_scanlines <= chain_max);
+    // scanlines: 160 labels 1.87 / 1.89, 2.31 / 2.41, 2.87 / 2.77 ms (a dense table ahead by 7 % at 2,560); up to 128 labels ahead to 2,560 (96
+    // labels by 5 %); 256 labels 1,536 1.43 / 1.46, 2,048 behind by 16 %.  Label counts that fill the lanes of mrf_bwd_sweep, which has a variant
+    // for them: 64 labels 2,304 1.05 / 1.10, 2,560 1.33 / 1.25; 128 labels 1,792 1.04 / 1.06, 2,048 1.37 / 1.26; 192 labels 1,536 1.14 /
+    // 1.19, 1,792 1.53 / 1.46, 2,048 2.02 / 1.78.  On long grids most of the scanlines are short and done when the longest still run, so these
+    // bounds are by nodes over the longest: 24 x 1026, 128 labels 0.45 / 1.53, 61 x 1168, 192 labels, K = 1 0.39 / 1.19.  Eight directions, whose
+    // launch has many short diagonal scanlines, 3,068 / 3,596 / 4,220 (2,048 / 2,400 / 2,816 by the longest): 128 labels 0.693 / 0.696, 0.926 /
+    // 0.897, 1.25 / 1.18, 192 labels 0.99 / 0.95 (2,300 by 9 % ahead), 160 labels 0.92 / 1.00, 1.23 / 1.29, level; 96 labels ahead by 15 % at all of them.
+    // TRWP, several source arrays: 2,048 scanlines 40 labels 1.55 / 1.77, 96 labels 2.09 / 2.69, 160 labels 2.86 / 3.59, 256
+    // labels 4.28 / 4.83; eight directions, 512 scanlines 160 labels 2.53 / 4.71, 256 labels 3.62 / 5.80)
+    const long long chain_max = ns >= 4 ? (LP == 1 ? 2560 : 2048)
+                                        : (LP == 4 ? 1536 : (P.r_count >= 8 ? (LP <= 2 ? 4224 : 3584) : 2560));
+    bool behind = false;
+    if (ns == 1 && LP <= 3 && pairwise_kind != MRF_PAIRWISE_DENSE && !P.gV) {
+        const bool full = L == 64 * LP;
+        const long long most = full && LP == 2 ? 2000 : (full && LP == 3 ? 1536 : 2432);
+        behind = (full || LP == 3) && P.g.N * P.r_count > most * longest_scanline(P.g, P.r_first, P.r_count);
+    }
+    const bool chain = chain_fits && (g_tune_chain == 2 || (P.total_scanlines <= chain_max && !behind));
     // Few labels, one direction per launch (TRWP): the chain layout for one scanline per compute unit, two scanlines
     // around a chain wavefront beyond that, mrf_bwd_sweep_narrow for more than the machine holds that way.  (Backward
     // pass of 256 x 512 grids, 21 labels, 4 directions, K = 3, one / two / four images: 0.83 / 1.35 / 2.15 ms chain,

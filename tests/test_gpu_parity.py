@@ -339,17 +339,19 @@ def test_which_backward_sweep_runs_for_few_labels(oracle, B, H, L, dirs, kernel)
     assert mrf.mrf_last_sweep_kernel(True) == kernel, mrf.mrf_last_sweep_launch(True)
 
 
-@pytest.mark.parametrize("B,L,dirs,kernel", [
-    (28, 64, DIRS4, "chain"), (29, 64, DIRS4, ""), (32, 63, DIRS4, "chain"), (33, 63, DIRS4, ""), (25, 128, DIRS4, "chain"), (26, 128, DIRS4, ""),
-    (32, 127, DIRS4, "chain"), (19, 192, DIRS4, "chain"), (20, 192, DIRS4, ""), (28, 191, DIRS4, "chain"), (29, 191, DIRS4, ""),
-    (13, 128, DIRS8, "chain"), (14, 128, DIRS8, ""), (10, 192, DIRS8, "chain"), (11, 192, DIRS8, ""), (15, 191, DIRS8, "chain"), (16, 191, DIRS8, "")])
-def test_which_backward_sweep_runs_with_one_source(oracle, B, L, dirs, kernel):
-    """ISGMR, truncated model, 16 x 24 images of 80 scanlines (236 with eight directions): both sides of the chain layout's bounds, which lie
-    lower for label counts that fill the lanes of the sweep that runs beyond."""
+@pytest.mark.parametrize("B,H,W,L,dirs,kernel", [
+    (38, 16, 16, 64, DIRS4, "chain"), (39, 16, 16, 64, DIRS4, ""), (40, 16, 16, 63, DIRS4, "chain"), (41, 16, 16, 63, DIRS4, ""),
+    (31, 16, 16, 128, DIRS4, "chain"), (32, 16, 16, 128, DIRS4, ""), (40, 16, 16, 127, DIRS4, "chain"), (24, 16, 16, 192, DIRS4, "chain"),
+    (25, 16, 16, 192, DIRS4, ""), (38, 16, 16, 191, DIRS4, "chain"), (39, 16, 16, 191, DIRS4, ""), (15, 16, 16, 128, DIRS8, "chain"),
+    (16, 16, 16, 128, DIRS8, ""), (12, 16, 16, 192, DIRS8, "chain"), (13, 16, 16, 192, DIRS8, ""), (19, 16, 16, 191, DIRS8, "chain"),
+    (20, 16, 16, 191, DIRS8, ""), (2, 4, 500, 192, DIRS4, "chain"), (3, 400, 4, 128, DIRS4, "chain")])
+def test_which_backward_sweep_runs_with_one_source(oracle, B, H, W, L, dirs, kernel):
+    """ISGMR, truncated model: both sides of the chain layout's bounds, which lie lower for label counts that fill the lanes of the
+    sweep that runs beyond, but not on long grids."""
     import paper_1910_10892_amd as mrf
     from mrf_inputs import truncated_linear
-    print("case which backward sweep, one source", B, L, len(dirs), kernel, flush=True)
-    pr = random_problem(830 + L, "isgmr", B, 16, 24, L, dirs, 1)
+    print("case which backward sweep, one source", B, H, W, L, len(dirs), kernel, flush=True)
+    pr = random_problem(830 + L, "isgmr", B, H, W, L, dirs, 1)
     pr.pairwise = truncated_linear(L, 4.0, 1.0)
     pr.pairwise_kind, pr.trunc, pr.scale = 1, 4.0, 1.0
     full_check(oracle, pr, want_V=False)
