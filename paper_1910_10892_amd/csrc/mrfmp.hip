@@ -1089,7 +1089,7 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
     const bool far = chain_far(P.g, gs && !edge);
     note_launch(1, "mrf_bwd_sweep_chain", P.total_scanlines, 64 * (1 + ni), "%d,%d,%d,%d,%s,%s,%s%s", LP, NS, D, ni,
                 (!(LP == 1 && gv) && vg) ? "true" : "false", ((LP == 1 && gv) || gs) ? "true" : "false", hot ? "true" : "false",
-                edge ? ",true" : (far ? ",false,true" : ""));
+                edge ? ",true" : (LP == 1 && gv && !P.gw ? (far ? ",false,true,false" : ",false,false,false") : (far ? ",false,true" : "")));
     if (gv && (LP != 1 || P.total_scanlines > grad_slots(P.g.L))) return hipErrorInvalidValue;
     MrfChainParams C;
     memset(&C, 0, sizeof(C));
@@ -1135,6 +1135,7 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
             if (ni != MRF_CHAIN_FAR_HELPERS || edge) return hipErrorInvalidValue;
             constexpr int n = MRF_CHAIN_FAR_HELPERS;
             if constexpr (LP == 1) {
+                if (gv && !P.gw) { MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, false, true, false, false, true, false>); return hipGetLastError(); }
                 if (gv) { MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, false, true, false, false, true>); return hipGetLastError(); }
             }
             if constexpr (LP <= 2) {
@@ -1156,7 +1157,8 @@ hipError_t launch_bwd_chain(const MrfBwdParams &P, int ni, bool vg, hipStream_t 
         } \
         if constexpr (LP == 1) { \
             if (gv) { \
-                MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, false, true, false>); \
+                if (P.gw) MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, false, true, false>); \
+                else MRF_CH_GO(mrf_bwd_sweep_chain<LP, NS, D, n, false, true, false, false, false, false>); \
                 return hipGetLastError(); \
             } \
         } \

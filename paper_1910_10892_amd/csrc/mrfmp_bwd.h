@@ -537,7 +537,10 @@ struct MrfChainParams {
 // sweeps with 64-bit addresses: 1024 x 16640, 64 labels, two directions 11.5 / 19.6 ms; 512 x 8400, 256 labels 7.4 / 16.1; 512 x 16800, 128
 // labels, four directions 16.0 / 40.2, with grad V 36 / 81.  Six helpers; HOT beyond 128 labels and with stored gradients (64 and 128
 // labels without: 12.9 -> 11.5, 18.8 -> 16.0 ms).
-template <int LP, int NS, int D, int NI, bool VG, bool GV, bool HOT, bool EDGE = false, bool FAR = false>
+// SUMS = false: V-gradient tables, but no edge-weight gradient (a learned table with a scalar weight): no V in LDS, no g V, no sum (backward
+// pass, 128 x 256, 48 labels, ISGMR, K = 3 0.335 -> 0.272 ms, 37 x 53, 21 labels, TRWP, K = 5 0.215 -> 0.197).  A variant, because a branch in the
+// turn took 0.7 % of a learning step that wants both.
+template <int LP, int NS, int D, int NI, bool VG, bool GV, bool HOT, bool EDGE = false, bool FAR = false, bool SUMS = true>
 __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfChainParams P)
 {
     static_assert(D == 1 || D == 2, "sets of registers");
@@ -550,6 +553,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
     constexpr bool GS = GV && VG;            // node gradients stored for mrf_bwd_pairwise_*
     constexpr bool VROW = !VG && !GV;        // first row of V in LDS
     static_assert(!GVT || LP == 1, "V-gradient tables");
+    static_assert(SUMS || GVT, "edge-weight gradient");
     static_assert(!EDGE || (GS && !HOT && !FAR), "per-edge tables");
     const int L = P.L;
     // carved in the order of mrf_bwd_chain_lds_bytes
@@ -581,7 +585,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
     // LDS, by all wavefronts together; those of the helpers have their first loads under way
     auto prepare = [&]() {
         if (GVT) {
-            for (int e = threadIdx.x; e < L * L; e += 64 * (1 + NI)) vl[e] = P.V[e];
+            for (int e = threadIdx.x; SUMS && e < L * L; e += 64 * (1 + NI)) vl[e] = P.V[e];
             for (int e = threadIdx.x; e < NI * L * L; e += 64 * (1 + NI)) gvacc[e] = 0.0;
         } else if (VROW) {
             for (int e = threadIdx.x; e < L; e += 64 * (1 + NI)) vd[e] = (double)P.V[e];
@@ -785,7 +789,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
     Kept kept = {};
     double *gvl = gvacc + (GVT ? jw * L * L : 0);
     int chain_seen = -1;
-    const bool want_w = P.gw && !GS;
+    const bool want_w = SUMS && (P.gw || GVT) && !GS;      // (GVT: the host takes SUMS = false without P.gw)
 
     auto turn = [&](In &in_, int it, auto parity) {
         constexpr int par = decltype(parity)::value;
@@ -887,7 +891,7 @@ __global__ void __launch_bounds__(64 * (1 + NI)) mrf_bwd_sweep_chain(const MrfCh
                     if (s == LP - 1) dist = lam < L ? dist : 0;
                     V[s] = vd[dist];
                 } else if (GVT) {
-                    V[s] = (double)vl[lam < L ? __mul24(kept.p[s], L) + lam : 0];
+                    if (SUMS) V[s] = (double)vl[lam < L ? __mul24(kept.p[s], L) + lam : 0];
                 } else if (!GS) {
                     V[s] = (double)kept.vv[s];
                 }

@@ -1403,6 +1403,7 @@ def test_optional_outputs_may_be_null(oracle):
 def test_each_gradient_alone(oracle, algo, B, H, W, L, per_edge):
     """Every combination of the optional gradients, with a scalar weight and with one per edge, on a workspace that holds garbage
     when the backward pass starts: its header, what the sweeps add to and what nobody asked for."""
+    import paper_1910_10892_amd as mrf
     from gpu_harness import GpuProblem
     print("case each gradient alone", algo, B, H, W, L, per_edge, flush=True)
     pr = random_problem(820 + L, algo, B, H, W, L, DIRS4, 2, symmetric=False, per_edge=per_edge, rho=np.linspace(0.3, 0.9, 4))
@@ -1418,6 +1419,9 @@ def test_each_gradient_alone(oracle, algo, B, H, W, L, per_edge):
         g.workspace.fill_(0xFF)
         g.backward(want_w=want_w, want_V=want_V)
         got = g.results()
+        launch = mrf.mrf_last_sweep_launch(True)
+        if want_V and launch.startswith("mrf_bwd_sweep_chain<1,") and ",false,true,false" in launch:      # tables in LDS
+            assert launch.split(">")[0].endswith(",false,true,false" if want_w else ",false,true,false,false,false,false"), launch
         check_grad("grad_unary", got.grad_unary, None, ref.grad_unary)
         for name, want in (("grad_edge_weight", want_w), ("grad_pairwise", want_V)):
             if want:
