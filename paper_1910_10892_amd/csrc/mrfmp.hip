@@ -1852,9 +1852,10 @@ int run_backward(const mrf_problem *pr, int algo, const float *grad_cost, const 
         // per node) and the sweep of direction 0 adds all of them, and its own s, to grad theta; one
         // combine pass at the end adds what the other directions scattered in the last sweep.  The s
         // arrays of two iterations alternate between the two buffers.
-        // Pays only where the pass is bound by its launches (the combine passes are a third of them): on the
-        // stereo and segmentation shapes the sweeps, which are bound by instruction issue and latency, lose
-        // more on the extra arrays (2.29 against 1.80 ms, 4.05 against 3.76 ms) than the combine passes cost.
+        // Pays where the pass is bound by its launches (the combine passes are a third of them); on the segmentation shape
+        // the sweeps, which are bound by instruction issue and latency, lose more on the extra arrays (2.51 against 1.83 ms) than
+        // the combine passes cost.  (On the stereo shape, 256 x 512, 96 labels, it is 1.36 against 1.46 ms: the line could lie higher for the
+        // chain layout.)
         const bool lazy = R <= 4 && g_tune_isgmr_lazy != 1 && (g_tune_isgmr_lazy == 2 || NL <= (1LL << 19));
         for (int k = K - 1; lazy && k >= 0; --k) {
             float *s_cur = ((K - 1 - k) & 1) ? buf0 : buf1, *s_prev = ((K - 1 - k) & 1) ? buf1 : buf0;

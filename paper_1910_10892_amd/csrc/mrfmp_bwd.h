@@ -512,10 +512,10 @@ struct MrfChainParams {
 // entries, grad theta less g.  Loads and stores go through buffer views of the image: a lane's
 // offset is its label, the node's is a scalar, and what must not be stored gets the offset
 // at which the view ends; so a turn is one straight piece of code.  Label sums are formed by
-// the matrix unit (mrf_wave_sum_mat_f64).  A turn of a helper is some 95 vector instructions at 96 labels and three sources and
-// a step of the chain 26, where exec-masked stores, 64-bit addresses and sums by DPP took 300 and 50: those bounded launches of two and
-// more workgroups per compute unit, the chain's own writes (carry, scattered vector, clearing) the others.  256 x 512, 96 labels, TRWP,
-// K = 5: 1.66 -> 1.19 ms (65 us for the 265 MB of a launch, 4.1 TB/s); 256 x 256, 256 labels, TRWP, K = 10 4.51 -> 3.16 ms; 283 x 411, 70
+// the matrix unit (mrf_wave_sum_mat_f64).  A helper's turn and the chain's step of a node are 87 vector instructions at
+// 96 labels and three sources (counters), where exec-masked stores, 64-bit addresses and sums by DPP took 169: those bounded launches of two
+// and more workgroups per compute unit, the chain's own writes (carry, scattered vector, clearing) the others.  256 x 512, 96 labels, TRWP,
+// K = 5: 1.66 -> 1.19 ms (65 us for the 269 MB of a launch of 256 scanlines, 4.1 TB/s, 59 us for 226 MB of one of 512); 256 x 256, 256 labels, TRWP, K = 10 4.51 -> 3.16 ms; 283 x 411, 70
 // labels, ISGMR, K = 5 1.52 -> 1.22 ms; 32 x 48, 16 labels, ISGMR, K = 5 65 -> 51 us, where half of a launch was the way to its first loads
 // (arguments per direction, no 64-bit products, no division for steps of one, loads in front of the preparation of LDS).
 //

@@ -2459,7 +2459,7 @@ mrf_fwd_sweep_window_split(const MrfFwdParams P)
 // TRWP, 256 x 256, 256 labels, window 16, K = 10: sweeps 8.27 ms with index wavefronts alone beside the values and every neighbour
 // read by itself, now 5.2; window 8, K = 2: 1.32 ms (mrf_fwd_sweep_window_duo), now 1.00.  What is left: a part of the step is the
 // value wavefronts waiting for each other (K = 2, before the looks were moved: 1.16 ms, 0.93 without looking at flags and posts), the rest
-// vector issue: 934 instructions of twelve wavefronts per node are 934 clocks of the four SIMDs.
+// vector issue: 924 instructions of twelve wavefronts per node are 924 clocks of the four SIMDs.
 // (four wavefronts per SIMD with four beside the values, so that two scanlines share a compute unit)
 template <int RMAX, int D, bool TRWP, int TW, int NI>
 __global__ void __launch_bounds__(64 * (4 + NI), NI <= 4 ? 4 : 3)
